@@ -88,6 +88,56 @@ __device__ inline int lanes_below(u64 ballot)
     return (int)__builtin_amdgcn_mbcnt_hi((u32)(ballot >> 32), __builtin_amdgcn_mbcnt_lo((u32)ballot, 0u));
 }
 
+// a 16-byte load at any multiple of four bytes (more than that no global load asks for)
+typedef float ef_f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
+__device__ inline float4 load_unaligned4(const float *p)
+{
+    const ef_f32x4_u v = *reinterpret_cast<const ef_f32x4_u *>(p);
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+
+// The register kernels read vectors in 16-byte pieces: the lanes (r, g) of row r take the
+// coordinates c0 + 16 s + 4 g .. + 3, s = 0..7, of a 128-coordinate stretch; what lies beyond d
+// counts as zero (zeros on both sides add nothing to a distance, in any position).
+// ALIGNED (d % 4 == 0 and X 16-byte aligned): a piece is inside the vector or not at all.
+// Else (d >= 4, rows at any multiple of four bytes): the pieces of the last, incomplete sixteen
+// coordinates are read from d - 4 where they would leave the vector, and moved into place.
+// (Such rows took the LDS kernels before.  Builds, before and after: 200 003 x 50, degree 15:
+// 10.5 -> 5.6 ms; 100 000 x 187, degree 10: 9.8 -> 3.5; 50 000 x 957: 55 -> 4.6; 50 000 x 77, degree 60:
+// 27 -> 15.4.)
+// ok: this lane has a row (`row` names a vector of the data either way: no branch around the loads)
+template <bool ALIGNED>
+__device__ inline void load_pieces(float4 (&v)[8], const float *row, int c0, int g, int d, bool ok)
+{
+    if (ALIGNED) {
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            const int j = c0 + 16 * s + 4 * g;
+            v[s] = ok && j + 3 < d ? *reinterpret_cast<const float4 *>(row + j) : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+        return;
+    }
+    const int n_whole = (d - c0) >> 4;      // sixteens that lie inside (uniform)
+    const float *p = row + c0 + 4 * g;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) v[s] = s < n_whole ? load_unaligned4(p + 16 * s) : make_float4(0.f, 0.f, 0.f, 0.f);
+    if (n_whole < 8 && ((d - c0) & 15)) {
+        const int j = c0 + 16 * n_whole + 4 * g, jb = min(j, d - 4), over = j - jb;
+        const float4 w = load_unaligned4(row + jb);
+        float4 t;
+        t.x = over == 0 ? w.x : over == 1 ? w.y : over == 2 ? w.z : over == 3 ? w.w : 0.f;
+        t.y = over == 0 ? w.y : over == 1 ? w.z : over == 2 ? w.w : 0.f;
+        t.z = over == 0 ? w.z : over == 1 ? w.w : 0.f;
+        t.w = over == 0 ? w.w : 0.f;
+#pragma unroll
+        for (int s = 0; s < 8; ++s)
+            if (s == n_whole) v[s] = t;
+    }
+    if (!ok)
+#pragma unroll
+        for (int s = 0; s < 8; ++s) v[s] = make_float4(0.f, 0.f, 0.f, 0.f);
+}
+
 // A proposal waiting in the block's LDS queue: entry `key` offered to row `target`.
 struct Proposal {
     u64 key;
@@ -95,10 +145,11 @@ struct Proposal {
     int pad;
 };
 
-// Coalesced gather of m rows of X into LDS.  Fast path (d multiple of 4): the block's
-// threads walk the m*(d/4) 16-byte pieces, eight loads in flight per thread.
-// q4_magic = ceil(2^32 / (d/4)) turns the piece index into (row, column) without a
-// division (exact while pieces * (d/4) < 2^32).
+// Coalesced gather of m rows of X into LDS.  The block's threads walk the 16-byte pieces,
+// ceil(d/4) per row, eight loads in flight per thread (rows that are not 16-byte aligned: four at
+// 4-byte alignment, the last piece of a row moved back so that it ends with the row).
+// q4_magic = ceil(2^32 / ceil(d/4)) turns the piece index into (row, column) without a
+// division (exact while pieces * ceil(d/4) < 2^32).
 __device__ inline void gather_rows(const float *__restrict__ X, int d, int stride, u32 q4_magic,
                                    const int *uid, int m, float *rows, int tid, int nthr)
 {
@@ -120,6 +171,21 @@ __device__ inline void gather_rows(const float *__restrict__ X, int d, int strid
                     *reinterpret_cast<float4 *>(rows + r * stride + 4 * c) = v[k];
                 }
             }
+        }
+    } else if (d >= 4) {
+        const int q4 = (d + 3) >> 2, total = m * q4;
+        for (int f0 = tid; f0 < total; f0 += nthr * 4) {
+            ef_f32x4_u v[4];
+            int to[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int f = min(f0 + k * nthr, total - 1);      // (a piece may be copied twice)
+                const int r = q4 == 1 ? f : (int)(((u64)(u32)f * q4_magic) >> 32), c = min(4 * (f - r * q4), d - 4);
+                v[k] = *reinterpret_cast<const ef_f32x4_u *>(X + (size_t)uid[r] * d + c);
+                to[k] = r * stride + c;
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) *reinterpret_cast<ef_f32x4_u *>(rows + to[k]) = v[k];
         }
     } else {
         const int total = m * d;
@@ -292,7 +358,7 @@ init_tree_kernel(const float *__restrict__ X, int d, int stride, u32 q4_magic, i
 }
 
 // ---------------------------------------------------------------------------------------
-// The same step for leaves of at most 16 points (d % 4 == 0, X 16-byte aligned), without a
+// The same step for leaves of at most 16 points (d >= 4), without a
 // row buffer: persistent waves, one leaf at a time.
 //
 // Lane (r, g) = lane r + 16 g keeps, of member r of the leaf, the coordinates 16 s + 4 g + k
@@ -351,6 +417,7 @@ __device__ inline void cross_round(const float4 (&va)[8], const float4 (&vb)[8],
 
 constexpr int kCandPitch = 17;      // u64 per row of the candidate table (odd: rows on different banks)
 
+template <bool ALIGNED>      // (see load_pieces)
 __global__ void __launch_bounds__(EF_WAVE) __attribute__((amdgpu_waves_per_eu(4)))
 init_reg_kernel(const float *__restrict__ X, int d, const int *__restrict__ perm_t,
                 const int *__restrict__ leaf_off_t, int n_leaves, int K, u64 *graph, int first_tree)
@@ -389,14 +456,10 @@ init_reg_kernel(const float *__restrict__ X, int d, const int *__restrict__ perm
         float P[8][4];
 #pragma unroll
         for (int t = 0; t < 8; ++t) P[t][0] = P[t][1] = P[t][2] = P[t][3] = 0.0f;
-        const float *pa = X + (size_t)max(my_id, 0) * d + 4 * g;
+        const float *pa = X + (size_t)max(my_id, 0) * d;
         for (int c0 = 0; c0 < d; c0 += 128) {
             float4 va[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const bool in = r16 < s && c0 + 16 * q + 4 * g + 3 < d;   // d % 4 == 0: a piece is in or out
-                va[q] = in ? *reinterpret_cast<const float4 *>(pa + c0 + 16 * q) : make_float4(0.f, 0.f, 0.f, 0.f);
-            }
+            load_pieces<ALIGNED>(va, pa, c0, g, d, r16 < s);
             const int n_pieces = min(8, (d - c0 + 15) >> 4);
             init_round<1>(va, n_pieces, P[0]);
             init_round<2>(va, n_pieces, P[1]);
@@ -493,7 +556,7 @@ init_reg_kernel(const float *__restrict__ X, int d, const int *__restrict__ perm
 // find those rows in the cache).  Eight such members give eight sets of partial sums, which
 // the four lanes of a row add up in the fixed tree, transposed, as for rotations.  Rows are
 // merged by rank in LDS after every level and stored at the end.
-// Requires leaves of at most 16 points, d % 4 == 0 and a 16-byte aligned X.
+// Requires leaves of at most 16 points and d >= 4.
 
 // partial sums of one pair: lane (r, g) adds the terms of its coordinates
 __device__ inline void accumulate_pair(const float4 (&va)[8], const float4 (&vb)[8], int n_pieces, float (&p)[4])
@@ -615,7 +678,8 @@ classify_kernel(const float *__restrict__ X, int d, const int *__restrict__ perm
     }
 }
 
-__global__ void __launch_bounds__(EF_WAVE)
+template <bool ALIGNED>      // (three waves per SIMD: two lose 20 % on the headline data, whatever the spills of the unaligned form)
+__global__ void __launch_bounds__(EF_WAVE) __attribute__((amdgpu_waves_per_eu(3)))
 conquer_kernel(const float *__restrict__ X, int d, const int *__restrict__ perm_t,
                const int *__restrict__ leaf_off_t, int n_leaves, const int *__restrict__ etab,
                int levels, int K, u64 *graph)
@@ -633,7 +697,7 @@ conquer_kernel(const float *__restrict__ X, int d, const int *__restrict__ perm_
         int e = r16 < s ? etab[(size_t)(b0 + r16) * levels] : -1;
         if (__ballot(e >= 0) == 0) continue;      // nothing above this leaf to visit
         const int my_id = r16 < s ? perm_t[b0 + r16] : -1;
-        const float *pa = X + (size_t)max(my_id, 0) * d + 4 * g;
+        const float *pa = X + (size_t)max(my_id, 0) * d;
         __syncthreads();                  // the previous leaf's LDS reads are done
         u64 *cur = pools_a, *nxt = pools_b;
         for (int c = g; c < K; c += 4)
@@ -663,24 +727,13 @@ conquer_kernel(const float *__restrict__ X, int d, const int *__restrict__ perm_
                     for (int t = 0; t < 8; ++t) P[t][0] = P[t][1] = P[t][2] = P[t][3] = 0.0f;
                     for (int c0 = 0; c0 < d; c0 += 128) {
                         float4 va[8];
-#pragma unroll
-                        for (int q = 0; q < 8; ++q) {
-                            const bool in = c0 + 16 * q + 4 * g + 3 < d;      // d % 4 == 0: a piece is in or out
-                            va[q] = in && r16 < s ? *reinterpret_cast<const float4 *>(pa + c0 + 16 * q)
-                                                  : make_float4(0.f, 0.f, 0.f, 0.f);
-                        }
+                        load_pieces<ALIGNED>(va, pa, c0, g, d, r16 < s);
                         const int n_pieces = min(8, (d - c0 + 15) >> 4);
 #pragma unroll
                         for (int t = 0; t < 8; ++t) {
                             const int id_b = uid_b[r16 * 16 + 8 * half + t];
-                            const float *pb = X + (size_t)max(id_b, 0) * d + 4 * g + c0;
                             float4 vb[8];
-#pragma unroll
-                            for (int q = 0; q < 8; ++q) {
-                                const bool in = c0 + 16 * q + 4 * g + 3 < d;
-                                vb[q] = in && id_b >= 0 ? *reinterpret_cast<const float4 *>(pb + 16 * q)
-                                                        : make_float4(0.f, 0.f, 0.f, 0.f);
-                            }
+                            load_pieces<ALIGNED>(vb, X + (size_t)max(id_b, 0) * d, c0, g, d, id_b >= 0);
                             accumulate_pair(va, vb, n_pieces, P[t]);
                         }
                     }
@@ -742,7 +795,7 @@ conquer_kernel(const float *__restrict__ X, int d, const int *__restrict__ perm_
 
 // ---------------------------------------------------------------------------------------
 // The same step for any leaf size up to 64 and any dimension (the kernels above want leaves of at
-// most 16 points and d % 4 == 0).  classify_any_kernel: one wave per leaf, lane r sends member r
+// most 16 points and d >= 4).  classify_any_kernel: one wave per leaf, lane r sends member r
 // down the sibling subtree of every ancestor in range.  conquer_any_kernel: one wave per member
 // (the waves of a block take the members of one home leaf, which owns its members' rows during
 // the launch); per level the wave evaluates its member against the members of the leaf reached,
@@ -1901,7 +1954,7 @@ prepare_wave_kernel(const int *__restrict__ nw, const int *__restrict__ od,
 // sums it owns (coordinates = 4g..4g+3 mod 16, ascending) and the 16 partial sums are
 // added in the fixed tree across the four lanes of row a.  Longer vectors are re-read
 // from memory (they are still in L2) by one 16-lane group per pair.
-// Requires d % 4 == 0 and a 16-byte aligned X.
+// Requires d >= 4.
 
 // where the survivors of Gram blocks (0,0), (0,1), (1,1) start in the LDS survivor buffer
 __device__ constexpr int kSurvBase[3] = {0, 120, 376};
@@ -1934,7 +1987,7 @@ __device__ inline int propose_pair(Proposal *queue, int fill, bool mine, float d
     return fill + __popcll(mask_b);
 }
 
-template <int NB, bool ONE, int KT>      // KT: the row length if fixed at compile time (the row scans unroll), else 0
+template <int NB, bool ONE, int KT, bool ALIGNED>      // KT: the row length if fixed at compile time (the row scans unroll), else 0
 __global__ void __launch_bounds__(EF_WAVE) __attribute__((amdgpu_waves_per_eu(NB > 1 ? 3 : 4)))
 join_reg_kernel(const float *__restrict__ X, int d, int K_,
                 const int *__restrict__ work, const int *__restrict__ work_count, int q_cap,
@@ -2005,8 +2058,8 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
         c_pre = i >= 0 ? ucount[i] : make_int2(0, 0);
         i_next = w + 2 * (int)gridDim.x < count ? work[w + 2 * gridDim.x] : -1;
         // ---- 1+2. Gram blocks from register operands ---------------------------------------
-        const float *pa = X + (size_t)__shfl(u_cur, min(r16, m - 1), EF_WAVE) * d + 4 * g;
-        const float *pb = NB > 1 ? X + (size_t)__shfl(u_cur, min(16 + r16, m - 1), EF_WAVE) * d + 4 * g : pa;
+        const float *pa = X + (size_t)__shfl(u_cur, min(r16, m - 1), EF_WAVE) * d;
+        const float *pb = NB > 1 ? X + (size_t)__shfl(u_cur, min(16 + r16, m - 1), EF_WAVE) * d : pa;
         const bool need11 = NB > 1 && m_new > 16;      // block (1,1) only if new rows reach it
         constexpr int NQ = NB > 1 ? 3 : 1;      // Gram blocks (0,0), (0,1), (1,1)
         floatx4 acc[NQ][2];
@@ -2036,11 +2089,7 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
             }
             for (int c0 = 0; c0 < d; c0 += 128) {
                 const int n_pieces = min(8, (d - c0 + 15) >> 4);
-#pragma unroll
-                for (int s = 0; s < 8; ++s) {
-                    const bool in = c0 + 16 * s + 4 * g + 3 < d;      // d % 4 == 0: a piece is in or out
-                    va[s] = in ? *reinterpret_cast<const float4 *>(pa + c0 + 16 * s) : make_float4(0.f, 0.f, 0.f, 0.f);
-                }
+                load_pieces<ALIGNED>(va, pa, c0, g, d, true);
                 init_round<1>(va, n_pieces, P[0]);
                 init_round<2>(va, n_pieces, P[1]);
                 init_round<3>(va, n_pieces, P[2]);
@@ -2051,11 +2100,7 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
                 init_round<8>(va, n_pieces, P[7]);
                 if (NB > 1 && need11) {      // pairs inside rows 16..31 are wanted only if new rows reach them
                     float4 (&wb)[8] = reinterpret_cast<float4 (&)[8]>(vb);
-#pragma unroll
-                    for (int s = 0; s < 8; ++s) {
-                        const bool in = c0 + 16 * s + 4 * g + 3 < d;
-                        wb[s] = in ? *reinterpret_cast<const float4 *>(pb + c0 + 16 * s) : make_float4(0.f, 0.f, 0.f, 0.f);
-                    }
+                    load_pieces<ALIGNED>(wb, pb, c0, g, d, true);
                     init_round<1>(wb, n_pieces, PB[0]);
                     init_round<2>(wb, n_pieces, PB[NB > 1 ? 1 : 0]);
                     init_round<3>(wb, n_pieces, PB[NB > 1 ? 2 : 0]);
@@ -2073,18 +2118,13 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
             if (c0 + 128 <= d) {     // a whole 128-coordinate piece: no per-load bounds test
 #pragma unroll
                 for (int s = 0; s < 8; ++s) {
-                    va[s] = *reinterpret_cast<const float4 *>(pa + c0 + 16 * s);
-                    if (NB > 1) vb[NB > 1 ? s : 0] = *reinterpret_cast<const float4 *>(pb + c0 + 16 * s);
+                    const int j = c0 + 16 * s + 4 * g;
+                    va[s] = ALIGNED ? *reinterpret_cast<const float4 *>(pa + j) : load_unaligned4(pa + j);
+                    if (NB > 1) vb[NB > 1 ? s : 0] = ALIGNED ? *reinterpret_cast<const float4 *>(pb + j) : load_unaligned4(pb + j);
                 }
             } else {
-#pragma unroll
-                for (int s = 0; s < 8; ++s) {
-                    const int j = c0 + 16 * s + 4 * g;
-                    const bool in = j + 3 < d;                 // d % 4 == 0: a piece is in or out
-                    va[s] = in ? *reinterpret_cast<const float4 *>(pa + c0 + 16 * s) : make_float4(0.f, 0.f, 0.f, 0.f);
-                    if (NB > 1)
-                        vb[NB > 1 ? s : 0] = in ? *reinterpret_cast<const float4 *>(pb + c0 + 16 * s) : make_float4(0.f, 0.f, 0.f, 0.f);
-                }
+                load_pieces<ALIGNED>(va, pa, c0, g, d, true);
+                if (NB > 1) load_pieces<ALIGNED>(reinterpret_cast<float4 (&)[8]>(vb), pb, c0, g, d, true);
             }
             auto gram = [&](auto scaled) {
 #pragma unroll
@@ -2199,12 +2239,8 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
                 float4 (&wb)[8] = reinterpret_cast<float4 (&)[8]>(vb);
                 for (int c0 = 0; c0 < d; c0 += 128) {
                     const int n_pieces = min(8, (d - c0 + 15) >> 4);
-#pragma unroll
-                    for (int s = 0; s < 8; ++s) {
-                        const bool in = c0 + 16 * s + 4 * g + 3 < d;
-                        va[s] = in ? *reinterpret_cast<const float4 *>(pa + c0 + 16 * s) : make_float4(0.f, 0.f, 0.f, 0.f);
-                        wb[s] = in ? *reinterpret_cast<const float4 *>(pb + c0 + 16 * s) : make_float4(0.f, 0.f, 0.f, 0.f);
-                    }
+                    load_pieces<ALIGNED>(va, pa, c0, g, d, true);
+                    load_pieces<ALIGNED>(wb, pb, c0, g, d, true);
                     cross_round<0>(va, wb, n_pieces, PX[0][0]);
                     cross_round<1>(va, wb, n_pieces, PX[0][1]);
                     cross_round<2>(va, wb, n_pieces, PX[0][2]);
@@ -2346,7 +2382,7 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
 
 // ---------------------------------------------------------------------------------------
 // The local join for points whose join gathers more than 32 vectors of at most 128 coordinates
-// (d % 4 == 0, X 16-byte aligned), without a row buffer: one wave per point, the vectors pass
+// (d >= 4), without a row buffer: one wave per point, the vectors pass
 // through registers sixteen at a time.  For every tile of sixteen new rows (A) and every tile of
 // sixteen rows from it onwards (B) the wave loads both tiles as join_reg_kernel does - lane
 // (r, g) the 16-byte pieces 16 s + 4 g of row r - forms their Gram block with fp32 MFMA, filters,
@@ -2396,7 +2432,7 @@ __device__ inline TileLds tile_lds_carve(float *smem, int cap)
 }
 
 constexpr int kTileWaves = 3;      // waves per SIMD the tile join is compiled for (four would spill)
-template <bool LONG_ROWS>      // graph rows of even length, 16-byte aligned, more than 16 entries: sixteen lanes per proposal
+template <bool LONG_ROWS, bool ALIGNED>      // LONG_ROWS: graph rows of even length, 16-byte aligned, more than 16 entries: sixteen lanes per proposal
 __global__ void __launch_bounds__(EF_WAVE) __attribute__((amdgpu_waves_per_eu(kTileWaves)))
 join_tile_kernel(const float *__restrict__ X, const float *__restrict__ norms, int d, int K, u32 k_magic,
                  u32 kq_magic, int *gid, const int *__restrict__ work, const int *__restrict__ work_count, int cap, int q_cap,
@@ -2511,12 +2547,8 @@ join_tile_kernel(const float *__restrict__ X, const float *__restrict__ norms, i
         for (int bi = 0; bi < nbr; ++bi) {
             float4 va[8];
             {
-                const float *pa = X + (size_t)lds.uid[min(16 * bi + r16, m - 1)] * d + 4 * g;
-#pragma unroll
-                for (int s = 0; s < 8; ++s) {
-                    const bool in = 16 * s + 4 * g + 3 < d;      // d % 4 == 0: a piece is in or out
-                    va[s] = in ? *reinterpret_cast<const float4 *>(pa + 16 * s) : make_float4(0.f, 0.f, 0.f, 0.f);
-                }
+                const float *pa = X + (size_t)lds.uid[min(16 * bi + r16, m - 1)] * d;
+                load_pieces<ALIGNED>(va, pa, 0, g, d, true);
             }
             for (int bj = bi; bj < nbc; ++bj) {
                 float4 vb[8];
@@ -2524,12 +2556,8 @@ join_tile_kernel(const float *__restrict__ X, const float *__restrict__ norms, i
 #pragma unroll
                     for (int s = 0; s < 8; ++s) vb[s] = va[s];
                 } else {
-                    const float *pb = X + (size_t)lds.uid[min(16 * bj + r16, m - 1)] * d + 4 * g;
-#pragma unroll
-                    for (int s = 0; s < 8; ++s) {
-                        const bool in = 16 * s + 4 * g + 3 < d;
-                        vb[s] = in ? *reinterpret_cast<const float4 *>(pb + 16 * s) : make_float4(0.f, 0.f, 0.f, 0.f);
-                    }
+                    const float *pb = X + (size_t)lds.uid[min(16 * bj + r16, m - 1)] * d;
+                    load_pieces<ALIGNED>(vb, pb, 0, g, d, true);
                 }
                 floatx4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -2859,7 +2887,7 @@ constexpr size_t kLdsLimit = 160 * 1024;
 
 inline u32 q4_magic_for(int d)
 {
-    const u64 q4 = (u64)(d >> 2 ? d >> 2 : 1);
+    const u64 q4 = (u64)((d + 3) >> 2);
     return q4 == 1 ? 0xFFFFFFFFu : (u32)(((1ULL << 32) + q4 - 1) / q4);
 }
 
@@ -2920,22 +2948,34 @@ extern "C" int efanna_init_graph(const float *X, int64_t n, int32_t d, const int
     // (a block per leaf and, with leaves of 64 and rows of 100, one block per CU: sixteen waves
     // of it keep the CU busy through the loads of the rows)
     const int block_threads = 4 * EF_WAVE * ((leaf_size + 15) / 16);
-    const bool reg_ok = leaf_size <= 16 && d % 4 == 0 && ((uintptr_t)X & 15) == 0;
+    // Leaves of at most 16 points: rows in registers, with 16-byte loads at any multiple of four
+    // bytes where rows are not aligned.  (Below four coordinates a row is shorter than a load.)
+    const bool aligned = d % 4 == 0 && ((uintptr_t)X & 15) == 0;
+    const bool reg_ok = leaf_size <= 16 && (aligned || d >= 4);
     if (leaf_size > EF_WAVE) return EFANNA_EUNSUPPORTED;
+    if (!aligned && lds > kLdsLimit) return EFANNA_EUNSUPPORTED;      // (the documented limit of unaligned rows)
     if (reg_ok) {
         const size_t reg_lds = (size_t)16 * k * 8 + (size_t)16 * kCandPitch * 8 + 16 * 4;
         const size_t conquer_lds = (size_t)2 * 16 * k * 8 + (size_t)16 * kCandPitch * 8 + 16 * 16 * 4;
         for (int t = 0; t < n_trees; ++t) {
             const int32_t *perm_t = perm + (size_t)t * n, *off_t = leaf_off + (size_t)t * (max_leaves + 1);
-            init_reg_kernel<<<min(n_leaves[t], kLeafGrid), EF_WAVE, reg_lds, st>>>(
-                X, d, perm_t, off_t, n_leaves[t], k, graph, t == 0);
+            if (aligned)
+                init_reg_kernel<true><<<min(n_leaves[t], kLeafGrid), EF_WAVE, reg_lds, st>>>(
+                    X, d, perm_t, off_t, n_leaves[t], k, graph, t == 0);
+            else
+                init_reg_kernel<false><<<min(n_leaves[t], kLeafGrid), EF_WAVE, reg_lds, st>>>(
+                    X, d, perm_t, off_t, n_leaves[t], k, graph, t == 0);
             if (levels > 0) {
                 int *etab = (int *)ws;
                 classify_kernel<<<min(grid_for((size_t)n_leaves[t], kBlock / EF_WAVE), 256 * 8), kBlock, 0, st>>>(
                     X, d, perm_t, off_t, n_leaves[t], nodes + (size_t)t * (max_leaves + 1),
                     leaf_up + (size_t)t * (max_leaves + 1), conquer_depth, levels, etab);
-                conquer_kernel<<<min(n_leaves[t], kLeafGrid), EF_WAVE, conquer_lds, st>>>(
-                    X, d, perm_t, off_t, n_leaves[t], etab, levels, k, graph);
+                if (aligned)
+                    conquer_kernel<true><<<min(n_leaves[t], kLeafGrid), EF_WAVE, conquer_lds, st>>>(
+                        X, d, perm_t, off_t, n_leaves[t], etab, levels, k, graph);
+                else
+                    conquer_kernel<false><<<min(n_leaves[t], kLeafGrid), EF_WAVE, conquer_lds, st>>>(
+                        X, d, perm_t, off_t, n_leaves[t], etab, levels, k, graph);
             }
         }
         EF_HIP_CHECK(hipGetLastError());
@@ -3050,9 +3090,10 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
     // a join gathers at most K + 2L vectors: new and old sets together come from one row
     // of K entries, each reverse list adds at most L
     const int max_rows = K + 2 * L;
-    // work lists: joins of at most 16 and at most 32 vectors run from register operands (needs
-    // 16-byte aligned rows), the rest through LDS row buffers, one launch per size class
-    const bool reg_ok = (d & 3) == 0 && ((uintptr_t)X & 15) == 0;
+    // work lists: joins of at most 16 and at most 32 vectors run from register operands, the rest
+    // tile by tile or through LDS row buffers, one launch per size class
+    const bool aligned = (d & 3) == 0 && ((uintptr_t)X & 15) == 0;
+    const bool reg_ok = aligned || d >= 4;
     const int rows1 = reg_ok ? 32 : 0;
     const JoinClasses jc = join_classes(max_rows, reg_ok);
     const int n_upd_block = 2 * kRegGrid + (jc.n - 2) * kMaxLargeGrid;
@@ -3101,6 +3142,7 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
     const bool tiles = reg_ok && d <= 128;
     if (tiles && max_rows > rows1 && tile_lds_bytes(max_rows, 256) > kLdsLimit) return EFANNA_EUNSUPPORTED;
     if (!tiles && max_rows > rows1 && large_lds > kLdsLimit) return EFANNA_EUNSUPPORTED;
+    if (!aligned && shape_for(max_rows).lds > kLdsLimit) return EFANNA_EUNSUPPORTED;      // (the documented limit of unaligned rows)
     // joins of at most 16 vectors from registers (d <= 128): room for a whole point's proposals
     // (240) above the drain mark; the others drain between rounds as well (joins of 17..32
     // vectors: 256 entries measured 3 % faster than 128, 512 no better)
@@ -3160,10 +3202,9 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)bucket_lists_lds(L, n_bkt)));
     }
     if (max_rows > rows1 && tiles && tile_lds_bytes(max_rows, 256) > 64 * 1024) {
-        EF_HIP_CHECK(hipFuncSetAttribute((const void *)join_tile_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                         (int)tile_lds_bytes(max_rows, 256)));
-        EF_HIP_CHECK(hipFuncSetAttribute((const void *)join_tile_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                         (int)tile_lds_bytes(max_rows, 256)));
+        for (const void *f : {(const void *)join_tile_kernel<true, true>, (const void *)join_tile_kernel<false, true>,
+                              (const void *)join_tile_kernel<true, false>, (const void *)join_tile_kernel<false, false>})
+            EF_HIP_CHECK(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)tile_lds_bytes(max_rows, 256)));
     }
     if (max_rows > rows1 && !tiles)
         EF_HIP_CHECK(hipFuncSetAttribute(K >= 2 * EF_WIDE_PIECES ? (const void *)join_kernel<true>
@@ -3284,8 +3325,8 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
         const int mode = cross_old ? 1 + pass : 0;
         const bool timed = ev && pass == n_pass - 1;
         if (reg_ok) {
-#define EF_JOIN_REG_K(NB, ONE, LIST, KT)                                                           \
-    join_reg_kernel<NB, ONE, KT><<<reg_grid, EF_WAVE, reg_lds(16 * NB), st>>>(                     \
+#define EF_JOIN_REG_K(NB, ONE, LIST, KT, ALIGNED)                                                  \
+    join_reg_kernel<NB, ONE, KT, ALIGNED><<<reg_grid, EF_WAVE, reg_lds(16 * NB), st>>>(                     \
         X, d, K, w.work + (size_t)(LIST) * n, w.work_count + (LIST), reg_q_cap_for(16 * NB), \
         (ONE) ? margin_f16 : margin_rel, (ONE) ? thr_scale_f16 : thr_scale, u_f16, rho0_f16,       \
         w.ulist, w.ucount, max_rows, graph, w.worst, w.upd_block + (LIST) * reg_grid, mode,        \
@@ -3293,8 +3334,13 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
     // (a row length of 10 is compiled in: 3 % off the joins of 17..32 vectors)
 #define EF_JOIN_REG(NB, ONE, LIST)                                                                 \
     do {                                                                                           \
-        if (K == 10) EF_JOIN_REG_K(NB, ONE, LIST, 10);                                             \
-        else EF_JOIN_REG_K(NB, ONE, LIST, 0);                                                      \
+        if (aligned) {                                                                             \
+            if (K == 10) EF_JOIN_REG_K(NB, ONE, LIST, 10, true);                                   \
+            else EF_JOIN_REG_K(NB, ONE, LIST, 0, true);                                            \
+        } else {                                                                                   \
+            if (K == 10) EF_JOIN_REG_K(NB, ONE, LIST, 10, false);                                  \
+            else EF_JOIN_REG_K(NB, ONE, LIST, 0, false);                                           \
+        }                                                                                          \
     } while (0)
             if (d <= 128) EF_JOIN_REG(1, true, 0);
             else EF_JOIN_REG(1, false, 0);
@@ -3326,14 +3372,19 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
                 int *upd = w.upd_block + 2 * reg_grid + (c - 2) * kMaxLargeGrid;
                 const u32 km = (u32)(((1ULL << 32) + K - 1) / K);
                 const u32 kqm = K >= 4 ? (u32)(((1ULL << 32) + (K >> 2) - 1) / (K >> 2)) : 0u;
-                if (K > 16 && (K & 1) == 0 && ((uintptr_t)graph & 15) == 0)
-                    join_tile_kernel<true><<<tgrid, EF_WAVE, tl, st>>>(
-                        X, w.norms, d, K, km, kqm, w.gid, w.work + (size_t)c * n, w.work_count + c, jc.bound[c], tq,
-                        margin_rel, thr_scale, w.ulist, w.ucount, max_rows, graph, w.worst, upd, mode);
-                else
-                    join_tile_kernel<false><<<tgrid, EF_WAVE, tl, st>>>(
-                        X, w.norms, d, K, km, kqm, w.gid, w.work + (size_t)c * n, w.work_count + c, jc.bound[c], tq,
-                        margin_rel, thr_scale, w.ulist, w.ucount, max_rows, graph, w.worst, upd, mode);
+#define EF_JOIN_TILE(LONG_ROWS, ALIGNED)                                                                   \
+    join_tile_kernel<LONG_ROWS, ALIGNED><<<tgrid, EF_WAVE, tl, st>>>(                                      \
+        X, w.norms, d, K, km, kqm, w.gid, w.work + (size_t)c * n, w.work_count + c, jc.bound[c], tq,       \
+        margin_rel, thr_scale, w.ulist, w.ucount, max_rows, graph, w.worst, upd, mode)
+                const bool long_rows = K > 16 && (K & 1) == 0 && ((uintptr_t)graph & 15) == 0;
+                if (aligned) {
+                    if (long_rows) EF_JOIN_TILE(true, true);
+                    else EF_JOIN_TILE(false, true);
+                } else {
+                    if (long_rows) EF_JOIN_TILE(true, false);
+                    else EF_JOIN_TILE(false, false);
+                }
+#undef EF_JOIN_TILE
             } else if (K >= 2 * EF_WIDE_PIECES) EF_JOIN_LARGE(true, c);
             else EF_JOIN_LARGE(false, c);
         }

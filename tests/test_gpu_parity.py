@@ -411,6 +411,38 @@ def test_nndescent_more_shapes(ef, n, d, T, S, K, L, I):
     oracle.check_graph_invariants(X, ids, dists)
 
 
+@pytest.mark.parametrize("d,shift", [
+    (4, 1), (5, 0), (7, 0), (17, 0), (50, 0), (61, 0), (126, 0), (127, 0),      # one stretch of 128 coordinates
+    (129, 0), (131, 0), (255, 0), (300, 1),                                    # more than one
+    (32, 1), (128, 3), (132, 2),      # d a multiple of four, X not 16-byte aligned
+])
+def test_rows_that_are_not_16_byte_aligned(ef, d, shift):
+    """Rows at any multiple of four bytes in the register kernels: leaves of at most 16 points and of
+    more, conquer step, joins of at most 16, of 17..32 and of more vectors; the last point's vector
+    ends where the data ends."""
+    n = 2_003
+    rng = np.random.default_rng(d + shift)
+    X = rng.standard_normal((n, d)).astype(np.float32)
+    flat = torch.empty(n * d + shift, dtype=torch.float32, device="cuda:0")
+    Xd = flat[shift:].view(n, d)
+    Xd.copy_(dev(X))
+    assert d % 4 or Xd.data_ptr() % 16
+    for S, K, L in ((13, 10, 10), (9, 7, 5), (40, 30, 20)):
+        if d > 128 and K > 10:
+            continue      # (joins of more than 32 long vectors: the LDS kernel)
+        g, o = tree_nodes_equal(ef, X, 2, S, 3)
+        graph = ef.efanna_init_graph(Xd, g[0], g[1], g[2], S, K, nodes=g[3], leaf_up=g[4], tree_depth=g[5],
+                                     conquer_depth=max(0, g[5] - 3))
+        graph_equal(ef, graph, oracle.conquer_graph(X, *o, max(0, g[5] - 3), K))
+        graph = ef.efanna_init_graph(Xd, g[0], g[1], g[2], S, K)
+        want = oracle.init_graph(X, o[0], o[1], o[2], K)
+        graph_equal(ef, graph, want)
+        for it in range(2):
+            ef.efanna_nndescent(Xd, graph, 1, L, 11, first_iter=it)
+            want = oracle.nndescent(X, *want[:3], 1, L, 11, iter0=it)
+            graph_equal(ef, graph, want)
+
+
 @pytest.mark.parametrize("n,d,T,S,K,L,I", [
     (6_000, 32, 3, 8, 10, 10, 4),        # joins of at most 16 and of 17..32 vectors, rows of ten
     (4_000, 128, 2, 16, 20, 20, 3),      # tile joins (more than 32 vectors of up to 128 coordinates)
