@@ -1,7 +1,7 @@
 // Search with the finished index (Alg. 1) for gfx950: the trees give a query its first
 // candidates, the kNN graph expands them (NN-expansion).
 //
-// One wave per query, queries grid-strided over persistent waves.
+// One wave per query (a few when there are few queries), queries grid-strided over blocks.
 //   1. trees   lane t searches tree t for the N_node = P / S / T + 1 closest leaves, best
 //              bin first: going down it takes the child on the query's side of the split and
 //              puts the other aside with the priority of the branch it follows plus the
@@ -9,19 +9,25 @@
 //              it continues from the branch with the smallest (priority, link) put aside.
 //              Priorities are float64, computed with the same operations as any other
 //              implementation of this rule would use (one division, one fused multiply-add).
-//   2. pool    the members of those leaves are checked 64 at a time (one lane per point: the
-//              lane evaluates the library's fixed-order distance on its own, sixteen running
-//              sums) and merged by rank into the pool, a sorted list in LDS of at most E keys.
+//   2. pool    the members of those leaves are looked up in the set of checked points, those that
+//              are new to it wait until 64 are there, are evaluated together (four lanes per
+//              row, the library's fixed-order distance) and merged into the pool, a sorted
+//              list in LDS of at most E keys.
 //   3. expand  `iters` times: every pool member that has not been expanded yet hands in its
 //              graph neighbours; those not checked before are evaluated and merged, the pool
 //              keeping the P closest.
-// "Checked" is a hash set in the wave's slice of the workspace; an entry carries the number of
-// the query it belongs to, so the table is never cleared between queries.
+// "Checked" is a hash set in LDS; a query that fills it goes on in one in the block's slice of the
+// workspace, whose entries carry the number of the query they belong to (cleared when a block
+// first needs it, never between queries).
+// Bound: fetching the rows.  100 000 queries against 10^6 x 128, pool of 200: 37.6 GB at the fabric in 6.4 ms
+// = 5.9 TB/s, a copy reaches 6.2.  (12.5 ms with the set in memory, batches of 64 neighbours
+// evaluated whether four or sixty of them were new, and counting merges.)
 #include "common.h"
 
 namespace {
 
 constexpr int kMaxPool = 1024;
+constexpr size_t kLdsLimit = 160 * 1024;
 
 struct Branch {
     double prio;
@@ -31,14 +37,49 @@ struct Branch {
 
 inline size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// LDS of a block, offsets in words
+struct SearchLds {
+    int cur, batch, keys, expand, fid, leaves, lofs, found, shared, tab;
+};
+__host__ __device__ inline SearchLds search_lds(int d, int P, int T, int want, int max_first, int W, bool q_lds)
+{
+    SearchLds l;
+    l.cur = q_lds ? (d + 15) & ~15 : 0;
+    l.batch = l.cur + 2 * P;
+    l.keys = l.batch + 2 * EF_WAVE;
+    l.expand = l.keys + (W > 1 ? 2 * EF_WAVE * W : 0);
+    l.fid = l.expand + (P > max_first ? P : max_first);
+    l.leaves = l.fid + 5 * EF_WAVE * W;
+    l.lofs = l.leaves + T * want;
+    l.found = l.lofs + T * want + 1;
+    l.shared = l.found + T;
+    l.tab = (l.shared + 4 + 3) & ~3;
+    return l;
+}
+
 struct SearchShape {
     int want;           // leaves per tree
     int heap_cap;       // branches one tree can have put aside
     int max_first;      // most points the trees can hand in
     int table;          // hash table entries per wave (power of two)
     int waves;          // persistent waves
-    size_t heap_bytes, table_bytes, roots_bytes, bytes, lds;
+    size_t heap_bytes, table_bytes, roots_bytes, bytes;
+    int lds_slots, w;   // entries of the LDS set, waves per query
+    bool q_lds;
+    size_t lds;
+    bool ok;
 };
+
+// LDS is handed out in pieces of 1280 bytes, 128 of them per CU.
+constexpr size_t kLdsGranule = 1280;
+constexpr int kLdsGranules = 128;
+
+// Waves per query.  A query is a chain of dependent steps (down the trees, look up, fetch, merge, look
+// up ...): with few queries its length is the call's time, and more waves make every step of it
+// wider; with many the chip is full and the waves that wait for wave 0's merges are lost.  100 000 x 128,
+// pool of 100, 1 / 4 / 8 waves: 64 queries 152 / 107 / 100 us, 256: 170 / 118 / 113, 512: 180 / 125 / 173,
+// 1024: 186 / 187 / 303.
+inline int waves_per_query(int64_t nq) { return nq <= 256 ? 8 : nq <= 768 ? 4 : 1; }
 
 SearchShape search_shape(int64_t nq, int d, int T, int S, int tree_depth, int Kg, int P, int iters)
 {
@@ -49,32 +90,64 @@ SearchShape search_shape(int64_t nq, int d, int T, int S, int tree_depth, int Kg
     long most = (long)sh.max_first + (long)iters * P * Kg;
     sh.table = 64;
     while (sh.table < 2 * most) sh.table <<= 1;
-    // persistent waves, six per SIMD (the kernel takes 71 vector registers; measured on 10^5 queries:
-    // 2 per SIMD 4.0 M queries/s at P = 200, 4: 6.3 M, 6: 6.7 M, 8: 5.8 M)
+    // blocks: twice what is resident at a time evens out queries of different length
     sh.waves = (int)(nq < 1024 * 6 ? nq : 1024 * 6);
     if (sh.waves < 1) sh.waves = 1;
     sh.heap_bytes = align_up((size_t)sh.waves * T * sh.heap_cap * sizeof(Branch));
     sh.table_bytes = align_up((size_t)sh.waves * sh.table * 8);
     sh.roots_bytes = align_up((size_t)2 * T * 4);      // roots and a device copy of the leaf counts
     sh.bytes = sh.heap_bytes + sh.table_bytes + sh.roots_bytes;
-    // LDS: query, pool, batch keys, expansion list, first candidates, leaves found
-    sh.lds = (size_t)((d + 15) & ~15) * 4 + (size_t)P * 8 + 64 * 8 + (size_t)P * 4 +
-             (size_t)sh.max_first * 4 + (size_t)T * sh.want * 4 + (size_t)T * 4 + 64;
+    // The documented limit: query, pool, a batch's keys, expansion list, leaf members and leaves in 160 KB.
+    sh.ok = (size_t)((d + 15) & ~15) * 4 + (size_t)P * 8 + 64 * 8 + (size_t)P * 4 + (size_t)sh.max_first * 4 +
+                (size_t)T * sh.want * 4 + (size_t)T * 4 + 64 <= kLdsLimit;
+    if (!sh.ok) return sh;
+    sh.w = waves_per_query(nq);
+    sh.q_lds = true;
+    auto base = [&]() { return (size_t)search_lds(d, P, T, sh.want, sh.max_first, sh.w, sh.q_lds).tab * 4; };
+    sh.lds_slots = 0;
+    if (sh.w > 1) {      // few queries: LDS is there for the asking
+        sh.lds_slots = sh.w == 8 ? 8192 : 4096;
+        if (base() + (size_t)sh.lds_slots * 4 > kLdsLimit) {
+            sh.w = 1;
+            sh.lds_slots = 0;
+        }
+    }
+    if (sh.w == 1) {
+        if (base() + 256 > kLdsLimit) sh.q_lds = false;      // (vectors of forty thousand coordinates)
+        // As many blocks per CU as leave a set that few queries overflow (the number of points checked
+        // grows slowly with the pool: 370, 500, 630, 830, 1030 on average for 50 .. 800, longer lists more),
+        // a multiple of the four SIMDs: P = 200 with 12 / 11 blocks 6.4 / 8.2 ms per 10^5 queries, P = 400
+        // with 9 / 8 blocks 16.0 / 13.9.
+        const long need = 1400 + P / 2 + (Kg > 20 ? 16 * (Kg - 20) : 0);
+        for (int blocks : {12, 8, 4, 2, 1}) {
+            const size_t room = (size_t)(kLdsGranules / blocks) * kLdsGranule;
+            if (room < base() + 256) continue;
+            const long slots = (long)((room - base()) / 16 * 4);
+            sh.lds_slots = (int)(slots < 8192 ? slots : 8192);
+            if (slots >= need) break;
+        }
+    }
+    sh.lds = base() + (size_t)sh.lds_slots * 4;
     return sh;
 }
 
+struct LeafCounts {      // the trees' leaf counts, handed to the kernels by value
+    int of[EFANNA_MAX_TREES];
+};
+
 // root of every tree: the node without a parent (0 for a tree that is a single leaf)
 __global__ void find_roots_kernel(const efanna_node *__restrict__ nodes, int max_leaves, int T,
-                                  const int *__restrict__ n_leaves_dev, int *roots)
+                                  LeafCounts n_leaves, int *roots)
 {
     const int t = blockIdx.y;
     const int j = blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= T) return;
-    if (j == 0 && n_leaves_dev[t] <= 1) roots[t] = 0;
-    if (j >= 1 && j < n_leaves_dev[t] && nodes[(size_t)t * (max_leaves + 1) + j].parent < 0) roots[t] = j;
+    if (j == 0 && n_leaves.of[t] <= 1) roots[t] = 0;
+    if (j >= 1 && j < n_leaves.of[t] && nodes[(size_t)t * (max_leaves + 1) + j].parent < 0) roots[t] = j;
 }
 
-// id joins the wave's checked set; true if it was not in it.  Entries are tag << 32 | id.
+// id joins the set of checked points in the workspace; true if it was not in it.  Entries are
+// tag << 32 | id, the tag naming the query, so that one query's entries are free slots to the next.
 __device__ inline bool checked_insert(u64 *table, int mask, u32 tag, int id)
 {
     u32 h = (u32)(ef_mix64((u64)(u32)id) >> 40) & (u32)mask;
@@ -91,63 +164,101 @@ __device__ inline bool checked_insert(u64 *table, int mask, u32 tag, int id)
     }
     return false;      // a full table cannot happen: it holds twice what a query can check
 }
+// The same set in LDS (ids, -1 = free; never more than seven eighths full).  ADD: the id goes in.
+template <bool ADD>
+__device__ inline bool checked_lds(int *tab, int slots, int id)      // true: was not in it
+{
+    int h = (int)__umulhi((u32)id * 0x9E3779B1u, (u32)slots);
+    for (;;) {
+        const int v = ADD ? atomicCAS(&tab[h], -1, id) : tab[h];
+        if (v == -1) return true;
+        if (v == id) return false;
+        h = h + 1 == slots ? 0 : h + 1;
+    }
+}
 
-// The library's distance between the query (LDS) and the row of every lane's candidate (`id`, -1
-// = none), by the whole wave: sixteen candidates at a time, four lanes each.  Lane (r, g) = lane
-// r + 16 g loads the 16-byte pieces 16 s + 4 g of row r, so that four lanes fetch 64 contiguous
-// bytes and every byte fetched is used (a lane reading a whole row alone touches 64 rows per
-// load and finds their lines evicted before it comes back for the rest); it accumulates
+// The library's distance between the query (LDS) and the row of every lane's candidate (`id`, lanes
+// 0 .. cnt-1 have one), by the whole wave: sixteen candidates at a time, four lanes each.  Lane
+// (r, g) = lane r + 16 g loads the 16-byte pieces 16 s + 4 g of row r, so that four lanes fetch 64
+// contiguous bytes and every byte fetched is used (a lane reading a whole row alone touches 64 rows
+// per load and finds their lines evicted before it comes back for the rest); it accumulates
 // partial sums 4g..4g+3 of the fixed order, and the four lanes of a row add up 8 apart, 4
 // apart, 2 apart, 1 apart.  The candidate of lane 16 g + r is handled in round g by column r,
-// so the lane that owns it is among the four that end up with its distance.
-// Requires d % 4 == 0 and a 16-byte aligned X; q holds the query padded with zeros to a multiple of 16.
-__device__ inline float wave_distances(const float *q, const float *__restrict__ X, int d, int id)
+// so the lane that owns it is among the four that end up with its distance.  Two rounds' rows
+// travel together.
+// Requires d % 4 == 0 and a 16-byte aligned X; PADDED: q holds zeros from d up to a multiple of 16.
+template <bool PADDED>
+__device__ inline float wave_distances(const float *q, const float *__restrict__ X, int d, int id, int cnt)
 {
     const int lane = ef_lane(), r16 = lane & 15, g = lane >> 4;
     float mine = 0.0f;
-    for (int round = 0; round < 4; ++round) {
-        const int rid = __shfl(id, 16 * round + r16, EF_WAVE);
-        if (__ballot(rid >= 0) == 0) continue;
-        const float *row = X + (size_t)max(rid, 0) * d + 4 * g;
-        float p0 = 0.f, p1 = 0.f, p2 = 0.f, p3 = 0.f;
-        for (int c0 = 0; c0 < d; c0 += 128) {
-            float4 v[8];
+    for (int round = 0; 16 * round < cnt; round += 2) {
+        const bool both = 16 * (round + 1) < cnt;
+        const float *row[2];
+        float p[2][4];
 #pragma unroll
-            for (int s = 0; s < 8; ++s)
-                v[s] = rid >= 0 && c0 + 16 * s + 4 * g + 3 < d ? *reinterpret_cast<const float4 *>(row + c0 + 16 * s)
-                                                               : make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int h = 0; h < 2; ++h) {      // (a lane without a candidate reads row 0 along)
+            row[h] = X + (size_t)max(__shfl(id, 16 * (round + h) + r16, EF_WAVE), 0) * d;
+            p[h][0] = p[h][1] = p[h][2] = p[h][3] = 0.0f;
+        }
+        for (int c0 = 0; c0 < d; c0 += 128) {
+            float4 v[2][8];
+            const int n_whole = (d - c0) >> 4;      // sixteens that lie inside (uniform)
+            const bool tail_in = 16 * n_whole + 4 * g < d - c0;      // d % 4 == 0: a piece is in or out
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                if (h == 1 && !both) break;
+#pragma unroll
+                for (int s = 0; s < 8; ++s) {
+                    v[h][s] = make_float4(0.f, 0.f, 0.f, 0.f);
+                    if (s < n_whole || (s == n_whole && tail_in))
+                        v[h][s] = *reinterpret_cast<const float4 *>(row[h] + c0 + 4 * g + 16 * s);
+                }
+            }
 #pragma unroll
             for (int s = 0; s < 8; ++s) {
                 if (c0 + 16 * s >= d) break;
-                const float4 y = *reinterpret_cast<const float4 *>(q + c0 + 16 * s + 4 * g);
-                const bool in = c0 + 16 * s + 4 * g + 3 < d;      // beyond d both sides count as zero
-                const float d0 = in ? y.x - v[s].x : 0.f, d1 = in ? y.y - v[s].y : 0.f,
-                            d2 = in ? y.z - v[s].z : 0.f, d3 = in ? y.w - v[s].w : 0.f;
-                p0 = __builtin_fmaf(d0, d0, p0);
-                p1 = __builtin_fmaf(d1, d1, p1);
-                p2 = __builtin_fmaf(d2, d2, p2);
-                p3 = __builtin_fmaf(d3, d3, p3);
+                const int j = c0 + 16 * s + 4 * g;      // (zeros beyond d on both sides)
+                const float4 y = PADDED || j + 3 < d ? *reinterpret_cast<const float4 *>(q + j) : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    if (h == 1 && !both) break;
+                    const float d0 = y.x - v[h][s].x, d1 = y.y - v[h][s].y, d2 = y.z - v[h][s].z, d3 = y.w - v[h][s].w;
+                    p[h][0] = __builtin_fmaf(d0, d0, p[h][0]);
+                    p[h][1] = __builtin_fmaf(d1, d1, p[h][1]);
+                    p[h][2] = __builtin_fmaf(d2, d2, p[h][2]);
+                    p[h][3] = __builtin_fmaf(d3, d3, p[h][3]);
+                }
             }
         }
-        p0 += __shfl_xor(p0, 32, EF_WAVE);
-        p1 += __shfl_xor(p1, 32, EF_WAVE);
-        p2 += __shfl_xor(p2, 32, EF_WAVE);
-        p3 += __shfl_xor(p3, 32, EF_WAVE);
-        p0 += __shfl_xor(p0, 16, EF_WAVE);
-        p1 += __shfl_xor(p1, 16, EF_WAVE);
-        p2 += __shfl_xor(p2, 16, EF_WAVE);
-        p3 += __shfl_xor(p3, 16, EF_WAVE);
-        const float dist = (p0 + p2) + (p1 + p3);
-        if (g == round) mine = dist;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) p[h][k] += __shfl_xor(p[h][k], 32, EF_WAVE);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) p[h][k] += __shfl_xor(p[h][k], 16, EF_WAVE);
+            const float dist = (p[h][0] + p[h][2]) + (p[h][1] + p[h][3]);
+            if (g == round + h) mine = dist;
+        }
     }
     return mine;
 }
 
+// orders the LDS accesses of one wave (its LDS operations complete in program order)
+__device__ inline void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Merge the wave's batch (one key per lane, ~0 = none) into the sorted pool (count keys, room for
 // cap), in place.  Returns the new count.  Keys are distinct.
-// The batch is packed to the front of `batch` first: usually only a few of its keys are there
-// at all (the others were checked before or lie beyond a full pool).  Pool members below the
-// smallest fresh key stay where they are; the others move up by the number of fresh keys below
+// The fresh keys are packed to the front of `batch` and ranked among each other (every lane looks at
+// all of them, eight at a time), and put in order; a pool member then finds the number of fresh keys
+// below it with a binary search, a fresh key the number of pool members below it.  (Counting for
+// the pool members as well was two thirds of the search's instructions: P = 200 9.4 -> 8.0 ms
+// per 10^5 queries, P = 800 41 -> 31.8.)  Pool members below the smallest fresh key stay where
+// they are; the others move up by the number of fresh keys below
 // them, 64 at a time from the top (a chunk is read before it is written, and it only writes at
 // or above its own places), and the fresh keys take the places left free.
 __device__ inline int pool_merge(u64 *pool, int count, int cap, u64 key, u64 *batch)
@@ -155,9 +266,15 @@ __device__ inline int pool_merge(u64 *pool, int count, int cap, u64 key, u64 *ba
     const int lane = ef_lane();
     const u64 there = __ballot(key != ~0ULL);
     const int fresh = __popcll(there);
+    if (lane >= fresh) batch[lane] = ~0ULL;
     if (key != ~0ULL) batch[__popcll(there & ((1ULL << lane) - 1))] = key;
-    __syncthreads();
-    int lo = count, pos = 0;
+    wave_sync();
+    int rank = 0;
+    for (int o = 0; o < fresh; o += 8) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) rank += batch[o + k] < key ? 1 : 0;
+    }
+    int lo = count;
     if (key != ~0ULL) {
         int hi = count;
         lo = 0;
@@ -166,61 +283,80 @@ __device__ inline int pool_merge(u64 *pool, int count, int cap, u64 key, u64 *ba
             if (pool[mid] < key) lo = mid + 1;
             else hi = mid;
         }
-        pos = lo;
-        for (int o = 0; o < fresh; ++o) pos += batch[o] < key ? 1 : 0;
     }
-    int first = lo;                  // the lowest place any fresh key takes
-    for (int m = 32; m >= 1; m >>= 1) first = min(first, __shfl_xor(first, m, EF_WAVE));
+    wave_sync();
+    if (key != ~0ULL) batch[rank] = key;
+    wave_sync();
+    const int first = __shfl(lo, __ffsll((unsigned long long)__ballot(key != ~0ULL && rank == 0)) - 1, EF_WAVE);
+    int step0 = 1;                   // a power of two above half the fresh keys
+    while (2 * step0 <= fresh) step0 <<= 1;
     for (int top = count; top > first; top -= EF_WAVE) {
         const int j = top - EF_WAVE + lane;
         u64 e = 0;
         int up = 0;
         if (j >= first) {
             e = pool[j];
-            for (int o = 0; o < fresh; ++o) up += batch[o] < e ? 1 : 0;
+            for (int step = step0; step > 0; step >>= 1)
+                if (up + step <= EF_WAVE && batch[up + step - 1] < e) up += step;
         }
-        __syncthreads();             // the chunk is in registers before any of it is overwritten
+        wave_sync();                 // the chunk is in registers before any of it is overwritten
         if (j >= first && j + up < cap) pool[j + up] = e;
+        wave_sync();
     }
-    if (key != ~0ULL && pos < cap) pool[pos] = key;
-    __syncthreads();
+    if (key != ~0ULL && lo + rank < cap) pool[lo + rank] = key;
+    wave_sync();
     return min(cap, count + fresh);
 }
 
-__global__ void __launch_bounds__(EF_WAVE)
+// W waves per query.  The waves of a block look candidates up together and evaluate 64 each; wave 0
+// searches the trees and keeps the pool.
+// Q_LDS: the query sits in LDS (else, for vectors that fill it, it is read from memory every time).
+template <int W, bool Q_LDS>
+__global__ void __launch_bounds__(W * EF_WAVE) __attribute__((amdgpu_waves_per_eu(3)))
 search_kernel(const float *__restrict__ X, int d, int n, const int *__restrict__ perm,
-              const int *__restrict__ leaf_off, int max_leaves, const int *__restrict__ n_leaves_dev,
+              const int *__restrict__ leaf_off, int max_leaves, LeafCounts n_leaves,
               const efanna_node *__restrict__ nodes, const int *__restrict__ roots, int T, int S,
-              const int *__restrict__ graph_ids, int Kg, const float *__restrict__ queries, int nq,
-              int K, int P, int E, int iters, int want, int heap_cap, int max_first, int table_size,
+              const int *__restrict__ graph_ids, int Kg, u32 kg_magic, const float *__restrict__ queries, int nq,
+              int K, int P, int E, int iters, int want, int heap_cap, int max_first, int table_size, int lds_slots,
               Branch *heaps, u64 *tables, int *out_ids, float *out_dists, int *out_checked)
 {
     extern __shared__ __align__(16) float smem[];
+    constexpr int kThreads = W * EF_WAVE;
+    const SearchLds at = search_lds(d, P, T, want, max_first, W, Q_LDS);
+    u64 *cur = (u64 *)(smem + at.cur);                 // [P] the pool, ascending
+    u64 *batch = (u64 *)(smem + at.batch);             // [64]
+    u64 *keys = (u64 *)(smem + at.keys);               // [64 W] evaluated candidates on their way to wave 0 (W > 1)
+    int *expand = (int *)smem + at.expand;             // [P] members whose neighbours are next; before that
+    int *first = expand;                               // [max_first] members of the leaves found
+    int *fid = (int *)smem + at.fid;                   // [320 W] candidates waiting to be evaluated
+    int *leaves = (int *)smem + at.leaves;             // [T][want] leaves, then where they start
+    int *lofs = (int *)smem + at.lofs;                 // [T][want] where their members start in `first`, and the end
+    int *n_found = (int *)smem + at.found;             // [T]
+    int *shared = (int *)smem + at.shared;             // [4] waiting candidates, pool members, members to expand, leaf members
+    int *tab = (int *)smem + at.tab;                   // [lds_slots] points checked (the trees' branches before that)
     const int dq = (d + 15) & ~15;
-    float *q = smem;                                   // [dq]
-    u64 *cur = (u64 *)(smem + dq);                     // [P] the pool, ascending
-    u64 *batch = cur + P;                              // [64]
-    int *expand = (int *)(batch + EF_WAVE);            // [P]
-    int *first = expand + P;                           // [max_first] members of the leaves found
-    int *leaves = first + max_first;                   // [T][want]
-    int *n_found = leaves + T * want;                  // [T]
-    const int lane = threadIdx.x;
+    const int tid = threadIdx.x, lane = ef_lane(), wave = tid / EF_WAVE;
     u64 *table = tables + (size_t)blockIdx.x * table_size;
     const int mask = table_size - 1;
+    const int lds_limit = lds_slots - lds_slots / 8;
+    bool table_clear = false;      // the block's table in the workspace has been cleared
+    const bool lds_heap = (size_t)T * heap_cap * sizeof(Branch) <= (size_t)lds_slots * 4;
     for (int qi = blockIdx.x; qi < nq; qi += gridDim.x) {
         const u32 tag = (u32)qi + 1u;
         __syncthreads();                  // the previous query's LDS reads are done
-        for (int j = lane; j < dq; j += EF_WAVE) q[j] = j < d ? queries[(size_t)qi * d + j] : 0.0f;
+        const float *q = Q_LDS ? smem : queries + (size_t)qi * d;      // in LDS: [dq], zeros from d on
+        if (Q_LDS)
+            for (int j = tid; j < dq; j += kThreads) smem[j] = j < d ? queries[(size_t)qi * d + j] : 0.0f;
         __syncthreads();
         // ---- 1. trees: lane t searches tree t -----------------------------------------------
-        for (int t = lane; t < T; t += EF_WAVE) {
+        for (int t = tid; t < T; t += kThreads) {
             const efanna_node *nd_t = nodes + (size_t)t * (max_leaves + 1);
-            const int last = n_leaves_dev[t] - 1;
-            Branch *heap = heaps + ((size_t)blockIdx.x * T + t) * heap_cap;
+            const int last = n_leaves.of[t] - 1;
+            Branch *heap = lds_heap ? (Branch *)tab + t * heap_cap : heaps + ((size_t)blockIdx.x * T + t) * heap_cap;
             int n_heap = 0, found = 0;
             int link = last <= 0 ? ~0 : roots[t];
             double prio = 0.0;
-            while (found < want) {
+            for (;;) {
                 for (int steps = 0; link >= 0 && steps < 4096; ++steps) {      // down to a leaf
                     const efanna_node nd = nd_t[min(link, last)];
                     bool left = true;
@@ -239,7 +375,7 @@ search_kernel(const float *__restrict__ X, int d, int n, const int *__restrict__
                     link = nd.child[left ? 0 : 1];
                 }
                 leaves[t * want + found++] = link >= 0 ? 0 : min(~link, max(last, 0));
-                if (n_heap == 0) break;
+                if (found == want || n_heap == 0) break;
                 int best = 0;
                 double bp = heap[0].prio;
                 int bl = heap[0].link;
@@ -260,81 +396,169 @@ search_kernel(const float *__restrict__ X, int d, int n, const int *__restrict__
             n_found[t] = found;
         }
         __syncthreads();
-        // ---- 2. first pool: the members of the leaves found, 64 at a time ---------------------
-        int n_first = 0;
-        for (int t = 0; t < T; ++t)
-            for (int f = 0; f < n_found[t]; ++f) {
-                const int leaf = leaves[t * want + f];
-                const int b = leaf_off[(size_t)t * (max_leaves + 1) + leaf];
-                const int s = min(leaf_off[(size_t)t * (max_leaves + 1) + leaf + 1] - b, S);
-                for (int r = lane; r < s; r += EF_WAVE) first[n_first + r] = perm[(size_t)t * n + b + r];
-                n_first += s;
+        // ---- 2. the members of the leaves found; nothing is checked yet -----------------------
+        for (int j = tid; j < lds_slots / 4; j += kThreads) reinterpret_cast<int4 *>(tab)[j] = make_int4(-1, -1, -1, -1);
+        const int n_lists = T * want;
+        if (wave == 0) {
+            int end = 0;
+            for (int l0 = 0; l0 < n_lists; l0 += EF_WAVE) {
+                const int l = l0 + lane;
+                int b = 0, s = 0;
+                if (l < n_lists) {
+                    const int t = l / want;
+                    if (l - t * want < n_found[t]) {
+                        const int *off = leaf_off + (size_t)t * (max_leaves + 1) + leaves[l];
+                        b = off[0];
+                        s = max(0, min(off[1] - b, S));
+                    }
+                }
+                const int upto = end + ef_wave_scan_i32(s);
+                if (l < n_lists) {
+                    leaves[l] = b;
+                    lofs[l] = upto - s;
+                }
+                end = __shfl(upto, EF_WAVE - 1, EF_WAVE);
             }
-        __syncthreads();
-        int count = 0, checked = 0;
-        for (int c0 = 0; c0 < n_first; c0 += EF_WAVE) {
-            u64 key = ~0ULL;
-            int cand = -1;
-            if (c0 + lane < n_first) {
-                const int id = first[c0 + lane];
-                if (id >= 0 && id < n && checked_insert(table, mask, tag, id)) cand = id;
+            if (lane == 0) {
+                lofs[n_lists] = end;
+                shared[0] = 0;
             }
-            const float dist = wave_distances(q, X, d, cand);
-            if (cand >= 0) key = ef_pack(dist, cand, 1);
-            checked += __popcll(__ballot(key != ~0ULL));
-            if (count == E && key >= cur[E - 1]) key = ~0ULL;      // a full pool takes nothing beyond its last key
-            if (__ballot(key != ~0ULL) == 0) continue;
-            count = pool_merge(cur, count, E, key, batch);
         }
-        // ---- 3. NN-expansion ---------------------------------------------------------------------
-        for (int it = 0; it < iters; ++it) {
-            // members not expanded yet (mark bit set) lose the mark and go to the list
-            int n_exp = 0;
-            for (int j0 = 0; j0 < count; j0 += EF_WAVE) {
-                const int j = j0 + lane;
-                const u64 e = j < count ? cur[j] : 0;
-                const bool take = j < count && (e & 1);
-                const u64 bal = __ballot(take);
-                if (take) {
-                    cur[j] = e & ~1ULL;
-                    expand[n_exp + __popcll(bal & ((1ULL << lane) - 1))] = ef_id(e);
+        __syncthreads();
+        for (int l = tid >> 4; l < n_lists; l += kThreads / 16) {
+            const int at0 = lofs[l], s = lofs[l + 1] - at0;
+            const int *src = perm + (size_t)(l / want) * n + leaves[l];
+            for (int r = tid & 15; r < s; r += 16) first[at0 + r] = src[r];
+        }
+        __syncthreads();
+        int count = 0, checked = 0, in_lds = 0;      // count: kept by wave 0
+        bool spilled = false;                        // the LDS set is full: further points go to the workspace's
+        int waiting = 0;
+        // ---- 3. the first pool from the leaves' members (it = -1), then NN-expansion -----------------
+        for (int it = -1; it < iters; ++it) {
+            int total = lofs[n_lists];
+            const int cap = it < 0 ? E : P;
+            if (it >= 0) {
+                // members not expanded yet (mark bit set) lose the mark and go to the list
+                int n_exp = 0;
+                if (wave == 0) {
+                    for (int j0 = 0; j0 < count; j0 += EF_WAVE) {
+                        const int j = j0 + lane;
+                        const u64 e = j < count ? cur[j] : 0;
+                        const bool take = j < count && (e & 1);
+                        const u64 bal = __ballot(take);
+                        if (take) {
+                            cur[j] = e & ~1ULL;
+                            expand[n_exp + __popcll(bal & ((1ULL << lane) - 1))] = ef_id(e);
+                        }
+                        n_exp += __popcll(bal);
+                    }
+                    if (W > 1 && lane == 0) shared[1] = n_exp;
                 }
-                n_exp += __popcll(bal);
+                __syncthreads();
+                if (W > 1) n_exp = shared[1];
+                if (n_exp == 0) break;
+                total = n_exp * Kg;
             }
-            __syncthreads();
-            if (n_exp == 0) break;
-            const int total = n_exp * Kg;
-            for (int f0 = 0; f0 < total; f0 += EF_WAVE) {
-                u64 key = ~0ULL;
-                int cand = -1;
-                const int f = f0 + lane;
-                if (f < total) {
-                    const int src = expand[f / Kg];
-                    const int id = graph_ids[(size_t)src * Kg + f % Kg];
-                    if (id >= 0 && id < n && checked_insert(table, mask, tag, id)) cand = id;
+            // Looks the candidates up, four per thread at a time, and evaluates those that were never
+            // checked before in full batches: most neighbours of neighbours were (four in five at a
+            // pool of 200), and the rows of a batch cost the same however many of its lanes have one.
+            for (int f0 = 0; f0 < total; f0 += 4 * kThreads) {
+                if (!spilled && in_lds + min(total - f0, 4 * kThreads) > lds_limit) {
+                    spilled = true;
+                    if (!table_clear) {
+                        for (int j = tid; j < table_size; j += kThreads) table[j] = 0;
+                        table_clear = true;
+                        __threadfence_block();
+                        __syncthreads();
+                    }
                 }
-                const float dist = wave_distances(q, X, d, cand);
-                if (cand >= 0) key = ef_pack(dist, cand, 1);
-                checked += __popcll(__ballot(key != ~0ULL));
-                if (count == P && key >= cur[P - 1]) key = ~0ULL;      // a full pool takes nothing beyond its last key
-                if (__ballot(key != ~0ULL) == 0) continue;
-                count = pool_merge(cur, count, P, key, batch);
+                int id[4];
+                u64 new_mask[4];
+                int n_new = 0;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int f = f0 + k * kThreads + tid;
+                    id[k] = -1;
+                    if (f < total) {
+                        if (it < 0) {
+                            id[k] = first[f];
+                        } else {
+                            const int src = Kg == 1 ? f : (int)(((u64)(u32)f * kg_magic) >> 32);
+                            id[k] = graph_ids[(size_t)expand[src] * Kg + (f - src * Kg)];
+                        }
+                    }
+                }
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    bool fresh = false;
+                    if (id[k] >= 0 && id[k] < n) {
+                        if (!spilled)
+                            fresh = checked_lds<true>(tab, lds_slots, id[k]);
+                        else
+                            fresh = checked_lds<false>(tab, lds_slots, id[k]) && checked_insert(table, mask, tag, id[k]);
+                    }
+                    new_mask[k] = __ballot(fresh);
+                    n_new += __popcll(new_mask[k]);
+                }
+                int to = waiting;
+                if (W > 1) {
+                    if (lane == 0 && n_new) to = atomicAdd(&shared[0], n_new);
+                    to = __shfl(to, 0, EF_WAVE);
+                }
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    if ((new_mask[k] >> lane) & 1) fid[to + __popcll(new_mask[k] & ((1ULL << lane) - 1))] = id[k];
+                    to += __popcll(new_mask[k]);
+                }
+                __syncthreads();
+                const int now = W > 1 ? shared[0] : waiting + n_new;
+                checked += now - waiting;
+                if (!spilled) in_lds += now - waiting;
+                waiting = now;
+                const bool last = f0 + 4 * kThreads >= total;
+                while (waiting >= kThreads || (last && waiting > 0)) {
+                    // up to 64 candidates per wave are evaluated and merged into the pool
+                    const int cnt = min(waiting, kThreads), mine = min(cnt - EF_WAVE * wave, EF_WAVE);
+                    waiting -= cnt;
+                    u64 key = ~0ULL;
+                    if (mine > 0) {
+                        const int c = lane < mine ? fid[waiting + EF_WAVE * wave + lane] : -1;
+                        const float dist = wave_distances<Q_LDS>(q, X, d, c, mine);
+                        if (c >= 0) key = ef_pack(dist, c, 1);
+                    }
+                    if (W > 1) {
+                        keys[tid] = key;
+                        __syncthreads();
+                    }
+                    if (wave == 0)
+                        for (int c0 = 0; c0 < cnt; c0 += EF_WAVE) {
+                            if (W > 1) key = keys[c0 + lane];
+                            if (count == cap && key >= cur[cap - 1]) key = ~0ULL;      // a full pool takes nothing beyond its last key
+                            if (__ballot(key != ~0ULL) != 0) count = pool_merge(cur, count, cap, key, batch);
+                        }
+                    __syncthreads();
+                }
+                if (W > 1) {
+                    __syncthreads();      // everyone has read the count
+                    if (tid == 0) shared[0] = waiting;
+                    __syncthreads();
+                }
             }
         }
         // ---- result: the K closest --------------------------------------------------------------
-        for (int c = lane; c < K; c += EF_WAVE) {
+        if (W > 1) {
+            if (tid == 0) shared[1] = count;
+            __syncthreads();
+            count = shared[1];
+        }
+        for (int c = tid; c < K; c += kThreads) {
             const bool live = c < count;
             out_ids[(size_t)qi * K + c] = live ? ef_id(cur[c]) : -1;
             out_dists[(size_t)qi * K + c] = live ? __uint_as_float(ef_dist_bits(cur[c])) : __uint_as_float(EF_INF_BITS);
         }
-        if (out_checked && lane == 0) out_checked[qi] = checked;
+        if (out_checked && tid == 0) out_checked[qi] = checked;
     }
-}
-
-__global__ void zero_tables_kernel(u64 *p, size_t count)
-{
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += (size_t)gridDim.x * blockDim.x)
-        p[i] = 0;
 }
 
 }  // namespace
@@ -369,26 +593,34 @@ extern "C" int efanna_search(const float *X, int64_t n, int32_t d, const int32_t
     if (pool > kMaxPool || (d & 3) || ((uintptr_t)X & 15) || ((uintptr_t)queries & 15) || tree_depth > 4000)
         return EFANNA_EUNSUPPORTED;
     const SearchShape sh = search_shape(nq, d, n_trees, leaf_size, tree_depth, graph_k, pool, iters);
-    if (sh.lds > 160 * 1024) return EFANNA_EUNSUPPORTED;
+    if (!sh.ok) return EFANNA_EUNSUPPORTED;
     if (!ws || ((uintptr_t)ws & 255) || ws_bytes < sh.bytes) return EFANNA_EWORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     char *base = (char *)ws;
     Branch *heaps = (Branch *)base;
     u64 *tables = (u64 *)(base + sh.heap_bytes);
     int *roots = (int *)(base + sh.heap_bytes + sh.table_bytes);
-    int *n_leaves_dev = roots + n_trees;
-    EF_HIP_CHECK(hipMemcpyAsync(n_leaves_dev, n_leaves, (size_t)n_trees * 4, hipMemcpyHostToDevice, st));
-    zero_tables_kernel<<<1024, 256, 0, st>>>(tables, (size_t)sh.waves * sh.table);
+    LeafCounts counts = {};
+    for (int t = 0; t < n_trees; ++t) counts.of[t] = n_leaves[t];
     find_roots_kernel<<<dim3((unsigned)((max_leaves + 255) / 256), (unsigned)n_trees), 256, 0, st>>>(
-        nodes, max_leaves, n_trees, n_leaves_dev, roots);
-    EF_HIP_CHECK(hipFuncSetAttribute((const void *)search_kernel,
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh.lds));
-    search_kernel<<<sh.waves, EF_WAVE, sh.lds, st>>>(
-        X, d, (int)n, perm, leaf_off, max_leaves, n_leaves_dev, nodes, roots, n_trees, leaf_size, graph_ids,
-        graph_k, queries, (int)nq, k, pool, expand, iters, sh.want, sh.heap_cap, sh.max_first, sh.table,
-        heaps, tables, ids, dists, checked);
+        nodes, max_leaves, n_trees, counts, roots);
+    const u32 kg_magic = (u32)(((1ULL << 32) + graph_k - 1) / graph_k);      // f / graph_k for f < 2^32 / graph_k
+#define EF_SEARCH(W, Q_LDS)                                                                              \
+    do {                                                                                                 \
+        EF_HIP_CHECK(hipFuncSetAttribute((const void *)search_kernel<W, Q_LDS>,                          \
+                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh.lds));      \
+        search_kernel<W, Q_LDS><<<sh.waves, (W) * EF_WAVE, sh.lds, st>>>(                                \
+            X, d, (int)n, perm, leaf_off, max_leaves, counts, nodes, roots, n_trees, leaf_size,          \
+            graph_ids, graph_k, kg_magic, queries, (int)nq, k, pool, expand, iters, sh.want,             \
+            sh.heap_cap, sh.max_first, sh.table, sh.lds_slots, heaps, tables, ids, dists, checked);      \
+    } while (0)
+    if (!sh.q_lds) EF_SEARCH(1, false);
+    else if (sh.w == 1) EF_SEARCH(1, true);
+    else if (sh.w == 4) EF_SEARCH(4, true);
+    else EF_SEARCH(8, true);
+#undef EF_SEARCH
     EF_HIP_CHECK(hipGetLastError());
-    // the copy of n_leaves reads host memory the caller may reuse: wait for it
+    // (the call is documented to wait)
     EF_HIP_CHECK(hipStreamSynchronize(st));
     return EFANNA_OK;
 }

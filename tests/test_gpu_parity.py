@@ -574,6 +574,30 @@ def test_search_bit_exact(ef, name, n, T, S, K, P, E, I):
     assert np.array_equal(host(got[2]), want[2])
 
 
+@pytest.mark.parametrize("n,d,T,S,K,P,E,I,nq", [
+    (5_000, 32, 4, 8, 10, 50, 20, 3, 1),         # eight waves per query, one query
+    (5_000, 100, 4, 8, 10, 50, 20, 3, 256),      # ... and the most
+    (5_000, 32, 4, 8, 10, 50, 20, 3, 257),       # four
+    (5_000, 36, 3, 8, 10, 70, 30, 3, 769),       # one; a ragged last piece of the vectors
+    (5_000, 132, 3, 8, 10, 200, 64, 2, 900),     # more than one stretch of 128 coordinates
+    (9_000, 8, 4, 16, 64, 512, 200, 3, 20),      # more points checked than the sets in LDS hold: eight waves,
+    (9_000, 8, 4, 16, 64, 512, 200, 3, 300),     # four,
+    (9_000, 8, 4, 16, 64, 512, 200, 3, 800),     # one
+    (2_000, 4, 20, 5, 6, 1024, 1024, 2, 10),     # the largest pool, several leaves of many trees
+    (40, 40_500, 1, 4, 3, 10, 8, 2, 5),          # vectors that leave no room in LDS for a copy of the query
+])
+def test_search_batches_and_sets_bit_exact(ef, n, d, T, S, K, P, E, I, nq):
+    rng = np.random.default_rng(n + nq)
+    X = rng.standard_normal((n, d)).astype(np.float32)
+    Xd, g, o, ids = build_index(ef, X, T, S, K, 0)
+    Q = rng.standard_normal((nq, d)).astype(np.float32)
+    got = ef.efanna_search(Xd, g[0], g[1], g[2], g[3], g[5], S, ids, dev(Q), K, P, E, I)
+    want = oracle.search(X, o[0], o[1], o[2], o[3], S, host(ids), Q, K, P, E, I)
+    assert np.array_equal(host(got[0]), want[0])
+    assert host(got[1]).tobytes() == want[1].tobytes()
+    assert np.array_equal(host(got[2]), want[2])
+
+
 def test_search_edge_cases(ef):
     rng = np.random.default_rng(4)
     X = rng.standard_normal((50, 8)).astype(np.float32)            # every tree a single leaf
