@@ -140,50 +140,135 @@ __device__ inline bool var_before(const VarKey &a, const VarKey &b)
     return a.v > b.v || (a.v == b.v && a.j < b.j);
 }
 
+// The variance of dimension j of the sample, slowly: any values.
+__device__ inline __int128 variance_any(const float *__restrict__ X, int d, const int *ids, int m, int j)
+{
+    long long s1 = 0;
+    __int128 s2 = 0;
+    for (int p = 0; p < m; ++p) {
+        const long long q = ef_quantise(X[(size_t)ids[p] * d + j]);
+        s1 += q;
+        s2 += (__int128)q * q;
+    }
+    return (__int128)m * s2 - (__int128)s1 * s1;
+}
+
+// What bounds this: the rows of the samples, up to 100 whole rows per node and level.  Two dimensions
+// per lane and eight rows are fetched together (one row at a time left a node waiting for a hundred
+// memory round trips in turn), and sums are taken of q - q(first row), which leaves the variance as
+// it is and keeps them in 64 bits unless the values of a dimension lie 2^28 steps (256.0) or more
+// apart; then that wave falls back to 128-bit sums.  Scaling by 2^20 and rounding are exact in
+// float32 as well: a power of two, and an integer of at most 24 bits.
+// 10^6 x 128, eight trees of leaves of 16: the in-LDS finish 14.9 -> 9.0 ms, the levels above 3.05 -> 0.55.
 __device__ inline int variance_dim_wave(const float *__restrict__ X, int d, const int *ids, int cnt, u64 draw)
 {
     const int lane = ef_lane();
     const int m = cnt < kVarSample ? cnt : kVarSample;
+    const int id_lo = ids[min(lane, m - 1)], id_hi = m > EF_WAVE ? ids[min(EF_WAVE + lane, m - 1)] : 0;
     VarKey top[kVarDims];
 #pragma unroll
     for (int r = 0; r < kVarDims; ++r) {
         top[r].v = -1;      // below every variance
         top[r].j = 0x7FFFFFFF;
     }
-    for (int j = lane; j < d; j += EF_WAVE) {
-        long long s1 = 0;
-        __int128 s2 = 0;
-        for (int p = 0; p < m; ++p) {
-            const long long q = ef_quantise(X[(size_t)ids[p] * d + j]);
-            s1 += q;
-            s2 += (__int128)q * q;
-        }
-        VarKey c;
-        c.v = (__int128)m * s2 - (__int128)s1 * s1;
-        c.j = j;
+    for (int j0 = 0; j0 < d; j0 += 2 * EF_WAVE) {
+        const int j[2] = {j0 + lane, j0 + EF_WAVE + lane};
+        const int jc[2] = {min(j[0], d - 1), min(j[1], d - 1)};      // (lanes beyond d read along)
+        const bool second = j0 + EF_WAVE < d;
+        float y0[2], widest[2] = {0.f, 0.f};
+        int q0[2];
+        long long s1[2] = {0, 0}, s2[2] = {0, 0};
+        for (int p0 = 0; p0 < m; p0 += 8) {
+            float x[2][8];
 #pragma unroll
-        for (int r = 0; r < kVarDims; ++r)
-            if (var_before(c, top[r])) {
-                const VarKey t = top[r];
-                top[r] = c;
-                c = t;
+            for (int u = 0; u < 8; ++u) {
+                const int p = min(p0 + u, m - 1);
+                const int id = p < EF_WAVE ? __builtin_amdgcn_readlane(id_lo, p) : __builtin_amdgcn_readlane(id_hi, p - EF_WAVE);
+                const float *row = X + (size_t)id * d;
+                x[0][u] = row[jc[0]];
+                x[1][u] = second ? row[jc[1]] : 0.f;
             }
-    }
-    const int n_top = d < kVarDims ? d : kVarDims;
-    const int want = (int)(draw % (u64)n_top);
-    int chosen = 0;
-    for (int r = 0; r < n_top; ++r) {      // (uniform)
-        VarKey best = top[0];
-        for (int o = EF_WAVE / 2; o >= 1; o >>= 1) {
-            VarKey other;
-            const u64 lo = __shfl_xor((u64)best.v, o, EF_WAVE);
-            const u64 hi = __shfl_xor((u64)(best.v >> 64), o, EF_WAVE);
-            other.v = (__int128)(((unsigned __int128)hi << 64) | lo);
-            other.j = __shfl_xor(best.j, o, EF_WAVE);
-            if (var_before(other, best)) best = other;
+            if (p0 == 0) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    y0[h] = __builtin_rintf(x[h][0] * 1048576.0f);
+                    q0[h] = (int)y0[h];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                if (p0 + u >= m) break;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const float y = __builtin_rintf(x[h][u] * 1048576.0f);
+                    const int dq = (int)y - q0[h];
+                    widest[h] = fmaxf(widest[h], fabsf(y - y0[h]));
+                    s1[h] += dq;
+                    s2[h] += (long long)dq * dq;
+                }
+            }
         }
-        if (r == want) chosen = best.j;
-        if (top[0].j == best.j) {      // the winner's lane moves on to its next one
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            if (h == 1 && !second) break;
+            VarKey c;
+            c.j = j[h];
+            // |dq| < 2^28 and a hundred of them: the sum of squares stays below 2^63; |q| < 2^30: (int)y is exact
+            const bool narrow = fabsf(y0[h]) < 536870912.0f && widest[h] < 268435456.0f;
+            const u64 a1 = (u64)(s1[h] < 0 ? -s1[h] : s1[h]);
+            c.v = (__int128)((unsigned __int128)(u64)m * (u64)s2[h] - (unsigned __int128)a1 * a1);
+            if (!narrow) c.v = variance_any(X, d, ids, m, jc[h]);
+            if (j[h] >= d) continue;
+            if (j0 == 0 && h == 0) {      // (up to 128 dimensions a lane has two: one comparison puts them in order)
+                top[0] = c;
+            } else if (j0 == 0) {
+                top[1] = c;
+                if (var_before(c, top[0])) {
+                    top[1] = top[0];
+                    top[0] = c;
+                }
+            } else {
+#pragma unroll
+                for (int r = 0; r < kVarDims; ++r)
+                    if (var_before(c, top[r])) {
+                        const VarKey t = top[r];
+                        top[r] = c;
+                        c = t;
+                    }
+            }
+        }
+    }
+    const int want = d < kVarDims ? (int)(draw % (u64)d) : (int)(draw % (u64)kVarDims);
+    int chosen = 0;
+    for (int r = 0; r <= want; ++r) {      // (uniform)
+        // the largest of the lanes' best: by the leading 64 bits of variances below 2^71 (all bits of
+        // them where one is larger), the rare ties among those exactly
+        const u64 head = top[0].v < 0 ? 0 : (u64)(top[0].v >> 64) >= 128 ? ~0ULL : (u64)(top[0].v >> 7);
+        u64 best = head;
+        for (int o = EF_WAVE / 2; o >= 1; o >>= 1) {
+            const u64 other = __shfl_xor(best, o, EF_WAVE);
+            best = other > best ? other : best;
+        }
+        u64 tied = __ballot(head == best && top[0].v >= 0);
+        int winner = __ffsll((unsigned long long)tied) - 1;
+        if (tied & (tied - 1)) {
+            VarKey w;
+            w.v = -1;
+            w.j = 0x7FFFFFFF;
+            for (u64 left = tied; left; left &= left - 1) {
+                const int l = __ffsll((unsigned long long)left) - 1;
+                VarKey k;
+                const u64 lo = __shfl((u64)top[0].v, l, EF_WAVE), hi = __shfl((u64)(top[0].v >> 64), l, EF_WAVE);
+                k.v = (__int128)(((unsigned __int128)hi << 64) | lo);
+                k.j = __shfl(top[0].j, l, EF_WAVE);
+                if (var_before(k, w)) {
+                    w = k;
+                    winner = l;
+                }
+            }
+        }
+        chosen = __shfl(top[0].j, winner, EF_WAVE);
+        if (lane == winner) {      // the winner's lane moves on to its next one
 #pragma unroll
             for (int q = 0; q + 1 < kVarDims; ++q) top[q] = top[q + 1];
             top[kVarDims - 1].v = -1;
@@ -932,7 +1017,8 @@ extern "C" int efanna_build_trees_rule(const float *X, int64_t n, int32_t d, int
         // sixteen tiles per block while nodes are a million positions and more (levels 0..3 of the headline)
         const int tiles = (total >> level) / (size_t)T >= (size_t)kBlock * 256 ? 16 : 1;
         if (split_rule == EFANNA_SPLIT_VARIANCE)
-            choose_dims_kernel<<<min(grid_nodes * (kBlock / EF_WAVE), 2048), kBlock, 0, st>>>(
+            // (a wave per node: a quarter of the waves and the level waits four nodes long)
+            choose_dims_kernel<<<min((max_live + kBlock / EF_WAVE - 1) / (kBlock / EF_WAVE), 2048), kBlock, 0, st>>>(
                 X, d, (int)n, perm_cur, nodes_cur, dims_cur, w.counters, level, seed);
         sum_kernel<<<(grid_pos + tiles - 1) / tiles, kBlock, 0, st>>>(w.xt, (int)n, perm_cur, node_cur, nodes_cur,
                                                                       dims_cur, w.val, total, w.counters, level, tiles, X, d);

@@ -268,6 +268,24 @@ def test_trees_variance_rule_shapes(ef):
     assert e.value.status == -1
 
 
+@pytest.mark.parametrize("d", [1, 4, 63, 64, 65, 128, 129, 193])
+@pytest.mark.parametrize("kind", ["ties", "just_narrow", "just_wide", "huge"])
+def test_trees_variance_rule_sums(ef, kind, d):
+    """The 64-bit sums of the variance rule and the 128-bit ones they fall back to, on either side of
+    the switch (values 256.0 apart, values of 512.0), with equal variances among the lanes."""
+    rng = np.random.default_rng(d)
+    n = 3_000
+    X = rng.integers(0, 2, (n, d)).astype(np.float32)      # many dimensions of equal variance
+    if kind == "just_narrow":
+        X = X * np.float32(256.0 - 2.0 ** -12)
+    elif kind == "just_wide":
+        X = X * np.float32(256.0)
+    elif kind == "huge":
+        X = (X - np.float32(0.5)) * np.float32(2.0 ** 20) * np.float32(0.999)
+        X[:, :: 3] *= np.float32(1e-6)
+    tree_nodes_equal(ef, X, 2, 9, 4, split_rule=1)
+
+
 def test_tree_nodes_edge_cases(ef):
     X = np.zeros((300, 4), dtype=np.float32)                    # every split positional
     tree_nodes_equal(ef, X, 2, 4, 5)
