@@ -349,12 +349,19 @@ __global__ void roots_kernel(Node *nodes, int *dims, int *node_of, unsigned char
 // lies in the same node: their sums are carried in a register and go out as one atomic (the
 // few node records of the top levels would otherwise take one atomic per tile, all to the same
 // few addresses, which serialise).
+// What the split test will look at is kept for it: the coordinate in val, a projection as 64 bits in
+// val and val_hi (8 gathers and 8 numbers drawn per position: adding them up again for the test made
+// the test as expensive as the sums, 200 000 x 960 with eight trees 5.9 -> 3.4 ms).
+// A projection's coordinates come from the rows, or from the transposed copy where the ids of a
+// node lie so close together that a 128-byte line of a column holds several of them: about 32 >> level,
+// times eight lines per position, against as many lines as a row has but eight at most.
 __global__ void __launch_bounds__(kBlock)
 sum_kernel(const float *__restrict__ XT, int n, const int *__restrict__ perm,
            const int *__restrict__ node_of, Node *nodes, const int *__restrict__ dims,
            float *__restrict__ val, size_t total, Counters *c, int level, int tiles,
-           const float *__restrict__ X, int d)      // X: the rows (a projection adds up coordinates of one row)
+           int *__restrict__ val_hi, const float *__restrict__ X, int d)      // X: the rows
 {
+    const bool columns = level < 5 && (1 << level) < 4 * min(kProjectionTerms, (d + 31) / 32);
     if (blockIdx.x == 0 && threadIdx.x == 0) c->n_nodes[(level + 1) & 1] = 0;      // filled by children_kernel
     __shared__ long long wave_tot[kBlock / EF_WAVE];
     __shared__ int wave_node[kBlock / EF_WAVE];
@@ -376,8 +383,12 @@ sum_kernel(const float *__restrict__ XT, int n, const int *__restrict__ perm,
                     val[p] = x;
                     q = ef_quantise(x);
                 } else if (dim <= -3) {
-                    const float *row = X + (size_t)perm[p] * d;
-                    q = ef_node_value([&](int j) { return row[j]; }, d, dim);
+                    const int id = perm[p];
+                    const float *row = columns ? XT + id : X + (size_t)id * d;
+                    const size_t pitch = columns ? (size_t)n : 1;
+                    q = ef_node_value([&](int j) { return row[j * pitch]; }, d, dim);
+                    val[p] = __int_as_float((int)(u32)(u64)q);
+                    val_hi[p] = (int)(q >> 32);
                 } else {
                     s = -1;
                 }
@@ -427,19 +438,17 @@ struct LeftPred {
     const int *node_of;
     const Node *nodes;
     const float *val;
-    const float *X;      // rows and ids, for the nodes that split on a projection
-    const int *perm;
-    int d;
+    const int *val_hi;      // (see sum_kernel)
     __device__ int operator()(size_t p) const
     {
         int s = node_of[p];
         if (s < 0) return 0;
         const Node &nd = nodes[s];
         if (!ef_has_test(nd.dim)) return 0;
-        long long cnt = nd.e - nd.b;
-        if (nd.dim >= 0) return cnt * ef_quantise(val[p]) < nd.sum ? 1 : 0;
-        const float *row = X + (size_t)perm[p] * d;
-        return cnt * ef_node_value([&](int j) { return row[j]; }, d, nd.dim) < nd.sum ? 1 : 0;
+        const long long cnt = nd.e - nd.b;
+        const long long q = nd.dim >= 0 ? ef_quantise(val[p])
+                                        : (long long)(((u64)(u32)val_hi[p] << 32) | (u32)__float_as_int(val[p]));
+        return cnt * q < nd.sum ? 1 : 0;
     }
 };
 struct FlagPred {
@@ -1021,8 +1030,9 @@ extern "C" int efanna_build_trees_rule(const float *X, int64_t n, int32_t d, int
             choose_dims_kernel<<<min((max_live + kBlock / EF_WAVE - 1) / (kBlock / EF_WAVE), 2048), kBlock, 0, st>>>(
                 X, d, (int)n, perm_cur, nodes_cur, dims_cur, w.counters, level, seed);
         sum_kernel<<<(grid_pos + tiles - 1) / tiles, kBlock, 0, st>>>(w.xt, (int)n, perm_cur, node_cur, nodes_cur,
-                                                                      dims_cur, w.val, total, w.counters, level, tiles, X, d);
-        LeftPred pred{node_cur, nodes_cur, w.val, X, perm_cur, d};
+                                                                      dims_cur, w.val, total, w.counters, level, tiles, node_nxt,
+                                                                      X, d);      // (node_nxt: free until the scatter)
+        LeftPred pred{node_cur, nodes_cur, w.val, node_nxt};
         device_scan(pred, total, w.block_sums, w.lcount, w.left_bits, st);
         children_kernel<<<grid_nodes, kBlock, 0, st>>>(
             nodes_cur, level, nodes_nxt, dims_nxt, w.lcount, w.leaf_flag, S, fin, w.small, seed, (int)n, d,
