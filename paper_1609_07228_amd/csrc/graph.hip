@@ -2385,67 +2385,79 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
 // (d >= 4), without a row buffer: one wave per point, the vectors pass
 // through registers sixteen at a time.  For every tile of sixteen new rows (A) and every tile of
 // sixteen rows from it onwards (B) the wave loads both tiles as join_reg_kernel does - lane
-// (r, g) the 16-byte pieces 16 s + 4 g of row r - forms their Gram block with fp32 MFMA, filters,
+// (r, g) the 16-byte pieces 16 s + 4 g of row r - forms their Gram block in half precision, filters
+// with join_reg_kernel's bound (the squared norms of the rounded rows are the diagonals of the
+// blocks (A, A) and (B, B): a few more matrix instructions per tile, nothing to keep),
 // and evaluates the surviving pairs exactly from the same registers.  B tiles are read once per
 // A tile: the rows of a join (some tens of KB) come from the caches after the first time.  What
 // a block keeps in LDS is small (ids, thresholds, the table of pairs already known, queues: a few
-// KB against the tens of KB of a row buffer), its waves never wait for one another, and a dozen
-// joins are in flight on a CU instead of one or two.
+// KB against the tens of KB of a row buffer), its waves never wait for one another, and
+// as many joins are in flight on a CU as its LDS holds: eleven of the largest of 200 vectors.
+// (Blocks in fp32 cost 32 clocks of the matrix unit per four coordinates, a quarter of the join's
+// time, and norms, scaled thresholds and a table of 8-byte slots left room for seven joins.
+// 10^6 x 96, degree 100: tile joins 421 -> 314 ms per build.)
 struct TileLds {
-    int *uid;          // [cap] U_new ++ U_old
-    u32 *thr;          // [cap] threshold bits (exact test)
-    float *nf, *tf;    // [cap] |x|^2 (1 - margin), threshold * scale (filter)
+    int *uid;          // [c16] U_new ++ U_old
+    u32 *thr;          // [c16] threshold bits
     u32 *known;        // [cap][known_words(cap)]
-    int2 *hslot;       // [tile_slots(cap)] (id, its place in uid) in buckets of two slots, id -1 = free
-    u32 *surv;         // [256] surviving pairs of the tile pair in hand
+    int *hid;          // [tile_slots(cap)] members' ids in buckets of four slots, -1 = free
+    unsigned char *hplace;      // [tile_slots(cap)] their places in uid
+    unsigned short *surv;       // [256] surviving pairs of the tile pair in hand
+    float *fa, *fb;    // [4][16] the filter's terms of the rows of tile A and of tile B
     Proposal *queue;   // [q_cap]
 };
-// The table that maps an id to its place in the list: buckets of two slots, a quarter full at
-// most, so that nearly every look-up is one 16-byte read of the id's own bucket (ten thousand
+// The table that maps an id to its place in the list: buckets of four slots, four slots per id the
+// list can have, so that nearly every look-up is one 16-byte read of the id's own bucket (ten thousand
 // look-ups per join: a probe loop whose length differs from lane to lane was most of a join).
 // An id goes to the first free slot of its bucket, else of the buckets after it; a look-up
 // therefore ends at the first bucket with a free slot.
-__host__ __device__ inline int tile_slots(int cap)
+constexpr int kTileQueue = 96;      // proposals that can wait
+__host__ __device__ inline int tile_slots(int cap) { return 4 * cap; }
+__host__ __device__ inline size_t tile_lds_bytes(int cap)
 {
-    int s = 128;
-    while (s < 4 * cap) s <<= 1;
-    return s;
-}
-__host__ __device__ inline size_t tile_lds_bytes(int cap, int q_cap)
-{
-    return (size_t)(align4(cap) * 4 + align4(cap * known_words(cap)) + 2 * tile_slots(cap) + 256) * 4 +
-           (size_t)q_cap * sizeof(Proposal);
+    const int c16 = (cap + 15) & ~15;
+    return (size_t)(2 * c16 + align4(cap * known_words(cap)) + tile_slots(cap) + tile_slots(cap) / 4 + 128 + 128) * 4 +
+           (size_t)kTileQueue * sizeof(Proposal);
 }
 __device__ inline TileLds tile_lds_carve(float *smem, int cap)
 {
     TileLds l;
-    const int c4 = align4(cap);
-    l.uid = (int *)smem;
-    l.thr = (u32 *)(l.uid + c4);
-    l.nf = (float *)(l.thr + c4);
-    l.tf = l.nf + c4;
-    l.known = (u32 *)(l.tf + c4);
-    l.hslot = (int2 *)(l.known + align4(cap * known_words(cap)));
-    l.surv = (u32 *)(l.hslot + tile_slots(cap));
-    l.queue = (Proposal *)(l.surv + 256);
+    const int c16 = (cap + 15) & ~15;
+    l.queue = (Proposal *)smem;
+    l.fa = (float *)(l.queue + kTileQueue);
+    l.fb = l.fa + 64;
+    l.hid = (int *)(l.fb + 64);
+    l.uid = l.hid + tile_slots(cap);
+    l.thr = (u32 *)(l.uid + c16);
+    l.known = l.thr + c16;
+    l.surv = (unsigned short *)(l.known + align4(cap * known_words(cap)));
+    l.hplace = (unsigned char *)(l.surv + 256);
     return l;
 }
 
-constexpr int kTileWaves = 3;      // waves per SIMD the tile join is compiled for (four would spill)
+constexpr int kTileWaves = 4;      // waves per SIMD the tile join is compiled for (three: 371 ms instead of 314)
 template <bool LONG_ROWS, bool ALIGNED>      // LONG_ROWS: graph rows of even length, 16-byte aligned, more than 16 entries: sixteen lanes per proposal
 __global__ void __launch_bounds__(EF_WAVE) __attribute__((amdgpu_waves_per_eu(kTileWaves)))
-join_tile_kernel(const float *__restrict__ X, const float *__restrict__ norms, int d, int K, u32 k_magic,
-                 u32 kq_magic, int *gid, const int *__restrict__ work, const int *__restrict__ work_count, int cap, int q_cap,
-                 float margin_rel, float thr_scale, const int *__restrict__ ulist,
+join_tile_kernel(const float *__restrict__ X, int d, int K, u32 k_magic,
+                 u32 kq_magic, int *gid, const int *__restrict__ work, const int *__restrict__ work_count, int cap,
+                 float margin_rel, float thr_scale, float u_rel, float rho0, const int *__restrict__ ulist,
                  const int2 *__restrict__ ucount, int ucap, u64 *graph, u32 *worst,
-                 int *__restrict__ upd_block, int mode)
+                 int *__restrict__ upd_block, int mode, const u32 *__restrict__ xmax)
 {
     extern __shared__ __align__(16) float smem[];
     const TileLds lds = tile_lds_carve(smem, cap);
     const int mark = mode != 2;      // (modes: see join_reg_kernel)
     const int lane = threadIdx.x, r16 = lane & 15, g = lane >> 4;
-    const int kw = known_words(cap), hslots = tile_slots(cap), n_buckets = hslots >> 1;
-    const int hshift = 32 - (31 - __clz(n_buckets));      // id * odd constant >> hshift: the id's bucket
+    const int kw = known_words(cap), hslots = tile_slots(cap);
+    const u32 n_buckets = (u32)hslots >> 2;
+    auto first_slot = [&](int id) { return 4 * (int)__umulhi((u32)id * 0x9E3779B1u, n_buckets); };      // of the id's bucket
+    // the power of two that keeps the data's halves from overflowing (see join_reg_kernel)
+    const int x_exp = (int)(*xmax >> 23) - 127;
+    const float scale = x_exp >= 15 ? __uint_as_float((u32)(127 + 14 - x_exp) << 23) : 1.0f;
+    const float t_scale = thr_scale * scale * scale;
+    // square roots for the filter only, never too small: the instruction is good to one unit in the
+    // last place, and inputs below the normal numbers are taken for the smallest of them
+    auto sqrt_up = [](float t) { return fmaxf(__builtin_amdgcn_sqrtf(t), 1.1e-19f) * 1.000001f; };
     const int count = *work_count;
     const int n_pieces = (d + 15) >> 4;      // 16-coordinate pieces of a vector (at most 8)
     int updates = 0, q_fill = 0;
@@ -2466,39 +2478,39 @@ join_tile_kernel(const float *__restrict__ X, const float *__restrict__ norms, i
         const int m_new = mc.x, m = min(mc.y, cap);
         // ---- 0. ids, thresholds, norms; the members' places by id ---------------------------
         for (int f = lane; f < m * kw; f += EF_WAVE) lds.known[f] = 0u;
-        for (int f = lane; f < hslots; f += EF_WAVE) lds.hslot[f].x = -1;
+        for (int f = lane; f < hslots; f += EF_WAVE) lds.hid[f] = -1;
         __syncthreads();
         for (int r = lane; r < m; r += EF_WAVE) {
             const int id = ulist[(size_t)i * ucap + r];
             const u32 t = ef_load_coherent(worst + id);
             lds.uid[r] = id;
             lds.thr[r] = t;
-            lds.tf[r] = __uint_as_float(t) * thr_scale;
-            lds.nf[r] = norms[id] * (1.0f - margin_rel);
-            int h = 2 * (int)(((u32)id * 0x9E3779B1u) >> hshift);      // ids of a list are distinct: every one finds a slot
-            while (atomicCAS(&lds.hslot[h].x, -1, id) != -1) h = (h + 1) & (hslots - 1);
-            lds.hslot[h].y = r;
+            int h = first_slot(id);      // ids of a list are distinct: every one finds a slot
+            while (atomicCAS(&lds.hid[h], -1, id) != -1) h = h + 1 == hslots ? 0 : h + 1;
+            lds.hplace[h] = (unsigned char)r;
         }
         __syncthreads();
         // ---- 1. which members already know which (see join_kernel): the members' rows of ids, sixteen
         //         loads in flight per lane, four ids per load where rows allow it -----------------
-        // `two`: the id's own bucket, read beforehand (several look-ups are issued together: one
+        // `four`: the id's own bucket, read beforehand (several look-ups are issued together: one
         // after the other, each would wait out its own LDS round trips)
-        auto note = [&](int row, int id, int4 two) {
+        auto note = [&](int row, int id, int4 four) {
             if (id < 0) return;
-            int c = two.x == id ? two.y : (two.z == id ? two.w : -1);
-            if (c < 0 && two.x != -1 && two.z != -1) {      // a full bucket without the id: it may have moved on (rare)
-                int b = (int)(((u32)id * 0x9E3779B1u) >> hshift);
-                do {
-                    b = (b + 1) & (n_buckets - 1);
-                    two = *reinterpret_cast<const int4 *>(lds.hslot + 2 * b);
-                    c = two.x == id ? two.y : (two.z == id ? two.w : -1);
-                } while (c < 0 && two.x != -1 && two.z != -1);
+            int h = first_slot(id);
+            for (;;) {
+                const int at = four.x == id ? 0 : four.y == id ? 1 : four.z == id ? 2 : four.w == id ? 3 : -1;
+                if (at >= 0) {
+                    const int c = lds.hplace[h + at];
+                    atomicOr(&lds.known[c * kw + (row >> 5)], 1u << (row & 31));
+                    return;
+                }
+                if (four.w == -1) return;      // (slots fill in order: a free one ends the search)
+                h = h + 4 == hslots ? 0 : h + 4;      // a full bucket without the id: it may have moved on (rare)
+                four = *reinterpret_cast<const int4 *>(lds.hid + h);
             }
-            if (c >= 0) atomicOr(&lds.known[c * kw + (row >> 5)], 1u << (row & 31));
         };
         auto bucket_of = [&](int id) {      // (an id of -1 reads some bucket and is dropped afterwards)
-            return *reinterpret_cast<const int4 *>(lds.hslot + 2 * (int)(((u32)id * 0x9E3779B1u) >> hshift));
+            return *reinterpret_cast<const int4 *>(lds.hid + first_slot(id));
         };
         if ((K & 3) == 0 && ((uintptr_t)gid & 15) == 0) {
             const int kq = K >> 2, total = m * kq;
@@ -2544,45 +2556,78 @@ join_tile_kernel(const float *__restrict__ X, const float *__restrict__ norms, i
         __syncthreads();
         // ---- 2. tile pairs ---------------------------------------------------------------------
         const int nbr = (m_new + 15) >> 4, nbc = (m + 15) >> 4;
+        auto row_of = [&](int tile) { return X + (size_t)lds.uid[min(16 * tile + r16, m - 1)] * d; };
+        // Gram block of two tiles in half precision (the operands are packed again for every block:
+        // kept, they would not fit next to the rows), and from a tile's block with itself the squared
+        // norm of the rounded row r16, which lane (r16, r16 >> 2) holds on the diagonal
+        auto halves = [&](const float4 &lo, const float4 &hi) {
+            return scale != 1.0f ? ef_pack_f16<true>(lo, hi, scale) : ef_pack_f16<false>(lo, hi, scale);
+        };
+        auto gram = [&](const float4 (&a)[8], const float4 (&b)[8], floatx4 &ab, floatx4 &bb) {
+            ab = bb = (floatx4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int s = 0; s < 8; s += 2) {
+                if (16 * s >= d) break;      // (pieces beyond d are zeros)
+                const f16x8 oa = halves(a[s], a[s + 1]), ob = halves(b[s], b[s + 1]);
+                ab = __builtin_amdgcn_mfma_f32_16x16x32_f16(oa, ob, ab, 0, 0, 0);
+                bb = __builtin_amdgcn_mfma_f32_16x16x32_f16(ob, ob, bb, 0, 0, 0);
+            }
+        };
+        // the filter's terms of the tile's sixteen rows: |x'|^2 (1 - margin), rounding radius, scaled
+        // threshold and twice its square root (junk beyond m is masked below)
+        auto terms = [&](const floatx4 &acc, int row0, float *f) {
+            if ((r16 >> 2) != g) return;
+            const int kd = r16 & 3;
+            const float dg = kd == 0 ? acc[0] : kd == 1 ? acc[1] : kd == 2 ? acc[2] : acc[3];
+            const float t = __uint_as_float(lds.thr[row0 + r16]) * t_scale;
+            f[r16] = dg * (1.0f - margin_rel);
+            f[16 + r16] = __builtin_fmaf(u_rel, sqrt_up(dg), rho0);
+            f[32 + r16] = t;
+            f[48 + r16] = 2.0f * sqrt_up(t);
+        };
         for (int bi = 0; bi < nbr; ++bi) {
             float4 va[8];
-            {
-                const float *pa = X + (size_t)lds.uid[min(16 * bi + r16, m - 1)] * d;
-                load_pieces<ALIGNED>(va, pa, 0, g, d, true);
-            }
+            floatx4 gaa, gbb;
+            load_pieces<ALIGNED>(va, row_of(bi), 0, g, d, true);
+            gram(va, va, gaa, gbb);
+            terms(gbb, 16 * bi, lds.fa);
             for (int bj = bi; bj < nbc; ++bj) {
                 float4 vb[8];
+                floatx4 acc = gaa;
+                const float *fb = lds.fa;
                 if (bj == bi) {
 #pragma unroll
                     for (int s = 0; s < 8; ++s) vb[s] = va[s];
                 } else {
-                    const float *pb = X + (size_t)lds.uid[min(16 * bj + r16, m - 1)] * d;
-                    load_pieces<ALIGNED>(vb, pb, 0, g, d, true);
-                }
-                floatx4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int s = 0; s < 8; ++s) {
-                    if (s >= n_pieces) break;
-                    acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(va[s].x, vb[s].x, acc0, 0, 0, 0);
-                    acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(va[s].y, vb[s].y, acc1, 0, 0, 0);
-                    acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(va[s].z, vb[s].z, acc0, 0, 0, 0);
-                    acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(va[s].w, vb[s].w, acc1, 0, 0, 0);
+                    load_pieces<ALIGNED>(vb, row_of(bj), 0, g, d, true);
+                    gram(va, vb, acc, gbb);
+                    terms(gbb, 16 * bj, lds.fb);
+                    fb = lds.fb;
                 }
                 // ---- filter: the lane holds G[a = 16 bi + 4 g + k][b = 16 bj + r16] ---------------
                 const int b = 16 * bj + r16, bc = min(b, m - 1);
-                const float nfb = lds.nf[bc], tfb = lds.tf[bc];
+                __syncthreads();
+                const float nfb = fb[r16], rrb = fb[16 + r16], tfb = fb[32 + r16], sqb = fb[48 + r16];
+                const float4 nfa = *reinterpret_cast<const float4 *>(lds.fa + 4 * g);
+                const float4 rra = *reinterpret_cast<const float4 *>(lds.fa + 16 + 4 * g);
+                const float4 tfa = *reinterpret_cast<const float4 *>(lds.fa + 32 + 4 * g);
+                const float4 sqa = *reinterpret_cast<const float4 *>(lds.fa + 48 + 4 * g);
+                const float nfa_k[4] = {nfa.x, nfa.y, nfa.z, nfa.w}, rra_k[4] = {rra.x, rra.y, rra.z, rra.w};
+                const float tfa_k[4] = {tfa.x, tfa.y, tfa.z, tfa.w}, sqa_k[4] = {sqa.x, sqa.y, sqa.z, sqa.w};
                 const u32 knows_b = lds.known[bc * kw + (bi >> 1)] >> (16 * (bi & 1));      // which of rows 16 bi .. know b
+                // valid pairs: a < lim
+                const int lim = b >= m ? 0 : mode == 0 ? min(m_new, b) : mode == 1 ? (b < m_new ? b : 0) : (b >= m_new ? m_new : 0);
                 int n_surv = 0;
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     const int a = 16 * bi + 4 * g + k, ac = min(a, m - 1);
-                    const float low = __builtin_fmaf(-2.0f, acc0[k] + acc1[k], lds.nf[ac] + nfb);
-                    const bool valid = a < m_new && b < m && a < b && (mode == 0 || (mode == 1) == (b < m_new));
+                    const float lhs = __builtin_fmaf(-2.0f, acc[k], nfa_k[k] + nfb), rad = rra_k[k] + rrb;
                     // wanted by a row that may still accept the pair and does not know it yet
-                    const bool keep = valid && ((low <= lds.tf[ac] && !((knows_b >> (4 * g + k)) & 1u)) ||
-                                                (low <= tfb && !is_known(bc, ac)));
+                    const bool for_a = !(lhs > __builtin_fmaf(rad, sqa_k[k] + rad, tfa_k[k])) && !((knows_b >> (4 * g + k)) & 1u);
+                    const bool for_b = !(lhs > __builtin_fmaf(rad, sqb + rad, tfb)) && !is_known(bc, ac);
+                    const bool keep = a < lim && (for_a || for_b);
                     const u64 kept = __ballot(keep);
-                    if (keep) lds.surv[n_surv + lanes_below(kept)] = (u32)(4 * g + k) | ((u32)r16 << 8);
+                    if (keep) lds.surv[n_surv + lanes_below(kept)] = (unsigned short)((4 * g + k) | (r16 << 8));
                     n_surv += __popcll(kept);
                 }
                 __syncthreads();
@@ -2633,12 +2678,20 @@ join_tile_kernel(const float *__restrict__ X, const float *__restrict__ norms, i
                     }
                     q_fill += __popcll(mask_b);
                     __syncthreads();
-                    if (q_fill + 32 > q_cap) drain();      // a round adds at most two proposals per pair
+                    if (q_fill + 32 > kTileQueue) {      // a round adds at most two proposals per pair
+                        drain();
+                        // (the rows are fetched again: kept across the drain they would not fit the registers)
+                        load_pieces<ALIGNED>(va, row_of(bi), 0, g, d, true);
+                        if (bj != bi) load_pieces<ALIGNED>(vb, row_of(bj), 0, g, d, true);
+                        else
+#pragma unroll
+                            for (int s = 0; s < 8; ++s) vb[s] = va[s];
+                    }
                 }
                 __syncthreads();      // the survivor list is free again
             }
         }
-        if (q_fill >= q_cap / 2) drain();
+        if (q_fill >= kTileQueue / 2) drain();
         __syncthreads();
     }
     drain();
@@ -3140,7 +3193,7 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
     }
     // joins of more than 32 vectors: register tiles for vectors of at most 128 coordinates, else rows in LDS
     const bool tiles = reg_ok && d <= 128;
-    if (tiles && max_rows > rows1 && tile_lds_bytes(max_rows, 256) > kLdsLimit) return EFANNA_EUNSUPPORTED;
+    if (tiles && max_rows > rows1 && tile_lds_bytes(max_rows) > kLdsLimit) return EFANNA_EUNSUPPORTED;
     if (!tiles && max_rows > rows1 && large_lds > kLdsLimit) return EFANNA_EUNSUPPORTED;
     if (!aligned && shape_for(max_rows).lds > kLdsLimit) return EFANNA_EUNSUPPORTED;      // (the documented limit of unaligned rows)
     // joins of at most 16 vectors from registers (d <= 128): room for a whole point's proposals
@@ -3201,10 +3254,10 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
                                                         : (const void *)bucket_lists_kernel<9, 0>,
                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)bucket_lists_lds(L, n_bkt)));
     }
-    if (max_rows > rows1 && tiles && tile_lds_bytes(max_rows, 256) > 64 * 1024) {
+    if (max_rows > rows1 && tiles && tile_lds_bytes(max_rows) > 64 * 1024) {
         for (const void *f : {(const void *)join_tile_kernel<true, true>, (const void *)join_tile_kernel<false, true>,
                               (const void *)join_tile_kernel<true, false>, (const void *)join_tile_kernel<false, false>})
-            EF_HIP_CHECK(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)tile_lds_bytes(max_rows, 256)));
+            EF_HIP_CHECK(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)tile_lds_bytes(max_rows)));
     }
     if (max_rows > rows1 && !tiles)
         EF_HIP_CHECK(hipFuncSetAttribute(K >= 2 * EF_WIDE_PIECES ? (const void *)join_kernel<true>
@@ -3364,8 +3417,7 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
         // the larger classes first: their blocks run longest
         for (int c = jc.n - 1; c >= 2 && max_rows > rows1; --c) {
             if (tiles) {      // vectors of at most 128 coordinates pass through registers
-                const int tq = 256;
-                const size_t tl = tile_lds_bytes(jc.bound[c], tq);
+                const size_t tl = tile_lds_bytes(jc.bound[c]);
                 long per_cu = (long)(kLdsLimit / tl);
                 per_cu = per_cu > 4 * kTileWaves ? 4 * kTileWaves : (per_cu < 1 ? 1 : per_cu);      // by registers
                 const int tgrid = (int)(256 * per_cu * 4);
@@ -3374,8 +3426,9 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
                 const u32 kqm = K >= 4 ? (u32)(((1ULL << 32) + (K >> 2) - 1) / (K >> 2)) : 0u;
 #define EF_JOIN_TILE(LONG_ROWS, ALIGNED)                                                                   \
     join_tile_kernel<LONG_ROWS, ALIGNED><<<tgrid, EF_WAVE, tl, st>>>(                                      \
-        X, w.norms, d, K, km, kqm, w.gid, w.work + (size_t)c * n, w.work_count + c, jc.bound[c], tq,       \
-        margin_rel, thr_scale, w.ulist, w.ucount, max_rows, graph, w.worst, upd, mode)
+        X, d, K, km, kqm, w.gid, w.work + (size_t)c * n, w.work_count + c, jc.bound[c],                    \
+        margin_f16, thr_scale_f16, u_f16, rho0_f16, w.ulist, w.ucount, max_rows, graph, w.worst, upd,      \
+        mode, w.xmax)
                 const bool long_rows = K > 16 && (K & 1) == 0 && ((uintptr_t)graph & 15) == 0;
                 if (aligned) {
                     if (long_rows) EF_JOIN_TILE(true, true);

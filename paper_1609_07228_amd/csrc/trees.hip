@@ -355,13 +355,14 @@ __global__ void roots_kernel(Node *nodes, int *dims, int *node_of, unsigned char
 // A projection's coordinates come from the rows, or from the transposed copy where the ids of a
 // node lie so close together that a 128-byte line of a column holds several of them: about 32 >> level,
 // times eight lines per position, against as many lines as a row has but eight at most.
+template <bool PROJECTION>      // (compiled apart: the other rules' kernels carry none of it)
 __global__ void __launch_bounds__(kBlock)
 sum_kernel(const float *__restrict__ XT, int n, const int *__restrict__ perm,
            const int *__restrict__ node_of, Node *nodes, const int *__restrict__ dims,
            float *__restrict__ val, size_t total, Counters *c, int level, int tiles,
            int *__restrict__ val_hi, const float *__restrict__ X, int d)      // X: the rows
 {
-    const bool columns = level < 5 && (1 << level) < 4 * min(kProjectionTerms, (d + 31) / 32);
+    const bool columns = PROJECTION && level < 5 && (1 << level) < 4 * min(kProjectionTerms, (d + 31) / 32);
     if (blockIdx.x == 0 && threadIdx.x == 0) c->n_nodes[(level + 1) & 1] = 0;      // filled by children_kernel
     __shared__ long long wave_tot[kBlock / EF_WAVE];
     __shared__ int wave_node[kBlock / EF_WAVE];
@@ -382,7 +383,7 @@ sum_kernel(const float *__restrict__ XT, int n, const int *__restrict__ perm,
                     float x = XT[(size_t)dim * n + perm[p]];
                     val[p] = x;
                     q = ef_quantise(x);
-                } else if (dim <= -3) {
+                } else if (PROJECTION && dim <= -3) {
                     const int id = perm[p];
                     const float *row = columns ? XT + id : X + (size_t)id * d;
                     const size_t pitch = columns ? (size_t)n : 1;
@@ -434,6 +435,7 @@ sum_kernel(const float *__restrict__ XT, int n, const int *__restrict__ perm,
 }
 
 // predicate sources for the scan
+template <bool PROJECTION>
 struct LeftPred {
     const int *node_of;
     const Node *nodes;
@@ -446,8 +448,9 @@ struct LeftPred {
         const Node &nd = nodes[s];
         if (!ef_has_test(nd.dim)) return 0;
         const long long cnt = nd.e - nd.b;
-        const long long q = nd.dim >= 0 ? ef_quantise(val[p])
-                                        : (long long)(((u64)(u32)val_hi[p] << 32) | (u32)__float_as_int(val[p]));
+        const long long q = !PROJECTION || nd.dim >= 0
+                                ? ef_quantise(val[p])
+                                : (long long)(((u64)(u32)val_hi[p] << 32) | (u32)__float_as_int(val[p]));
         return cnt * q < nd.sum ? 1 : 0;
     }
 };
@@ -1029,11 +1032,17 @@ extern "C" int efanna_build_trees_rule(const float *X, int64_t n, int32_t d, int
             // (a wave per node: a quarter of the waves and the level waits four nodes long)
             choose_dims_kernel<<<min((max_live + kBlock / EF_WAVE - 1) / (kBlock / EF_WAVE), 2048), kBlock, 0, st>>>(
                 X, d, (int)n, perm_cur, nodes_cur, dims_cur, w.counters, level, seed);
-        sum_kernel<<<(grid_pos + tiles - 1) / tiles, kBlock, 0, st>>>(w.xt, (int)n, perm_cur, node_cur, nodes_cur,
-                                                                      dims_cur, w.val, total, w.counters, level, tiles, node_nxt,
-                                                                      X, d);      // (node_nxt: free until the scatter)
-        LeftPred pred{node_cur, nodes_cur, w.val, node_nxt};
-        device_scan(pred, total, w.block_sums, w.lcount, w.left_bits, st);
+#define EF_SUM_AND_SCAN(PROJECTION)      /* (node_nxt: free until the scatter) */                            \
+    do {                                                                                                 \
+        sum_kernel<PROJECTION><<<(grid_pos + tiles - 1) / tiles, kBlock, 0, st>>>(                       \
+            w.xt, (int)n, perm_cur, node_cur, nodes_cur, dims_cur, w.val, total, w.counters, level,      \
+            tiles, node_nxt, X, d);                                                                      \
+        device_scan(LeftPred<PROJECTION>{node_cur, nodes_cur, w.val, node_nxt}, total, w.block_sums,     \
+                    w.lcount, w.left_bits, st);                                                          \
+    } while (0)
+        if (split_rule == EFANNA_SPLIT_PROJECTION) EF_SUM_AND_SCAN(true);
+        else EF_SUM_AND_SCAN(false);
+#undef EF_SUM_AND_SCAN
         children_kernel<<<grid_nodes, kBlock, 0, st>>>(
             nodes_cur, level, nodes_nxt, dims_nxt, w.lcount, w.leaf_flag, S, fin, w.small, seed, (int)n, d,
             w.counters, w.rec, w.leaf_rec, split_rule);
