@@ -437,14 +437,18 @@ __device__ inline void ef_load_pieces_at(const void *p0, const void *p1, const v
 // All sixteen lanes of a group (lane gl = 0..15 of it) call this with the same arguments and get
 // the same result.  Lane gl reads the 16-byte pieces gl, gl + 16, ... of the row, so that the
 // group fetches 256 contiguous bytes per load: a quarter of the memory transactions that a lane
-// reading the whole row alone needs, and one round trip for rows of up to 128 entries.  The
-// row must be 16-byte aligned and of even length; the group's lanes must all be active.
+// reading the whole row alone needs, and one round trip for rows of up to 128 entries.  ODD: rows of
+// any length of at least two, at any multiple of 8 bytes (a 16-byte load asks for 4-byte alignment, and
+// an 8-byte aligned entry never straddles a cache line); the last piece of a row of odd length starts
+// one entry earlier, at an entry that the piece before it delivers as well.  Else the row must be
+// 16-byte aligned and of even length.  The group's lanes must all be active.
 // slot (or null): receives the slot the key went into.
+template <bool ODD>
 __device__ inline bool ef_bounded_insert_g16(u64 *list, int cap, u64 key, int ignore, u64 *new_max, int gl,
                                              int *slot = nullptr)
 {
     const u64 kcmp = key >> ignore;
-    const int np = cap >> 1;
+    const int np = ODD ? (cap + 1) >> 1 : cap >> 1;
     for (;;) {
         u64 mx = 0, mx2 = 0;
         int ms = 0;
@@ -452,10 +456,12 @@ __device__ inline bool ef_bounded_insert_g16(u64 *list, int cap, u64 key, int ig
         for (int p0 = 0; p0 < np; p0 += 64) {
             const int n_ld = min(4, (np - p0 + 15) >> 4);
             ef_u32x4 q[4];
-            const ef_u32x4 *row = reinterpret_cast<const ef_u32x4 *>(list);
             // pieces beyond the row read its last piece again and are not looked at
-            ef_load_pieces_at(row + min(p0 + gl, np - 1), row + min(p0 + gl + 16, np - 1),
-                              row + min(p0 + gl + 32, np - 1), row + min(p0 + gl + 48, np - 1), n_ld, q);
+            auto at = [&](int piece) {
+                return ODD ? (const void *)(list + min(2 * piece, cap - 2))
+                           : (const void *)(reinterpret_cast<const ef_u32x4 *>(list) + min(piece, np - 1));
+            };
+            ef_load_pieces_at(at(p0 + gl), at(p0 + gl + 16), at(p0 + gl + 32), at(p0 + gl + 48), n_ld, q);
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const int piece = p0 + gl + 16 * k;
@@ -463,11 +469,13 @@ __device__ inline bool ef_bounded_insert_g16(u64 *list, int cap, u64 key, int ig
                 const u64 e2[2] = {((u64)q[k].y << 32) | q[k].x, ((u64)q[k].w << 32) | q[k].z};
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
+                    const int s = ODD ? min(2 * piece, cap - 2) + h : 2 * piece + h;
+                    if (ODD && s < 2 * piece) continue;      // (looked at already)
                     dup |= (e2[h] >> ignore) == kcmp;
                     if (e2[h] > mx) {
                         mx2 = mx;
                         mx = e2[h];
-                        ms = 2 * piece + h;
+                        ms = s;
                     } else if (e2[h] > mx2) {
                         mx2 = e2[h];
                     }

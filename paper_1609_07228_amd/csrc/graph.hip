@@ -90,6 +90,7 @@ __device__ inline int lanes_below(u64 ballot)
 
 // a 16-byte load at any multiple of four bytes (more than that no global load asks for)
 typedef float ef_f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
+typedef int ef_i32x4_u __attribute__((ext_vector_type(4), aligned(4)));
 __device__ inline float4 load_unaligned4(const float *p)
 {
     const ef_f32x4_u v = *reinterpret_cast<const ef_f32x4_u *>(p);
@@ -214,9 +215,10 @@ __device__ inline int drain_queue(const Proposal *queue, int count, u64 *graph, 
     return updates;
 }
 
-// The same for long rows (even length, 16-byte aligned): a group of sixteen threads per
+// The same for long rows: a group of sixteen threads per
 // proposal (nthr a multiple of 16; all threads of the block call this together).
 // gid (or null): the mirror of the rows' ids (graph_ids_kernel), kept up to date with the insertions.
+template <bool ODD>      // (see ef_bounded_insert_g16)
 __device__ inline int drain_queue_g16(const Proposal *queue, int count, u64 *graph, u32 *worst, int K,
                                       int tid, int nthr, int *gid = nullptr)
 {
@@ -226,7 +228,7 @@ __device__ inline int drain_queue_g16(const Proposal *queue, int count, u64 *gra
         const Proposal p = queue[e];
         u64 new_max;
         int slot = 0;
-        if (ef_bounded_insert_g16(graph + (size_t)p.target * K, K, p.key, 1, &new_max, gl, &slot) && gl == 0) {
+        if (ef_bounded_insert_g16<ODD>(graph + (size_t)p.target * K, K, p.key, 1, &new_max, gl, &slot) && gl == 0) {
             atomicMin(worst + p.target, ef_dist_bits(new_max));
             // (a plain store: whatever order stores to a slot land in, the slot names an id that was in the row)
             if (gid) gid[(size_t)p.target * K + slot] = ef_id(p.key);
@@ -1790,9 +1792,9 @@ __global__ void __launch_bounds__(512) join_kernel(const float *__restrict__ X, 
                     }
                     __syncthreads();
                     // ---- 4. drain -----------------------------------------------------------
-                    updates += WIDE && (K & 1) == 0 && ((uintptr_t)graph & 15) == 0
-                                   ? drain_queue_g16(lds.queue, lds.meta[3], graph, worst, K, tid, nthr)
-                                   : drain_queue<WIDE>(lds.queue, lds.meta[3], graph, worst, K, tid, nthr);
+                    updates += WIDE
+                                   ? drain_queue_g16<true>(lds.queue, lds.meta[3], graph, worst, K, tid, nthr)
+                                   : drain_queue(lds.queue, lds.meta[3], graph, worst, K, tid, nthr);
                     __syncthreads();
                     if (tid == 0) lds.meta[3] = 0;
                     __syncthreads();
@@ -2436,7 +2438,10 @@ __device__ inline TileLds tile_lds_carve(float *smem, int cap)
 }
 
 constexpr int kTileWaves = 4;      // waves per SIMD the tile join is compiled for (three: 371 ms instead of 314)
-template <bool LONG_ROWS, bool ALIGNED>      // LONG_ROWS: graph rows of even length, 16-byte aligned, more than 16 entries: sixteen lanes per proposal
+// LONG_ROWS: longer graph rows (see the launch): sixteen lanes per proposal.  QUADS: K % 4 == 0, rows of
+// ids and of entries are 16-byte aligned (compiled apart: addressing for any K cost such rows 2 %;
+// before other lengths had it, a thread scanned a row alone: 10^5 x 64, degree 81 53 -> 36 ms per build).
+template <bool LONG_ROWS, bool ALIGNED, bool QUADS>
 __global__ void __launch_bounds__(EF_WAVE) __attribute__((amdgpu_waves_per_eu(kTileWaves)))
 join_tile_kernel(const float *__restrict__ X, int d, int K, u32 k_magic,
                  u32 kq_magic, int *gid, const int *__restrict__ work, const int *__restrict__ work_count, int cap,
@@ -2462,7 +2467,7 @@ join_tile_kernel(const float *__restrict__ X, int d, int K, u32 k_magic,
     const int n_pieces = (d + 15) >> 4;      // 16-coordinate pieces of a vector (at most 8)
     int updates = 0, q_fill = 0;
     auto drain = [&]() {
-        updates += LONG_ROWS ? drain_queue_g16(lds.queue, q_fill, graph, worst, K, lane, EF_WAVE, gid)
+        updates += LONG_ROWS ? drain_queue_g16<!QUADS>(lds.queue, q_fill, graph, worst, K, lane, EF_WAVE, gid)
                              : drain_queue<false, false>(lds.queue, q_fill, graph, worst, K, lane, EF_WAVE);
         q_fill = 0;
         __syncthreads();
@@ -2512,8 +2517,8 @@ join_tile_kernel(const float *__restrict__ X, int d, int K, u32 k_magic,
         auto bucket_of = [&](int id) {      // (an id of -1 reads some bucket and is dropped afterwards)
             return *reinterpret_cast<const int4 *>(lds.hid + first_slot(id));
         };
-        if ((K & 3) == 0 && ((uintptr_t)gid & 15) == 0) {
-            const int kq = K >> 2, total = m * kq;
+        if (QUADS || K >= 4) {      // (rows at any multiple of four bytes; the last load of a row may repeat ids)
+            const int kq = QUADS ? K >> 2 : (K + 3) >> 2, total = m * kq;
             for (int f0 = lane; f0 < total; f0 += 16 * EF_WAVE) {
                 int4 four[16];
                 int rr[16];
@@ -2521,8 +2526,15 @@ join_tile_kernel(const float *__restrict__ X, int d, int K, u32 k_magic,
                 for (int q = 0; q < 16; ++q) {
                     const int f = f0 + q * EF_WAVE;
                     rr[q] = kq == 1 ? min(f, total - 1) : (int)(((u64)(u32)min(f, total - 1) * kq_magic) >> 32);
-                    four[q] = f < total ? *reinterpret_cast<const int4 *>(gid + (size_t)lds.uid[rr[q]] * K + 4 * (f - rr[q] * kq))
-                                        : make_int4(-1, -1, -1, -1);
+                    four[q] = make_int4(-1, -1, -1, -1);
+                    if (QUADS) {
+                        if (f < total)
+                            four[q] = *reinterpret_cast<const int4 *>(gid + (size_t)lds.uid[rr[q]] * K + 4 * (f - rr[q] * kq));
+                    } else if (f < total) {
+                        const ef_i32x4_u v = *reinterpret_cast<const ef_i32x4_u *>(gid + (size_t)lds.uid[rr[q]] * K +
+                                                                                   min(4 * (f - rr[q] * kq), K - 4));
+                        four[q] = make_int4(v.x, v.y, v.z, v.w);
+                    }
                 }
 #pragma unroll
                 for (int q = 0; q < 16; ++q) {
@@ -3193,7 +3205,6 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
     }
     // joins of more than 32 vectors: register tiles for vectors of at most 128 coordinates, else rows in LDS
     const bool tiles = reg_ok && d <= 128;
-    if (tiles && max_rows > rows1 && tile_lds_bytes(max_rows) > kLdsLimit) return EFANNA_EUNSUPPORTED;
     if (!tiles && max_rows > rows1 && large_lds > kLdsLimit) return EFANNA_EUNSUPPORTED;
     if (!aligned && shape_for(max_rows).lds > kLdsLimit) return EFANNA_EUNSUPPORTED;      // (the documented limit of unaligned rows)
     // joins of at most 16 vectors from registers (d <= 128): room for a whole point's proposals
@@ -3253,11 +3264,6 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
                                          : bshift == 10 ? (const void *)bucket_lists_kernel<10, 0>
                                                         : (const void *)bucket_lists_kernel<9, 0>,
                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)bucket_lists_lds(L, n_bkt)));
-    }
-    if (max_rows > rows1 && tiles && tile_lds_bytes(max_rows) > 64 * 1024) {
-        for (const void *f : {(const void *)join_tile_kernel<true, true>, (const void *)join_tile_kernel<false, true>,
-                              (const void *)join_tile_kernel<true, false>, (const void *)join_tile_kernel<false, false>})
-            EF_HIP_CHECK(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)tile_lds_bytes(max_rows)));
     }
     if (max_rows > rows1 && !tiles)
         EF_HIP_CHECK(hipFuncSetAttribute(K >= 2 * EF_WIDE_PIECES ? (const void *)join_kernel<true>
@@ -3423,19 +3429,24 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
                 const int tgrid = (int)(256 * per_cu * 4);
                 int *upd = w.upd_block + 2 * reg_grid + (c - 2) * kMaxLargeGrid;
                 const u32 km = (u32)(((1ULL << 32) + K - 1) / K);
-                const u32 kqm = K >= 4 ? (u32)(((1ULL << 32) + (K >> 2) - 1) / (K >> 2)) : 0u;
-#define EF_JOIN_TILE(LONG_ROWS, ALIGNED)                                                                   \
-    join_tile_kernel<LONG_ROWS, ALIGNED><<<tgrid, EF_WAVE, tl, st>>>(                                      \
+                const u32 kqm = (u32)(((1ULL << 32) + ((K + 3) >> 2) - 1) / ((K + 3) >> 2));
+#define EF_JOIN_TILE(LONG_ROWS, ALIGNED, QUADS)                                                            \
+    join_tile_kernel<LONG_ROWS, ALIGNED, QUADS><<<tgrid, EF_WAVE, tl, st>>>(                               \
         X, d, K, km, kqm, w.gid, w.work + (size_t)c * n, w.work_count + c, jc.bound[c],                    \
         margin_f16, thr_scale_f16, u_f16, rho0_f16, w.ulist, w.ucount, max_rows, graph, w.worst, upd,      \
         mode, w.xmax)
-                const bool long_rows = K > 16 && (K & 1) == 0 && ((uintptr_t)graph & 15) == 0;
-                if (aligned) {
-                    if (long_rows) EF_JOIN_TILE(true, true);
-                    else EF_JOIN_TILE(false, true);
+                const bool quads = K % 4 == 0 && ((uintptr_t)graph & 15) == 0;
+                // (odd rows of up to 32 entries: 64 threads scanning a row each are the better ones still,
+                // 300 000 x 112, degree 23: 15.3 ms per build against 15.7)
+                if (K <= 16 || (K <= 32 && (K & 1))) {
+                    if (aligned) EF_JOIN_TILE(false, true, false);
+                    else EF_JOIN_TILE(false, false, false);
+                } else if (aligned) {
+                    if (quads) EF_JOIN_TILE(true, true, true);
+                    else EF_JOIN_TILE(true, true, false);
                 } else {
-                    if (long_rows) EF_JOIN_TILE(true, false);
-                    else EF_JOIN_TILE(false, false);
+                    if (quads) EF_JOIN_TILE(true, false, true);
+                    else EF_JOIN_TILE(true, false, false);
                 }
 #undef EF_JOIN_TILE
             } else if (K >= 2 * EF_WIDE_PIECES) EF_JOIN_LARGE(true, c);

@@ -413,6 +413,14 @@ def test_nndescent_filter_ranges_bit_exact(ef, kind, d, K, L):
     (2_000, 16, 2, 16, 64, 32, 2),       # join lists of 128 ids: a wave per point, hash table of 256 slots
     (1_500, 8, 2, 16, 128, 64, 1),       # the longest rows and samples the library takes (lists of 256 ids)
     (1_200, 20, 2, 16, 40, 29, 2),       # lists of 98 ids: just over the switch to a wave per point
+    (2_000, 16, 2, 16, 17, 16, 2),       # odd rows (8-byte aligned): the shortest and the longest of the
+    (1_500, 24, 2, 16, 127, 51, 1),      # sixteen-lane insertion, odd lists of fifty and one
+    (2_000, 140, 2, 16, 15, 12, 2),      # odd rows of at most sixteen entries, joins by rotations
+    (2_000, 40, 2, 16, 13, 7, 3),        # ... and with the filter
+    (1_000, 150, 2, 16, 51, 33, 1),      # rows in LDS (long vectors, more than 32 of them), odd rows and lists
+    (1_000, 8, 2, 16, 34, 3, 2),         # rows of two modulo four ids: the last load of a row repeats two
+    (900, 8, 2, 16, 1, 20, 2),           # rows of one entry, joins of more than 32 vectors
+    (900, 8, 2, 16, 3, 20, 2),
 ])
 def test_nndescent_more_shapes(ef, n, d, T, S, K, L, I):
     rng = np.random.default_rng(n + d + K)
