@@ -1191,9 +1191,10 @@ reverse_overflow_kernel(const Overflow *__restrict__ overflow, size_t ovf_region
 // Reverse lists without device-wide atomics, for short rows and lists (K, L <= 32) of at most
 // 2^21 points (2^20 if L > 16).  A counter bump per offer is bound by the rate of atomics on random addresses;
 // here the offers are sorted by target range instead, and the lists of a range are built in LDS:
-//   1. an offer block (1024 threads) handles kBktRows consecutive source rows, keeps their
-//      offers (one word: target << 10 | source row inside the block) in LDS, counts them per
-//      bucket (a range of 1024 targets, of 512 if L > 16: the lists of a range have to fit the
+//   1. an offer block (one thread per row) handles 1024 consecutive source rows (256 of few points,
+//      see BucketShape), keeps their
+//      offers (one word: target << row bits | source row inside the block) in LDS, counts them per
+//      bucket (a range of up to 1024 targets, of 512 if L > 16: the lists of a range have to fit the
 //      LDS), and writes them to its own part of the offer array, bucket after bucket;
 //      table[bucket][block] = start << 16 | count of that run;
 //   2. a list block (one per bucket) walks the runs of its bucket, one thread per offer, and
@@ -1201,25 +1202,56 @@ reverse_overflow_kernel(const Overflow *__restrict__ overflow, size_t ovf_region
 //      counts (filled slots) go out in one contiguous piece.
 // Whatever the order of the offers, a list ends up with the L smallest keys offered to it.
 
-constexpr int kBktRows = 1024;        // source rows per offer block
+constexpr int kBktRows = 1024;        // source rows per offer block, at most
 constexpr int kBktThreads = 1024;
 constexpr int kBktMaxRuns = 2 * kBktThreads;    // buckets and offer blocks a block-wide scan of two per thread takes
-static_assert(kBktRows == 1024, "an offer word keeps the source row in ten bits");
 
-// log2 of the targets per bucket
+// log2 of the targets per bucket where the buckets are as large as LDS lets them be
 __host__ __device__ inline int bucket_shift(int L) { return L <= 16 ? 10 : 9; }
 
-__host__ __device__ inline size_t bucket_lists_lds(int L, int n_blocks);
+__host__ __device__ inline size_t bucket_lists_lds(int L, int shift, int n_blocks);
 
 __host__ __device__ inline bool bucketed_lists(int64_t n, int K, int L)
 {
     if (K > 32 || L > 32 || n > (1 << 21)) return false;      // (targets fit 21 bits of an offer word)
     const int64_t n_blocks = (n + kBktRows - 1) / kBktRows, n_buckets = ((n - 1) >> bucket_shift(L)) + 1;
     return n_blocks <= kBktMaxRuns && n_buckets <= kBktMaxRuns &&
-           bucket_lists_lds(L, (int)n_blocks) <= 160 * 1024 - 256;
+           bucket_lists_lds(L, bucket_shift(L), (int)n_blocks) <= 160 * 1024 - 256;
+}
+
+// How the offers are cut up.  Blocks of 1024 rows and ranges of 1024 targets leave most of the 256 CUs
+// idle below some ten thousand points (10 blocks at 10^4), each with ten thousand offers to enter.
+// Up to 2^16 points: offer blocks of 256 rows, and the smallest
+// ranges that make at most 512 buckets (from 32 targets up).  (The table of runs is then larger, up to
+// 8 bytes per point, and lies in the half of the reverse-old lists' room that 32-bit sources leave
+// free: L >= 4.)  Builds of 2500 x 24 / 10^4 x 32 / 6 10^4 x 100: 921 -> 762 us, 1221 -> 1100, 4009 -> 3933; from
+// 10^5 points on nothing is gained (the insertions of popular points decide), and at 2.6 10^5 2 % lost.
+struct BucketShape {
+    int row_bits, blocks;           // log2 of the source rows of an offer block, number of blocks
+    int shift, buckets, threads;    // log2 of the targets of a bucket, number of buckets, threads of a list block
+};
+inline BucketShape bucket_shape(int64_t n, int L)
+{
+    BucketShape b;
+    if (n <= (1 << 16) && L >= 4) {
+        b.row_bits = 8;
+        b.shift = 5;
+        while (((n - 1) >> b.shift) + 1 > 512) ++b.shift;
+        b.blocks = (int)((n + 255) >> 8);
+        b.buckets = (int)((n - 1) >> b.shift) + 1;
+        b.threads = b.shift <= 7 ? 256 : b.shift == 8 ? 512 : 1024;
+        if ((int64_t)b.blocks * b.buckets <= n * L) return b;
+    }
+    b.row_bits = 10;
+    b.shift = bucket_shift(L);
+    b.blocks = (int)((n + kBktRows - 1) / kBktRows);
+    b.buckets = (int)((n - 1) >> b.shift) + 1;
+    b.threads = kBktThreads;
+    return b;
 }
 
 // All lanes of the wave call this together; lanes with `take` set append `offer`.
+template <int RB>      // RB: row bits of an offer
 __device__ inline void offer_append(bool take, u32 offer, int shift, u32 *offers, int *hist, int *fill)
 {
     const u64 mask = __ballot(take);
@@ -1230,16 +1262,18 @@ __device__ inline void offer_append(bool take, u32 offer, int shift, u32 *offers
     base = __shfl(base, leader, EF_WAVE);
     if (take) {
         offers[base + lanes_below(mask)] = offer;
-        atomicAdd(&hist[offer >> (10 + shift)], 1);
+        atomicAdd(&hist[offer >> (RB + shift)], 1);
     }
 }
 
 // End of an offer block: runs per bucket in `out` (this block's part of the offer array) and
-// the block's column of the table.  hist, cursor: [n_buckets] in LDS, n_buckets <= kBktMaxRuns.
+// the block's column of the table.  hist, cursor: [n_buckets] in LDS; the block has 1 << RB threads and
+// n_buckets is at most twice that.
+template <int RB>
 __device__ inline void offers_flush(const u32 *offers, const int *hist, int *cursor, int n_buckets, int shift,
                                     int total, u32 *__restrict__ out, u32 *__restrict__ table)
 {
-    __shared__ int wave_tot[kBktThreads / EF_WAVE];
+    __shared__ int wave_tot[(1 << RB) / EF_WAVE];
     const int t = threadIdx.x, b0 = 2 * t;
     const int c0 = b0 < n_buckets ? hist[b0] : 0, c1 = b0 + 1 < n_buckets ? hist[b0 + 1] : 0;
     const int incl = ef_wave_scan_i32(c0 + c1);
@@ -1256,26 +1290,27 @@ __device__ inline void offers_flush(const u32 *offers, const int *hist, int *cur
         table[(size_t)(b0 + 1) * gridDim.x + blockIdx.x] = (u32)(off + c0) << 16 | (u32)c1;
     }
     __syncthreads();
-    for (int e = t; e < total; e += kBktThreads) {
+    for (int e = t; e < total; e += 1 << RB) {
         const u32 o = offers[e];
-        out[atomicAdd(&cursor[o >> (10 + shift)], 1)] = o;
+        out[atomicAdd(&cursor[o >> (RB + shift)], 1)] = o;
     }
 }
 
-// Alg. 4 step 1+2 for short rows: sample_row for kBktRows rows, the reverse-new offers to the
-// block's runs.  LDS: offers [kBktRows * L] words, hist and cursor [n_buckets] int each.
+// Alg. 4 step 1+2 for short rows: sample_row for 1 << RB rows, the reverse-new offers to the
+// block's runs.  LDS: offers [L << RB] words, hist and cursor [n_buckets] int each.
 // E: entries per lane of a row's eight lanes (8 E >= K).
-template <int E>
-__global__ void __launch_bounds__(kBktThreads)
+template <int E, int RB>
+__global__ void __launch_bounds__(1 << RB)
 sample_bucket_kernel(u64 *graph, int n, int K, int L, int *__restrict__ nw, int *__restrict__ od,
                      int *__restrict__ nw_c, int *__restrict__ od_c, u32 *worst, int n_buckets, int shift,
                      u32 *__restrict__ offer_runs, u32 *__restrict__ table)
 {
     extern __shared__ __align__(16) u32 offer_sm[];
     u32 *offers = offer_sm;
-    int *hist = (int *)(offers + (size_t)kBktRows * L), *cursor = hist + n_buckets;
+    constexpr int kRows = 1 << RB, kThreads = 1 << RB;
+    int *hist = (int *)(offers + (size_t)kRows * L), *cursor = hist + n_buckets;
     __shared__ int fill;
-    for (int b = threadIdx.x; b < n_buckets; b += kBktThreads) hist[b] = 0;
+    for (int b = threadIdx.x; b < n_buckets; b += kThreads) hist[b] = 0;
     if (threadIdx.x == 0) fill = 0;
     __syncthreads();
     // (loading the entries of several of a thread's rows ahead of time gains nothing measurable,
@@ -1283,51 +1318,53 @@ sample_bucket_kernel(u64 *graph, int n, int K, int L, int *__restrict__ nw, int 
     // eight lanes with two entries each per row: a wave ranks eight rows with the broadcasts that
     // four rows of sixteen lanes would take (147 -> 93 us on the headline; four or two lanes
     // per row: the same again)
-    constexpr int G = 8, kRowsPerPass = kBktThreads / G;
-    for (int pass = 0; pass < kBktRows / kRowsPerPass; ++pass) {
-        const int i = blockIdx.x * kBktRows + pass * kRowsPerPass + (int)(threadIdx.x / G);
+    constexpr int G = 8, kRowsPerPass = kThreads / G;
+    for (int pass = 0; pass < kRows / kRowsPerPass; ++pass) {
+        const int i = blockIdx.x * kRows + pass * kRowsPerPass + (int)(threadIdx.x / G);
         u64 e[E];
         sample_load<G, E>(graph, i, i < n, K, e);
         sample_row<G, E>(graph, e, i, i < n, K, L, nw, od, nw_c, od_c, worst, [&](bool take, int id) {
             // (an id outside the data, from a graph the library did not write, is not offered:
             // it would index the bucket counters out of bounds)
-            offer_append(take && (unsigned)id < (unsigned)n, ((u32)id << 10) | (u32)(i & (kBktRows - 1)), shift, offers,
-                         hist, &fill);
+            offer_append<RB>(take && (unsigned)id < (unsigned)n, ((u32)id << RB) | (u32)(i & (kRows - 1)), shift, offers,
+                             hist, &fill);
         });
     }
     __syncthreads();
-    offers_flush(offers, hist, cursor, n_buckets, shift, fill, offer_runs + (size_t)blockIdx.x * kBktRows * L, table);
+    offers_flush<RB>(offers, hist, cursor, n_buckets, shift, fill, offer_runs + (size_t)blockIdx.x * kRows * L, table);
 }
 
-// Reverse-old offers of kBktRows rows (to points that join something, as in reverse_old_kernel).
-// LDS: offers [kBktRows * K] words, hist and cursor [n_buckets] int each.
-__global__ void __launch_bounds__(kBktThreads)
+// Reverse-old offers of 1 << RB rows (to points that join something, as in reverse_old_kernel).
+// LDS: offers [K << RB] words, hist and cursor [n_buckets] int each.
+template <int RB>
+__global__ void __launch_bounds__(1 << RB)
 reverse_old_bucket_kernel(const int *__restrict__ od, int n, int K, const u64 *__restrict__ active,
                           int n_buckets, int shift, u32 *__restrict__ offer_runs, u32 *__restrict__ table)
 {
     extern __shared__ __align__(16) u32 offer_sm[];
     u32 *offers = offer_sm;
-    int *hist = (int *)(offers + (size_t)kBktRows * K), *cursor = hist + n_buckets;
+    constexpr int kRows = 1 << RB, kThreads = 1 << RB;
+    int *hist = (int *)(offers + (size_t)kRows * K), *cursor = hist + n_buckets;
     __shared__ int fill;
-    for (int b = threadIdx.x; b < n_buckets; b += kBktThreads) hist[b] = 0;
+    for (int b = threadIdx.x; b < n_buckets; b += kThreads) hist[b] = 0;
     if (threadIdx.x == 0) fill = 0;
     __syncthreads();
-    const int first = blockIdx.x * kBktRows, rows_here = min(kBktRows, n - first);
-    for (int f0 = 0; f0 < rows_here * K; f0 += kBktThreads) {      // all threads take every round
+    const int first = blockIdx.x * kRows, rows_here = min(kRows, n - first);
+    for (int f0 = 0; f0 < rows_here * K; f0 += kThreads) {      // all threads take every round
         const int f = f0 + (int)threadIdx.x;
         const int id = f < rows_here * K ? od[(size_t)first * K + f] : -1;
         const bool take = id >= 0 && id < n && ((active[id / EF_WAVE] >> (id % EF_WAVE)) & 1);
-        offer_append(take, ((u32)id << 10) | (u32)(f / K), shift, offers, hist, &fill);
+        offer_append<RB>(take, ((u32)id << RB) | (u32)(f / K), shift, offers, hist, &fill);
     }
     __syncthreads();
-    offers_flush(offers, hist, cursor, n_buckets, shift, fill, offer_runs + (size_t)blockIdx.x * kBktRows * K, table);
+    offers_flush<RB>(offers, hist, cursor, n_buckets, shift, fill, offer_runs + (size_t)blockIdx.x * kRows * K, table);
 }
 
-// The lists of one bucket.  run_cap: offers per part of an offer block (kBktRows * L or * K).
+// The lists of one bucket.  run_cap: offers per part of an offer block (its rows * L or * K).
 // Every key goes through the bounded insertion; all slots start as the largest key, so a list
 // fills from slot 0 up and then keeps its L smallest keys.
 // LDS: lists [bucket's targets * L] u64, scan [n_blocks + 1] and start [n_blocks] int;
-// n_blocks <= kBktMaxRuns.
+// n_blocks <= twice the threads, at least one thread per target.
 // What the time is made of (headline workload, 82 us per launch on average, 170 us for the
 // ten million offers of the first iteration): 18 us fixed, about 5 ns per thousand offers to
 // find and load them, the rest the insertions; by the counters the SIMDs issue an instruction
@@ -1340,25 +1377,26 @@ reverse_old_bucket_kernel(const int *__restrict__ od, int n, int K, const u64 *_
 // target in LDS (count, prefix sum, scatter) and one thread per target selecting its L smallest
 // alone, without atomics (175 us: the popular points' threads run long, and the offers are
 // found twice).
-__host__ __device__ inline size_t bucket_lists_lds(int L, int n_blocks)
+__host__ __device__ inline size_t bucket_lists_lds(int L, int shift, int n_blocks)
 {
-    return ((size_t)L << bucket_shift(L)) * 8 + ((size_t)2 * n_blocks + 2) * 4;
+    return ((size_t)L << shift) * 8 + ((size_t)2 * n_blocks + 2) * 4;
 }
 
-template <int SHIFT, int LT>      // log2 of the bucket's targets; the list length if fixed at compile time, else 0
+// SHIFT: log2 of the bucket's targets, LT: the list length, if fixed at compile time (else 0); RB: row bits of an offer
+template <int SHIFT, int LT, int RB>
 __global__ void __launch_bounds__(kBktThreads)
 bucket_lists_kernel(const u32 *__restrict__ offer_runs, const u32 *__restrict__ table, int n_blocks,
-                    int run_cap, u64 stream_key, int n, int L_, u32 *__restrict__ lists,
+                    int run_cap, u64 stream_key, int n, int L_, int shift, u32 *__restrict__ lists,
                     int *__restrict__ counts)
 {
     const int L = LT ? LT : L_;
     extern __shared__ __align__(16) u64 list_sm[];
     u64 *ll = list_sm;
-    constexpr int targets = 1 << SHIFT;
+    const int targets = 1 << (SHIFT ? SHIFT : shift), n_thr = SHIFT ? kBktThreads : (int)blockDim.x;
     int *scan = (int *)(ll + (size_t)targets * L), *start = scan + n_blocks + 1;
     __shared__ int wave_tot[kBktThreads / EF_WAVE];
     const int t = threadIdx.x, first = blockIdx.x * targets, rows_here = min(targets, n - first);
-    for (int f = t; f < targets * L; f += kBktThreads) ll[f] = ~0ULL;
+    for (int f = t; f < targets * L; f += n_thr) ll[f] = ~0ULL;
     const u32 *runs = table + (size_t)blockIdx.x * n_blocks;
     {
         const int k0 = 2 * t;
@@ -1377,11 +1415,11 @@ bucket_lists_kernel(const u32 *__restrict__ offer_runs, const u32 *__restrict__ 
             scan[k0 + 1] = off + c0;
             start[k0 + 1] = (int)(r1 >> 16);
         }
-        if (t == kBktThreads - 1) scan[n_blocks] = off + c0 + c1;      // everything before it, and its own
+        if (t == n_thr - 1) scan[n_blocks] = off + c0 + c1;      // everything before it, and its own
     }
     __syncthreads();
     const int total = scan[n_blocks];
-    for (int j = t; j < total; j += kBktThreads) {      // neighbouring threads take neighbouring offers
+    for (int j = t; j < total; j += n_thr) {      // neighbouring threads take neighbouring offers
         int lo = 0, hi = n_blocks;      // scan[lo] <= j < scan[hi]
         while (hi - lo > 1) {
             const int mid = (lo + hi) >> 1;
@@ -1389,7 +1427,7 @@ bucket_lists_kernel(const u32 *__restrict__ offer_runs, const u32 *__restrict__ 
             else hi = mid;
         }
         const u32 o = offer_runs[(size_t)lo * run_cap + start[lo] + (j - scan[lo])];
-        const int target = (int)(o >> 10), source = lo * kBktRows + (int)(o & (kBktRows - 1));
+        const int target = (int)(o >> RB), source = (lo << RB) + (int)(o & ((1u << RB) - 1));
         const int row = target - first;
         if ((unsigned)row >= (unsigned)rows_here) continue;      // cannot happen: runs are filed by bucket
         const u64 key = reverse_key(stream_key, target, source);
@@ -1411,7 +1449,7 @@ bucket_lists_kernel(const u32 *__restrict__ offer_runs, const u32 *__restrict__ 
     }
     __syncthreads();
     // only the sources are wanted from here on (the keys decided who is in the list)
-    for (int f = t; f < rows_here * L; f += kBktThreads) lists[(size_t)first * L + f] = (u32)ll[f];
+    for (int f = t; f < rows_here * L; f += n_thr) lists[(size_t)first * L + f] = (u32)ll[f];
     if (t < rows_here) {
         int c = 0;
         for (int a = 0; a < L; ++a) c += ll[t * L + a] != ~0ULL ? 1 : 0;
@@ -1443,76 +1481,16 @@ inline JoinClasses join_classes(int max_rows, bool reg_ok)
     return jc;
 }
 
-// After sampling and the reverse lists: one thread per point merges its four id lists
-// into U_new ++ U_old (Alg. 4: G_new U G_rnew, G_old U G_rold), without duplicates and
-// with everything already in U_new left out of U_old, and files the point under one of
-// the work lists by the number of vectors its join gathers.
-// Points with an empty U_new are dropped.  A thread compares only what can collide:
-// ids inside one sampled list are distinct, and so are the sources inside one reverse
-// list.  ulist: [n][cap] (written through LDS so that the stores coalesce), ucount: [n]
-// (m_new, m); work: [jc.n][n], work_count: [kMaxClasses].
-template <bool IDS32>      // reverse lists hold 32-bit sources (bucket scheme), not 64-bit keys
-__global__ void prepare_kernel(const int *__restrict__ nw, const int *__restrict__ od,
-                               const int *__restrict__ nw_c, const int *__restrict__ od_c,
-                               const u64 *__restrict__ rnew, const u64 *__restrict__ rold,
-                               const int *__restrict__ rnew_c, const int *__restrict__ rold_c,
-                               int n, int K, int L, int cap, u32 cap_magic, JoinClasses jc,
-                               int *__restrict__ ulist, int2 *__restrict__ ucount,
-                               int *__restrict__ work, int *__restrict__ work_count,
-                               long long *__restrict__ part)
+// End of the kernels below: every thread of the block holds a point (i; class cls, -1 = no join; its pairs and
+// vectors) and files it.
+__device__ inline void append_points(int cls, int i, int n, int evals, int rows, const JoinClasses &jc,
+                                     int *__restrict__ work, int *__restrict__ work_count,
+                                     long long *__restrict__ part)
 {
-    extern __shared__ int ids_sh[];
-    const int pitch = cap | 1;                      // odd: threads hit different banks
-    int *mine = ids_sh + threadIdx.x * pitch;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    int cls = -1, m = 0;
-    int evals = 0, rows = 0;      // this point's share of the iteration's work counters
-    if (i < n) {
-        const int c_new = nw_c[i];
-        int c_old = od_c[i];
-        const int rn = min(rnew_c[i], L), ro = min(rold_c[i], L);
-        if (c_new + rn == 0) c_old = 0;      // empty U_new: no join, nothing to list
-        for (int a = 0; a < c_new; ++a) mine[m++] = nw[(size_t)i * L + a];
-        for (int a = 0; a < rn; ++a) {
-            const int id = IDS32 ? (int)((const u32 *)rnew)[(size_t)i * L + a] : (int)(u32)rnew[(size_t)i * L + a];
-            bool dup = false;
-            for (int k = 0; k < c_new; ++k) dup |= mine[k] == id;
-            if (!dup) mine[m++] = id;
-        }
-        const int m_new = m;
-        for (int a = 0; a < c_old; ++a) {
-            const int id = od[(size_t)i * K + a];
-            bool dup = false;
-            for (int k = c_new; k < m_new; ++k) dup |= mine[k] == id;      // only reverse-new can collide
-            if (!dup) mine[m++] = id;
-        }
-        const int m_mid = m;
-        for (int a = 0; a < ro; ++a) {
-            const int id = IDS32 ? (int)((const u32 *)rold)[(size_t)i * L + a] : (int)(u32)rold[(size_t)i * L + a];
-            bool dup = false;
-            for (int k = 0; k < m_mid; ++k) dup |= mine[k] == id;
-            if (!dup) mine[m++] = id;
-        }
-        ucount[i] = make_int2(m_new, m);
-        if (m_new >= 1 && m >= 2) {
-            cls = 0;
-            while (cls < jc.n - 1 && m > jc.bound[cls]) ++cls;
-            evals = m_new * (m_new - 1) / 2 + m_new * (m - m_new);
-            rows = m;
-        }
-    }
-    for (int k = m; k < cap; ++k) mine[k] = -1;
-    __syncthreads();
-    // coalesced write-out of the block's lists
-    const int first = blockIdx.x * blockDim.x, rows_here = min((int)blockDim.x, n - first);
-    for (int f = threadIdx.x; f < rows_here * cap; f += blockDim.x) {
-        const int r = (int)(((u64)(u32)f * cap_magic) >> 32), c = f - r * cap;
-        ulist[(size_t)first * cap + f] = ids_sh[r * pitch + c];
-    }
     // append to the work lists: ranks inside the block first, then one counter bump per
     // list and block (bumps of one address serialise at about 11 ns each)
-    __shared__ int wave_cnt[kMaxClasses][kBlock / EF_WAVE], block_base[kMaxClasses];
-    __shared__ int wave_sum[3][kBlock / EF_WAVE];
+    __shared__ int wave_cnt[kMaxClasses][16], block_base[kMaxClasses];
+    __shared__ int wave_sum[3][16];
     const int lane = ef_lane(), wave = threadIdx.x / EF_WAVE, n_waves = blockDim.x / EF_WAVE;
     int rank = 0;
     for (int c = 0; c < jc.n; ++c) {
@@ -1546,6 +1524,162 @@ __global__ void prepare_kernel(const int *__restrict__ nw, const int *__restrict
         for (int v = 0; v < wave; ++v) off += wave_cnt[cls][v];
         work[(size_t)cls * n + off] = i;
     }
+}
+
+// After sampling and the reverse lists: one thread per point merges its four id lists
+// into U_new ++ U_old (Alg. 4: G_new U G_rnew, G_old U G_rold), without duplicates and
+// with everything already in U_new left out of U_old, and files the point under one of
+// the work lists by the number of vectors its join gathers.
+// Points with an empty U_new are dropped.  A thread compares only what can collide:
+// ids inside one sampled list are distinct, and so are the sources inside one reverse
+// list.  ulist: [n][cap] (written through LDS so that the stores coalesce), ucount: [n]
+// (m_new, m); work: [jc.n][n], work_count: [kMaxClasses].
+__global__ void prepare_kernel(const int *__restrict__ nw, const int *__restrict__ od,
+                               const int *__restrict__ nw_c, const int *__restrict__ od_c,
+                               const u64 *__restrict__ rnew, const u64 *__restrict__ rold,
+                               const int *__restrict__ rnew_c, const int *__restrict__ rold_c,
+                               int n, int K, int L, int cap, u32 cap_magic, JoinClasses jc,
+                               int *__restrict__ ulist, int2 *__restrict__ ucount,
+                               int *__restrict__ work, int *__restrict__ work_count,
+                               long long *__restrict__ part)
+{
+    extern __shared__ int ids_sh[];
+    const int pitch = cap | 1;                      // odd: threads hit different banks
+    int *mine = ids_sh + threadIdx.x * pitch;
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    int cls = -1, m = 0;
+    int evals = 0, rows = 0;      // this point's share of the iteration's work counters
+    if (i < n) {
+        const int c_new = nw_c[i];
+        int c_old = od_c[i];
+        const int rn = min(rnew_c[i], L), ro = min(rold_c[i], L);
+        if (c_new + rn == 0) c_old = 0;      // empty U_new: no join, nothing to list
+        for (int a = 0; a < c_new; ++a) mine[m++] = nw[(size_t)i * L + a];
+        for (int a = 0; a < rn; ++a) {
+            const int id = (int)(u32)rnew[(size_t)i * L + a];
+            bool dup = false;
+            for (int k = 0; k < c_new; ++k) dup |= mine[k] == id;
+            if (!dup) mine[m++] = id;
+        }
+        const int m_new = m;
+        for (int a = 0; a < c_old; ++a) {
+            const int id = od[(size_t)i * K + a];
+            bool dup = false;
+            for (int k = c_new; k < m_new; ++k) dup |= mine[k] == id;      // only reverse-new can collide
+            if (!dup) mine[m++] = id;
+        }
+        const int m_mid = m;
+        for (int a = 0; a < ro; ++a) {
+            const int id = (int)(u32)rold[(size_t)i * L + a];
+            bool dup = false;
+            for (int k = 0; k < m_mid; ++k) dup |= mine[k] == id;
+            if (!dup) mine[m++] = id;
+        }
+        ucount[i] = make_int2(m_new, m);
+        if (m_new >= 1 && m >= 2) {
+            cls = 0;
+            while (cls < jc.n - 1 && m > jc.bound[cls]) ++cls;
+            evals = m_new * (m_new - 1) / 2 + m_new * (m - m_new);
+            rows = m;
+        }
+    }
+    for (int k = m; k < cap; ++k) mine[k] = -1;
+    __syncthreads();
+    // coalesced write-out of the block's lists
+    const int first = blockIdx.x * blockDim.x, rows_here = min((int)blockDim.x, n - first);
+    for (int f = threadIdx.x; f < rows_here * cap; f += blockDim.x) {
+        const int r = (int)(((u64)(u32)f * cap_magic) >> 32), c = f - r * cap;
+        ulist[(size_t)first * cap + f] = ids_sh[r * pitch + c];
+    }
+    append_points(cls, i, n, evals, rows, jc, work, work_count, part);
+}
+
+// The same for short lists (the bucket scheme: K, L <= 32, 32-bit sources), eight lanes per point, E ids
+// of every list per lane (8 E >= K, L): all four lists travel together, where a thread that walks
+// them alone waits for one id after the other; duplicates are found against the ids already in
+// LDS, places come from ballots.  64 points per pass, `passes` (at most 4) per block of 512 threads: a
+// block bumps the work lists' counters once (11 ns each, one after the other).  Per launch, before and after: 10^4 points of
+// degree 10 23.5 -> 9.3 us, 10^5 of degree 20 50 -> 31, 10^6 of degree 10 108 -> 104.
+constexpr int kPrepPoints = 64, kPrepThreads = 8 * kPrepPoints, kPrepMaxPasses = 4;
+template <int E>
+__global__ void __launch_bounds__(kPrepThreads)
+prepare_group_kernel(const int *__restrict__ nw, const int *__restrict__ od,
+                     const int *__restrict__ nw_c, const int *__restrict__ od_c,
+                     const u32 *__restrict__ rnew, const u32 *__restrict__ rold,
+                     const int *__restrict__ rnew_c, const int *__restrict__ rold_c,
+                     int n, int K, int L, int cap, u32 cap_magic, JoinClasses jc, int passes,
+                     int *__restrict__ ulist, int2 *__restrict__ ucount,
+                     int *__restrict__ work, int *__restrict__ work_count,
+                     long long *__restrict__ part)
+{
+    extern __shared__ int ids_sh[];
+    const int pitch = cap | 1;                      // odd: points hit different banks
+    __shared__ int2 sizes[kPrepPoints * kPrepMaxPasses];      // (m_new, m) of every point
+    const int tid = threadIdx.x, gl = tid & 7, grp_shift = ef_lane() & 56;
+    const int first = blockIdx.x * kPrepPoints * passes;
+    auto wave_sync = [&]() {      // one wave: its LDS operations complete in program order
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
+    for (int pass = 0; pass < passes; ++pass) {
+        const int p = pass * kPrepPoints + (tid >> 3), i = first + p;
+        const bool ok = i < n;
+        const size_t row_l = (size_t)(ok ? i : 0) * L, row_k = (size_t)(ok ? i : 0) * K;
+        int *mine = ids_sh + p * pitch;
+        int c_new = ok ? nw_c[i] : 0, c_old = ok ? od_c[i] : 0, rn = ok ? min(rnew_c[i], L) : 0, ro = ok ? min(rold_c[i], L) : 0;
+        int a_new[E], a_rn[E], a_old[E], a_ro[E];
+#pragma unroll
+        for (int h = 0; h < E; ++h) {      // (entries beyond a list's count are read along)
+            const int al = min(gl + 8 * h, L - 1), ak = min(gl + 8 * h, K - 1);
+            a_new[h] = nw[row_l + al];
+            a_rn[h] = (int)rnew[row_l + al];
+            a_old[h] = od[row_k + ak];
+            a_ro[h] = (int)rold[row_l + al];
+        }
+        if (c_new + rn == 0) c_old = ro = 0;      // empty U_new: no join, nothing to list
+        // entries [0, cnt) of a list join `mine` behind the m there are, but for those among mine[from .. to)
+        int m = 0;
+        auto merge = [&](const int (&a)[E], int cnt, int from, int to) {
+#pragma unroll
+            for (int h = 0; h < E; ++h) {
+                bool fresh = gl + 8 * h < cnt;
+                if (fresh)
+                    for (int k = from; k < to; ++k) fresh &= mine[k] != a[h];
+                const int mask = (int)((__ballot(fresh) >> grp_shift) & 0xFF);
+                if (fresh) mine[m + __popc(mask & ((1 << gl) - 1))] = a[h];
+                m += __popc(mask);
+            }
+            wave_sync();
+        };
+        merge(a_new, c_new, 0, 0);
+        merge(a_rn, rn, 0, c_new);
+        const int m_new = m;
+        merge(a_old, c_old, c_new, m_new);      // only reverse-new can collide
+        merge(a_ro, ro, 0, m);
+        for (int k = m + gl; k < cap; k += 8) mine[k] = -1;
+        if (gl == 0) {
+            sizes[p] = make_int2(m_new, m);
+            if (ok) ucount[i] = make_int2(m_new, m);
+        }
+    }
+    __syncthreads();
+    // coalesced write-out of the block's lists
+    const int here = min(kPrepPoints * passes, n - first);
+    for (int f = tid; f < here * cap; f += kPrepThreads) {
+        const int r = (int)(((u64)(u32)f * cap_magic) >> 32), c = f - r * cap;
+        ulist[(size_t)first * cap + f] = ids_sh[r * pitch + c];
+    }
+    int cls = -1, evals = 0, rows = 0;
+    if (tid < here) {
+        const int m_new = sizes[tid].x, m = sizes[tid].y;
+        if (m_new >= 1 && m >= 2) {
+            cls = 0;
+            while (cls < jc.n - 1 && m > jc.bound[cls]) ++cls;
+            evals = m_new * (m_new - 1) / 2 + m_new * (m - m_new);
+            rows = m;
+        }
+    }
+    append_points(cls, first + tid, n, evals, rows, jc, work, work_count, part);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1820,7 +1954,6 @@ __global__ void __launch_bounds__(512) join_kernel(const float *__restrict__ X, 
 // points per round and appends them to the work lists together (one counter bump per list and
 // round).  Same lists as prepare_kernel up to the order of the ids inside U_new and U_old,
 // which nothing depends on.  part: one triple per block.
-template <bool IDS32>
 __global__ void __launch_bounds__(kBlock)
 prepare_wave_kernel(const int *__restrict__ nw, const int *__restrict__ od,
                     const int *__restrict__ nw_c, const int *__restrict__ od_c,
@@ -1880,7 +2013,7 @@ prepare_wave_kernel(const int *__restrict__ nw, const int *__restrict__ od,
                 }
                 for (int a0 = 0; a0 < rn; a0 += EF_WAVE) {
                     const int a = a0 + lane;
-                    const int id = a < rn ? (IDS32 ? (int)((const u32 *)rnew)[(size_t)i * L + a] : (int)(u32)rnew[(size_t)i * L + a]) : -1;
+                    const int id = a < rn ? (int)(u32)rnew[(size_t)i * L + a] : -1;
                     add(id, a < rn);
                 }
                 m_new = m;
@@ -1890,7 +2023,7 @@ prepare_wave_kernel(const int *__restrict__ nw, const int *__restrict__ od,
                 }
                 for (int a0 = 0; a0 < ro; a0 += EF_WAVE) {
                     const int a = a0 + lane;
-                    const int id = a < ro ? (IDS32 ? (int)((const u32 *)rold)[(size_t)i * L + a] : (int)(u32)rold[(size_t)i * L + a]) : -1;
+                    const int id = a < ro ? (int)(u32)rold[(size_t)i * L + a] : -1;
                     add(id, a < ro);
                 }
                 wave_sync();
@@ -2937,6 +3070,8 @@ NndWs carve_nnd(void *ws, int64_t n, int K, int L)
     w.upd_block = (int *)take((size_t)(2 * kRegGrid + (n_lists - 2) * kMaxLargeGrid) * 4);
     w.rnew = (u64 *)take((size_t)n * L * 8);
     w.rold = (u64 *)take((size_t)n * L * 8);
+    // (32-bit sources fill the first half; the table of many small runs lies behind them)
+    if (bkt && bucket_shape(n, L).row_bits == 8) w.run_table = (u32 *)w.rold + (size_t)n * L;
     w.list_max = (u64 *)take((size_t)n * 2 * 8);
     w.active = (u64 *)take((size_t)(n + 63) / 64 * 8);
     w.fresh = (u64 *)take(8);
@@ -3161,7 +3296,9 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
     const bool reg_ok = aligned || d >= 4;
     const int rows1 = reg_ok ? 32 : 0;
     const JoinClasses jc = join_classes(max_rows, reg_ok);
-    const int n_upd_block = 2 * kRegGrid + (jc.n - 2) * kMaxLargeGrid;
+    // (a work list has n entries at most: of few points more blocks would only start and end)
+    const int reg_grid = n < kRegGrid ? (int)n : kRegGrid;
+    const int n_upd_block = 2 * reg_grid + (jc.n - 2) * kMaxLargeGrid;
     struct Shape {
         int cap_rows, threads, s_cap, q_cap, grid;
         size_t lds;
@@ -3216,7 +3353,6 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
         return (size_t)(6 * R + align4(R * (R - 1) / 2 + 8)) * 4 +
                (size_t)reg_q_cap * sizeof(Proposal);
     };
-    const int reg_grid = kRegGrid;
     // prepare: one thread per point with max_rows ids of LDS each
     int prep_threads = (int)(65536 / ((size_t)(max_rows | 1) * 4)) / EF_WAVE * EF_WAVE;
     prep_threads = prep_threads > kBlock ? kBlock : (prep_threads < EF_WAVE ? EF_WAVE : prep_threads);
@@ -3227,7 +3363,16 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
     while (prep_hash < 2 * max_rows) prep_hash <<= 1;
     const size_t prep_wave_lds = (size_t)(kBlock / EF_WAVE) * (prep_hash + max_rows + EF_WAVE) * 4;
     const int prep_wave_grid = min(grid_for((size_t)n, kBlock), 256 * 8);
-    const int n_part = prep_wave ? prep_wave_grid : grid_for((size_t)n, prep_threads);
+    // short lists: eight lanes per point, as many points per block as keep a thousand blocks busy
+    const bool prep_group = bucketed_lists(n, K, L);
+    int prep_passes = 1;
+    while (prep_passes < kPrepMaxPasses && n > (int64_t)kPrepPoints * prep_passes * 512 &&
+           (size_t)kPrepPoints * 2 * prep_passes * (max_rows | 1) * 4 <= 65536)
+        prep_passes *= 2;
+    const size_t prep_group_lds = (size_t)kPrepPoints * prep_passes * (max_rows | 1) * 4;
+    const int n_part = prep_group  ? grid_for((size_t)n, kPrepPoints * prep_passes)
+                       : prep_wave ? prep_wave_grid
+                                   : grid_for((size_t)n, prep_threads);
     // filter margins: Gram-form rounding error <= (2*dpad + 4) u (|a|^2 + |b|^2), u = 2^-24,
     // doubled; the fixed-order distance is within (d/16 + 8) u of the true one, doubled twice
     const float margin_rel = (float)((4.0 * dpad + 16.0) * 5.9604644775390625e-08);
@@ -3250,20 +3395,27 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
     // reverse lists by buckets (short rows and lists): LDS of an offer block (words) or a list
     // block (keys) with `per_row` of them per row, and one int per bucket or offer block twice over
     const bool bkt = bucketed_lists(n, K, L);
-    const int n_bkt = (int)((n + kBktRows - 1) / kBktRows);      // offer blocks
-    const int bshift = bucket_shift(L), n_buckets = (int)(((n - 1) >> bshift) + 1);
-    auto bkt_lds = [&](int per_row) { return (size_t)kBktRows * per_row * 4 + ((size_t)2 * n_buckets + 4) * 4; };
+    const BucketShape bs = bucket_shape(n, L);
+    const int bkt_rows = 1 << bs.row_bits;
+    const bool bkt_small = bs.row_bits == 8;
+    auto bkt_lds = [&](int per_row) { return (size_t)bkt_rows * per_row * 4 + ((size_t)2 * bs.buckets + 4) * 4; };
+    const size_t lists_lds = bkt ? bucket_lists_lds(L, bs.shift, bs.blocks) : 0;
+    // (list lengths of 10 and 20 are compiled in: the scan of a list unrolls, 8 % off the kernel)
+    typedef void (*SampleKernel)(u64 *, int, int, int, int *, int *, int *, int *, u32 *, int, int, u32 *, u32 *);
+    typedef void (*ReverseOldKernel)(const int *, int, int, const u64 *, int, int, u32 *, u32 *);
+    typedef void (*ListsKernel)(const u32 *, const u32 *, int, int, u64, int, int, int, u32 *, int *);
+    const SampleKernel bkt_sample = bkt_small ? (K <= 16 ? sample_bucket_kernel<2, 8> : sample_bucket_kernel<4, 8>)
+                                              : (K <= 16 ? sample_bucket_kernel<2, 10> : sample_bucket_kernel<4, 10>);
+    const ReverseOldKernel bkt_old = bkt_small ? reverse_old_bucket_kernel<8> : reverse_old_bucket_kernel<10>;
+    const ListsKernel bkt_lists =
+        bkt_small ? (L == 10 ? bucket_lists_kernel<0, 10, 8> : L == 20 ? bucket_lists_kernel<0, 20, 8> : bucket_lists_kernel<0, 0, 8>)
+        : L == 10 ? bucket_lists_kernel<10, 10, 10>
+        : L == 20 ? bucket_lists_kernel<9, 20, 10>
+        : bs.shift == 10 ? bucket_lists_kernel<10, 0, 10> : bucket_lists_kernel<9, 0, 10>;
     if (bkt) {
-        EF_HIP_CHECK(hipFuncSetAttribute(K <= 16 ? (const void *)sample_bucket_kernel<2> : (const void *)sample_bucket_kernel<4>,
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)bkt_lds(L)));
-        EF_HIP_CHECK(hipFuncSetAttribute((const void *)reverse_old_bucket_kernel,
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)bkt_lds(K)));
-        // (list lengths of 10 and 20 are compiled in: the scan of a list unrolls, 8 % off the kernel)
-        EF_HIP_CHECK(hipFuncSetAttribute(L == 10   ? (const void *)bucket_lists_kernel<10, 10>
-                                         : L == 20 ? (const void *)bucket_lists_kernel<9, 20>
-                                         : bshift == 10 ? (const void *)bucket_lists_kernel<10, 0>
-                                                        : (const void *)bucket_lists_kernel<9, 0>,
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)bucket_lists_lds(L, n_bkt)));
+        EF_HIP_CHECK(hipFuncSetAttribute((const void *)bkt_sample, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bkt_lds(L)));
+        EF_HIP_CHECK(hipFuncSetAttribute((const void *)bkt_old, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bkt_lds(K)));
+        EF_HIP_CHECK(hipFuncSetAttribute((const void *)bkt_lists, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lists_lds));
     }
     if (max_rows > rows1 && !tiles)
         EF_HIP_CHECK(hipFuncSetAttribute(K >= 2 * EF_WIDE_PIECES ? (const void *)join_kernel<true>
@@ -3306,47 +3458,29 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
     sample_kernel<G, E><<<grid_for((size_t)n * G, kBlock), kBlock, 0, st>>>(                     \
         graph, (int)n, K, L, kn, w.nw, w.od, w.nw_c, w.od_c, w.rnew, w.rnew_c, ovf,              \
         ovf_region, w.ovf_count, w.worst)
-#define EF_BUCKET_LISTS(RUN_CAP, KEY, LISTS, COUNTS)                                             \
-    do {                                                                                         \
-        if (L == 10)                                                                             \
-            bucket_lists_kernel<10, 10><<<n_buckets, kBktThreads, bucket_lists_lds(L, n_bkt), st>>>( \
-                w.offer_runs, w.run_table, n_bkt, RUN_CAP, KEY, (int)n, L, (u32 *)(LISTS), COUNTS); \
-        else if (L == 20)                                                                        \
-            bucket_lists_kernel<9, 20><<<n_buckets, kBktThreads, bucket_lists_lds(L, n_bkt), st>>>( \
-                w.offer_runs, w.run_table, n_bkt, RUN_CAP, KEY, (int)n, L, (u32 *)(LISTS), COUNTS); \
-        else if (bshift == 10)                                                                   \
-            bucket_lists_kernel<10, 0><<<n_buckets, kBktThreads, bucket_lists_lds(L, n_bkt), st>>>( \
-                w.offer_runs, w.run_table, n_bkt, RUN_CAP, KEY, (int)n, L, (u32 *)(LISTS), COUNTS); \
-        else                                                                                     \
-            bucket_lists_kernel<9, 0><<<n_buckets, kBktThreads, bucket_lists_lds(L, n_bkt), st>>>( \
-                w.offer_runs, w.run_table, n_bkt, RUN_CAP, KEY, (int)n, L, (u32 *)(LISTS), COUNTS); \
-    } while (0)
 #define EF_REVERSE_OLD(G)                                                                        \
     reverse_old_kernel<G><<<grid_for((size_t)n * G, kBlock), kBlock, 0, st>>>(                   \
         w.od, (int)n, K, L, ko, w.active, w.rold, w.rold_c, ovf, ovf_region, w.ovf_count)
             if (bkt) {
-                if (K <= 16)
-                    sample_bucket_kernel<2><<<n_bkt, kBktThreads, bkt_lds(L), st>>>(
-                        graph, (int)n, K, L, w.nw, w.od, w.nw_c, w.od_c, w.worst, n_buckets, bshift, w.offer_runs, w.run_table);
-                else
-                    sample_bucket_kernel<4><<<n_bkt, kBktThreads, bkt_lds(L), st>>>(
-                        graph, (int)n, K, L, w.nw, w.od, w.nw_c, w.od_c, w.worst, n_buckets, bshift, w.offer_runs, w.run_table);
-                EF_BUCKET_LISTS(kBktRows * L, kn, w.rnew, w.rnew_c);
+                bkt_sample<<<bs.blocks, bkt_rows, bkt_lds(L), st>>>(graph, (int)n, K, L, w.nw, w.od, w.nw_c, w.od_c, w.worst,
+                                                                   bs.buckets, bs.shift, w.offer_runs, w.run_table);
+                bkt_lists<<<bs.buckets, bs.threads, lists_lds, st>>>(w.offer_runs, w.run_table, bs.blocks, bkt_rows * L, kn,
+                                                                    (int)n, L, bs.shift, (u32 *)w.rnew, w.rnew_c);
             } else if (K <= 16) EF_SAMPLE(16, 1);
             else if (K <= 32) EF_SAMPLE(32, 1);
             else if (K <= 64) EF_SAMPLE(64, 1);
             else EF_SAMPLE(64, 2);
             active_kernel<<<grid_for((size_t)n, kBlock), kBlock, 0, st>>>(w.nw_c, w.rnew_c, (int)n, w.active);
             if (bkt) {
-                reverse_old_bucket_kernel<<<n_bkt, kBktThreads, bkt_lds(K), st>>>(
-                    w.od, (int)n, K, w.active, n_buckets, bshift, w.offer_runs, w.run_table);
-                EF_BUCKET_LISTS(kBktRows * K, ko, w.rold, w.rold_c);
+                bkt_old<<<bs.blocks, bkt_rows, bkt_lds(K), st>>>(w.od, (int)n, K, w.active, bs.buckets, bs.shift, w.offer_runs,
+                                                                w.run_table);
+                bkt_lists<<<bs.buckets, bs.threads, lists_lds, st>>>(w.offer_runs, w.run_table, bs.blocks, bkt_rows * K, ko,
+                                                                    (int)n, L, bs.shift, (u32 *)w.rold, w.rold_c);
             } else if (K <= 16) EF_REVERSE_OLD(16);
             else if (K <= 32) EF_REVERSE_OLD(32);
             else EF_REVERSE_OLD(64);
 #undef EF_SAMPLE
 #undef EF_REVERSE_OLD
-#undef EF_BUCKET_LISTS
             if (bkt) {
             } else if (L >= 2 * EF_WIDE_PIECES)
                 reverse_overflow_kernel<true><<<dim3(kOvfBlocksPerQueue, kOvfQueues), kBlock, 0, st>>>(
@@ -3355,24 +3489,25 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
                 reverse_overflow_kernel<false><<<dim3(kOvfBlocksPerQueue, kOvfQueues), kBlock, 0, st>>>(
                     ovf, ovf_region, w.ovf_count, (size_t)n, w.rnew, w.rold, w.list_max, L);
         }
-#define EF_PREPARE(IDS32)                                                                          \
-    prepare_kernel<IDS32><<<grid_for((size_t)n, prep_threads), prep_threads, prep_lds, st>>>(       \
-        w.nw, w.od, w.nw_c, w.od_c, w.rnew, w.rold, w.rnew_c, w.rold_c, (int)n, K, L, max_rows,     \
-        (u32)(((1ULL << 32) + max_rows - 1) / max_rows), jc, w.ulist, w.ucount, w.work,            \
+        const u32 rows_magic = (u32)(((1ULL << 32) + max_rows - 1) / max_rows);
+#define EF_PREPARE_GROUP(E)                                                                        \
+    prepare_group_kernel<E><<<n_part, kPrepThreads, prep_group_lds, st>>>(                          \
+        w.nw, w.od, w.nw_c, w.od_c, (const u32 *)w.rnew, (const u32 *)w.rold, w.rnew_c, w.rold_c,   \
+        (int)n, K, L, max_rows, rows_magic, jc, prep_passes, w.ulist, w.ucount, w.work,            \
         w.work_count, w.part)
-#define EF_PREPARE_WAVE(IDS32)                                                                      \
-    prepare_wave_kernel<IDS32><<<prep_wave_grid, kBlock, prep_wave_lds, st>>>(                      \
-        w.nw, w.od, w.nw_c, w.od_c, w.rnew, w.rold, w.rnew_c, w.rold_c, (int)n, K, L, max_rows,     \
-        prep_hash, jc, w.ulist, w.ucount, w.work, w.work_count, w.part)
-        if (prep_wave) {
-            if (bkt) EF_PREPARE_WAVE(true);
-            else EF_PREPARE_WAVE(false);
+        if (prep_group) {
+            if (K <= 16 && L <= 16) EF_PREPARE_GROUP(2);
+            else EF_PREPARE_GROUP(4);
+        } else if (prep_wave) {
+            prepare_wave_kernel<<<prep_wave_grid, kBlock, prep_wave_lds, st>>>(
+                w.nw, w.od, w.nw_c, w.od_c, w.rnew, w.rold, w.rnew_c, w.rold_c, (int)n, K, L, max_rows, prep_hash, jc,
+                w.ulist, w.ucount, w.work, w.work_count, w.part);
         } else {
-            if (bkt) EF_PREPARE(true);
-            else EF_PREPARE(false);
+            prepare_kernel<<<n_part, prep_threads, prep_lds, st>>>(
+                w.nw, w.od, w.nw_c, w.od_c, w.rnew, w.rold, w.rnew_c, w.rold_c, (int)n, K, L, max_rows, rows_magic, jc,
+                w.ulist, w.ucount, w.work, w.work_count, w.part);
         }
-#undef EF_PREPARE_WAVE
-#undef EF_PREPARE
+#undef EF_PREPARE_GROUP
         if (ev) EF_HIP_CHECK(hipEventRecord(ev[5 * it + 1], st));
         if (tiles && max_rows > rows1)
             graph_ids_kernel<<<min(grid_for((size_t)n * K, kBlock), 256 * 64), kBlock, 0, st>>>(graph, (size_t)n * K, w.gid);
@@ -3426,7 +3561,7 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
                 const size_t tl = tile_lds_bytes(jc.bound[c]);
                 long per_cu = (long)(kLdsLimit / tl);
                 per_cu = per_cu > 4 * kTileWaves ? 4 * kTileWaves : (per_cu < 1 ? 1 : per_cu);      // by registers
-                const int tgrid = (int)(256 * per_cu * 4);
+                const int tgrid = (int)min((long)n, 256 * per_cu * 4);
                 int *upd = w.upd_block + 2 * reg_grid + (c - 2) * kMaxLargeGrid;
                 const u32 km = (u32)(((1ULL << 32) + K - 1) / K);
                 const u32 kqm = (u32)(((1ULL << 32) + ((K + 3) >> 2) - 1) / ((K + 3) >> 2));

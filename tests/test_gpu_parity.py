@@ -419,6 +419,12 @@ def test_nndescent_filter_ranges_bit_exact(ef, kind, d, K, L):
     (2_000, 40, 2, 16, 13, 7, 3),        # ... and with the filter
     (1_000, 150, 2, 16, 51, 33, 1),      # rows in LDS (long vectors, more than 32 of them), odd rows and lists
     (1_000, 8, 2, 16, 34, 3, 2),         # rows of two modulo four ids: the last load of a row repeats two
+    (65_536, 4, 1, 16, 4, 4, 2),         # the most points of the small offer blocks: 512 ranges of 128 targets,
+    (65_537, 4, 1, 16, 4, 4, 2),         # one more
+    (16_385, 4, 1, 16, 5, 3, 2),         # lists too short for their table
+    (16_385, 4, 1, 16, 32, 32, 1),       # the longest lists, ranges of 64
+    (70_000, 4, 1, 16, 3, 2, 2),         # two passes per block of the join lists, a ragged last block
+    (140_000, 4, 1, 16, 3, 2, 1),        # four
     (900, 8, 2, 16, 1, 20, 2),           # rows of one entry, joins of more than 32 vectors
     (900, 8, 2, 16, 3, 20, 2),
 ])
