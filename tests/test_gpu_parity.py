@@ -531,6 +531,29 @@ def test_reverse_lists_of_popular_points(ef, hubs):
     oracle.check_graph_invariants(X, ids, dists)
 
 
+@pytest.mark.parametrize("K,L", [(33, 32), (64, 20), (100, 50), (128, 64), (128, 1)])
+def test_sampling_of_long_rows_with_ties(ef, K, L):
+    """Rows of more than 32 entries on an integer grid (many equal distances): the L-th new entry is
+    decided by the id among entries at the same distance, exactly L marked entries stop the walk too."""
+    rng = np.random.default_rng(K + L)
+    X = rng.integers(0, 3, (1_200, 8)).astype(np.float32)
+    Xd = dev(X)
+    (perm, off, nl), (operm, ooff, onl) = trees_equal(ef, X, 3, 64, 7)
+    graph = ef.efanna_init_graph(Xd, perm, off, nl, 64, K)
+    want = oracle.init_graph(X, operm, ooff, onl, K)
+    flags = want[2].copy()
+    for i in range(0, 1_200, 3):      # a third of the rows carries exactly L new marks
+        marked = rng.permutation(K)[:L]
+        flags[i] = 0
+        flags[i, marked] = (want[0][i, marked] >= 0)
+    want = (want[0], want[1], flags)
+    graph = ef.efanna_set_graph(dev(want[0]), dev(want[1]), dev(flags))
+    for it in range(3):
+        ef.efanna_nndescent(Xd, graph, 1, L, 7, first_iter=it)
+        want = oracle.nndescent(X, *want[:3], 1, L, 7, iter0=it)
+        graph_equal(ef, graph, want)
+
+
 def test_nndescent_resume_and_recall(ef):
     name = "gmm10k_d32"
     p = synth.params(name)
