@@ -543,6 +543,60 @@ init_reg_kernel(const float *__restrict__ X, int d, const int *__restrict__ perm
     }
 }
 
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef __fp16 fp16x2 __attribute__((ext_vector_type(2)));
+
+// Eight coordinates of a vector, times a power of two, as half-precision numbers rounded towards
+// zero: an operand of the 16x16x32 matrix instruction.  Both operands of a Gram block are packed
+// the same way, so the order of the coordinates inside the operand does not matter.
+template <bool SCALED>
+__device__ inline f16x8 ef_pack_f16(const float4 &lo, const float4 &hi, float s)
+{
+    union {
+        fp16x2 h[4];
+        f16x8 v;
+    } u;
+    if (SCALED) {
+        u.h[0] = __builtin_amdgcn_cvt_pkrtz(lo.x * s, lo.y * s);
+        u.h[1] = __builtin_amdgcn_cvt_pkrtz(lo.z * s, lo.w * s);
+        u.h[2] = __builtin_amdgcn_cvt_pkrtz(hi.x * s, hi.y * s);
+        u.h[3] = __builtin_amdgcn_cvt_pkrtz(hi.z * s, hi.w * s);
+    } else {
+        u.h[0] = __builtin_amdgcn_cvt_pkrtz(lo.x, lo.y);
+        u.h[1] = __builtin_amdgcn_cvt_pkrtz(lo.z, lo.w);
+        u.h[2] = __builtin_amdgcn_cvt_pkrtz(hi.x, hi.y);
+        u.h[3] = __builtin_amdgcn_cvt_pkrtz(hi.z, hi.w);
+    }
+    return u.v;
+}
+
+// The power of two that brings numbers of at most the given magnitude (its float bits) below 2^15, 1 for
+// those below that already: half precision then never overflows.
+__device__ inline float ef_f16_scale(u32 max_bits)
+{
+    const int x_exp = (int)(max_bits >> 23) - 127;
+    return x_exp >= 15 ? __uint_as_float((u32)(127 + 14 - x_exp) << 23) : 1.0f;
+}
+// Square roots for the filter only, never too small: the instruction is good to one unit in the last
+// place, and inputs below the normal numbers are taken for the smallest of them.
+__device__ inline float ef_sqrt_up(float t) { return fmaxf(__builtin_amdgcn_sqrtf(t), 1.1e-19f) * 1.000001f; }
+
+// What the half-precision filter needs to know about the dimension (see nndescent_run for the bound).
+struct F16Filter {
+    float margin, thr_scale, u, rho0;
+};
+inline F16Filter f16_filter(int d)
+{
+    const int dpad = (d + 15) & ~15;
+    F16Filter f;
+    f.margin = (float)(4.0 * (dpad + 4.0) * 1.1920928955078125e-07 + 16.0 * 5.9604644775390625e-08);
+    f.thr_scale = (float)((1.0 + 4.0 * (d / 16.0 + 8.0) * 5.9604644775390625e-08) * (1.0 + 1e-6));
+    f.u = (float)(1.01 / 1023.0);
+    f.rho0 = (float)(1.01 * sqrt((double)d) * 5.9604644775390625e-08);
+    return f;
+}
+
 // ---------------------------------------------------------------------------------------
 // Alg. 3 above the leaves: for every ancestor N of a point's leaf with depth >= dep, the point
 // is sent down the subtree of N's other child by the split test of each node it meets, and the
@@ -789,6 +843,193 @@ conquer_kernel(const float *__restrict__ X, int d, const int *__restrict__ perm_
                 cur = nxt;
                 nxt = tmp;
             }
+        }
+        if (r16 < s)
+            for (int c = g; c < K; c += 4) graph[(size_t)my_id * K + c] = cur[r16 * K + c];
+    }
+}
+
+// The same for vectors of at most 128 coordinates, by the leaves reached instead of by members: the
+// members of a home leaf that reach the same leaf are handled together, so that the rows of that leaf are
+// fetched once for all of them (the sibling of a leaf is mostly a leaf: one fetch where conquer_kernel
+// has up to sixteen; three levels up there are four leaves to reach), and the home rows once for all
+// levels.  A Gram block in half precision with the joins' bound and the rows' own K-th distances
+// drops most pairs (scale: from the rows in hand); the others get their fixed-order distance from
+// the same registers as in join_tile_kernel and become candidates of their row.
+// conquer_kernel fetched 135 GB of rows through the caches for three levels of eight trees of 10^6 x 128:
+// 12.3 -> 6.2 ms.  (At one level above the leaves, 10^5 x 96: 1.31 -> 1.12 ms with the trees; at seven, 3 10^5 x 100:
+// 10.5 -> 6.2.)
+template <bool ALIGNED>
+__global__ void __launch_bounds__(EF_WAVE) __attribute__((amdgpu_waves_per_eu(4)))
+conquer_tile_kernel(const float *__restrict__ X, int d, const int *__restrict__ perm_t,
+                    const int *__restrict__ leaf_off_t, int n_leaves, const int *__restrict__ etab,
+                    int levels, int K, F16Filter flt, u64 *graph)
+{
+    extern __shared__ __align__(16) float smem[];
+    u64 *pools_a = (u64 *)smem;                       // [16][K] rows being merged, ascending
+    u64 *pools_b = pools_a + 16 * (size_t)K;          // [16][K] the other copy
+    u64 *cand = pools_b + 16 * (size_t)K;             // [16][kCandPitch]
+    float *fa = (float *)(cand + 16 * kCandPitch);    // [4][16] the filter's terms of the home rows
+    float *fb = fa + 64;                              // [2][16] ... of the rows of the leaf reached
+    int *uid_b = (int *)(fb + 32);                    // [16] members of the leaf reached
+    int *ncand = uid_b + 16;                          // [16] candidates of each home row
+    unsigned short *surv = (unsigned short *)(ncand + 16);      // [256] surviving pairs
+    const int lane = threadIdx.x, r16 = lane & 15, g = lane >> 4;
+    auto wave_max = [](u32 m) {
+        for (int o = 32; o >= 1; o >>= 1) m = max(m, (u32)__shfl_xor((int)m, o, EF_WAVE));
+        return m;
+    };
+    auto magnitude = [&](const float4 (&v)[8]) {      // float bits of the largest |coordinate| of a tile
+        float m = 0.f;
+#pragma unroll
+        for (int s = 0; s < 8; ++s) m = fmaxf(fmaxf(fmaxf(m, fabsf(v[s].x)), fmaxf(fabsf(v[s].y), fabsf(v[s].z))), fabsf(v[s].w));
+        return wave_max(__float_as_uint(m));
+    };
+    auto diagonal = [&](const floatx4 &acc) {      // in lane (r16, r16 >> 2): row r16's
+        const int kd = r16 & 3;
+        return kd == 0 ? acc[0] : kd == 1 ? acc[1] : kd == 2 ? acc[2] : acc[3];
+    };
+    for (int leaf = blockIdx.x; leaf < n_leaves; leaf += gridDim.x) {
+        const int b0 = leaf_off_t[leaf];
+        const int s = min(leaf_off_t[leaf + 1] - b0, 16);
+        // the ancestors are those of the leaf: a level exists for all members or for none
+        int e = r16 < s ? etab[(size_t)(b0 + r16) * levels] : -1;
+        if (__ballot(e >= 0) == 0) continue;      // nothing above this leaf to visit
+        const int my_id = r16 < s ? perm_t[b0 + r16] : -1;
+        float4 va[8];
+        load_pieces<ALIGNED>(va, X + (size_t)max(my_id, 0) * d, 0, g, d, r16 < s);
+        __syncthreads();                  // the previous leaf's LDS reads are done
+        u64 *cur = pools_a, *nxt = pools_b;
+        for (int c = g; c < K; c += 4)
+            cur[r16 * K + c] = r16 < s ? graph[(size_t)my_id * K + c] : ef_empty_entry(K - 1 - c);
+        const u32 mag_a = magnitude(va);
+        for (int k = 0; k < levels; ++k) {
+            if (k > 0) {
+                e = r16 < s ? etab[(size_t)(b0 + r16) * levels + k] : -1;
+                if (__ballot(e >= 0) == 0) break;
+            }
+            e = min(e, n_leaves - 1);
+            if (lane < 16) ncand[lane] = 0;
+            __syncthreads();
+            const u32 thr = ef_dist_bits(cur[r16 * K + K - 1]);      // a row's largest entry
+            for (u32 left = (u32)__ballot(e >= 0) & 0xFFFFu; left;) {
+                // ---- the members that reach the same leaf as the first of those left --------------
+                const int t = __shfl(e, __ffs(left) - 1, EF_WAVE);
+                const u32 members = (u32)__ballot(e == t) & 0xFFFFu;
+                left &= ~members;
+                const int bb = leaf_off_t[t], sb = min(leaf_off_t[t + 1] - bb, 16);
+                const int id_b = r16 < sb ? perm_t[bb + r16] : -1;
+                float4 vb[8];
+                load_pieces<ALIGNED>(vb, X + (size_t)max(id_b, 0) * d, 0, g, d, r16 < sb);
+                const float scale = ef_f16_scale(max(mag_a, magnitude(vb)));
+                floatx4 ab = {0.f, 0.f, 0.f, 0.f}, aa = ab, bbq = ab;
+#pragma unroll
+                for (int q = 0; q < 8; q += 2) {
+                    if (16 * q >= d) break;
+                    const f16x8 oa = ef_pack_f16<true>(va[q], va[q + 1], scale), ob = ef_pack_f16<true>(vb[q], vb[q + 1], scale);
+                    ab = __builtin_amdgcn_mfma_f32_16x16x32_f16(oa, ob, ab, 0, 0, 0);
+                    aa = __builtin_amdgcn_mfma_f32_16x16x32_f16(oa, oa, aa, 0, 0, 0);
+                    bbq = __builtin_amdgcn_mfma_f32_16x16x32_f16(ob, ob, bbq, 0, 0, 0);
+                }
+                if (g == 0) uid_b[r16] = id_b;
+                if ((r16 >> 2) == g) {
+                    const float da = diagonal(aa), db = diagonal(bbq), th = __uint_as_float(thr) * (flt.thr_scale * scale * scale);
+                    fa[r16] = da * (1.0f - flt.margin);
+                    fa[16 + r16] = __builtin_fmaf(flt.u, ef_sqrt_up(da), flt.rho0);
+                    fa[32 + r16] = th;
+                    fa[48 + r16] = 2.0f * ef_sqrt_up(th);
+                    fb[r16] = db * (1.0f - flt.margin);
+                    fb[16 + r16] = __builtin_fmaf(flt.u, ef_sqrt_up(db), flt.rho0);
+                }
+                __syncthreads();
+                // ---- filter: the lane holds G[a = 4 g + k][b = r16] --------------------------------
+                const float nfb = fb[r16], rrb = fb[16 + r16];
+                int n_surv = 0;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int a = 4 * g + q;
+                    const float lhs = __builtin_fmaf(-2.0f, ab[q], fa[a] + nfb), rad = fa[16 + a] + rrb;
+                    const bool keep = r16 < sb && ((members >> a) & 1) && !(lhs > __builtin_fmaf(rad, fa[48 + a] + rad, fa[32 + a]));
+                    const u64 kept = __ballot(keep);
+                    if (keep) surv[n_surv + lanes_below(kept)] = (unsigned short)(a | (r16 << 8));
+                    n_surv += __popcll(kept);
+                }
+                __syncthreads();
+                // ---- survivors from registers, sixteen pairs per round (see join_reg_kernel) ---------
+                for (int p0 = 0; p0 < n_surv; p0 += 16) {
+                    const bool has = p0 + r16 < n_surv;
+                    const u32 ent = surv[min(p0 + r16, n_surv - 1)];
+                    const int al = ent & 15, bl = (ent >> 8) & 15;
+                    const int src_a = al + 16 * g, src_b = bl + 16 * g;
+                    float p[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) {
+                        if (16 * q >= d) break;
+                        const float d0 = __shfl(va[q].x, src_a, EF_WAVE) - __shfl(vb[q].x, src_b, EF_WAVE);
+                        const float d1 = __shfl(va[q].y, src_a, EF_WAVE) - __shfl(vb[q].y, src_b, EF_WAVE);
+                        const float d2 = __shfl(va[q].z, src_a, EF_WAVE) - __shfl(vb[q].z, src_b, EF_WAVE);
+                        const float d3 = __shfl(va[q].w, src_a, EF_WAVE) - __shfl(vb[q].w, src_b, EF_WAVE);
+                        p[0] = __builtin_fmaf(d0, d0, p[0]);
+                        p[1] = __builtin_fmaf(d1, d1, p[1]);
+                        p[2] = __builtin_fmaf(d2, d2, p[2]);
+                        p[3] = __builtin_fmaf(d3, d3, p[3]);
+                    }
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) p[q] += __shfl_xor(p[q], 32, EF_WAVE);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) p[q] += __shfl_xor(p[q], 16, EF_WAVE);
+                    const float dist = (p[0] + p[2]) + (p[1] + p[3]);
+                    if (has && g == 0) cand[al * kCandPitch + atomicAdd(&ncand[al], 1)] = ef_pack(dist, uid_b[bl], 1);
+                }
+                __syncthreads();
+            }
+            // ---- candidates of row r16 and their ranks ------------------------------------------
+            const int nc = ncand[r16];
+            if (__ballot(nc > 0) == 0) continue;      // no row has one: the rows stay as they are
+            u64 key[4];
+            int lt[4];
+            const u64 *row = cur + r16 * K;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                key[c] = 4 * g + c < nc ? cand[r16 * kCandPitch + 4 * g + c] : ~0ULL;
+                int lo = 0, hi_ = K;
+                if (key[c] != ~0ULL) {
+                    while (lo < hi_) {
+                        const int mid = (lo + hi_) >> 1;
+                        if (row[mid] < key[c]) lo = mid + 1;
+                        else hi_ = mid;
+                    }
+                    if (lo < K && row[lo] == key[c]) key[c] = ~0ULL;      // already in the row
+                }
+                lt[c] = lo;
+            }
+            __syncthreads();                  // every candidate is read before any slot is written again
+#pragma unroll
+            for (int c = 0; c < 4; ++c) cand[r16 * kCandPitch + 4 * g + c] = key[c];
+            __syncthreads();
+            u64 cs[16];
+#pragma unroll
+            for (int o = 0; o < 16; ++o) cs[o] = cand[r16 * kCandPitch + o];
+            u64 *out = nxt + r16 * K;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                if (key[c] == ~0ULL) continue;
+                int rank = lt[c];
+#pragma unroll
+                for (int o = 0; o < 16; ++o) rank += cs[o] < key[c] ? 1 : 0;
+                if (rank < K) out[rank] = key[c];
+            }
+            for (int j = g; j < K; j += 4) {
+                const u64 en = row[j];
+                int rank = j;
+#pragma unroll
+                for (int o = 0; o < 16; ++o) rank += cs[o] < en ? 1 : 0;
+                if (rank < K) out[rank] = en;
+            }
+            __syncthreads();                  // merged rows complete before they are read again
+            u64 *tmp = cur;
+            cur = nxt;
+            nxt = tmp;
         }
         if (r16 < s)
             for (int c = g; c < K; c += 4) graph[(size_t)my_id * K + c] = cur[r16 * K + c];
@@ -1751,34 +1992,6 @@ prepare_group_kernel(const int *__restrict__ nw, const int *__restrict__ od,
 //   4. the queue is drained into the graph rows with the lock-free insertion.
 // cap_rows: how many vectors the LDS row buffer of this launch holds.
 
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef __fp16 fp16x2 __attribute__((ext_vector_type(2)));
-
-// Eight coordinates of a vector, times a power of two, as half-precision numbers rounded towards
-// zero: an operand of the 16x16x32 matrix instruction.  Both operands of a Gram block are packed
-// the same way, so the order of the coordinates inside the operand does not matter.
-template <bool SCALED>
-__device__ inline f16x8 ef_pack_f16(const float4 &lo, const float4 &hi, float s)
-{
-    union {
-        fp16x2 h[4];
-        f16x8 v;
-    } u;
-    if (SCALED) {
-        u.h[0] = __builtin_amdgcn_cvt_pkrtz(lo.x * s, lo.y * s);
-        u.h[1] = __builtin_amdgcn_cvt_pkrtz(lo.z * s, lo.w * s);
-        u.h[2] = __builtin_amdgcn_cvt_pkrtz(hi.x * s, hi.y * s);
-        u.h[3] = __builtin_amdgcn_cvt_pkrtz(hi.z * s, hi.w * s);
-    } else {
-        u.h[0] = __builtin_amdgcn_cvt_pkrtz(lo.x, lo.y);
-        u.h[1] = __builtin_amdgcn_cvt_pkrtz(lo.z, lo.w);
-        u.h[2] = __builtin_amdgcn_cvt_pkrtz(hi.x, hi.y);
-        u.h[3] = __builtin_amdgcn_cvt_pkrtz(hi.z, hi.w);
-    }
-    return u.v;
-}
-
 struct JoinLds {
     float *rows;      // [cap_rows][stride], columns d..dpad-1 zero
     int *uid;         // [cap_rows] U_new ++ U_old
@@ -2204,8 +2417,7 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
     const int count = *work_count;
     // The filter works on the vectors times a power of two that brings the largest coordinate of
     // the data below 2^15 (1 for all data below that already): half precision then never overflows.
-    const int x_exp = (int)(*xmax >> 23) - 127;
-    const float scale = x_exp >= 15 ? __uint_as_float((u32)(127 + 14 - x_exp) << 23) : 1.0f;
+    const float scale = ef_f16_scale(*xmax);
     const float t_scale = thr_scale * scale * scale;
     // The id list and the sizes of a point are fetched one point ahead, and the thresholds of
     // its vectors as soon as those ids are there, so that they travel while the point before
@@ -2642,12 +2854,8 @@ join_tile_kernel(const float *__restrict__ X, int d, int K, u32 k_magic,
     const u32 n_buckets = (u32)hslots >> 2;
     auto first_slot = [&](int id) { return 4 * (int)__umulhi((u32)id * 0x9E3779B1u, n_buckets); };      // of the id's bucket
     // the power of two that keeps the data's halves from overflowing (see join_reg_kernel)
-    const int x_exp = (int)(*xmax >> 23) - 127;
-    const float scale = x_exp >= 15 ? __uint_as_float((u32)(127 + 14 - x_exp) << 23) : 1.0f;
+    const float scale = ef_f16_scale(*xmax);
     const float t_scale = thr_scale * scale * scale;
-    // square roots for the filter only, never too small: the instruction is good to one unit in the
-    // last place, and inputs below the normal numbers are taken for the smallest of them
-    auto sqrt_up = [](float t) { return fmaxf(__builtin_amdgcn_sqrtf(t), 1.1e-19f) * 1.000001f; };
     const int count = *work_count;
     const int n_pieces = (d + 15) >> 4;      // 16-coordinate pieces of a vector (at most 8)
     int updates = 0, q_fill = 0;
@@ -2778,9 +2986,9 @@ join_tile_kernel(const float *__restrict__ X, int d, int K, u32 k_magic,
             const float dg = kd == 0 ? acc[0] : kd == 1 ? acc[1] : kd == 2 ? acc[2] : acc[3];
             const float t = __uint_as_float(lds.thr[row0 + r16]) * t_scale;
             f[r16] = dg * (1.0f - margin_rel);
-            f[16 + r16] = __builtin_fmaf(u_rel, sqrt_up(dg), rho0);
+            f[16 + r16] = __builtin_fmaf(u_rel, ef_sqrt_up(dg), rho0);
             f[32 + r16] = t;
-            f[48 + r16] = 2.0f * sqrt_up(t);
+            f[48 + r16] = 2.0f * ef_sqrt_up(t);
         };
         for (int bi = 0; bi < nbr; ++bi) {
             float4 va[8];
@@ -3209,6 +3417,7 @@ extern "C" int efanna_init_graph(const float *X, int64_t n, int32_t d, const int
     if (reg_ok) {
         const size_t reg_lds = (size_t)16 * k * 8 + (size_t)16 * kCandPitch * 8 + 16 * 4;
         const size_t conquer_lds = (size_t)2 * 16 * k * 8 + (size_t)16 * kCandPitch * 8 + 16 * 16 * 4;
+        const size_t conquer_tile_lds = (size_t)2 * 16 * k * 8 + (size_t)16 * kCandPitch * 8 + (64 + 32 + 16 + 16) * 4 + 512;
         for (int t = 0; t < n_trees; ++t) {
             const int32_t *perm_t = perm + (size_t)t * n, *off_t = leaf_off + (size_t)t * (max_leaves + 1);
             if (aligned)
@@ -3222,11 +3431,18 @@ extern "C" int efanna_init_graph(const float *X, int64_t n, int32_t d, const int
                 classify_kernel<<<min(grid_for((size_t)n_leaves[t], kBlock / EF_WAVE), 256 * 8), kBlock, 0, st>>>(
                     X, d, perm_t, off_t, n_leaves[t], nodes + (size_t)t * (max_leaves + 1),
                     leaf_up + (size_t)t * (max_leaves + 1), conquer_depth, levels, etab);
-                if (aligned)
-                    conquer_kernel<true><<<min(n_leaves[t], kLeafGrid), EF_WAVE, conquer_lds, st>>>(
+                const int grid = min(n_leaves[t], kLeafGrid);
+                if (d <= 128 && aligned)
+                    conquer_tile_kernel<true><<<grid, EF_WAVE, conquer_tile_lds, st>>>(
+                        X, d, perm_t, off_t, n_leaves[t], etab, levels, k, f16_filter(d), graph);
+                else if (d <= 128)
+                    conquer_tile_kernel<false><<<grid, EF_WAVE, conquer_tile_lds, st>>>(
+                        X, d, perm_t, off_t, n_leaves[t], etab, levels, k, f16_filter(d), graph);
+                else if (aligned)
+                    conquer_kernel<true><<<grid, EF_WAVE, conquer_lds, st>>>(
                         X, d, perm_t, off_t, n_leaves[t], etab, levels, k, graph);
                 else
-                    conquer_kernel<false><<<min(n_leaves[t], kLeafGrid), EF_WAVE, conquer_lds, st>>>(
+                    conquer_kernel<false><<<grid, EF_WAVE, conquer_lds, st>>>(
                         X, d, perm_t, off_t, n_leaves[t], etab, levels, k, graph);
             }
         }
@@ -3438,10 +3654,8 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
     // error), r0 = 1.01 sqrt(d) 2^-24.  The margin on the norms pays for the three accumulations in
     // single precision: four times (dpad + 4) 2^-23, a bound that holds whether the matrix unit
     // rounds or truncates its partial sums.
-    const float margin_f16 = (float)(4.0 * (dpad + 4.0) * 1.1920928955078125e-07 + 16.0 * 5.9604644775390625e-08);
-    const float thr_scale_f16 = (float)((1.0 + 4.0 * (d / 16.0 + 8.0) * 5.9604644775390625e-08) * (1.0 + 1e-6));
-    const float u_f16 = (float)(1.01 / 1023.0);
-    const float rho0_f16 = (float)(1.01 * sqrt((double)d) * 5.9604644775390625e-08);
+    const F16Filter f16 = f16_filter(d);
+    const float margin_f16 = f16.margin, thr_scale_f16 = f16.thr_scale, u_f16 = f16.u, rho0_f16 = f16.rho0;
     hipStream_t st = (hipStream_t)stream;
     NndWs w = carve_nnd(ws, n, K, L);
     // reverse lists by buckets (short rows and lists): LDS of an offer block (words) or a list

@@ -334,6 +334,22 @@ def test_conquer_shapes_and_limits(ef):
         oracle.check_graph_invariants(X, ids, dists)
 
 
+@pytest.mark.parametrize("kind", ["large", "just_below", "tiny", "offset", "far_offset", "outlier", "integers",
+                                  "mixed_scales"])
+@pytest.mark.parametrize("d,S,K,T", [(128, 16, 10, 4), (36, 7, 3, 3), (29, 16, 40, 2)])
+def test_conquer_filter_ranges_bit_exact(ef, kind, d, S, K, T):
+    """The conquer step's half-precision filter on data that strains it (a candidate dropped by mistake
+    shows as a row that differs from the oracle's); rows that fill up and rows that stay under-full."""
+    X = filter_data(kind, 3_000, d)
+    g, o = tree_nodes_equal(ef, X, T, S, 13)
+    for dep in (0, max(0, g[5] - 5)):
+        if g[5] - dep + 1 > 64:
+            continue
+        graph = ef.efanna_init_graph(dev(X), g[0], g[1], g[2], S, K, nodes=g[3], leaf_up=g[4], tree_depth=g[5],
+                                     conquer_depth=dep)
+        graph_equal(ef, graph, oracle.conquer_graph(X, *o, dep, K))
+
+
 @pytest.mark.parametrize("name,n,T,S,K,L,I", [
     ("gmm10k_d32", 10_000, 4, 8, 10, 10, 4),      # the small configuration as quoted
     ("sift100k_like", 20_000, 8, 16, 20, 20, 3),
