@@ -66,6 +66,10 @@ __device__ inline long long ef_node_value(Coord coord, int d, int dim)
     return v;
 }
 
+// 16-byte accesses at any multiple of four bytes (more than that no global load or store asks for)
+typedef float ef_f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
+typedef int ef_i32x4_u __attribute__((ext_vector_type(4), aligned(4)));
+
 // ---- packed graph entries -------------------------------------------------------------
 __device__ inline u64 ef_pack(float dist, int id, int is_new)
 {

@@ -88,9 +88,6 @@ __device__ inline int lanes_below(u64 ballot)
     return (int)__builtin_amdgcn_mbcnt_hi((u32)(ballot >> 32), __builtin_amdgcn_mbcnt_lo((u32)ballot, 0u));
 }
 
-// a 16-byte load at any multiple of four bytes (more than that no global load asks for)
-typedef float ef_f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
-typedef int ef_i32x4_u __attribute__((ext_vector_type(4), aligned(4)));
 __device__ inline float4 load_unaligned4(const float *p)
 {
     const ef_f32x4_u v = *reinterpret_cast<const ef_f32x4_u *>(p);
@@ -3116,34 +3113,46 @@ __global__ void __launch_bounds__(kBlock) graph_ids_kernel(const u64 *__restrict
     }
 }
 
-// squared norms in float32 (only the join's filter uses them; any summation order will do) and
-// the largest |coordinate| of the data (its bits, which order like the values; *xmax starts at 0).
-// A group of sixteen lanes per point, points strided over the grid: one atomic per block.
+// squared norms in float32 (only the LDS join's filter uses them; any summation order will do).
+// A group of sixteen lanes per point, points strided over the grid.
 __global__ void __launch_bounds__(kBlock)
-norms_kernel(const float *__restrict__ X, int n, int d, float *__restrict__ norms, u32 *xmax)
+norms_kernel(const float *__restrict__ X, int n, int d, float *__restrict__ norms)
 {
-    __shared__ u32 wave_max[kBlock / EF_WAVE];
     const int gl = threadIdx.x & 15;
     const size_t n_groups = (size_t)gridDim.x * (kBlock / 16);
-    float mx = 0.0f;
     for (size_t g = ((size_t)blockIdx.x * kBlock + threadIdx.x) >> 4; g < (size_t)n; g += n_groups) {
         const float *a = X + g * d;
         float acc = 0.0f;
-        for (int j = gl; j < d; j += 16) {
-            const float v = a[j];
-            acc = __builtin_fmaf(v, v, acc);
-            mx = fmaxf(mx, fabsf(v));
-        }
+        for (int j = gl; j < d; j += 16) acc = __builtin_fmaf(a[j], a[j], acc);
         acc = ef_group_reduce16(acc);
         if (gl == 0) norms[g] = acc;
     }
-    for (int o = EF_WAVE / 2; o >= 1; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, EF_WAVE));
-    if (ef_lane() == 0) wave_max[threadIdx.x / EF_WAVE] = __float_as_uint(mx);
+}
+
+// Only the bits of the largest |coordinate|, for the joins that take their norms from Gram diagonals: one
+// pass at full width (the norms took 151 us for 10^6 x 128, this 93).  xmax is zeroed beforehand.
+__global__ void __launch_bounds__(kBlock)
+xmax_kernel(const float *__restrict__ X, size_t total, u32 *xmax)
+{
+    const size_t step = (size_t)gridDim.x * kBlock, quads = total / 4;
+    float m = 0.f;
+    for (size_t q = (size_t)blockIdx.x * kBlock + threadIdx.x; q < quads; q += 4 * step) {
+        float4 v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            v[k] = load_unaligned4(X + 4 * min(q + k * step, quads - 1));
+#pragma unroll
+        for (int k = 0; k < 4; ++k) m = fmaxf(fmaxf(fmaxf(m, fabsf(v[k].x)), fmaxf(fabsf(v[k].y), fabsf(v[k].z))), fabsf(v[k].w));
+    }
+    if (blockIdx.x == 0 && threadIdx.x < (total & 3)) m = fmaxf(m, fabsf(X[4 * quads + threadIdx.x]));
+    u32 b = __float_as_uint(m);
+    for (int o = 32; o >= 1; o >>= 1) b = max(b, (u32)__shfl_xor((int)b, o, EF_WAVE));
+    __shared__ u32 wave_max[kBlock / EF_WAVE];
+    if (ef_lane() == 0) wave_max[threadIdx.x / EF_WAVE] = b;
     __syncthreads();
     if (threadIdx.x == 0) {
-        u32 m = 0;
-        for (int w = 0; w < kBlock / EF_WAVE; ++w) m = max(m, wave_max[w]);
-        if (m) atomicMax(xmax, m);
+        for (int v = 1; v < kBlock / EF_WAVE; ++v) b = max(b, wave_max[v]);
+        atomicMax(xmax, b);
     }
 }
 
@@ -3688,7 +3697,11 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
                                                                  : (const void *)join_kernel<false>,
                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)large_lds));
     zero_u64_kernel<<<1, EF_WAVE, 0, st>>>((u64 *)w.xmax, 1);
-    norms_kernel<<<min(grid_for((size_t)n * 16, kBlock), 256 * 8), kBlock, 0, st>>>(X, (int)n, d, w.norms, w.xmax);
+    // the half-precision filters want the data's magnitude, the joins with rows in LDS its norms, the joins of
+    // up to 32 long vectors neither (10^6 x 960: a pass of 1.08 ms less)
+    if (tiles) xmax_kernel<<<(int)min((size_t)grid_for((size_t)n * d / 4 + 1, 4 * kBlock), (size_t)256 * 8), kBlock, 0, st>>>(X, (size_t)n * d, w.xmax);
+    else if (max_rows > rows1)
+        norms_kernel<<<min(grid_for((size_t)n * 16, kBlock), 256 * 8), kBlock, 0, st>>>(X, (int)n, d, w.norms);
     if (stats) zero_u64_kernel<<<grid_for((size_t)iters * 4 + 1, kBlock), kBlock, 0, st>>>(stats, iters * 4);
     // optional phase timing: events around the sampling and the join of every iteration
     struct PhaseEvents {      // destroyed on every way out of the call

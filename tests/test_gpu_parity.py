@@ -67,6 +67,23 @@ def test_trees_bit_exact(ef, name, n, T, S):
     trees_equal(ef, X, T, S, synth.ALGO_SEED)
 
 
+@pytest.mark.parametrize("n,d,shift", [(63, 1, 0), (64, 64, 0), (65, 65, 1), (127, 130, 2), (1_001, 3, 3)])
+def test_trees_transposed_copy_edges(ef, n, d, shift):
+    """Edges of the 64 x 64 tiles of the transposed copy, rows at any multiple of four bytes, and the
+    input check on the last coordinate of the last point."""
+    X = np.random.default_rng(n + d).standard_normal((n, d)).astype(np.float32)
+    Xd = torch.empty(n * d + shift, dtype=torch.float32, device="cuda:0")[shift:].view(n, d)
+    Xd.copy_(dev(X))
+    perm, off, nl = ef.efanna_build_trees(Xd, 3, 2, 8)
+    operm, _, onl = oracle.build_trees(X, 3, 2, 8)
+    assert np.array_equal(nl, onl) and np.array_equal(host(perm), operm)
+    for bad in (np.nan, np.inf, -2.0 ** 20):
+        Xd[n - 1, d - 1] = float(bad)
+        with pytest.raises(ef.EfannaError) as e:
+            ef.efanna_build_trees(Xd, 3, 2, 8)
+        assert e.value.status == -3
+
+
 def test_trees_edge_cases(ef):
     rng = np.random.default_rng(3)
     # n <= S: one leaf per tree
