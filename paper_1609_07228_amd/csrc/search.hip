@@ -469,7 +469,7 @@ search_kernel(const float *__restrict__ X, int d, int n, const int *__restrict__
                     if (!table_clear) {
                         for (int j = tid; j < table_size; j += kThreads) table[j] = 0;
                         table_clear = true;
-                        __threadfence_block();
+                        __threadfence();      // (the cleared entries are in place before any wave swaps one)
                         __syncthreads();
                     }
                 }
