@@ -37,6 +37,10 @@ struct Branch {
 
 inline size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// What the waves of a block tell one another, a word of LDS each: a word that stood for two things could be
+// written for the one before every wave has read the other.
+enum { kWaiting, kToExpand, kPoolMembers, kSharedWords };
+
 // LDS of a block, offsets in words
 struct SearchLds {
     int cur, batch, keys, expand, fid, leaves, lofs, found, shared, tab;
@@ -53,7 +57,7 @@ __host__ __device__ inline SearchLds search_lds(int d, int P, int T, int want, i
     l.lofs = l.leaves + T * want;
     l.found = l.lofs + T * want + 1;
     l.shared = l.found + T;
-    l.tab = (l.shared + 4 + 3) & ~3;
+    l.tab = (l.shared + kSharedWords + 3) & ~3;
     return l;
 }
 
@@ -332,7 +336,7 @@ search_kernel(const float *__restrict__ X, int d, int n, const int *__restrict__
     int *leaves = (int *)smem + at.leaves;             // [T][want] leaves, then where they start
     int *lofs = (int *)smem + at.lofs;                 // [T][want] where their members start in `first`, and the end
     int *n_found = (int *)smem + at.found;             // [T]
-    int *shared = (int *)smem + at.shared;             // [4] waiting candidates, pool members, members to expand, leaf members
+    int *shared = (int *)smem + at.shared;             // [kSharedWords] candidates waiting, members to expand, pool members at the end
     int *tab = (int *)smem + at.tab;                   // [lds_slots] points checked (the trees' branches before that)
     const int dq = (d + 15) & ~15;
     const int tid = threadIdx.x, lane = ef_lane(), wave = tid / EF_WAVE;
@@ -421,7 +425,7 @@ search_kernel(const float *__restrict__ X, int d, int n, const int *__restrict__
             }
             if (lane == 0) {
                 lofs[n_lists] = end;
-                shared[0] = 0;
+                shared[kWaiting] = 0;
             }
         }
         __syncthreads();
@@ -453,10 +457,10 @@ search_kernel(const float *__restrict__ X, int d, int n, const int *__restrict__
                         }
                         n_exp += __popcll(bal);
                     }
-                    if (W > 1 && lane == 0) shared[1] = n_exp;
+                    if (W > 1 && lane == 0) shared[kToExpand] = n_exp;
                 }
                 __syncthreads();
-                if (W > 1) n_exp = shared[1];
+                if (W > 1) n_exp = shared[kToExpand];
                 if (n_exp == 0) break;
                 total = n_exp * Kg;
             }
@@ -503,7 +507,7 @@ search_kernel(const float *__restrict__ X, int d, int n, const int *__restrict__
                 }
                 int to = waiting;
                 if (W > 1) {
-                    if (lane == 0 && n_new) to = atomicAdd(&shared[0], n_new);
+                    if (lane == 0 && n_new) to = atomicAdd(&shared[kWaiting], n_new);
                     to = __shfl(to, 0, EF_WAVE);
                 }
 #pragma unroll
@@ -512,7 +516,7 @@ search_kernel(const float *__restrict__ X, int d, int n, const int *__restrict__
                     to += __popcll(new_mask[k]);
                 }
                 __syncthreads();
-                const int now = W > 1 ? shared[0] : waiting + n_new;
+                const int now = W > 1 ? shared[kWaiting] : waiting + n_new;
                 checked += now - waiting;
                 if (!spilled) in_lds += now - waiting;
                 waiting = now;
@@ -541,16 +545,16 @@ search_kernel(const float *__restrict__ X, int d, int n, const int *__restrict__
                 }
                 if (W > 1) {
                     __syncthreads();      // everyone has read the count
-                    if (tid == 0) shared[0] = waiting;
+                    if (tid == 0) shared[kWaiting] = waiting;
                     __syncthreads();
                 }
             }
         }
         // ---- result: the K closest --------------------------------------------------------------
         if (W > 1) {
-            if (tid == 0) shared[1] = count;
+            if (tid == 0) shared[kPoolMembers] = count;      // (a late wave may still be reading what there was to expand)
             __syncthreads();
-            count = shared[1];
+            count = shared[kPoolMembers];
         }
         for (int c = tid; c < K; c += kThreads) {
             const bool live = c < count;

@@ -686,6 +686,22 @@ def test_search_batches_and_sets_bit_exact(ef, n, d, T, S, K, P, E, I, nq):
     assert np.array_equal(host(got[2]), want[2])
 
 
+@pytest.mark.parametrize("nq", [1, 200, 256, 257, 700, 768, 900])      # eight waves per query, four, one
+@pytest.mark.parametrize("K,P,E", [(10, 200, 50), (100, 200, 200), (150, 1024, 300)])
+def test_search_pools_that_run_dry(ef, nq, K, P, E):
+    """Every pool has nothing left to expand long before the last round (300 points), so the waves of a
+    query leave the expansion early; more results than a wave has lanes."""
+    rng = np.random.default_rng(nq + K)
+    X = rng.standard_normal((300, 8)).astype(np.float32)
+    Xd, g, o, ids = build_index(ef, X, 2, 8, min(K, 128), 0)
+    Q = rng.standard_normal((nq, 8)).astype(np.float32)
+    got = ef.efanna_search(Xd, g[0], g[1], g[2], g[3], g[5], 8, ids, dev(Q), K, P, E, 40)
+    want = oracle.search(X, o[0], o[1], o[2], o[3], 8, host(ids), Q, K, P, E, 40)
+    assert np.array_equal(host(got[0]), want[0])
+    assert host(got[1]).tobytes() == want[1].tobytes()
+    assert np.array_equal(host(got[2]), want[2])
+
+
 def test_search_edge_cases(ef):
     rng = np.random.default_rng(4)
     X = rng.standard_normal((50, 8)).astype(np.float32)            # every tree a single leaf
