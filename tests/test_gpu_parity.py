@@ -695,8 +695,8 @@ def test_search_pools_that_run_dry(ef, nq, K, P, E):
     X = rng.standard_normal((300, 8)).astype(np.float32)
     Xd, g, o, ids = build_index(ef, X, 2, 8, min(K, 128), 0)
     Q = rng.standard_normal((nq, 8)).astype(np.float32)
-    got = ef.efanna_search(Xd, g[0], g[1], g[2], g[3], g[5], 8, ids, dev(Q), K, P, E, 40)
-    want = oracle.search(X, o[0], o[1], o[2], o[3], 8, host(ids), Q, K, P, E, 40)
+    got = ef.efanna_search(Xd, g[0], g[1], g[2], g[3], g[5], 8, ids, dev(Q), K, P, E, 12)
+    want = oracle.search(X, o[0], o[1], o[2], o[3], 8, host(ids), Q, K, P, E, 12)
     assert np.array_equal(host(got[0]), want[0])
     assert host(got[1]).tobytes() == want[1].tobytes()
     assert np.array_equal(host(got[2]), want[2])
