@@ -488,7 +488,7 @@ search_kernel(const float *__restrict__ X, int d, int n, const int *__restrict__
                         if (it < 0) {
                             id[k] = first[f];
                         } else {
-                            const int src = Kg == 1 ? f : (int)(((u64)(u32)f * kg_magic) >> 32);
+                            const int src = kg_magic ? (int)(((u64)(u32)f * kg_magic) >> 32) : f / Kg;
                             id[k] = graph_ids[(size_t)expand[src] * Kg + (f - src * Kg)];
                         }
                     }
@@ -608,7 +608,10 @@ extern "C" int efanna_search(const float *X, int64_t n, int32_t d, const int32_t
     for (int t = 0; t < n_trees; ++t) counts.of[t] = n_leaves[t];
     find_roots_kernel<<<dim3((unsigned)((max_leaves + 255) / 256), (unsigned)n_trees), 256, 0, st>>>(
         nodes, max_leaves, n_trees, counts, roots);
-    const u32 kg_magic = (u32)(((1ULL << 32) + graph_k - 1) / graph_k);      // f / graph_k for f < 2^32 / graph_k
+    // f / graph_k as f * kg_magic >> 32 for the f < pool * graph_k there are: ceil(2^32 / graph_k) is less than
+    // graph_k / 2^32 of it too large, so exact while f * graph_k <= 2^32.  Rows too long for that (or of one id): 0, divide.
+    const u32 kg_magic = graph_k > 1 && (u64)graph_k * graph_k * pool <= 1ULL << 32
+                             ? (u32)(((1ULL << 32) + graph_k - 1) / graph_k) : 0;
 #define EF_SEARCH(W, Q_LDS)                                                                              \
     do {                                                                                                 \
         EF_HIP_CHECK(hipFuncSetAttribute((const void *)search_kernel<W, Q_LDS>,                          \

@@ -702,6 +702,26 @@ def test_search_pools_that_run_dry(ef, nq, K, P, E):
     assert np.array_equal(host(got[2]), want[2])
 
 
+@pytest.mark.parametrize("Kg,P,nq", [(1, 200, 3), (1, 200, 800), (2_048, 1_024, 3), (2_049, 1_024, 300),
+                                     (5_000, 1_024, 3), (5_000, 200, 800)])
+def test_search_long_rows_of_neighbours(ef, Kg, P, nq):
+    """Neighbour tables far wider than the library writes them, the ids in the last column (where a quotient by
+    the row length that is a little too large lands in the next row) and a few in others."""
+    rng = np.random.default_rng(Kg)
+    n, S, T = 6_000, 16, 4
+    X = rng.standard_normal((n, 8)).astype(np.float32)
+    Xd, g, o, _ = build_index(ef, X, T, S, 10, 0)
+    ids = np.full((n, Kg), -1, dtype=np.int32)
+    ids[:, rng.integers(0, Kg, 5)] = rng.integers(0, n, (n, 5))
+    ids[:, -1] = rng.integers(0, n, n)
+    Q = rng.standard_normal((nq, 8)).astype(np.float32)
+    got = ef.efanna_search(Xd, g[0], g[1], g[2], g[3], g[5], S, dev(ids), dev(Q), 100, P, P, 1)
+    want = oracle.search(X, o[0], o[1], o[2], o[3], S, ids, Q, 100, P, P, 1)
+    assert np.array_equal(host(got[0]), want[0])
+    assert host(got[1]).tobytes() == want[1].tobytes()
+    assert np.array_equal(host(got[2]), want[2])
+
+
 def test_search_edge_cases(ef):
     rng = np.random.default_rng(4)
     X = rng.standard_normal((50, 8)).astype(np.float32)            # every tree a single leaf
