@@ -1891,6 +1891,9 @@ __global__ void prepare_kernel(const int *__restrict__ nw, const int *__restrict
 // block bumps the work lists' counters once (11 ns each, one after the other).  Per launch, before and after: 10^4 points of
 // degree 10 23.5 -> 9.3 us, 10^5 of degree 20 50 -> 31, 10^6 of degree 10 108 -> 104.
 constexpr int kPrepPoints = 64, kPrepThreads = 8 * kPrepPoints, kPrepMaxPasses = 4;
+// LDS for the ids in the kernels that write the join lists: with the arrays they declare (at most 2.8 KB) it
+// stays within the 64 KB that a launch gets without asking for more.
+constexpr size_t kPrepLds = 64 * 1024 - 4096;
 template <int E>
 __global__ void __launch_bounds__(kPrepThreads)
 prepare_group_kernel(const int *__restrict__ nw, const int *__restrict__ od,
@@ -3631,7 +3634,7 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
                (size_t)reg_q_cap * sizeof(Proposal);
     };
     // prepare: one thread per point with max_rows ids of LDS each
-    int prep_threads = (int)(65536 / ((size_t)(max_rows | 1) * 4)) / EF_WAVE * EF_WAVE;
+    int prep_threads = (int)(kPrepLds / ((size_t)(max_rows | 1) * 4)) / EF_WAVE * EF_WAVE;
     prep_threads = prep_threads > kBlock ? kBlock : (prep_threads < EF_WAVE ? EF_WAVE : prep_threads);
     const size_t prep_lds = (size_t)prep_threads * (max_rows | 1) * 4;
     // long lists: a wave per point with a hash table of at least twice the longest list
@@ -3644,7 +3647,7 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
     const bool prep_group = bucketed_lists(n, K, L);
     int prep_passes = 1;
     while (prep_passes < kPrepMaxPasses && n > (int64_t)kPrepPoints * prep_passes * 512 &&
-           (size_t)kPrepPoints * 2 * prep_passes * (max_rows | 1) * 4 <= 65536)
+           (size_t)kPrepPoints * 2 * prep_passes * (max_rows | 1) * 4 <= kPrepLds)
         prep_passes *= 2;
     const size_t prep_group_lds = (size_t)kPrepPoints * prep_passes * (max_rows | 1) * 4;
     const int n_part = prep_group  ? grid_for((size_t)n, kPrepPoints * prep_passes)

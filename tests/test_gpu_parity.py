@@ -460,6 +460,8 @@ def test_nndescent_filter_ranges_bit_exact(ef, kind, d, K, L):
     (140_000, 4, 1, 16, 3, 2, 1),        # four
     (900, 8, 2, 16, 1, 20, 2),           # rows of one entry, joins of more than 32 vectors
     (900, 8, 2, 16, 3, 20, 2),
+    (140_000, 4, 1, 16, 21, 21, 1),      # join lists of 63 ids, four passes: the most LDS of either kernel that
+    (2_000, 8, 2, 16, 45, 20, 1),        # writes them, with eight lanes per point and with one (85 ids)
 ])
 def test_nndescent_more_shapes(ef, n, d, T, S, K, L, I):
     rng = np.random.default_rng(n + d + K)
