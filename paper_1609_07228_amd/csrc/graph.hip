@@ -575,6 +575,12 @@ __device__ inline float ef_f16_scale(u32 max_bits)
     const int x_exp = (int)(max_bits >> 23) - 127;
     return x_exp >= 15 ? __uint_as_float((u32)(127 + 14 - x_exp) << 23) : 1.0f;
 }
+// A threshold as the filter compares it: thr (a float's bits) times thr_scale scale^2.  One scale goes to either
+// factor: the square of a scale below 2^-74 (coordinates from 2^89 on) is no float, the product may well be one.
+__device__ inline float ef_scaled_threshold(u32 thr, float scale, float thr_scale)
+{
+    return (__uint_as_float(thr) * scale) * (scale * thr_scale);
+}
 // Square roots for the filter only, never too small: the instruction is good to one unit in the last
 // place, and inputs below the normal numbers are taken for the smallest of them.
 __device__ inline float ef_sqrt_up(float t) { return fmaxf(__builtin_amdgcn_sqrtf(t), 1.1e-19f) * 1.000001f; }
@@ -930,7 +936,7 @@ conquer_tile_kernel(const float *__restrict__ X, int d, const int *__restrict__ 
                 }
                 if (g == 0) uid_b[r16] = id_b;
                 if ((r16 >> 2) == g) {
-                    const float da = diagonal(aa), db = diagonal(bbq), th = __uint_as_float(thr) * (flt.thr_scale * scale * scale);
+                    const float da = diagonal(aa), db = diagonal(bbq), th = ef_scaled_threshold(thr, scale, flt.thr_scale);
                     fa[r16] = da * (1.0f - flt.margin);
                     fa[16 + r16] = __builtin_fmaf(flt.u, ef_sqrt_up(da), flt.rho0);
                     fa[32 + r16] = th;
@@ -2418,7 +2424,6 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
     // The filter works on the vectors times a power of two that brings the largest coordinate of
     // the data below 2^15 (1 for all data below that already): half precision then never overflows.
     const float scale = ef_f16_scale(*xmax);
-    const float t_scale = thr_scale * scale * scale;
     // The id list and the sizes of a point are fetched one point ahead, and the thresholds of
     // its vectors as soon as those ids are there, so that they travel while the point before
     // is being worked on: the row loads are the only latency a point waits for.
@@ -2448,7 +2453,7 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
         if (lane < R) {
             uid[lane] = u_cur;
             thr[lane] = t_pre;
-            const float t = __uint_as_float(t_pre) * t_scale;
+            const float t = ef_scaled_threshold(t_pre, scale, thr_scale);
             tf[lane] = t;
             sq[lane] = __builtin_sqrtf(t) * 1.000001f;
         }
@@ -2855,7 +2860,6 @@ join_tile_kernel(const float *__restrict__ X, int d, int K, u32 k_magic,
     auto first_slot = [&](int id) { return 4 * (int)__umulhi((u32)id * 0x9E3779B1u, n_buckets); };      // of the id's bucket
     // the power of two that keeps the data's halves from overflowing (see join_reg_kernel)
     const float scale = ef_f16_scale(*xmax);
-    const float t_scale = thr_scale * scale * scale;
     const int count = *work_count;
     const int n_pieces = (d + 15) >> 4;      // 16-coordinate pieces of a vector (at most 8)
     int updates = 0, q_fill = 0;
@@ -2984,7 +2988,7 @@ join_tile_kernel(const float *__restrict__ X, int d, int K, u32 k_magic,
             if ((r16 >> 2) != g) return;
             const int kd = r16 & 3;
             const float dg = kd == 0 ? acc[0] : kd == 1 ? acc[1] : kd == 2 ? acc[2] : acc[3];
-            const float t = __uint_as_float(lds.thr[row0 + r16]) * t_scale;
+            const float t = ef_scaled_threshold(lds.thr[row0 + r16], scale, thr_scale);
             f[r16] = dg * (1.0f - margin_rel);
             f[16 + r16] = __builtin_fmaf(u_rel, ef_sqrt_up(dg), rho0);
             f[32 + r16] = t;

@@ -589,6 +589,30 @@ def test_sampling_of_long_rows_with_ties(ef, K, L):
         graph_equal(ef, graph, want)
 
 
+@pytest.mark.parametrize("d,K,L", [(128, 10, 4), (36, 10, 10), (36, 40, 20)])      # joins of at most 18, of 30 and of more vectors
+def test_nndescent_one_vector_far_out(ef, d, K, L):
+    """A vector thirty binary orders above the others, of which no row knows: the power of two that brings it into
+    half precision's range has a square below the smallest float32, the thresholds times it have not."""
+    rng = np.random.default_rng(d + K)
+    n = 1_500
+    X = (rng.standard_normal((n, d)) * 2.0 ** 59).astype(np.float32)
+    X[17] = np.float32(2.0 ** 90)
+    ids = np.stack([rng.permutation(n)[:K] for _ in range(n)]).astype(np.int32)
+    ids[(ids == 17) | (ids == np.arange(n)[:, None])] = -1
+    ids[17] = -1
+    dists = np.array([[oracle.dist(X[i], X[j]) if j >= 0 else np.inf for j in ids[i]] for i in range(n)], dtype=np.float32)
+    assert np.isfinite(dists[ids >= 0]).all()
+    order = np.argsort(dists, axis=1, kind="stable")      # (empty slots last)
+    ids, dists = np.take_along_axis(ids, order, 1), np.take_along_axis(dists, order, 1)
+    flags = (ids >= 0).astype(np.uint8)
+    graph = ef.efanna_set_graph(dev(ids), dev(dists), dev(flags))
+    want = (ids, dists, flags)
+    for it in range(3):
+        ef.efanna_nndescent(dev(X), graph, 1, L, 3, first_iter=it)
+        want = oracle.nndescent(X, *want[:3], 1, L, 3, iter0=it)
+        graph_equal(ef, graph, want)
+
+
 def test_nndescent_resume_and_recall(ef):
     name = "gmm10k_d32"
     p = synth.params(name)
