@@ -205,8 +205,16 @@ __device__ inline int variance_dim_wave(const float *__restrict__ X, int d, cons
         const int jc[2] = {min(j[0], d - 1), min(j[1], d - 1)};      // (lanes beyond d read along)
         const bool second = j0 + EF_WAVE < d;
         float y0[2], widest[2] = {0.f, 0.f};
-        int q0[2];
-        long long s1[2] = {0, 0}, s2[2] = {0, 0};
+        u32 q0[2];
+        long long s1[2] = {0, 0};
+        u64 s2[2] = {0, 0};
+        // Values too wide for this are held at the ends of 32 bits by the instruction (the language leaves their
+        // conversion undefined), differences and sums of squares wrap, and the result is not looked at.
+        auto steps = [](float y) {
+            u32 q;
+            asm("v_cvt_i32_f32 %0, %1" : "=v"(q) : "v"(y));
+            return q;
+        };
         for (int p0 = 0; p0 < m; p0 += 8) {
             float x[2][8];
 #pragma unroll
@@ -221,7 +229,7 @@ __device__ inline int variance_dim_wave(const float *__restrict__ X, int d, cons
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     y0[h] = __builtin_rintf(x[h][0] * 1048576.0f);
-                    q0[h] = (int)y0[h];
+                    q0[h] = steps(y0[h]);
                 }
             }
 #pragma unroll
@@ -230,10 +238,10 @@ __device__ inline int variance_dim_wave(const float *__restrict__ X, int d, cons
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     const float y = __builtin_rintf(x[h][u] * 1048576.0f);
-                    const int dq = (int)y - q0[h];
+                    const int dq = (int)(steps(y) - q0[h]);
                     widest[h] = fmaxf(widest[h], fabsf(y - y0[h]));
                     s1[h] += dq;
-                    s2[h] += (long long)dq * dq;
+                    s2[h] += (u64)((long long)dq * dq);
                 }
             }
         }
@@ -242,10 +250,10 @@ __device__ inline int variance_dim_wave(const float *__restrict__ X, int d, cons
             if (h == 1 && !second) break;
             VarKey c;
             c.j = j[h];
-            // |dq| < 2^28 and a hundred of them: the sum of squares stays below 2^63; |q| < 2^30: (int)y is exact
+            // |dq| < 2^28 and a hundred of them: the sum of squares stays below 2^63; |q| < 2^30: steps() is exact
             const bool narrow = fabsf(y0[h]) < 536870912.0f && widest[h] < 268435456.0f;
             const u64 a1 = (u64)(s1[h] < 0 ? -s1[h] : s1[h]);
-            c.v = (__int128)((unsigned __int128)(u64)m * (u64)s2[h] - (unsigned __int128)a1 * a1);
+            c.v = (__int128)((unsigned __int128)(u64)m * s2[h] - (unsigned __int128)a1 * a1);
             if (!narrow) c.v = variance_any(X, d, ids, m, jc[h]);
             if (j[h] >= d) continue;
             if (j0 == 0 && h == 0) {      // (up to 128 dimensions a lane has two: one comparison puts them in order)

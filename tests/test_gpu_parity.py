@@ -286,7 +286,7 @@ def test_trees_variance_rule_shapes(ef):
 
 
 @pytest.mark.parametrize("d", [1, 4, 63, 64, 65, 128, 129, 193])
-@pytest.mark.parametrize("kind", ["ties", "just_narrow", "just_wide", "huge"])
+@pytest.mark.parametrize("kind", ["ties", "just_narrow", "just_wide", "huge", "far_offset", "opposite_ends"])
 def test_trees_variance_rule_sums(ef, kind, d):
     """The 64-bit sums of the variance rule and the 128-bit ones they fall back to, on either side of
     the switch (values 256.0 apart, values of 512.0), with equal variances among the lanes."""
@@ -300,6 +300,11 @@ def test_trees_variance_rule_sums(ef, kind, d):
     elif kind == "huge":
         X = (X - np.float32(0.5)) * np.float32(2.0 ** 20) * np.float32(0.999)
         X[:, :: 3] *= np.float32(1e-6)
+    elif kind == "far_offset":       # close together, but far from zero
+        X = X + np.float32(2.0 ** 19)
+    elif kind == "opposite_ends":    # differences beyond 31 bits, differences of the largest values held
+        X = np.where(X > 0, np.float32(1024.0), np.float32(-1024.0))
+        X[:, 1 :: 2] *= np.float32(1000.0)
     tree_nodes_equal(ef, X, 2, 9, 4, split_rule=1)
 
 
