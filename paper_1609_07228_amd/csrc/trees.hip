@@ -169,26 +169,14 @@ __device__ inline bool var_before(const VarKey &a, const VarKey &b)
     return a.v > b.v || (a.v == b.v && a.j < b.j);
 }
 
-// The variance of dimension j of the sample, slowly: any values.
-__device__ inline __int128 variance_any(const float *__restrict__ X, int d, const int *ids, int m, int j)
-{
-    long long s1 = 0;
-    __int128 s2 = 0;
-    for (int p = 0; p < m; ++p) {
-        const long long q = ef_quantise(X[(size_t)ids[p] * d + j]);
-        s1 += q;
-        s2 += (__int128)q * q;
-    }
-    return (__int128)m * s2 - (__int128)s1 * s1;
-}
-
 // What bounds this: the rows of the samples, up to 100 whole rows per node and level.  Two dimensions
 // per lane and eight rows are fetched together (one row at a time left a node waiting for a hundred
-// memory round trips in turn), and sums are taken of q - q(first row), which leaves the variance as
-// it is and keeps them in 64 bits unless the values of a dimension lie 2^28 steps (256.0) or more
-// apart; then that wave falls back to 128-bit sums.  Scaling by 2^20 and rounding are exact in
-// float32 as well: a power of two, and an integer of at most 24 bits.
-// 10^6 x 128, eight trees of leaves of 16: the in-LDS finish 14.9 -> 9.0 ms, the levels above 3.05 -> 0.55.
+// memory round trips in turn).  A value is taken apart into whole units and steps, q = hi 2^20 + lo with
+// |hi|, |lo| <= 2^20: truncation, the fraction and its 2^20-fold are exact in float32, the steps round
+// as q does (hi 2^20 is even), the products and sums of a hundred of them fit 64 bits whatever the values,
+// and only the result is put together in 128.  10^6 x 128, eight trees of leaves of 16: the in-LDS finish
+// 14.9 -> 5.0 ms, the levels above 3.05 -> 0.32.  (Sums of q - q(first row) in 64 bits, with a second pass in 128
+// where values lie 256.0 or more apart: 9.0 and 0.55; with that pass 10^4 x 32 took 1.20 ms in all, now 0.79.)
 __device__ inline int variance_dim_wave(const float *__restrict__ X, int d, const int *ids, int cnt, u64 draw)
 {
     const int lane = ef_lane();
@@ -204,17 +192,8 @@ __device__ inline int variance_dim_wave(const float *__restrict__ X, int d, cons
         const int j[2] = {j0 + lane, j0 + EF_WAVE + lane};
         const int jc[2] = {min(j[0], d - 1), min(j[1], d - 1)};      // (lanes beyond d read along)
         const bool second = j0 + EF_WAVE < d;
-        float y0[2], widest[2] = {0.f, 0.f};
-        u32 q0[2];
-        long long s1[2] = {0, 0};
-        u64 s2[2] = {0, 0};
-        // Values too wide for this are held at the ends of 32 bits by the instruction (the language leaves their
-        // conversion undefined), differences and sums of squares wrap, and the result is not looked at.
-        auto steps = [](float y) {
-            u32 q;
-            asm("v_cvt_i32_f32 %0, %1" : "=v"(q) : "v"(y));
-            return q;
-        };
+        int s_hi[2] = {0, 0}, s_lo[2] = {0, 0};                             // sums of hi and lo
+        long long s_hh[2] = {0, 0}, s_hl[2] = {0, 0}, s_ll[2] = {0, 0};     // ... of hi^2, hi lo and lo^2
         for (int p0 = 0; p0 < m; p0 += 8) {
             float x[2][8];
 #pragma unroll
@@ -225,23 +204,19 @@ __device__ inline int variance_dim_wave(const float *__restrict__ X, int d, cons
                 x[0][u] = row[jc[0]];
                 x[1][u] = second ? row[jc[1]] : 0.f;
             }
-            if (p0 == 0) {
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    y0[h] = __builtin_rintf(x[h][0] * 1048576.0f);
-                    q0[h] = steps(y0[h]);
-                }
-            }
+            for (int h = 0; h < 2; ++h) {
+                if (h == 1 && !second) break;
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                if (p0 + u >= m) break;
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const float y = __builtin_rintf(x[h][u] * 1048576.0f);
-                    const int dq = (int)(steps(y) - q0[h]);
-                    widest[h] = fmaxf(widest[h], fabsf(y - y0[h]));
-                    s1[h] += dq;
-                    s2[h] += (u64)((long long)dq * dq);
+                for (int u = 0; u < 8; ++u) {
+                    if (p0 + u >= m) break;
+                    const float whole = __builtin_truncf(x[h][u]);
+                    const int hi = (int)whole, lo = (int)__builtin_rintf((x[h][u] - whole) * 1048576.0f);
+                    s_hi[h] += hi;
+                    s_lo[h] += lo;
+                    s_hh[h] += (long long)hi * hi;
+                    s_hl[h] += (long long)hi * lo;
+                    s_ll[h] += (long long)lo * lo;
                 }
             }
         }
@@ -250,11 +225,9 @@ __device__ inline int variance_dim_wave(const float *__restrict__ X, int d, cons
             if (h == 1 && !second) break;
             VarKey c;
             c.j = j[h];
-            // |dq| < 2^28 and a hundred of them: the sum of squares stays below 2^63; |q| < 2^30: steps() is exact
-            const bool narrow = fabsf(y0[h]) < 536870912.0f && widest[h] < 268435456.0f;
-            const u64 a1 = (u64)(s1[h] < 0 ? -s1[h] : s1[h]);
-            c.v = (__int128)((unsigned __int128)(u64)m * s2[h] - (unsigned __int128)a1 * a1);
-            if (!narrow) c.v = variance_any(X, d, ids, m, jc[h]);
+            const long long s1 = (long long)s_hi[h] * 1048576 + s_lo[h];
+            const __int128 s2 = (__int128)s_hh[h] * ((__int128)1 << 40) + (__int128)s_hl[h] * ((__int128)1 << 21) + s_ll[h];
+            c.v = s2 * m - (__int128)s1 * s1;
             if (j[h] >= d) continue;
             if (j0 == 0 && h == 0) {      // (up to 128 dimensions a lane has two: one comparison puts them in order)
                 top[0] = c;

@@ -288,8 +288,8 @@ def test_trees_variance_rule_shapes(ef):
 @pytest.mark.parametrize("d", [1, 4, 63, 64, 65, 128, 129, 193])
 @pytest.mark.parametrize("kind", ["ties", "just_narrow", "just_wide", "huge", "far_offset", "opposite_ends"])
 def test_trees_variance_rule_sums(ef, kind, d):
-    """The 64-bit sums of the variance rule and the 128-bit ones they fall back to, on either side of
-    the switch (values 256.0 apart, values of 512.0), with equal variances among the lanes."""
+    """The variance rule's sums, with equal variances among the lanes: values whose squared steps fit 64
+    bits and values whose do not, negative values, fractions and whole numbers, far from zero and on both sides."""
     rng = np.random.default_rng(d)
     n = 3_000
     X = rng.integers(0, 2, (n, d)).astype(np.float32)      # many dimensions of equal variance
