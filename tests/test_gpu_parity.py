@@ -357,7 +357,7 @@ def test_conquer_shapes_and_limits(ef):
 
 
 @pytest.mark.parametrize("kind", ["large", "just_below", "tiny", "offset", "far_offset", "outlier", "integers",
-                                  "mixed_scales"])
+                                  "mixed_scales", "minute", "unscaled_small"])
 @pytest.mark.parametrize("d,S,K,T", [(128, 16, 10, 4), (36, 7, 3, 3), (29, 16, 40, 2)])
 def test_conquer_filter_ranges_bit_exact(ef, kind, d, S, K, T):
     """The conquer step's half-precision filter on data that strains it (a candidate dropped by mistake
@@ -402,8 +402,12 @@ def filter_data(kind, n, d):
         X = X * np.float32(90_000.0)
     elif kind == "just_below":     # largest coordinate just under 2^15: not scaled
         X = X * np.float32(32_000.0 / np.abs(X).max())
-    elif kind == "tiny":           # below the smallest normal half-precision number
+    elif kind == "tiny":           # below the smallest normal half-precision number: scaled up
         X = X * np.float32(3e-6)
+    elif kind == "minute":         # squares below the smallest float32, the most the scale goes up
+        X = X * np.float32(1e-22)
+    elif kind == "unscaled_small":  # largest coordinate just above what is scaled up
+        X = X * np.float32(0.99 * 2.0 ** -9 / np.abs(X).max())
     elif kind == "offset":         # norms a thousand times the distances
         X = X + np.float32(900.0)
     elif kind == "far_offset":     # neighbouring points round to the same few half-precision values
@@ -418,8 +422,8 @@ def filter_data(kind, n, d):
 
 
 @pytest.mark.parametrize("kind", ["large", "just_below", "tiny", "offset", "far_offset", "outlier", "integers",
-                                  "mixed_scales"])
-@pytest.mark.parametrize("d,K,L", [(128, 10, 10), (36, 10, 16)])      # joins of at most 16 and of 17..32 vectors
+                                  "mixed_scales", "minute", "unscaled_small"])
+@pytest.mark.parametrize("d,K,L", [(128, 10, 10), (36, 10, 16), (96, 40, 20)])      # joins of at most 16, of 17..32 and of more vectors
 def test_nndescent_filter_ranges_bit_exact(ef, kind, d, K, L):
     n, T, S, I = 6_000, 3, 16, 4
     X = filter_data(kind, n, d)
