@@ -16,9 +16,12 @@
 //   3. expand  `iters` times: every pool member that has not been expanded yet hands in its
 //              graph neighbours; those not checked before are evaluated and merged, the pool
 //              keeping the P closest.
-// "Checked" is a hash set in LDS; a query that fills it goes on in one in the block's slice of the
-// workspace, whose entries carry the number of the query they belong to (cleared when a block
-// first needs it, never between queries).
+// "Checked" is a hash set in LDS; a query that fills it moves it to one in the block's slice of the
+// workspace, and from there perhaps to a larger one; their entries carry the number of the query they
+// belong to (cleared when a block first needs them, never between queries).  Queries that find nothing near check
+// thousands of points, so it has to be cheap: 20 000 queries of 50 000 x 96, half of them uniform (4500 checked on
+// average, up to 10 000), rows of 50, pool of 200: 11.6 ms; with look-ups in the full set and in the other 35,
+// with the workspace's set alone 14.0.
 // Bound: fetching the rows.  100 000 queries against 10^6 x 128, pool of 200: 37.6 GB at the fabric in 6.4 ms
 // = 5.9 TB/s, a copy reaches 6.2.  (12.5 ms with the set in memory, batches of 64 neighbours
 // evaluated whether four or sixty of them were new, and counting merges.)
@@ -118,17 +121,19 @@ SearchShape search_shape(int64_t nq, int d, int T, int S, int tree_depth, int Kg
     }
     if (sh.w == 1) {
         if (base() + 256 > kLdsLimit) sh.q_lds = false;      // (vectors of forty thousand coordinates)
-        // As many blocks per CU as leave a set that few queries overflow (the number of points checked
-        // grows slowly with the pool: 370, 500, 630, 830, 1030 on average for 50 .. 800, longer lists more),
+        // As many blocks per CU as leave a set that few queries overflow where they find near neighbours (the
+        // number of points checked grows slowly with the pool: 370, 500, 630, 830, 1030 on average for 50 .. 800),
         // a multiple of the four SIMDs: P = 200 with 12 / 11 blocks 6.4 / 8.2 ms per 10^5 queries, P = 400
-        // with 9 / 8 blocks 16.0 / 13.9.
-        const long need = 1400 + P / 2 + (Kg > 20 ? 16 * (Kg - 20) : 0);
+        // with 9 / 8 blocks 16.0 / 13.9.  Fewer than eight only where they leave next to no set, or while four
+        // hold all queries: P = 1000 with 8 / 4 blocks 58 / 71 ms, of the queries described above 32 / 55 per
+        // 20 000, but 1000 queries 1.60 / 1.05.
+        const long need = 1400 + P / 2;
         for (int blocks : {12, 8, 4, 2, 1}) {
             const size_t room = (size_t)(kLdsGranules / blocks) * kLdsGranule;
             if (room < base() + 256) continue;
             const long slots = (long)((room - base()) / 16 * 4);
             sh.lds_slots = (int)(slots < 8192 ? slots : 8192);
-            if (slots >= need) break;
+            if (slots >= need || (blocks == 8 && slots >= 1024 && nq > 4 * 256)) break;
         }
     }
     sh.lds = base() + (size_t)sh.lds_slots * 4;
@@ -150,7 +155,12 @@ __global__ void find_roots_kernel(const efanna_node *__restrict__ nodes, int max
     if (j >= 1 && j < n_leaves.of[t] && nodes[(size_t)t * (max_leaves + 1) + j].parent < 0) roots[t] = j;
 }
 
-// id joins the set of checked points in the workspace; true if it was not in it.  Entries are
+// The sets of checked points in a block's slice of the workspace: kSmallSet entries at its start, then half the
+// slice, which holds all that a query can check (a slice of no more than two small ones: a single set, all of
+// it).  A block clears a set before its first use, and half a megabyte instead of two is most of what a
+// short call pays for sets that overflow (2000 queries of 50 000 x 32, pool of 1000: 1.95 -> 1.41 ms).
+constexpr int kSmallSet = 65536;
+// id joins such a set; true if it was not in it.  Entries are
 // tag << 32 | id, the tag naming the query, so that one query's entries are free slots to the next.
 __device__ inline bool checked_insert(u64 *table, int mask, u32 tag, int id)
 {
@@ -166,18 +176,37 @@ __device__ inline bool checked_insert(u64 *table, int mask, u32 tag, int id)
         if (v == mine) return false;
         h = (h + 1) & (u32)mask;
     }
-    return false;      // a full table cannot happen: it holds twice what a query can check
+    return false;      // (every id of the query is in it: a set has a slot for each)
 }
-// The same set in LDS (ids, -1 = free; never more than seven eighths full).  ADD: the id goes in.
-template <bool ADD>
+// The same set in LDS (ids, -1 = free; never more than fifteen sixteenths full).
+// BUCKETS: of four slots, which one read brings; they fill in order and are never freed, so whoever finds the id
+// absent and takes the first free slot has it alone, and whoever loses that slot looks again (10^5 x 128, pool of
+// 400: 12.9 -> 12.5 ms per 10^5 queries, 200 000 x 32 with rows of 100: 4.1 -> 2.9 per 20 000).  Else slot by slot: one
+// trip to LDS where most slots are free, which is so for few queries (a single one: 62.5 us instead of 64).
+template <bool BUCKETS>
 __device__ inline bool checked_lds(int *tab, int slots, int id)      // true: was not in it
 {
-    int h = (int)__umulhi((u32)id * 0x9E3779B1u, (u32)slots);
+    if (!BUCKETS) {
+        int h = (int)__umulhi((u32)id * 0x9E3779B1u, (u32)slots);
+        for (;;) {
+            const int v = atomicCAS(&tab[h], -1, id);
+            if (v == -1) return true;
+            if (v == id) return false;
+            h = h + 1 == slots ? 0 : h + 1;
+        }
+    }
+    int h = 4 * (int)__umulhi((u32)id * 0x9E3779B1u, (u32)slots >> 2);
     for (;;) {
-        const int v = ADD ? atomicCAS(&tab[h], -1, id) : tab[h];
+        const int4 four = *reinterpret_cast<const int4 *>(tab + h);
+        if (four.x == id || four.y == id || four.z == id || four.w == id) return false;
+        const int at = four.x == -1 ? 0 : four.y == -1 ? 1 : four.z == -1 ? 2 : four.w == -1 ? 3 : -1;
+        if (at < 0) {
+            h = h + 4 >= slots ? 0 : h + 4;
+            continue;
+        }
+        const int v = atomicCAS(&tab[h + at], -1, id);
         if (v == -1) return true;
         if (v == id) return false;
-        h = h + 1 == slots ? 0 : h + 1;
     }
 }
 
@@ -341,9 +370,9 @@ search_kernel(const float *__restrict__ X, int d, int n, const int *__restrict__
     const int dq = (d + 15) & ~15;
     const int tid = threadIdx.x, lane = ef_lane(), wave = tid / EF_WAVE;
     u64 *table = tables + (size_t)blockIdx.x * table_size;
-    const int mask = table_size - 1;
-    const int lds_limit = lds_slots - lds_slots / 8;
-    bool table_clear = false;      // the block's table in the workspace has been cleared
+    const int small_set = table_size > 2 * kSmallSet ? kSmallSet : table_size, large_set = table_size / 2;
+    const int lds_limit = lds_slots - lds_slots / 16;
+    int cleared = 0;      // entries of the largest set of the block's slice that has been cleared
     const bool lds_heap = (size_t)T * heap_cap * sizeof(Branch) <= (size_t)lds_slots * 4;
     for (int qi = blockIdx.x; qi < nq; qi += gridDim.x) {
         const u32 tag = (u32)qi + 1u;
@@ -435,8 +464,9 @@ search_kernel(const float *__restrict__ X, int d, int n, const int *__restrict__
             for (int r = tid & 15; r < s; r += 16) first[at0 + r] = src[r];
         }
         __syncthreads();
-        int count = 0, checked = 0, in_lds = 0;      // count: kept by wave 0
-        bool spilled = false;                        // the LDS set is full: further points go to the workspace's
+        int count = 0, checked = 0;      // count: kept by wave 0
+        int set_size = 0;                // entries of the workspace set in use (0: the set in LDS)
+        u64 *set = table;
         int waiting = 0;
         // ---- 3. the first pool from the leaves' members (it = -1), then NN-expansion -----------------
         for (int it = -1; it < iters; ++it) {
@@ -468,14 +498,33 @@ search_kernel(const float *__restrict__ X, int d, int n, const int *__restrict__
             // checked before in full batches: most neighbours of neighbours were (four in five at a
             // pool of 200), and the rows of a batch cost the same however many of its lanes have one.
             for (int f0 = 0; f0 < total; f0 += 4 * kThreads) {
-                if (!spilled && in_lds + min(total - f0, 4 * kThreads) > lds_limit) {
-                    spilled = true;
-                    if (!table_clear) {
-                        for (int j = tid; j < table_size; j += kThreads) table[j] = 0;
-                        table_clear = true;
+                const int then = checked + min(total - f0, 4 * kThreads);
+                if (set_size == 0 ? then > lds_limit : set_size < large_set && then > set_size - set_size / 4) {
+                    // on to the next larger set: all threads, what was checked so far goes along
+                    const int size = set_size == 0 ? small_set : large_set;
+                    u64 *to = set_size == 0 ? table : table + large_set;
+                    if (cleared < size) {
+                        for (int j = tid; j < size / 2; j += kThreads) reinterpret_cast<uint4 *>(to)[j] = make_uint4(0, 0, 0, 0);
+                        cleared = size;
                         __threadfence();      // (the cleared entries are in place before any wave swaps one)
                         __syncthreads();
                     }
+                    if (set_size == 0) {
+                        for (int j = tid; j < lds_slots; j += kThreads)
+                            if (tab[j] >= 0) checked_insert(to, size - 1, tag, tab[j]);
+                    } else {
+                        for (int j = tid; j < set_size; j += 4 * kThreads) {
+                            u64 v[4];
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) v[k] = j + k * kThreads < set_size ? ef_load_coherent(set + j + k * kThreads) : 0;
+#pragma unroll
+                            for (int k = 0; k < 4; ++k)
+                                if ((u32)(v[k] >> 32) == tag) checked_insert(to, size - 1, tag, (int)(u32)v[k]);
+                        }
+                    }
+                    set = to;
+                    set_size = size;
+                    __syncthreads();
                 }
                 int id[4];
                 u64 new_mask[4];
@@ -497,10 +546,8 @@ search_kernel(const float *__restrict__ X, int d, int n, const int *__restrict__
                 for (int k = 0; k < 4; ++k) {
                     bool fresh = false;
                     if (id[k] >= 0 && id[k] < n) {
-                        if (!spilled)
-                            fresh = checked_lds<true>(tab, lds_slots, id[k]);
-                        else
-                            fresh = checked_lds<false>(tab, lds_slots, id[k]) && checked_insert(table, mask, tag, id[k]);
+                        fresh = set_size == 0 ? checked_lds<W == 1>(tab, lds_slots, id[k])
+                                              : checked_insert(set, set_size - 1, tag, id[k]);
                     }
                     new_mask[k] = __ballot(fresh);
                     n_new += __popcll(new_mask[k]);
@@ -518,7 +565,6 @@ search_kernel(const float *__restrict__ X, int d, int n, const int *__restrict__
                 __syncthreads();
                 const int now = W > 1 ? shared[kWaiting] : waiting + n_new;
                 checked += now - waiting;
-                if (!spilled) in_lds += now - waiting;
                 waiting = now;
                 const bool last = f0 + 4 * kThreads >= total;
                 while (waiting >= kThreads || (last && waiting > 0)) {

@@ -706,6 +706,8 @@ def test_search_bit_exact(ef, name, n, T, S, K, P, E, I):
     (9_000, 8, 4, 16, 64, 512, 200, 3, 20),      # more points checked than the sets in LDS hold: eight waves,
     (9_000, 8, 4, 16, 64, 512, 200, 3, 300),     # four,
     (9_000, 8, 4, 16, 64, 512, 200, 3, 800),     # one
+    (3_000, 8, 4, 16, 64, 512, 200, 3, 6_500),   # ... and another query of the same block after it
+    (9_000, 8, 4, 16, 40, 1_000, 300, 2, 800),   # the smallest set of eight blocks per CU
     (2_000, 4, 20, 5, 6, 1024, 1024, 2, 10),     # the largest pool, several leaves of many trees
     (40, 40_500, 1, 4, 3, 10, 8, 2, 5),          # vectors that leave no room in LDS for a copy of the query
 ])
@@ -755,6 +757,25 @@ def test_search_long_rows_of_neighbours(ef, Kg, P, nq):
     assert np.array_equal(host(got[0]), want[0])
     assert host(got[1]).tobytes() == want[1].tobytes()
     assert np.array_equal(host(got[2]), want[2])
+
+
+@pytest.mark.parametrize("Kg,P,I,nq", [(128, 1_024, 2, 3), (128, 1_024, 2, 300), (128, 1_024, 2, 800), (128, 500, 3, 6_200)])
+def test_search_sets_that_grow(ef, Kg, P, I, nq):
+    """Random neighbours: a query checks most of 80 000 points, more than the small set in the workspace takes;
+    of 6200 queries the last 56 find the sets of the first ones."""
+    rng = np.random.default_rng(nq)
+    n, S, T = 80_000, 16, 2
+    X = rng.standard_normal((n, 4)).astype(np.float32)
+    Xd, g, o, _ = build_index(ef, X, T, S, 4, 0)
+    ids = rng.integers(0, n, (n, Kg)).astype(np.int32)
+    Q = rng.standard_normal((nq, 4)).astype(np.float32)
+    got = ef.efanna_search(Xd, g[0], g[1], g[2], g[3], g[5], S, dev(ids), dev(Q), 20, P, P, I)
+    some = np.r_[:min(nq, 60), max(60, nq - 60):nq]
+    want = oracle.search(X, o[0], o[1], o[2], o[3], S, ids, np.ascontiguousarray(Q[some]), 20, P, P, I)
+    assert np.median(want[2]) > 49_152
+    assert np.array_equal(host(got[0])[some], want[0])
+    assert host(got[1])[some].tobytes() == want[1].tobytes()
+    assert np.array_equal(host(got[2])[some], want[2])
 
 
 def test_search_edge_cases(ef):
