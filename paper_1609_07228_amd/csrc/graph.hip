@@ -196,7 +196,7 @@ __device__ inline void gather_rows(const float *__restrict__ X, int d, int strid
 
 // Drain the proposal queue: every thread applies whole proposals on its own, so all the
 // row reads of up to blockDim proposals are in flight together.
-template <bool WIDE = false, bool REFINE = false>
+template <bool REFINE = false>
 __device__ inline int drain_queue(const Proposal *queue, int count, u64 *graph, u32 *worst, int K,
                                   int tid, int nthr)
 {
@@ -204,7 +204,7 @@ __device__ inline int drain_queue(const Proposal *queue, int count, u64 *graph, 
     for (int e = tid; e < count; e += nthr) {
         const Proposal p = queue[e];
         u64 new_max;
-        if (ef_bounded_insert_t<WIDE, REFINE>(graph + (size_t)p.target * K, K, p.key, 1, &new_max)) {
+        if (ef_bounded_insert_t<false, REFINE>(graph + (size_t)p.target * K, K, p.key, 1, &new_max)) {
             atomicMin(worst + p.target, ef_dist_bits(new_max));
             ++updates;
         }
@@ -1277,7 +1277,7 @@ __device__ inline void sample_row(u64 *graph, const u64 (&e)[E], int i, bool row
             base_o += __popcll(bo);
         }
     } else if (G == 64) {
-        // A row to a wave (K > 32): the L-th smallest new key bit by bit from ballots - 31 steps over the
+        // A row to a wave (K > 32): the L-th smallest new key bit by bit from ballots - 32 steps over the
         // distances, and as many over the rest only if that distance is not unique - and then places by
         // compaction as above.  (Ranks by broadcasting every entry, as below, took 1400 instructions a
         // row at K = 100: 10^6 rows 2.6 -> 1.2 ms per iteration.)
@@ -1523,8 +1523,8 @@ __host__ __device__ inline bool bucketed_lists(int64_t n, int K, int L)
 // Up to 2^16 points: offer blocks of 256 rows, and the smallest
 // ranges that make at most 512 buckets (from 32 targets up).  (The table of runs is then larger, up to
 // 8 bytes per point, and lies in the half of the reverse-old lists' room that 32-bit sources leave
-// free: L >= 4.)  Builds of 2500 x 24 / 10^4 x 32 / 6 10^4 x 100: 921 -> 762 us, 1221 -> 1100, 4009 -> 3933; from
-// 10^5 points on nothing is gained (the insertions of popular points decide), and at 2.6 10^5 2 % lost.
+// free: L >= 4.)  Builds of 2500 x 24 / 10^4 x 32 / 6 10^4 x 100 with degree 10, and of the last with degree 20: 660 ->
+// 575 us, 890 -> 815, 2135 -> 2085, 3745 -> 3645; from 10^5 points on nothing is gained (the insertions of popular points decide), and at 2.6 10^5 2 % lost.
 struct BucketShape {
     int row_bits, blocks;           // log2 of the source rows of an offer block, number of blocks
     int shift, buckets, threads;    // log2 of the targets of a bucket, number of buckets, threads of a list block
@@ -2199,7 +2199,8 @@ __global__ void __launch_bounds__(512) join_kernel(const float *__restrict__ X, 
                         }
                     }
                     __syncthreads();
-                    // ---- 4. drain -----------------------------------------------------------
+                    // ---- 4. drain (one form for rows of any length: a second one for even, aligned rows makes
+                    //      degree 64 0.7 % slower and degree 100 1 % faster, 30 000 x 256 and 20 000 x 160) ----
                     updates += WIDE
                                    ? drain_queue_g16<true>(lds.queue, lds.meta[3], graph, worst, K, tid, nthr)
                                    : drain_queue(lds.queue, lds.meta[3], graph, worst, K, tid, nthr);
@@ -2444,7 +2445,7 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
     // registers, and a lane finds its slot from a ballot (no LDS counters, no round trips).
     int updates = 0, q_fill = 0;
     auto drain = [&](const Proposal *from, int cnt) {
-        return drain_queue<false, NB == 1>(from, cnt, graph, worst, K, lane, EF_WAVE);
+        return drain_queue<NB == 1>(from, cnt, graph, worst, K, lane, EF_WAVE);
     };
     auto drain_mid = drain;
     for (; i >= 0; w += gridDim.x) {
@@ -2867,7 +2868,7 @@ join_tile_kernel(const float *__restrict__ X, int d, int K, u32 k_magic,
     int updates = 0, q_fill = 0;
     auto drain = [&]() {
         updates += LONG_ROWS ? drain_queue_g16<!QUADS>(lds.queue, q_fill, graph, worst, K, lane, EF_WAVE, gid)
-                             : drain_queue<false, false>(lds.queue, q_fill, graph, worst, K, lane, EF_WAVE);
+                             : drain_queue(lds.queue, q_fill, graph, worst, K, lane, EF_WAVE);
         q_fill = 0;
         __syncthreads();
     };

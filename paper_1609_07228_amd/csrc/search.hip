@@ -22,8 +22,8 @@
 // thousands of points, so it has to be cheap: 20 000 queries of 50 000 x 96, half of them uniform (4500 checked on
 // average, up to 10 000), rows of 50, pool of 200: 11.6 ms; with look-ups in the full set and in the other 35,
 // with the workspace's set alone 14.0.
-// Bound: fetching the rows.  100 000 queries against 10^6 x 128, pool of 200: 37.6 GB at the fabric in 6.4 ms
-// = 5.9 TB/s, a copy reaches 6.2.  (12.5 ms with the set in memory, batches of 64 neighbours
+// Bound: fetching the rows.  100 000 queries against 10^6 x 128, pool of 200: 37.6 GB at the fabric in 6.25 ms
+// = 6.0 TB/s, a copy reaches 6.2.  (12.5 ms with the set in memory, batches of 64 neighbours
 // evaluated whether four or sixty of them were new, and counting merges.)
 #include "common.h"
 
@@ -68,8 +68,8 @@ struct SearchShape {
     int want;           // leaves per tree
     int heap_cap;       // branches one tree can have put aside
     int max_first;      // most points the trees can hand in
-    int table;          // hash table entries per wave (power of two)
-    int waves;          // persistent waves
+    int table;          // entries of a block's slice for sets of checked points (power of two)
+    int waves;          // blocks, a query at a time each (of w waves)
     size_t heap_bytes, table_bytes, roots_bytes, bytes;
     int lds_slots, w;   // entries of the LDS set, waves per query
     bool q_lds;
@@ -85,7 +85,8 @@ constexpr int kLdsGranules = 128;
 // up ...): with few queries its length is the call's time, and more waves make every step of it
 // wider; with many the chip is full and the waves that wait for wave 0's merges are lost.  100 000 x 128,
 // pool of 100, 1 / 4 / 8 waves: 64 queries 152 / 107 / 100 us, 256: 170 / 118 / 113, 512: 180 / 125 / 173,
-// 1024: 186 / 187 / 303.
+// 1024: 186 / 187 / 303.  (Either side of the lines at 50 000 x 32 and x 960, pools of 40 and 400: 256 queries on eight waves
+// 66, 147, 153, 253 us, 300 on four 68, 166, 161, 320; 768 on four 72, 170, 190, 430, 800 on one 81, 226, 222, 505.)
 inline int waves_per_query(int64_t nq) { return nq <= 256 ? 8 : nq <= 768 ? 4 : 1; }
 
 SearchShape search_shape(int64_t nq, int d, int T, int S, int tree_depth, int Kg, int P, int iters)
@@ -102,7 +103,7 @@ SearchShape search_shape(int64_t nq, int d, int T, int S, int tree_depth, int Kg
     if (sh.waves < 1) sh.waves = 1;
     sh.heap_bytes = align_up((size_t)sh.waves * T * sh.heap_cap * sizeof(Branch));
     sh.table_bytes = align_up((size_t)sh.waves * sh.table * 8);
-    sh.roots_bytes = align_up((size_t)2 * T * 4);      // roots and a device copy of the leaf counts
+    sh.roots_bytes = align_up((size_t)T * 4);
     sh.bytes = sh.heap_bytes + sh.table_bytes + sh.roots_bytes;
     // The documented limit: query, pool, a batch's keys, expansion list, leaf members and leaves in 160 KB.
     sh.ok = (size_t)((d + 15) & ~15) * 4 + (size_t)P * 8 + 64 * 8 + (size_t)P * 4 + (size_t)sh.max_first * 4 +
