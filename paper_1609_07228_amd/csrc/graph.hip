@@ -2789,60 +2789,67 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
 
 // ---------------------------------------------------------------------------------------
 // The local join for points whose join gathers more than 32 vectors of at most 128 coordinates
-// (d >= 4), without a row buffer: one wave per point, the vectors pass
-// through registers sixteen at a time.  For every tile of sixteen new rows (A) and every tile of
-// sixteen rows from it onwards (B) the wave loads both tiles as join_reg_kernel does - lane
-// (r, g) the 16-byte pieces 16 s + 4 g of row r - forms their Gram block in half precision, filters
-// with join_reg_kernel's bound (the squared norms of the rounded rows are the diagonals of the
-// blocks (A, A) and (B, B): a few more matrix instructions per tile, nothing to keep),
-// and evaluates the surviving pairs exactly from the same registers.  B tiles are read once per
-// A tile: the rows of a join (some tens of KB) come from the caches after the first time.  What
-// a block keeps in LDS is small (ids, thresholds, the table of pairs already known, queues: a few
-// KB against the tens of KB of a row buffer), its waves never wait for one another, and
-// as many joins are in flight on a CU as its LDS holds: eleven of the largest of 200 vectors.
-// (Blocks in fp32 cost 32 clocks of the matrix unit per four coordinates, a quarter of the join's
-// time, and norms, scaled thresholds and a table of 8-byte slots left room for seven joins.
-// 10^6 x 96, degree 100: tile joins 421 -> 314 ms per build.)
+// (d >= 4), without a row buffer: one wave per point.  Three passes over the join's list:
+//   1. Wants.  Up to four tiles of sixteen new rows (A) stand in registers as half-precision operands while
+//      every tile of sixteen rows from the first of them onwards (B) passes by once: a Gram block per tile
+//      pair, join_reg_kernel's filter (the squared norms of the rounded rows are the diagonals of the tiles'
+//      blocks with themselves), and for either row of a pair one bit that says whether its own threshold lets
+//      the other in.
+//   2. Known.  The rows of ids of the members that want anybody are scanned, and every entry that is itself a
+//      member loses its bit: with rows of a hundred entries most pairs inside the thresholds are in the rows
+//      already (two close points sit together in the lists of a hundred others), and offering them again
+//      would cost a scan of the row each.
+//   3. The wants that are left, one (row, member) per four lanes: both rows are loaded from memory (from
+//      the caches mostly), the fixed-order distance goes through the exact threshold test and into the queue.
+// The bound: vector issue and the gathers of rows and ids (fabric 4.5 TB/s).  Scanning only rows that want
+// somebody, after the filter, is what pays: 59 of 65 million members in the first iteration of 10^6 x 96 at
+// degree 100, 94 of 107, 39 of 98, 44 of 106, 32 of 102, 18 of 93, 11 of 83, 6 of 74 in the eighth.  (When the
+// scan came first, for all members, and each pair of tiles was loaded and evaluated together:
+// 318 ms of tile joins per build, now 234; from the fourth iteration on 136, now 68.)
 struct TileLds {
     int *uid;          // [c16] U_new ++ U_old
     u32 *thr;          // [c16] threshold bits
-    u32 *known;        // [cap][known_words(cap)]
-    int *hid;          // [tile_slots(cap)] members' ids in buckets of four slots, -1 = free
-    unsigned char *hplace;      // [tile_slots(cap)] their places in uid
-    unsigned short *surv;       // [256] surviving pairs of the tile pair in hand
-    float *fa, *fb;    // [4][16] the filter's terms of the rows of tile A and of tile B
-    Proposal *queue;   // [q_cap]
+    u32 *want;         // [cap][known_words(cap)] bit c of row r: r would take member c
+    u32 *bits;         // [kTileBits / 32] which hashes occur among the members' ids
+    unsigned short *head, *next;      // [kTileHeads], [c16] chains of places (+ 1; 0 = end) by hash
+    unsigned char *rows;              // [c16] members that want anybody
+    int *hit_id;       // [5 * EF_WAVE] ids that passed the hash bits
+    unsigned char *hit_row;     // [5 * EF_WAVE] and whose rows they are in
+    unsigned short *items;      // [2 * EF_WAVE] wants to evaluate, row << 8 | member (shares the room of hit_id)
+    float *fa, *fb;    // [kTileGroup][4][16], [4][16] the filter's terms of the rows of the A tiles and of tile B
+    Proposal *queue;   // [kTileQueue]
 };
-// The table that maps an id to its place in the list: buckets of four slots, four slots per id the
-// list can have, so that nearly every look-up is one 16-byte read of the id's own bucket (ten thousand
-// look-ups per join: a probe loop whose length differs from lane to lane was most of a join).
-// An id goes to the first free slot of its bucket, else of the buckets after it; a look-up
-// therefore ends at the first bucket with a free slot.
 constexpr int kTileQueue = 96;      // proposals that can wait
-__host__ __device__ inline int tile_slots(int cap) { return 4 * cap; }
+constexpr int kTileGroup = 2;       // A tiles in registers at a time (three: the same; four: 18 ms slower, 69 spills)
+constexpr int kTileBits = 4096, kTileHeads = 256;
 __host__ __device__ inline size_t tile_lds_bytes(int cap)
 {
     const int c16 = (cap + 15) & ~15;
-    return (size_t)(2 * c16 + align4(cap * known_words(cap)) + tile_slots(cap) + tile_slots(cap) / 4 + 128 + 128) * 4 +
-           (size_t)kTileQueue * sizeof(Proposal);
+    return (size_t)kTileQueue * sizeof(Proposal) + 5 * EF_WAVE * 5 +
+           (size_t)((kTileGroup + 1) * 64 + 2 * c16 + align4(cap * known_words(cap)) + kTileBits / 32) * 4 +
+           (size_t)(kTileHeads + c16) * 2 + c16;
 }
 __device__ inline TileLds tile_lds_carve(float *smem, int cap)
 {
     TileLds l;
     const int c16 = (cap + 15) & ~15;
     l.queue = (Proposal *)smem;
-    l.fa = (float *)(l.queue + kTileQueue);
-    l.fb = l.fa + 64;
-    l.hid = (int *)(l.fb + 64);
-    l.uid = l.hid + tile_slots(cap);
+    l.hit_id = (int *)(l.queue + kTileQueue);
+    l.hit_row = (unsigned char *)(l.hit_id + 5 * EF_WAVE);
+    l.items = (unsigned short *)l.hit_id;
+    l.fa = (float *)(l.hit_row + 5 * EF_WAVE);
+    l.fb = l.fa + kTileGroup * 64;
+    l.uid = (int *)(l.fb + 64);
     l.thr = (u32 *)(l.uid + c16);
-    l.known = l.thr + c16;
-    l.surv = (unsigned short *)(l.known + align4(cap * known_words(cap)));
-    l.hplace = (unsigned char *)(l.surv + 256);
+    l.want = l.thr + c16;
+    l.bits = l.want + align4(cap * known_words(cap));
+    l.head = (unsigned short *)(l.bits + kTileBits / 32);
+    l.next = l.head + kTileHeads;
+    l.rows = (unsigned char *)(l.next + c16);
     return l;
 }
 
-constexpr int kTileWaves = 4;      // waves per SIMD the tile join is compiled for (three: 371 ms instead of 314)
+constexpr int kTileWaves = 4;      // waves per SIMD the tile join is compiled for
 // LONG_ROWS: longer graph rows (see the launch): sixteen lanes per proposal.  QUADS: K % 4 == 0, rows of
 // ids and of entries are 16-byte aligned (compiled apart: addressing for any K cost such rows 2 %;
 // before other lengths had it, a thread scanned a row alone: 10^5 x 64, degree 81 53 -> 36 ms per build).
@@ -2858,13 +2865,10 @@ join_tile_kernel(const float *__restrict__ X, int d, int K, u32 k_magic,
     const TileLds lds = tile_lds_carve(smem, cap);
     const int mark = mode != 2;      // (modes: see join_reg_kernel)
     const int lane = threadIdx.x, r16 = lane & 15, g = lane >> 4;
-    const int kw = known_words(cap), hslots = tile_slots(cap);
-    const u32 n_buckets = (u32)hslots >> 2;
-    auto first_slot = [&](int id) { return 4 * (int)__umulhi((u32)id * 0x9E3779B1u, n_buckets); };      // of the id's bucket
+    const int kw = known_words(cap);
     // the power of two that suits the data's halves (see join_reg_kernel)
     const float scale = ef_f16_scale(*xmax);
     const int count = *work_count;
-    const int n_pieces = (d + 15) >> 4;      // 16-coordinate pieces of a vector (at most 8)
     int updates = 0, q_fill = 0;
     auto drain = [&]() {
         updates += LONG_ROWS ? drain_queue_g16<!QUADS>(lds.queue, q_fill, graph, worst, K, lane, EF_WAVE, gid)
@@ -2872,122 +2876,67 @@ join_tile_kernel(const float *__restrict__ X, int d, int K, u32 k_magic,
         q_fill = 0;
         __syncthreads();
     };
-    // The table of known pairs is kept by column: bit r of the words of member c says that row r
-    // holds (or held) c.  The lanes of a wave scan the same row or two at a time, and the ids of a
-    // row are distinct: their hits then fall into different words (by row, they would all be
-    // or-ed into the same few words, one after the other).
-    auto is_known = [&](int row, int col) { return (lds.known[col * kw + (row >> 5)] >> (row & 31)) & 1u; };
+    // A full-rate multiplication of the id's low 24 bits; bits 20..31 of the product pick one of
+    // kTileBits bits, bits 24..31 one of kTileHeads chains.
+    auto hash_of = [](int id) -> u32 { return ((u32)id & 0xFFFFFFu) * 0x9E3779u; };
+    static_assert(kTileBits == 1 << 12 && kTileHeads == 1 << 8, "hash bits");
     for (int w = blockIdx.x; w < count; w += gridDim.x) {
         const int i = work[w];
         const int2 mc = ucount[i];
         const int m_new = mc.x, m = min(mc.y, cap);
-        // ---- 0. ids, thresholds, norms; the members' places by id ---------------------------
-        for (int f = lane; f < m * kw; f += EF_WAVE) lds.known[f] = 0u;
-        for (int f = lane; f < hslots; f += EF_WAVE) lds.hid[f] = -1;
+        // ---- 0. ids, thresholds; the members' places by id ------------------------------------
+        for (int f = lane; f < m * kw; f += EF_WAVE) lds.want[f] = 0u;
+        for (int f = lane; f < kTileBits / 32; f += EF_WAVE) lds.bits[f] = 0u;
+        for (int f = lane; f < kTileHeads / 2; f += EF_WAVE) ((u32 *)lds.head)[f] = 0u;
         __syncthreads();
-        for (int r = lane; r < m; r += EF_WAVE) {
-            const int id = ulist[(size_t)i * ucap + r];
-            const u32 t = ef_load_coherent(worst + id);
-            lds.uid[r] = id;
-            lds.thr[r] = t;
-            int h = first_slot(id);      // ids of a list are distinct: every one finds a slot
-            while (atomicCAS(&lds.hid[h], -1, id) != -1) h = h + 1 == hslots ? 0 : h + 1;
-            lds.hplace[h] = (unsigned char)r;
-        }
-        __syncthreads();
-        // ---- 1. which members already know which (see join_kernel): the members' rows of ids, sixteen
-        //         loads in flight per lane, four ids per load where rows allow it -----------------
-        // `four`: the id's own bucket, read beforehand (several look-ups are issued together: one
-        // after the other, each would wait out its own LDS round trips)
-        auto note = [&](int row, int id, int4 four) {
-            if (id < 0) return;
-            int h = first_slot(id);
-            for (;;) {
-                const int at = four.x == id ? 0 : four.y == id ? 1 : four.z == id ? 2 : four.w == id ? 3 : -1;
-                if (at >= 0) {
-                    const int c = lds.hplace[h + at];
-                    atomicOr(&lds.known[c * kw + (row >> 5)], 1u << (row & 31));
-                    return;
+        for (int r0 = 0; r0 < m; r0 += EF_WAVE) {
+            const int r = r0 + lane;
+            if (r < m) {
+                const int id = ulist[(size_t)i * ucap + r];
+                const u32 t = ef_load_coherent(worst + id);
+                lds.uid[r] = id;
+                lds.thr[r] = t;
+                const u32 h = hash_of(id);
+                atomicOr(&lds.bits[h >> 25], 1u << ((h >> 20) & 31));
+                // the place enters its chain at the head (a 16-bit half of a word)
+                u32 *word = (u32 *)lds.head + (h >> 25);
+                const int sh = (h >> 20) & 16;
+                u32 old = *word, seen;
+                for (;;) {
+                    seen = atomicCAS(word, old, (old & ~(0xFFFFu << sh)) | (u32)(r + 1) << sh);
+                    if (seen == old) break;
+                    old = seen;
                 }
-                if (four.w == -1) return;      // (slots fill in order: a free one ends the search)
-                h = h + 4 == hslots ? 0 : h + 4;      // a full bucket without the id: it may have moved on (rare)
-                four = *reinterpret_cast<const int4 *>(lds.hid + h);
-            }
-        };
-        auto bucket_of = [&](int id) {      // (an id of -1 reads some bucket and is dropped afterwards)
-            return *reinterpret_cast<const int4 *>(lds.hid + first_slot(id));
-        };
-        if (QUADS || K >= 4) {      // (rows at any multiple of four bytes; the last load of a row may repeat ids)
-            const int kq = QUADS ? K >> 2 : (K + 3) >> 2, total = m * kq;
-            for (int f0 = lane; f0 < total; f0 += 16 * EF_WAVE) {
-                int4 four[16];
-                int rr[16];
-#pragma unroll
-                for (int q = 0; q < 16; ++q) {
-                    const int f = f0 + q * EF_WAVE;
-                    rr[q] = kq == 1 ? min(f, total - 1) : (int)(((u64)(u32)min(f, total - 1) * kq_magic) >> 32);
-                    four[q] = make_int4(-1, -1, -1, -1);
-                    if (QUADS) {
-                        if (f < total)
-                            four[q] = *reinterpret_cast<const int4 *>(gid + (size_t)lds.uid[rr[q]] * K + 4 * (f - rr[q] * kq));
-                    } else if (f < total) {
-                        const ef_i32x4_u v = *reinterpret_cast<const ef_i32x4_u *>(gid + (size_t)lds.uid[rr[q]] * K +
-                                                                                   min(4 * (f - rr[q] * kq), K - 4));
-                        four[q] = make_int4(v.x, v.y, v.z, v.w);
-                    }
-                }
-#pragma unroll
-                for (int q = 0; q < 16; ++q) {
-                    const int id4[4] = {four[q].x, four[q].y, four[q].z, four[q].w};
-                    int4 bk[4];
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) bk[t] = bucket_of(id4[t]);
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) note(rr[q], id4[t], bk[t]);
-                }
-            }
-        } else {
-            for (int f0 = lane; f0 < m * K; f0 += 8 * EF_WAVE) {
-                int one[8], rr[8];
-#pragma unroll
-                for (int q = 0; q < 8; ++q) {
-                    const int f = f0 + q * EF_WAVE;
-                    rr[q] = K == 1 ? min(f, m * K - 1) : (int)(((u64)(u32)min(f, m * K - 1) * k_magic) >> 32);
-                    one[q] = f < m * K ? gid[(size_t)lds.uid[rr[q]] * K + (f - rr[q] * K)] : -1;
-                }
-#pragma unroll
-                for (int q0 = 0; q0 < 8; q0 += 4) {
-                    int4 bk[4];
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) bk[t] = bucket_of(one[q0 + t]);
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) note(rr[q0 + t], one[q0 + t], bk[t]);
-                }
+                lds.next[r] = (unsigned short)(old >> sh);
             }
         }
         __syncthreads();
-        // ---- 2. tile pairs ---------------------------------------------------------------------
+        // ---- 1. wants ---------------------------------------------------------------------------
         const int nbr = (m_new + 15) >> 4, nbc = (m + 15) >> 4;
-        auto row_of = [&](int tile) { return X + (size_t)lds.uid[min(16 * tile + r16, m - 1)] * d; };
-        // Gram block of two tiles in half precision (the operands are packed again for every block:
-        // kept, they would not fit next to the rows), and from a tile's block with itself the squared
-        // norm of the rounded row r16, which lane (r16, r16 >> 2) holds on the diagonal
-        auto halves = [&](const float4 &lo, const float4 &hi) {
-            return scale != 1.0f ? ef_pack_f16<true>(lo, hi, scale) : ef_pack_f16<false>(lo, hi, scale);
-        };
-        auto gram = [&](const float4 (&a)[8], const float4 (&b)[8], floatx4 &ab, floatx4 &bb) {
-            ab = bb = (floatx4){0.f, 0.f, 0.f, 0.f};
+        auto load_tile = [&](int tile, f16x8 (&o)[4]) {
+            float4 v[8];
+            load_pieces<ALIGNED>(v, X + (size_t)lds.uid[min(16 * tile + r16, m - 1)] * d, 0, g, d, true);
+            if (scale != 1.0f) {
 #pragma unroll
-            for (int s = 0; s < 8; s += 2) {
-                if (16 * s >= d) break;      // (pieces beyond d are zeros)
-                const f16x8 oa = halves(a[s], a[s + 1]), ob = halves(b[s], b[s + 1]);
-                ab = __builtin_amdgcn_mfma_f32_16x16x32_f16(oa, ob, ab, 0, 0, 0);
-                bb = __builtin_amdgcn_mfma_f32_16x16x32_f16(ob, ob, bb, 0, 0, 0);
+                for (int s = 0; s < 4; ++s) o[s] = ef_pack_f16<true>(v[2 * s], v[2 * s + 1], scale);
+            } else {
+#pragma unroll
+                for (int s = 0; s < 4; ++s) o[s] = ef_pack_f16<false>(v[2 * s], v[2 * s + 1], scale);
             }
+        };
+        auto gram = [&](const f16x8 (&a)[4], const f16x8 (&b)[4]) {
+            floatx4 acc = (floatx4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                if (32 * s >= d) break;      // (pieces beyond d are zeros)
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[s], b[s], acc, 0, 0, 0);
+            }
+            return acc;
         };
         // the filter's terms of the tile's sixteen rows: |x'|^2 (1 - margin), rounding radius, scaled
         // threshold and twice its square root (junk beyond m is masked below)
-        auto terms = [&](const floatx4 &acc, int row0, float *f) {
+        auto terms = [&](const f16x8 (&o)[4], int row0, float *f) {
+            const floatx4 acc = gram(o, o);      // lane (r16, r16 >> 2) holds the diagonal
             if ((r16 >> 2) != g) return;
             const int kd = r16 & 3;
             const float dg = kd == 0 ? acc[0] : kd == 1 ? acc[1] : kd == 2 ? acc[2] : acc[3];
@@ -2997,110 +2946,192 @@ join_tile_kernel(const float *__restrict__ X, int d, int K, u32 k_magic,
             f[32 + r16] = t;
             f[48 + r16] = 2.0f * ef_sqrt_up(t);
         };
-        for (int bi = 0; bi < nbr; ++bi) {
-            float4 va[8];
-            floatx4 gaa, gbb;
-            load_pieces<ALIGNED>(va, row_of(bi), 0, g, d, true);
-            gram(va, va, gaa, gbb);
-            terms(gbb, 16 * bi, lds.fa);
-            for (int bj = bi; bj < nbc; ++bj) {
-                float4 vb[8];
-                floatx4 acc = gaa;
-                const float *fb = lds.fa;
-                if (bj == bi) {
+        unsigned short *const want16 = (unsigned short *)lds.want;      // [cap][2 kw]: sixteen members each
+        for (int bi0 = 0; bi0 < nbr; bi0 += kTileGroup) {
+            f16x8 oa[kTileGroup][4];
 #pragma unroll
-                    for (int s = 0; s < 8; ++s) vb[s] = va[s];
-                } else {
-                    load_pieces<ALIGNED>(vb, row_of(bj), 0, g, d, true);
-                    gram(va, vb, acc, gbb);
-                    terms(gbb, 16 * bj, lds.fb);
-                    fb = lds.fb;
-                }
-                // ---- filter: the lane holds G[a = 16 bi + 4 g + k][b = 16 bj + r16] ---------------
-                const int b = 16 * bj + r16, bc = min(b, m - 1);
+            for (int t = 0; t < kTileGroup; ++t) {
+                if (bi0 + t >= nbr) break;
+                load_tile(bi0 + t, oa[t]);
+                terms(oa[t], 16 * (bi0 + t), lds.fa + 64 * t);
+            }
+            for (int bj = bi0; bj < nbc; ++bj) {
+                f16x8 ob[4];
+                load_tile(bj, ob);
+                terms(ob, 16 * bj, lds.fb);
                 __syncthreads();
-                const float nfb = fb[r16], rrb = fb[16 + r16], tfb = fb[32 + r16], sqb = fb[48 + r16];
-                const float4 nfa = *reinterpret_cast<const float4 *>(lds.fa + 4 * g);
-                const float4 rra = *reinterpret_cast<const float4 *>(lds.fa + 16 + 4 * g);
-                const float4 tfa = *reinterpret_cast<const float4 *>(lds.fa + 32 + 4 * g);
-                const float4 sqa = *reinterpret_cast<const float4 *>(lds.fa + 48 + 4 * g);
-                const float nfa_k[4] = {nfa.x, nfa.y, nfa.z, nfa.w}, rra_k[4] = {rra.x, rra.y, rra.z, rra.w};
-                const float tfa_k[4] = {tfa.x, tfa.y, tfa.z, tfa.w}, sqa_k[4] = {sqa.x, sqa.y, sqa.z, sqa.w};
-                const u32 knows_b = lds.known[bc * kw + (bi >> 1)] >> (16 * (bi & 1));      // which of rows 16 bi .. know b
+                const int b = 16 * bj + r16;
+                const float nfb = lds.fb[r16], rrb = lds.fb[16 + r16], tfb = lds.fb[32 + r16], sqb = lds.fb[48 + r16];
                 // valid pairs: a < lim
                 const int lim = b >= m ? 0 : mode == 0 ? min(m_new, b) : mode == 1 ? (b < m_new ? b : 0) : (b >= m_new ? m_new : 0);
-                int n_surv = 0;
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const int a = 16 * bi + 4 * g + k, ac = min(a, m - 1);
-                    const float lhs = __builtin_fmaf(-2.0f, acc[k], nfa_k[k] + nfb), rad = rra_k[k] + rrb;
-                    // wanted by a row that may still accept the pair and does not know it yet
-                    const bool for_a = !(lhs > __builtin_fmaf(rad, sqa_k[k] + rad, tfa_k[k])) && !((knows_b >> (4 * g + k)) & 1u);
-                    const bool for_b = !(lhs > __builtin_fmaf(rad, sqb + rad, tfb)) && !is_known(bc, ac);
-                    const bool keep = a < lim && (for_a || for_b);
-                    const u64 kept = __ballot(keep);
-                    if (keep) lds.surv[n_surv + lanes_below(kept)] = (unsigned short)((4 * g + k) | (r16 << 8));
-                    n_surv += __popcll(kept);
+                for (int t = 0; t < kTileGroup; ++t) {
+                    const int bi = bi0 + t;
+                    if (bi >= nbr || bi > bj) break;
+                    const floatx4 acc = gram(oa[t], ob);      // the lane holds G[a = 16 bi + 4 g + k][b]
+                    const float *fa = lds.fa + 64 * t + 4 * g;
+                    const float4 nfa = *reinterpret_cast<const float4 *>(fa), rra = *reinterpret_cast<const float4 *>(fa + 16);
+                    const float4 tfa = *reinterpret_cast<const float4 *>(fa + 32), sqa = *reinterpret_cast<const float4 *>(fa + 48);
+                    const float nfa_k[4] = {nfa.x, nfa.y, nfa.z, nfa.w}, rra_k[4] = {rra.x, rra.y, rra.z, rra.w};
+                    const float tfa_k[4] = {tfa.x, tfa.y, tfa.z, tfa.w}, sqa_k[4] = {sqa.x, sqa.y, sqa.z, sqa.w};
+                    const int a0 = 16 * bi + 4 * g;
+                    u32 by_b = 0, by_a = 0;      // which of rows a0 .. a0 + 3 b wants; the sixteen members row a0 + r16 wants (r16 < 4)
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const float lhs = __builtin_fmaf(-2.0f, acc[k], nfa_k[k] + nfb), rad = rra_k[k] + rrb;
+                        // (a comparison with a NaN keeps the pair)
+                        const bool valid = a0 + k < lim;
+                        const u64 for_a = __ballot(valid && !(lhs > __builtin_fmaf(rad, sqa_k[k] + rad, tfa_k[k])));
+                        by_a = r16 == k ? (u32)(for_a >> (16 * g)) : by_a;
+                        by_b |= valid && !(lhs > __builtin_fmaf(rad, sqb + rad, tfb)) ? 1u << k : 0u;
+                    }
+                    by_b <<= 4 * g;
+                    by_b |= (u32)__shfl_xor((int)by_b, 16, EF_WAVE);
+                    by_b |= (u32)__shfl_xor((int)by_b, 32, EF_WAVE);
+                    if (r16 < 4 && a0 + r16 < m) want16[(size_t)(a0 + r16) * 2 * kw + bj] = (unsigned short)by_a;
+                    if (bi == bj) __syncthreads();      // (inside one tile the two halves of a row's bits meet)
+                    if (g == 0 && b < m) {
+                        unsigned short *const wb = want16 + (size_t)b * 2 * kw + bi;
+                        *wb = (unsigned short)(bi == bj ? by_b | *wb : by_b);
+                    }
+                }
+                __syncthreads();      // the terms of tile B are free again
+            }
+        }
+        // the members that want anybody
+        int n_rows = 0;
+        for (int r0 = 0; r0 < m; r0 += EF_WAVE) {
+            const int r = r0 + lane;
+            u32 any = 0;
+            if (r < m)
+                for (int q = 0; q < kw; ++q) any |= lds.want[r * kw + q];
+            const u64 mask = __ballot(any != 0);
+            if (any) lds.rows[n_rows + lanes_below(mask)] = (unsigned char)r;
+            n_rows += __popcll(mask);
+        }
+        __syncthreads();
+        // ---- 2. known pairs: the rows of ids of those members, four ids per load where rows allow it --
+        int n_hits = 0;
+        auto settle = [&](int most) {      // until at most that many hits (fewer than 64, or none) are left: members lose their bit
+            while (n_hits > most) {
+                const int n_h = min(n_hits, EF_WAVE);
+                n_hits -= n_h;
+                __syncthreads();
+                if (lane < n_h) {
+                    const int id = lds.hit_id[n_hits + lane], row = lds.hit_row[n_hits + lane];
+                    for (int p = lds.head[hash_of(id) >> 24]; p != 0; p = lds.next[p - 1])
+                        if (lds.uid[p - 1] == id) {
+                            atomicAnd(&lds.want[row * kw + ((p - 1) >> 5)], ~(1u << ((p - 1) & 31)));
+                            break;
+                        }
                 }
                 __syncthreads();
-                // ---- survivors from registers, sixteen pairs per round (see join_reg_kernel) ------
-                for (int p0 = 0; p0 < n_surv; p0 += 16) {
-                    const bool has = p0 + r16 < n_surv;
-                    const u32 ent = lds.surv[min(p0 + r16, n_surv - 1)];
-                    const int al = ent & 15, bl = (ent >> 8) & 15;
-                    const int src_a = al + 16 * g, src_b = bl + 16 * g;
-                    float p0s = 0.f, p1s = 0.f, p2s = 0.f, p3s = 0.f;
+            }
+        };
+        auto probe = [&](int id, int row, u32 word) {      // word: the id's word of hash bits
+            const bool hit = (word >> ((hash_of(id) >> 20) & 31)) & 1u;
+            const u64 mask = __ballot(hit);
+            if (hit) {
+                const int at = n_hits + lanes_below(mask);
+                lds.hit_id[at] = id;
+                lds.hit_row[at] = (unsigned char)row;
+            }
+            n_hits += __popcll(mask);
+        };
+        auto bits_of = [&](int id) { return lds.bits[hash_of(id) >> 25]; };
+        if (QUADS || K >= 4) {      // (rows at any multiple of four bytes; the last load of a row may repeat ids)
+            const int kq = QUADS ? K >> 2 : (K + 3) >> 2, total = n_rows * kq;
+            for (int f0 = lane; f0 - lane < total; f0 += 8 * EF_WAVE) {
+                int4 four[8];
+                int rr[8];
 #pragma unroll
-                    for (int s = 0; s < 8; ++s) {
-                        if (s >= n_pieces) break;
-                        const float d0 = __shfl(va[s].x, src_a, EF_WAVE) - __shfl(vb[s].x, src_b, EF_WAVE);
-                        const float d1 = __shfl(va[s].y, src_a, EF_WAVE) - __shfl(vb[s].y, src_b, EF_WAVE);
-                        const float d2 = __shfl(va[s].z, src_a, EF_WAVE) - __shfl(vb[s].z, src_b, EF_WAVE);
-                        const float d3 = __shfl(va[s].w, src_a, EF_WAVE) - __shfl(vb[s].w, src_b, EF_WAVE);
-                        p0s = __builtin_fmaf(d0, d0, p0s);
-                        p1s = __builtin_fmaf(d1, d1, p1s);
-                        p2s = __builtin_fmaf(d2, d2, p2s);
-                        p3s = __builtin_fmaf(d3, d3, p3s);
-                    }
-                    p0s += __shfl_xor(p0s, 32, EF_WAVE);
-                    p1s += __shfl_xor(p1s, 32, EF_WAVE);
-                    p2s += __shfl_xor(p2s, 32, EF_WAVE);
-                    p3s += __shfl_xor(p3s, 32, EF_WAVE);
-                    p0s += __shfl_xor(p0s, 16, EF_WAVE);
-                    p1s += __shfl_xor(p1s, 16, EF_WAVE);
-                    p2s += __shfl_xor(p2s, 16, EF_WAVE);
-                    p3s += __shfl_xor(p3s, 16, EF_WAVE);
-                    const float dist = (p0s + p2s) + (p1s + p3s);
-                    const int a = 16 * bi + al, bb = 16 * bj + bl;
-                    const u32 db = __float_as_uint(dist);
-                    const bool mine = has && g == 0;
-                    const bool to_a = mine && db <= lds.thr[a] && !is_known(a, bb);
-                    const bool to_b = mine && db <= lds.thr[bb] && !is_known(bb, a);
-                    const u64 mask_a = __ballot(to_a), mask_b = __ballot(to_b);
-                    if (to_a) {
-                        Proposal &pr = lds.queue[q_fill + lanes_below(mask_a)];
-                        pr.key = ef_pack(dist, lds.uid[bb], mark);
-                        pr.target = lds.uid[a];
-                    }
-                    q_fill += __popcll(mask_a);
-                    if (to_b) {
-                        Proposal &pr = lds.queue[q_fill + lanes_below(mask_b)];
-                        pr.key = ef_pack(dist, lds.uid[a], mark);
-                        pr.target = lds.uid[bb];
-                    }
-                    q_fill += __popcll(mask_b);
-                    __syncthreads();
-                    if (q_fill + 32 > kTileQueue) {      // a round adds at most two proposals per pair
-                        drain();
-                        // (the rows are fetched again: kept across the drain they would not fit the registers)
-                        load_pieces<ALIGNED>(va, row_of(bi), 0, g, d, true);
-                        if (bj != bi) load_pieces<ALIGNED>(vb, row_of(bj), 0, g, d, true);
-                        else
-#pragma unroll
-                            for (int s = 0; s < 8; ++s) vb[s] = va[s];
+                for (int q = 0; q < 8; ++q) {
+                    const int f = min(f0 + q * EF_WAVE, total - 1);
+                    const int at = kq == 1 ? f : (int)(((u64)(u32)f * kq_magic) >> 32);
+                    rr[q] = lds.rows[at];
+                    const int *row = gid + (size_t)lds.uid[rr[q]] * K;
+                    if (QUADS) {
+                        four[q] = *reinterpret_cast<const int4 *>(row + 4 * (f - at * kq));
+                    } else {
+                        const ef_i32x4_u v = *reinterpret_cast<const ef_i32x4_u *>(row + min(4 * (f - at * kq), K - 4));
+                        four[q] = make_int4(v.x, v.y, v.z, v.w);
                     }
                 }
-                __syncthreads();      // the survivor list is free again
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    if (f0 - lane + q * EF_WAVE >= total) break;
+                    const bool in = f0 + q * EF_WAVE < total;
+                    const int id4[4] = {four[q].x, four[q].y, four[q].z, four[q].w};
+                    u32 word[4];
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) word[t] = in ? bits_of(id4[t]) : 0u;
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) probe(id4[t], rr[q], word[t]);
+                    settle(EF_WAVE - 1);
+                }
+            }
+        } else {
+            for (int f0 = lane; f0 - lane < n_rows * K; f0 += EF_WAVE) {
+                const int f = min(f0, n_rows * K - 1), at = K == 1 ? f : (int)(((u64)(u32)f * k_magic) >> 32), row = lds.rows[at];
+                const int id = gid[(size_t)lds.uid[row] * K + (f - at * K)];
+                probe(id, row, f0 < n_rows * K ? bits_of(id) : 0u);
+                settle(EF_WAVE - 1);
+            }
+        }
+        settle(0);
+        // ---- 3. what is left: sixteen wants per round, four lanes each -----------------------------
+        int n_items = 0;
+        auto round = [&](int first, int n_r) {      // wants first .. first + n_r - 1 (at most sixteen)
+            const bool mine = r16 < n_r && g == 0;
+            const u32 ent = lds.items[first + min(r16, n_r - 1)];
+            const int a = ent >> 8, b = ent & 255;
+            const int ia = lds.uid[a], ib = lds.uid[b];
+            float4 va[8], vb[8];
+            load_pieces<ALIGNED>(va, X + (size_t)ia * d, 0, g, d, true);
+            load_pieces<ALIGNED>(vb, X + (size_t)ib * d, 0, g, d, true);
+            float p[4] = {0.f, 0.f, 0.f, 0.f};
+            accumulate_pair(va, vb, (d + 15) >> 4, p);
+            // partial sum l lives in lane g = l / 4, slot l % 4 (see join_reg_kernel)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) p[k] += __shfl_xor(p[k], 32, EF_WAVE);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) p[k] += __shfl_xor(p[k], 16, EF_WAVE);
+            const float dist = (p[0] + p[2]) + (p[1] + p[3]);
+            const bool take = mine && __float_as_uint(dist) <= lds.thr[a];
+            const u64 mask = __ballot(take);
+            if (take) {
+                Proposal &pr = lds.queue[q_fill + lanes_below(mask)];
+                pr.key = ef_pack(dist, ib, mark);
+                pr.target = ia;
+            }
+            q_fill += __popcll(mask);
+            __syncthreads();
+            if (q_fill + 16 > kTileQueue) drain();      // a round adds at most one proposal per want
+        };
+        bool more = true;
+        for (int f0 = 0; more; f0 += EF_WAVE) {
+            more = f0 + EF_WAVE < n_rows * kw;
+            const int f = f0 + lane, at = f / kw, c0 = 32 * (f - at * kw);
+            int row = 0;
+            u32 left = 0;
+            if (f < n_rows * kw) {
+                row = lds.rows[at];
+                left = lds.want[row * kw + (f - at * kw)];
+            }
+            for (u64 mask = ~0ULL; mask != 0;) {      // a bit per lane at a time
+                mask = __ballot(left != 0);
+                if (left) {
+                    lds.items[n_items + lanes_below(mask)] = (unsigned short)(row << 8 | (c0 + __ffs(left) - 1));
+                    left &= left - 1;
+                }
+                n_items += __popcll(mask);
+                __syncthreads();
+                const int keep = more || mask ? EF_WAVE - 1 : 0;
+                while (n_items > keep) {
+                    const int n_r = min(n_items, 16);
+                    n_items -= n_r;
+                    round(n_items, n_r);
+                }
             }
         }
         if (q_fill >= kTileQueue / 2) drain();

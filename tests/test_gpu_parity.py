@@ -487,6 +487,27 @@ def test_nndescent_more_shapes(ef, n, d, T, S, K, L, I):
     oracle.check_graph_invariants(X, ids, dists)
 
 
+@pytest.mark.parametrize("n,d,K,L", [
+    (260, 128, 32, 40),      # lists of a whole number of tiles, several groups of new tiles, nearly all points in each
+    (300, 33, 33, 24),       # an operand step of one coordinate; odd rows; tiles with remainders
+    (230, 64, 100, 50),      # most pairs known beforehand: hits settled many times per join
+    (400, 4, 4, 64),         # one load per row of ids, few of the many wants known
+    (200, 96, 128, 64),      # places up to 199, the longest rows
+])
+def test_nndescent_tile_join_edges(ef, n, d, K, L):
+    """Joins of more than 32 vectors with lists that cover most of the data (the oracle's graph, every iteration)."""
+    rng = np.random.default_rng(n + d)
+    X = rng.standard_normal((n, d)).astype(np.float32)
+    Xd = dev(X)
+    (perm, off, nl), (operm, ooff, onl) = trees_equal(ef, X, 2, 16, 11)
+    graph = ef.efanna_init_graph(Xd, perm, off, nl, 16, K)
+    want = oracle.init_graph(X, operm, ooff, onl, K)
+    for it in range(3):
+        ef.efanna_nndescent(Xd, graph, 1, L, 11, first_iter=it)
+        want = oracle.nndescent(X, *want[:3], 1, L, 11, iter0=it)
+        graph_equal(ef, graph, want)
+
+
 @pytest.mark.parametrize("d,shift", [
     (4, 1), (5, 0), (7, 0), (17, 0), (50, 0), (61, 0), (126, 0), (127, 0),      # one stretch of 128 coordinates
     (129, 0), (131, 0), (255, 0), (300, 1),                                    # more than one
