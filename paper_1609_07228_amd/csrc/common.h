@@ -392,10 +392,9 @@ __device__ inline bool ef_bounded_insert(u64 *list, int cap, u64 key, int ignore
     return ef_bounded_insert_t<false>(list, cap, key, ignore, new_max);
 }
 
-// ---- the same insertion by a group of sixteen lanes (long rows) ----------------------------
-// n (1..4) pieces from n addresses, in flight together
-__device__ inline void ef_load_pieces_at(const void *p0, const void *p1, const void *p2, const void *p3,
-                                         int n, ef_u32x4 (&q)[4])
+// ---- the same insertion by a group of eight lanes (long rows) -------------------------------
+// n (1..8) pieces in flight together: n - 1 from p, p + 128, ..., the last one from `last`
+__device__ inline void ef_load_pieces_strided(const void *p, const void *last, int n, ef_u32x4 (&q)[8])
 {
     switch (n) {
     case 1:
@@ -403,109 +402,187 @@ __device__ inline void ef_load_pieces_at(const void *p0, const void *p1, const v
                      "global_load_dwordx4 %0, %1, off sc1\n\t"
                      "s_waitcnt vmcnt(0)"
                      : "=&v"(q[0])
-                     : "v"(p0)
+                     : "v"(last)
                      : "memory");
         break;
     case 2:
         asm volatile(
-                     "global_load_dwordx4 %0, %2, off sc1\n\t"
+                     "global_load_dwordx4 %0, %2, off offset:0 sc1\n\t"
                      "global_load_dwordx4 %1, %3, off sc1\n\t"
                      "s_waitcnt vmcnt(0)"
                      : "=&v"(q[0]), "=&v"(q[1])
-                     : "v"(p0), "v"(p1)
+                     : "v"(p), "v"(last)
                      : "memory");
         break;
     case 3:
         asm volatile(
-                     "global_load_dwordx4 %0, %3, off sc1\n\t"
-                     "global_load_dwordx4 %1, %4, off sc1\n\t"
-                     "global_load_dwordx4 %2, %5, off sc1\n\t"
+                     "global_load_dwordx4 %0, %3, off offset:0 sc1\n\t"
+                     "global_load_dwordx4 %1, %3, off offset:128 sc1\n\t"
+                     "global_load_dwordx4 %2, %4, off sc1\n\t"
                      "s_waitcnt vmcnt(0)"
                      : "=&v"(q[0]), "=&v"(q[1]), "=&v"(q[2])
-                     : "v"(p0), "v"(p1), "v"(p2)
+                     : "v"(p), "v"(last)
+                     : "memory");
+        break;
+    case 4:
+        asm volatile(
+                     "global_load_dwordx4 %0, %4, off offset:0 sc1\n\t"
+                     "global_load_dwordx4 %1, %4, off offset:128 sc1\n\t"
+                     "global_load_dwordx4 %2, %4, off offset:256 sc1\n\t"
+                     "global_load_dwordx4 %3, %5, off sc1\n\t"
+                     "s_waitcnt vmcnt(0)"
+                     : "=&v"(q[0]), "=&v"(q[1]), "=&v"(q[2]), "=&v"(q[3])
+                     : "v"(p), "v"(last)
+                     : "memory");
+        break;
+    case 5:
+        asm volatile(
+                     "global_load_dwordx4 %0, %5, off offset:0 sc1\n\t"
+                     "global_load_dwordx4 %1, %5, off offset:128 sc1\n\t"
+                     "global_load_dwordx4 %2, %5, off offset:256 sc1\n\t"
+                     "global_load_dwordx4 %3, %5, off offset:384 sc1\n\t"
+                     "global_load_dwordx4 %4, %6, off sc1\n\t"
+                     "s_waitcnt vmcnt(0)"
+                     : "=&v"(q[0]), "=&v"(q[1]), "=&v"(q[2]), "=&v"(q[3]), "=&v"(q[4])
+                     : "v"(p), "v"(last)
+                     : "memory");
+        break;
+    case 6:
+        asm volatile(
+                     "global_load_dwordx4 %0, %6, off offset:0 sc1\n\t"
+                     "global_load_dwordx4 %1, %6, off offset:128 sc1\n\t"
+                     "global_load_dwordx4 %2, %6, off offset:256 sc1\n\t"
+                     "global_load_dwordx4 %3, %6, off offset:384 sc1\n\t"
+                     "global_load_dwordx4 %4, %6, off offset:512 sc1\n\t"
+                     "global_load_dwordx4 %5, %7, off sc1\n\t"
+                     "s_waitcnt vmcnt(0)"
+                     : "=&v"(q[0]), "=&v"(q[1]), "=&v"(q[2]), "=&v"(q[3]), "=&v"(q[4]), "=&v"(q[5])
+                     : "v"(p), "v"(last)
+                     : "memory");
+        break;
+    case 7:
+        asm volatile(
+                     "global_load_dwordx4 %0, %7, off offset:0 sc1\n\t"
+                     "global_load_dwordx4 %1, %7, off offset:128 sc1\n\t"
+                     "global_load_dwordx4 %2, %7, off offset:256 sc1\n\t"
+                     "global_load_dwordx4 %3, %7, off offset:384 sc1\n\t"
+                     "global_load_dwordx4 %4, %7, off offset:512 sc1\n\t"
+                     "global_load_dwordx4 %5, %7, off offset:640 sc1\n\t"
+                     "global_load_dwordx4 %6, %8, off sc1\n\t"
+                     "s_waitcnt vmcnt(0)"
+                     : "=&v"(q[0]), "=&v"(q[1]), "=&v"(q[2]), "=&v"(q[3]), "=&v"(q[4]), "=&v"(q[5]), "=&v"(q[6])
+                     : "v"(p), "v"(last)
                      : "memory");
         break;
     default:
         asm volatile(
-                     "global_load_dwordx4 %0, %4, off sc1\n\t"
-                     "global_load_dwordx4 %1, %5, off sc1\n\t"
-                     "global_load_dwordx4 %2, %6, off sc1\n\t"
-                     "global_load_dwordx4 %3, %7, off sc1\n\t"
+                     "global_load_dwordx4 %0, %8, off offset:0 sc1\n\t"
+                     "global_load_dwordx4 %1, %8, off offset:128 sc1\n\t"
+                     "global_load_dwordx4 %2, %8, off offset:256 sc1\n\t"
+                     "global_load_dwordx4 %3, %8, off offset:384 sc1\n\t"
+                     "global_load_dwordx4 %4, %8, off offset:512 sc1\n\t"
+                     "global_load_dwordx4 %5, %8, off offset:640 sc1\n\t"
+                     "global_load_dwordx4 %6, %8, off offset:768 sc1\n\t"
+                     "global_load_dwordx4 %7, %9, off sc1\n\t"
                      "s_waitcnt vmcnt(0)"
-                     : "=&v"(q[0]), "=&v"(q[1]), "=&v"(q[2]), "=&v"(q[3])
-                     : "v"(p0), "v"(p1), "v"(p2), "v"(p3)
+                     : "=&v"(q[0]), "=&v"(q[1]), "=&v"(q[2]), "=&v"(q[3]), "=&v"(q[4]), "=&v"(q[5]), "=&v"(q[6]), "=&v"(q[7])
+                     : "v"(p), "v"(last)
                      : "memory");
     }
 }
 
-// All sixteen lanes of a group (lane gl = 0..15 of it) call this with the same arguments and get
-// the same result.  Lane gl reads the 16-byte pieces gl, gl + 16, ... of the row, so that the
-// group fetches 256 contiguous bytes per load: a quarter of the memory transactions that a lane
-// reading the whole row alone needs, and one round trip for rows of up to 128 entries.  ODD: rows of
-// any length of at least two, at any multiple of 8 bytes (a 16-byte load asks for 4-byte alignment, and
+// a value from another lane of the eight: lane ^ 1, lane ^ 2 (inside a quad), lane 7 - gl
+#define EF_DPP(x, ctrl) ((u32)__builtin_amdgcn_update_dpp(0, (int)(x), (ctrl), 0xF, 0xF, false))
+#define EF_DPP_XOR1 0xB1
+#define EF_DPP_XOR2 0x4E
+#define EF_DPP_HALF_MIRROR 0x141
+
+// The entry `key` is offered to a graph row of at most 128 entries (keys that agree but for the new mark are
+// the same entry).  All eight lanes of a group (lane gl = 0..7 of it) call this with the same arguments and get
+// the same result.  Lane gl reads the 16-byte pieces gl, gl + 8, ... of the row, so that the group fetches 128
+// contiguous bytes per load, all of a row in one round trip.
+// The scan works on the distances' 32 bits - largest and second largest by a maximum and a median - and looks at
+// the rest of a key only where the largest distance is.  (Sixteen lanes and 64-bit compares took three times
+// the instructions per proposal and had half as many rows in flight: the first two iterations of 10^6 x 96,
+// degree 100, 61 + 88 -> 55 + 84 ms.)
+// ODD: rows of any length of at least two, at any multiple of 8 bytes (a 16-byte load asks for 4-byte alignment, and
 // an 8-byte aligned entry never straddles a cache line); the last piece of a row of odd length starts
 // one entry earlier, at an entry that the piece before it delivers as well.  Else the row must be
 // 16-byte aligned and of even length.  The group's lanes must all be active.
-// slot (or null): receives the slot the key went into.
+// Returns true if the key went in: new_max_bits is then the largest distance left (or a bound of it), and *slot
+// the place the key went to in the lane that put it there, -1 in the others.
 template <bool ODD>
-__device__ inline bool ef_bounded_insert_g16(u64 *list, int cap, u64 key, int ignore, u64 *new_max, int gl,
-                                             int *slot = nullptr)
+__device__ inline bool ef_bounded_insert_g8(u64 *list, int cap, u64 key, u32 *new_max_bits, int gl, int *slot)
 {
-    const u64 kcmp = key >> ignore;
-    const int np = ODD ? (cap + 1) >> 1 : cap >> 1;
+    const u32 khi = (u32)(key >> 32), klo = (u32)key;
+    const int np = ODD ? (cap + 1) >> 1 : cap >> 1, n_ld = (np + 7) >> 3, last = gl + 8 * (n_ld - 1);
+    const int last_at = ODD ? min(2 * last, cap - 2) : 2 * min(last, np - 1);      // (lanes beyond the row: its last piece again)
     for (;;) {
-        u64 mx = 0, mx2 = 0;
-        int ms = 0;
-        bool dup = false;
-        for (int p0 = 0; p0 < np; p0 += 64) {
-            const int n_ld = min(4, (np - p0 + 15) >> 4);
-            ef_u32x4 q[4];
-            // pieces beyond the row read its last piece again and are not looked at
-            auto at = [&](int piece) {
-                return ODD ? (const void *)(list + min(2 * piece, cap - 2))
-                           : (const void *)(reinterpret_cast<const ef_u32x4 *>(list) + min(piece, np - 1));
-            };
-            ef_load_pieces_at(at(p0 + gl), at(p0 + gl + 16), at(p0 + gl + 32), at(p0 + gl + 48), n_ld, q);
+        ef_u32x4 q[8];
+        ef_load_pieces_strided(list + 2 * gl, list + last_at, n_ld, q);
+        u32 m1 = 0, m2 = 0, other = ~0u;      // the two largest distances; 0 once the key itself was met
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int piece = p0 + gl + 16 * k;
-                if (k >= n_ld || piece >= np) continue;
-                const u64 e2[2] = {((u64)q[k].y << 32) | q[k].x, ((u64)q[k].w << 32) | q[k].z};
+        for (int k = 0; k < 8; ++k) {
+            if (k >= n_ld) break;
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const int s = ODD ? min(2 * piece, cap - 2) + h : 2 * piece + h;
-                    if (ODD && s < 2 * piece) continue;      // (looked at already)
-                    dup |= (e2[h] >> ignore) == kcmp;
-                    if (e2[h] > mx) {
-                        mx2 = mx;
-                        mx = e2[h];
-                        ms = s;
-                    } else if (e2[h] > mx2) {
-                        mx2 = e2[h];
-                    }
-                }
+            for (int h = 0; h < 2; ++h) {
+                const bool in = k < n_ld - 1 || (last < np && (!ODD || last_at + h >= 2 * last));
+                const u32 lo = h ? q[k].z : q[k].x, hi = in ? (h ? q[k].w : q[k].y) : 0u;
+                const u32 differ = ((lo ^ klo) & ~1u) | (hi ^ khi);
+                other = in ? min(other, differ) : other;
+                m2 = max(min(m1, hi), m2);
+                m1 = max(m1, hi);
             }
         }
-        // the group's largest and second largest entry (entries of a row are distinct)
-        for (int m = 8; m >= 1; m >>= 1) {
-            const u64 omx = __shfl_xor(mx, m, 16), omx2 = __shfl_xor(mx2, m, 16);
-            const int oms = __shfl_xor(ms, m, 16);
-            dup |= (bool)__shfl_xor((int)dup, m, 16);
-            if (omx > mx) {
-                mx2 = mx > omx2 ? mx : omx2;
-                mx = omx;
-                ms = oms;
-            } else if (omx > mx2) {
-                mx2 = omx;
+        u32 g1 = m1, g2 = m2;
+#define EF_MERGE(ctrl)                                        \
+    do {                                                      \
+        const u32 o1 = EF_DPP(g1, ctrl), o2 = EF_DPP(g2, ctrl); \
+        other = min(other, EF_DPP(other, ctrl));              \
+        g2 = max(min(g1, o1), max(g2, o2));                   \
+        g1 = max(g1, o1);                                     \
+    } while (0)
+        EF_MERGE(EF_DPP_XOR1);
+        EF_MERGE(EF_DPP_XOR2);
+        EF_MERGE(EF_DPP_HALF_MIRROR);
+#undef EF_MERGE
+        if (other == 0 || khi > g1) return false;
+        // the largest entry: the largest rest of a key among those of the largest distance
+        u32 lo1 = 0;
+        int at = -1;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            if (k >= n_ld) break;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const bool in = k < n_ld - 1 || (last < np && (!ODD || last_at + h >= 2 * last));
+                const u32 lo = h ? q[k].z : q[k].x, hi = h ? q[k].w : q[k].y;
+                const bool better = in && hi == g1 && lo >= lo1;
+                lo1 = better ? lo : lo1;
+                at = better ? (k < n_ld - 1 ? 2 * gl + 16 * k : last_at) + h : at;
             }
         }
-        if (dup || kcmp >= (mx >> ignore)) return false;
-        u64 seen = 0;
-        if (gl == 0) seen = atomicCAS(list + ms, mx, key);
-        seen = __shfl(seen, 0, 16);
-        if (seen == mx) {
-            *new_max = key > mx2 ? key : mx2;
-            if (slot) *slot = ms;
+        if (g1 == g2) {      // several of that distance (empty slots, mostly)
+            u32 g = lo1;
+            g = max(g, EF_DPP(g, EF_DPP_XOR1));
+            g = max(g, EF_DPP(g, EF_DPP_XOR2));
+            g = max(g, EF_DPP(g, EF_DPP_HALF_MIRROR));
+            if (lo1 != g) at = -1;
+        }
+        u32 outcome = 0;      // 1: not below the largest, 2: in, 3: the slot has changed since it was read
+        if (at >= 0) {
+            const u64 largest = (u64)g1 << 32 | lo1;
+            if ((key >> 1) >= (largest >> 1)) outcome = 1;
+            else outcome = atomicCAS(list + at, largest, key) == largest ? 2 : 3;
+        }
+        u32 all = outcome;
+        all = max(all, EF_DPP(all, EF_DPP_XOR1));
+        all = max(all, EF_DPP(all, EF_DPP_XOR2));
+        all = max(all, EF_DPP(all, EF_DPP_HALF_MIRROR));
+        if (all == 1) return false;
+        if (all == 2) {
+            *new_max_bits = max(khi, g2);
+            *slot = at;
             return true;
         }
     }

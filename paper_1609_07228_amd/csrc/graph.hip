@@ -136,6 +136,30 @@ __device__ inline void load_pieces(float4 (&v)[8], const float *row, int c0, int
         for (int s = 0; s < 8; ++s) v[s] = make_float4(0.f, 0.f, 0.f, 0.f);
 }
 
+// The same for a row of the data of at most 128 coordinates, without a mask per lane for the sixteens that lie inside
+// the vector (the tile join, where a sixth of the instructions went into those masks; the kernels that
+// hold more in registers spill with it).
+template <bool ALIGNED>
+__device__ inline void load_row(float4 (&v)[8], const float *row, int g, int d)
+{
+    if (!ALIGNED) return load_pieces<false>(v, row, 0, g, d, true);
+    const int n_whole = d >> 4;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+        v[s] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (s < n_whole) v[s] = *reinterpret_cast<const float4 *>(row + 16 * s + 4 * g);
+        else if (s == n_whole && 16 * s + 4 * g < d) v[s] = *reinterpret_cast<const float4 *>(row + 16 * s + 4 * g);
+    }
+}
+
+// The value, by a way the compiler does not see through: what is derived from it inside a loop is not kept in
+// registers across the rest of the loop.
+__device__ inline int ef_opaque(int x)
+{
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
 // A proposal waiting in the block's LDS queue: entry `key` offered to row `target`.
 struct Proposal {
     u64 key;
@@ -212,21 +236,20 @@ __device__ inline int drain_queue(const Proposal *queue, int count, u64 *graph, 
     return updates;
 }
 
-// The same for long rows: a group of sixteen threads per
-// proposal (nthr a multiple of 16; all threads of the block call this together).
+// The same for long rows: a group of eight threads per
+// proposal (nthr a multiple of 8; all threads of the block call this together).
 // gid (or null): the mirror of the rows' ids (graph_ids_kernel), kept up to date with the insertions.
-template <bool ODD>      // (see ef_bounded_insert_g16)
-__device__ inline int drain_queue_g16(const Proposal *queue, int count, u64 *graph, u32 *worst, int K,
-                                      int tid, int nthr, int *gid = nullptr)
+template <bool ODD>      // (see ef_bounded_insert_g8)
+__device__ inline int drain_queue_g8(const Proposal *queue, int count, u64 *graph, u32 *worst, int K,
+                                     int tid, int nthr, int *gid = nullptr)
 {
     int updates = 0;
-    const int gl = tid & 15;
-    for (int e = tid >> 4; e < count; e += nthr >> 4) {
+    for (int e = tid >> 3; e < count; e += nthr >> 3) {
         const Proposal p = queue[e];
-        u64 new_max;
-        int slot = 0;
-        if (ef_bounded_insert_g16<ODD>(graph + (size_t)p.target * K, K, p.key, 1, &new_max, gl, &slot) && gl == 0) {
-            atomicMin(worst + p.target, ef_dist_bits(new_max));
+        u32 new_max_bits;
+        int slot;
+        if (ef_bounded_insert_g8<ODD>(graph + (size_t)p.target * K, K, p.key, &new_max_bits, tid & 7, &slot) && slot >= 0) {
+            atomicMin(worst + p.target, new_max_bits);
             // (a plain store: whatever order stores to a slot land in, the slot names an id that was in the row)
             if (gid) gid[(size_t)p.target * K + slot] = ef_id(p.key);
             ++updates;
@@ -2202,7 +2225,7 @@ __global__ void __launch_bounds__(512) join_kernel(const float *__restrict__ X, 
                     // ---- 4. drain (one form for rows of any length: a second one for even, aligned rows makes
                     //      degree 64 0.7 % slower and degree 100 1 % faster, 30 000 x 256 and 20 000 x 160) ----
                     updates += WIDE
-                                   ? drain_queue_g16<true>(lds.queue, lds.meta[3], graph, worst, K, tid, nthr)
+                                   ? drain_queue_g8<true>(lds.queue, lds.meta[3], graph, worst, K, tid, nthr)
                                    : drain_queue(lds.queue, lds.meta[3], graph, worst, K, tid, nthr);
                     __syncthreads();
                     if (tid == 0) lds.meta[3] = 0;
@@ -2813,10 +2836,9 @@ struct TileLds {
     u32 *bits;         // [kTileBits / 32] which hashes occur among the members' ids
     unsigned short *head, *next;      // [kTileHeads], [c16] chains of places (+ 1; 0 = end) by hash
     unsigned char *rows;              // [c16] members that want anybody
-    int *hit_id;       // [5 * EF_WAVE] ids that passed the hash bits
-    unsigned char *hit_row;     // [5 * EF_WAVE] and whose rows they are in
-    unsigned short *items;      // [2 * EF_WAVE] wants to evaluate, row << 8 | member (shares the room of hit_id)
-    float *fa, *fb;    // [kTileGroup][4][16], [4][16] the filter's terms of the rows of the A tiles and of tile B
+    int2 *hits;        // [5 * EF_WAVE] ids that passed the hash bits, and the members whose rows they are in
+    unsigned short *items;      // [2 * EF_WAVE] wants to evaluate, row << 8 | member (shares the room of hits)
+    float *terms;      // [c16 / 16][4][16] the filter's terms of the rows, tile by tile (pass 1; shares the room of hits)
     Proposal *queue;   // [kTileQueue]
 };
 constexpr int kTileQueue = 96;      // proposals that can wait
@@ -2825,8 +2847,8 @@ constexpr int kTileBits = 4096, kTileHeads = 256;
 __host__ __device__ inline size_t tile_lds_bytes(int cap)
 {
     const int c16 = (cap + 15) & ~15;
-    return (size_t)kTileQueue * sizeof(Proposal) + 5 * EF_WAVE * 5 +
-           (size_t)((kTileGroup + 1) * 64 + 2 * c16 + align4(cap * known_words(cap)) + kTileBits / 32) * 4 +
+    const size_t hits = 5 * EF_WAVE * sizeof(int2), terms = (size_t)16 * c16;
+    return (size_t)kTileQueue * sizeof(Proposal) + (hits > terms ? hits : terms) + (size_t)(2 * c16 + align4(cap * known_words(cap)) + kTileBits / 32) * 4 +
            (size_t)(kTileHeads + c16) * 2 + c16;
 }
 __device__ inline TileLds tile_lds_carve(float *smem, int cap)
@@ -2834,12 +2856,10 @@ __device__ inline TileLds tile_lds_carve(float *smem, int cap)
     TileLds l;
     const int c16 = (cap + 15) & ~15;
     l.queue = (Proposal *)smem;
-    l.hit_id = (int *)(l.queue + kTileQueue);
-    l.hit_row = (unsigned char *)(l.hit_id + 5 * EF_WAVE);
-    l.items = (unsigned short *)l.hit_id;
-    l.fa = (float *)(l.hit_row + 5 * EF_WAVE);
-    l.fb = l.fa + kTileGroup * 64;
-    l.uid = (int *)(l.fb + 64);
+    l.hits = (int2 *)(l.queue + kTileQueue);
+    l.items = (unsigned short *)l.hits;
+    l.terms = (float *)l.hits;
+    l.uid = (int *)(l.hits + max(5 * EF_WAVE, 2 * c16));
     l.thr = (u32 *)(l.uid + c16);
     l.want = l.thr + c16;
     l.bits = l.want + align4(cap * known_words(cap));
@@ -2850,7 +2870,7 @@ __device__ inline TileLds tile_lds_carve(float *smem, int cap)
 }
 
 constexpr int kTileWaves = 4;      // waves per SIMD the tile join is compiled for
-// LONG_ROWS: longer graph rows (see the launch): sixteen lanes per proposal.  QUADS: K % 4 == 0, rows of
+// LONG_ROWS: longer graph rows (see the launch): eight lanes per proposal.  QUADS: K % 4 == 0, rows of
 // ids and of entries are 16-byte aligned (compiled apart: addressing for any K cost such rows 2 %;
 // before other lengths had it, a thread scanned a row alone: 10^5 x 64, degree 81 53 -> 36 ms per build).
 template <bool LONG_ROWS, bool ALIGNED, bool QUADS>
@@ -2869,9 +2889,10 @@ join_tile_kernel(const float *__restrict__ X, int d, int K, u32 k_magic,
     // the power of two that suits the data's halves (see join_reg_kernel)
     const float scale = ef_f16_scale(*xmax);
     const int count = *work_count;
-    int updates = 0, q_fill = 0;
+    int updates = 0, q_fill = 0, w = blockIdx.x;
     auto drain = [&]() {
-        updates += LONG_ROWS ? drain_queue_g16<!QUADS>(lds.queue, q_fill, graph, worst, K, lane, EF_WAVE, gid)
+        const int lane = ef_opaque(threadIdx.x);
+        updates += LONG_ROWS ? drain_queue_g8<!QUADS>(lds.queue, q_fill, graph, worst, K, lane, EF_WAVE, gid)
                              : drain_queue(lds.queue, q_fill, graph, worst, K, lane, EF_WAVE);
         q_fill = 0;
         __syncthreads();
@@ -2880,8 +2901,8 @@ join_tile_kernel(const float *__restrict__ X, int d, int K, u32 k_magic,
     // kTileBits bits, bits 24..31 one of kTileHeads chains.
     auto hash_of = [](int id) -> u32 { return ((u32)id & 0xFFFFFFu) * 0x9E3779u; };
     static_assert(kTileBits == 1 << 12 && kTileHeads == 1 << 8, "hash bits");
-    for (int w = blockIdx.x; w < count; w += gridDim.x) {
-        const int i = work[w];
+    // passes 0 to 2 for point i: returns how many members want anybody (lds.rows, lds.want)
+    auto wants_of = [&](int i) {
         const int2 mc = ucount[i];
         const int m_new = mc.x, m = min(mc.y, cap);
         // ---- 0. ids, thresholds; the members' places by id ------------------------------------
@@ -2915,7 +2936,7 @@ join_tile_kernel(const float *__restrict__ X, int d, int K, u32 k_magic,
         const int nbr = (m_new + 15) >> 4, nbc = (m + 15) >> 4;
         auto load_tile = [&](int tile, f16x8 (&o)[4]) {
             float4 v[8];
-            load_pieces<ALIGNED>(v, X + (size_t)lds.uid[min(16 * tile + r16, m - 1)] * d, 0, g, d, true);
+            load_row<ALIGNED>(v, X + (size_t)lds.uid[min(16 * tile + r16, m - 1)] * d, g, d);
             if (scale != 1.0f) {
 #pragma unroll
                 for (int s = 0; s < 4; ++s) o[s] = ef_pack_f16<true>(v[2 * s], v[2 * s + 1], scale);
@@ -2935,12 +2956,13 @@ join_tile_kernel(const float *__restrict__ X, int d, int K, u32 k_magic,
         };
         // the filter's terms of the tile's sixteen rows: |x'|^2 (1 - margin), rounding radius, scaled
         // threshold and twice its square root (junk beyond m is masked below)
-        auto terms = [&](const f16x8 (&o)[4], int row0, float *f) {
+        auto terms = [&](const f16x8 (&o)[4], int tile) {
+            float *const f = lds.terms + 64 * tile;
             const floatx4 acc = gram(o, o);      // lane (r16, r16 >> 2) holds the diagonal
             if ((r16 >> 2) != g) return;
             const int kd = r16 & 3;
             const float dg = kd == 0 ? acc[0] : kd == 1 ? acc[1] : kd == 2 ? acc[2] : acc[3];
-            const float t = ef_scaled_threshold(lds.thr[row0 + r16], scale, thr_scale);
+            const float t = ef_scaled_threshold(lds.thr[16 * tile + r16], scale, thr_scale);
             f[r16] = dg * (1.0f - margin_rel);
             f[16 + r16] = __builtin_fmaf(u_rel, ef_sqrt_up(dg), rho0);
             f[32 + r16] = t;
@@ -2953,15 +2975,16 @@ join_tile_kernel(const float *__restrict__ X, int d, int K, u32 k_magic,
             for (int t = 0; t < kTileGroup; ++t) {
                 if (bi0 + t >= nbr) break;
                 load_tile(bi0 + t, oa[t]);
-                terms(oa[t], 16 * (bi0 + t), lds.fa + 64 * t);
+                if (bi0 == 0) terms(oa[t], t);      // (later groups have passed by as B tiles)
             }
             for (int bj = bi0; bj < nbc; ++bj) {
                 f16x8 ob[4];
                 load_tile(bj, ob);
-                terms(ob, 16 * bj, lds.fb);
+                if (bi0 == 0 && bj >= min(kTileGroup, nbr)) terms(ob, bj);
                 __syncthreads();
+                const float *const fb = lds.terms + 64 * bj;
                 const int b = 16 * bj + r16;
-                const float nfb = lds.fb[r16], rrb = lds.fb[16 + r16], tfb = lds.fb[32 + r16], sqb = lds.fb[48 + r16];
+                const float nfb = fb[r16], rrb = fb[16 + r16], tfb = fb[32 + r16], sqb = fb[48 + r16];
                 // valid pairs: a < lim
                 const int lim = b >= m ? 0 : mode == 0 ? min(m_new, b) : mode == 1 ? (b < m_new ? b : 0) : (b >= m_new ? m_new : 0);
 #pragma unroll
@@ -2969,7 +2992,7 @@ join_tile_kernel(const float *__restrict__ X, int d, int K, u32 k_magic,
                     const int bi = bi0 + t;
                     if (bi >= nbr || bi > bj) break;
                     const floatx4 acc = gram(oa[t], ob);      // the lane holds G[a = 16 bi + 4 g + k][b]
-                    const float *fa = lds.fa + 64 * t + 4 * g;
+                    const float *fa = lds.terms + 64 * bi + 4 * g;
                     const float4 nfa = *reinterpret_cast<const float4 *>(fa), rra = *reinterpret_cast<const float4 *>(fa + 16);
                     const float4 tfa = *reinterpret_cast<const float4 *>(fa + 32), sqa = *reinterpret_cast<const float4 *>(fa + 48);
                     const float nfa_k[4] = {nfa.x, nfa.y, nfa.z, nfa.w}, rra_k[4] = {rra.x, rra.y, rra.z, rra.w};
@@ -2995,9 +3018,9 @@ join_tile_kernel(const float *__restrict__ X, int d, int K, u32 k_magic,
                         *wb = (unsigned short)(bi == bj ? by_b | *wb : by_b);
                     }
                 }
-                __syncthreads();      // the terms of tile B are free again
             }
         }
+        __syncthreads();
         // the members that want anybody
         int n_rows = 0;
         for (int r0 = 0; r0 < m; r0 += EF_WAVE) {
@@ -3011,6 +3034,7 @@ join_tile_kernel(const float *__restrict__ X, int d, int K, u32 k_magic,
         }
         __syncthreads();
         // ---- 2. known pairs: the rows of ids of those members, four ids per load where rows allow it --
+        const int lane = ef_opaque(threadIdx.x);
         int n_hits = 0;
         auto settle = [&](int most) {      // until at most that many hits (fewer than 64, or none) are left: members lose their bit
             while (n_hits > most) {
@@ -3018,7 +3042,8 @@ join_tile_kernel(const float *__restrict__ X, int d, int K, u32 k_magic,
                 n_hits -= n_h;
                 __syncthreads();
                 if (lane < n_h) {
-                    const int id = lds.hit_id[n_hits + lane], row = lds.hit_row[n_hits + lane];
+                    const int2 hit = lds.hits[n_hits + lane];
+                    const int id = hit.x, row = hit.y;
                     for (int p = lds.head[hash_of(id) >> 24]; p != 0; p = lds.next[p - 1])
                         if (lds.uid[p - 1] == id) {
                             atomicAnd(&lds.want[row * kw + ((p - 1) >> 5)], ~(1u << ((p - 1) & 31)));
@@ -3031,11 +3056,7 @@ join_tile_kernel(const float *__restrict__ X, int d, int K, u32 k_magic,
         auto probe = [&](int id, int row, u32 word) {      // word: the id's word of hash bits
             const bool hit = (word >> ((hash_of(id) >> 20) & 31)) & 1u;
             const u64 mask = __ballot(hit);
-            if (hit) {
-                const int at = n_hits + lanes_below(mask);
-                lds.hit_id[at] = id;
-                lds.hit_row[at] = (unsigned char)row;
-            }
+            if (hit) lds.hits[n_hits + lanes_below(mask)] = make_int2(id, row);
             n_hits += __popcll(mask);
         };
         auto bits_of = [&](int id) { return lds.bits[hash_of(id) >> 25]; };
@@ -3060,11 +3081,11 @@ join_tile_kernel(const float *__restrict__ X, int d, int K, u32 k_magic,
 #pragma unroll
                 for (int q = 0; q < 8; ++q) {
                     if (f0 - lane + q * EF_WAVE >= total) break;
-                    const bool in = f0 + q * EF_WAVE < total;
+                    // (lanes beyond the end have the last load again: its hits are settled twice, to the same effect)
                     const int id4[4] = {four[q].x, four[q].y, four[q].z, four[q].w};
                     u32 word[4];
 #pragma unroll
-                    for (int t = 0; t < 4; ++t) word[t] = in ? bits_of(id4[t]) : 0u;
+                    for (int t = 0; t < 4; ++t) word[t] = bits_of(id4[t]);
 #pragma unroll
                     for (int t = 0; t < 4; ++t) probe(id4[t], rr[q], word[t]);
                     settle(EF_WAVE - 1);
@@ -3074,11 +3095,19 @@ join_tile_kernel(const float *__restrict__ X, int d, int K, u32 k_magic,
             for (int f0 = lane; f0 - lane < n_rows * K; f0 += EF_WAVE) {
                 const int f = min(f0, n_rows * K - 1), at = K == 1 ? f : (int)(((u64)(u32)f * k_magic) >> 32), row = lds.rows[at];
                 const int id = gid[(size_t)lds.uid[row] * K + (f - at * K)];
-                probe(id, row, f0 < n_rows * K ? bits_of(id) : 0u);
+                probe(id, row, bits_of(id));
                 settle(EF_WAVE - 1);
             }
         }
         settle(0);
+        return n_rows;
+    };
+    // (one place that drains the queue: a copy of the insertion per place cost registers in all of the kernel)
+    for (bool end = false; !end;) {
+        end = w >= count;      // (one turn more: what is left in the queue)
+        const int n_rows = end ? 0 : wants_of(work[w]);
+        w += gridDim.x;
+        const int lane = ef_opaque(threadIdx.x), r16 = lane & 15, g = lane >> 4;
         // ---- 3. what is left: sixteen wants per round, four lanes each -----------------------------
         int n_items = 0;
         auto round = [&](int first, int n_r) {      // wants first .. first + n_r - 1 (at most sixteen)
@@ -3087,8 +3116,8 @@ join_tile_kernel(const float *__restrict__ X, int d, int K, u32 k_magic,
             const int a = ent >> 8, b = ent & 255;
             const int ia = lds.uid[a], ib = lds.uid[b];
             float4 va[8], vb[8];
-            load_pieces<ALIGNED>(va, X + (size_t)ia * d, 0, g, d, true);
-            load_pieces<ALIGNED>(vb, X + (size_t)ib * d, 0, g, d, true);
+            load_row<ALIGNED>(va, X + (size_t)ia * d, g, d);
+            load_row<ALIGNED>(vb, X + (size_t)ib * d, g, d);
             float p[4] = {0.f, 0.f, 0.f, 0.f};
             accumulate_pair(va, vb, (d + 15) >> 4, p);
             // partial sum l lives in lane g = l / 4, slot l % 4 (see join_reg_kernel)
@@ -3106,7 +3135,6 @@ join_tile_kernel(const float *__restrict__ X, int d, int K, u32 k_magic,
             }
             q_fill += __popcll(mask);
             __syncthreads();
-            if (q_fill + 16 > kTileQueue) drain();      // a round adds at most one proposal per want
         };
         bool more = true;
         for (int f0 = 0; more; f0 += EF_WAVE) {
@@ -3127,17 +3155,17 @@ join_tile_kernel(const float *__restrict__ X, int d, int K, u32 k_magic,
                 n_items += __popcll(mask);
                 __syncthreads();
                 const int keep = more || mask ? EF_WAVE - 1 : 0;
-                while (n_items > keep) {
+                for (;;) {
+                    if (q_fill > (end ? 0 : kTileQueue - 16)) drain();      // (a round adds at most one proposal per want)
+                    if (n_items <= keep) break;
                     const int n_r = min(n_items, 16);
                     n_items -= n_r;
                     round(n_items, n_r);
                 }
             }
         }
-        if (q_fill >= kTileQueue / 2) drain();
         __syncthreads();
     }
-    drain();
     updates = ef_wave_sum_i32(updates);
     if (lane == 0) upd_block[blockIdx.x] += updates;      // (zeroed once per iteration; passes add up)
 }
