@@ -104,12 +104,12 @@ __device__ inline float4 load_unaligned4(const float *p)
 // 10.5 -> 5.6 ms; 100 000 x 187, degree 10: 9.8 -> 3.5; 50 000 x 957: 55 -> 4.6; 50 000 x 77, degree 60:
 // 27 -> 15.4.)
 // ok: this lane has a row (`row` names a vector of the data either way: no branch around the loads)
-template <bool ALIGNED>
-__device__ inline void load_pieces(float4 (&v)[8], const float *row, int c0, int g, int d, bool ok)
+template <bool ALIGNED, int N>
+__device__ inline void load_pieces(float4 (&v)[N], const float *row, int c0, int g, int d, bool ok)
 {
     if (ALIGNED) {
 #pragma unroll
-        for (int s = 0; s < 8; ++s) {
+        for (int s = 0; s < N; ++s) {
             const int j = c0 + 16 * s + 4 * g;
             v[s] = ok && j + 3 < d ? *reinterpret_cast<const float4 *>(row + j) : make_float4(0.f, 0.f, 0.f, 0.f);
         }
@@ -118,8 +118,8 @@ __device__ inline void load_pieces(float4 (&v)[8], const float *row, int c0, int
     const int n_whole = (d - c0) >> 4;      // sixteens that lie inside (uniform)
     const float *p = row + c0 + 4 * g;
 #pragma unroll
-    for (int s = 0; s < 8; ++s) v[s] = s < n_whole ? load_unaligned4(p + 16 * s) : make_float4(0.f, 0.f, 0.f, 0.f);
-    if (n_whole < 8 && ((d - c0) & 15)) {
+    for (int s = 0; s < N; ++s) v[s] = s < n_whole ? load_unaligned4(p + 16 * s) : make_float4(0.f, 0.f, 0.f, 0.f);
+    if (n_whole < N && ((d - c0) & 15)) {
         const int j = c0 + 16 * n_whole + 4 * g, jb = min(j, d - 4), over = j - jb;
         const float4 w = load_unaligned4(row + jb);
         float4 t;
@@ -128,12 +128,12 @@ __device__ inline void load_pieces(float4 (&v)[8], const float *row, int c0, int
         t.z = over == 0 ? w.z : over == 1 ? w.w : 0.f;
         t.w = over == 0 ? w.w : 0.f;
 #pragma unroll
-        for (int s = 0; s < 8; ++s)
+        for (int s = 0; s < N; ++s)
             if (s == n_whole) v[s] = t;
     }
     if (!ok)
 #pragma unroll
-        for (int s = 0; s < 8; ++s) v[s] = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int s = 0; s < N; ++s) v[s] = make_float4(0.f, 0.f, 0.f, 0.f);
 }
 
 // The same for a row of the data of at most 128 coordinates, without a mask per lane for the sixteens that lie inside
@@ -396,13 +396,14 @@ init_tree_kernel(const float *__restrict__ X, int d, int stride, u32 q4_magic, i
 // number of old entries below it (binary search, which also finds it if it is already in
 // the row) plus the number of candidates below it; an old entry's rank is its index plus
 // the number of candidates below it.  Ranks below K are stored straight to the row.
+#define EF_ROW_BCAST(x, a) __builtin_amdgcn_update_dpp(0, (x), 0x150 | (a), 0xF, 0xF, false)      // lane a of each sixteen to all of them
 #define EF_ROW_ROR(x, t) __builtin_amdgcn_update_dpp(0, (x), 0x120 | (t), 0xF, 0xF, false)
 
-template <int T>
-__device__ inline void init_round(const float4 (&va)[8], int n_pieces, float (&p)[4])
+template <int T, int N>
+__device__ inline void init_round(const float4 (&va)[N], int n_pieces, float (&p)[4])
 {
 #pragma unroll
-    for (int s = 0; s < 8; ++s) {
+    for (int s = 0; s < N; ++s) {
         if (s >= n_pieces) break;
         const float d0 = va[s].x - __int_as_float(EF_ROW_ROR(__float_as_int(va[s].x), T));
         const float d1 = va[s].y - __int_as_float(EF_ROW_ROR(__float_as_int(va[s].y), T));
@@ -430,6 +431,24 @@ __device__ inline void cross_round(const float4 (&va)[8], const float4 (&vb)[8],
             w.w = __int_as_float(EF_ROW_ROR(__float_as_int(vb[s].w), T ? T : 1));
         }
         const float d0 = va[s].x - w.x, d1 = va[s].y - w.y, d2 = va[s].z - w.z, d3 = va[s].w - w.w;
+        p[0] = __builtin_fmaf(d0, d0, p[0]);
+        p[1] = __builtin_fmaf(d1, d1, p[1]);
+        p[2] = __builtin_fmaf(d2, d2, p[2]);
+        p[3] = __builtin_fmaf(d3, d3, p[3]);
+    }
+}
+
+// row A of the first set against every row of the second
+template <int A, int N>
+__device__ inline void broadcast_round(const float4 (&va)[N], const float4 (&vb)[N], int n_pieces, float (&p)[4])
+{
+#pragma unroll
+    for (int s = 0; s < N; ++s) {
+        if (s >= n_pieces) break;
+        const float d0 = vb[s].x - __int_as_float(EF_ROW_BCAST(__float_as_int(va[s].x), A));
+        const float d1 = vb[s].y - __int_as_float(EF_ROW_BCAST(__float_as_int(va[s].y), A));
+        const float d2 = vb[s].z - __int_as_float(EF_ROW_BCAST(__float_as_int(va[s].z), A));
+        const float d3 = vb[s].w - __int_as_float(EF_ROW_BCAST(__float_as_int(va[s].w), A));
         p[0] = __builtin_fmaf(d0, d0, p[0]);
         p[1] = __builtin_fmaf(d1, d1, p[1]);
         p[2] = __builtin_fmaf(d2, d2, p[2]);
@@ -2395,6 +2414,13 @@ __device__ constexpr int kSurvBase[3] = {0, 120, 376};
 constexpr int kFewPairs = 4;
 // d <= 128: more survivors than this inside one set of sixteen rows and all its pairs are evaluated by row rotations
 constexpr int kDenseSurvivors = 24;
+// d > 128: up to this many new members, or rows of the second set of sixteen, are broadcast to the others; the
+// registers set the limits.  Rotations meet all pairs whatever the join asks for, 512 vector instructions per
+// 8 KB of rows, 2048 per 16 KB of 17..32 rows, which also had to be streamed twice: the vector ALU was busy for
+// 71 to 90 % of the joins' time.  10^6 x 960, iterations 1 to 6: 13.0 14.3 12.7 10.5 7.1 3.9 -> 11.0 12.6 10.3 7.6 4.7 2.6 ms,
+// from the fourth on 5.6 to 5.8 TB/s; build 78.0 -> 64.3.  (For d <= 128 the same next to the filter's code spilled
+// and cost a quarter.)
+constexpr int kFewNew = 8, kFewRest = 8;
 
 // One surviving pair (rows a, b of the point's list) per lane with `mine` set: its distance is
 // offered to row a and to row b where it passes their thresholds.  All lanes of the wave call
@@ -2435,7 +2461,7 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
     const int mark = mode != 2;
     const int K = KT ? KT : K_;
     constexpr int R = 16 * NB;                    // rows
-    constexpr int S_CAP = R * (R - 1) / 2 + 8;    // every pair may survive
+    constexpr int S_CAP = ONE ? R * (R - 1) / 2 + 8 : 0;    // every pair may survive
     extern __shared__ __align__(16) float smem[];
     int *uid = (int *)smem;                       // [R]
     u32 *thr = (u32 *)(uid + R);                  // [R] threshold bits (exact test)
@@ -2507,8 +2533,112 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
         // filter.  At most 16 rows: one pass, eight rotations.  17..32 rows: a first pass for the
         // pairs inside rows 0..15 and inside rows 16..31, a second one for rows 0..15 against
         // rotations 0..15 of rows 16..31.
+        // Few new members (late iterations): each of them is broadcast to the sixteen lanes of a row set (a
+        // modifier on the subtract again) and meets all the others, 64 vector instructions per new member, row
+        // set and 128 coordinates; all rows are read once.  17..32 rows with few in the second set: rotations for
+        // the pairs of the first set, and the rows of the second are broadcast; again one pass.
         constexpr bool rotated = !ONE;
+        const bool few = rotated && m_new <= kFewNew, few_rest = rotated && NB > 1 && m <= 16 + kFewRest;
         float two[2] = {0.f, 0.f}, two_b[2] = {0.f, 0.f};
+        // may_drain: only where a join can propose more than the queue holds (see reg_q_cap_for; every
+        // place that drains is a copy of the insertion, in code and in registers)
+        auto offer = [&](auto may_drain, bool mine, float dist, int a, int b) {
+            if (decltype(may_drain)::value && q_fill + 2 * EF_WAVE > q_cap) {      // a step adds at most two proposals per lane
+                updates += drain_mid(queue, q_fill);
+                q_fill = 0;
+                __syncthreads();
+            }
+            q_fill = propose_pair(queue, q_fill, mine, dist, a, b, thr, uid, mark);
+            __syncthreads();
+        };
+        // the pairs inside rows 0..15 from rotations: lane (r, g) has the distances 2g+1 and 2g+2 places on
+        auto offer_rotations = [&](auto may_drain) {
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const int rot = 2 * g + 1 + t, b = (r16 + dirn * rot) & 15;
+                // rotation 8 meets every pair from both ends: the lower row keeps it
+                offer(may_drain, (rot != 8 || r16 < b) && r16 < m && b < m && min(r16, b) < m_new && mode_ok(max(r16, b)), two[t], r16, b);
+            }
+        };
+#define EF_EACH_FEW(X) X(0) X(1) X(2) X(3) X(4) X(5) X(6) X(7)
+        if (few) {
+            float P[kFewNew][4], PB[NB > 1 ? kFewNew : 1][4];
+#pragma unroll
+            for (int t = 0; t < kFewNew; ++t) {
+                P[t][0] = P[t][1] = P[t][2] = P[t][3] = 0.0f;
+                if (NB > 1) PB[NB > 1 ? t : 0][0] = PB[NB > 1 ? t : 0][1] = PB[NB > 1 ? t : 0][2] = PB[NB > 1 ? t : 0][3] = 0.0f;
+            }
+            for (int c0 = 0; c0 < d; c0 += 128) {
+                const int n_pieces = min(8, (d - c0 + 15) >> 4);
+                load_pieces<ALIGNED>(va, pa, c0, g, d, true);
+                float4 (&wb)[8] = reinterpret_cast<float4 (&)[8]>(NB > 1 ? *vb : *va);
+                if (NB > 1) load_pieces<ALIGNED>(wb, pb, c0, g, d, true);
+#define EF_BROADCAST(A)                                                                    \
+    if (A < m_new) {                                                                       \
+        broadcast_round<A>(va, va, n_pieces, P[A]);                                        \
+        if (NB > 1) broadcast_round<A>(va, wb, n_pieces, PB[NB > 1 ? A : 0]);              \
+    }
+                EF_EACH_FEW(EF_BROADCAST)
+#undef EF_BROADCAST
+            }
+            __syncthreads();      // uid, thr visible
+            t_pre = u_pre >= 0 ? worst[u_pre] : 0u;      // the next point's; its ids have arrived by now
+#pragma unroll
+            for (int a0 = 0; a0 < kFewNew; a0 += 4) {
+                if (a0 >= m_new) break;
+#pragma unroll
+                for (int set = 0; set < NB; ++set) {
+                    const float (&Q)[4][4] = reinterpret_cast<const float (&)[4][4]>(set == 0 ? P[a0] : PB[NB > 1 ? a0 : 0]);
+                    const float dist = reduce_rotations4(Q, g);      // row a0 + g to row 16 set + r16
+                    const int a = a0 + g, b = 16 * set + r16;
+                    offer(std::false_type{}, a < m_new && a < b && b < m && mode_ok(b), dist, a, b);
+                }
+            }
+        } else if (few_rest) {
+            float P[8][4], PX[kFewNew][4], PB[kFewNew][4];
+#pragma unroll
+            for (int t = 0; t < kFewNew; ++t) {
+                P[t][0] = P[t][1] = P[t][2] = P[t][3] = 0.0f;
+                PX[t][0] = PX[t][1] = PX[t][2] = PX[t][3] = 0.0f;
+                PB[t][0] = PB[t][1] = PB[t][2] = PB[t][3] = 0.0f;
+            }
+            for (int c0 = 0; c0 < d; c0 += 64) {      // (the registers hold half a stretch next to that many sums)
+                const int n_pieces = min(4, (d - c0 + 15) >> 4);
+                float4 ha[4], hb[4];
+                load_pieces<ALIGNED>(ha, pa, c0, g, d, true);
+                load_pieces<ALIGNED>(hb, pb, c0, g, d, true);
+                init_round<1>(ha, n_pieces, P[0]);
+                init_round<2>(ha, n_pieces, P[1]);
+                init_round<3>(ha, n_pieces, P[2]);
+                init_round<4>(ha, n_pieces, P[3]);
+                init_round<5>(ha, n_pieces, P[4]);
+                init_round<6>(ha, n_pieces, P[5]);
+                init_round<7>(ha, n_pieces, P[6]);
+                init_round<8>(ha, n_pieces, P[7]);
+#define EF_BROADCAST(B)                                                                    \
+    if (B < kFewRest && 16 + B < m) {                                                      \
+        broadcast_round<B>(hb, ha, n_pieces, PX[B]);                                       \
+        if (need11) broadcast_round<B>(hb, hb, n_pieces, PB[B]);                           \
+    }
+                EF_EACH_FEW(EF_BROADCAST)
+#undef EF_BROADCAST
+            }
+            reduce_rotations(P, g, two);
+            __syncthreads();      // uid, thr visible
+            t_pre = u_pre >= 0 ? worst[u_pre] : 0u;
+            offer_rotations(std::false_type{});
+#pragma unroll
+            for (int t0 = 0; t0 < kFewNew; t0 += 4) {
+                if (16 + t0 >= m) break;
+                const int x = 16 + t0 + g, y = 16 + r16;      // the broadcast row; the lane's row of the second set
+                const float dist = reduce_rotations4(reinterpret_cast<const float (&)[4][4]>(PX[t0]), g);
+                offer(std::false_type{}, x < m && r16 < m_new && mode_ok(x), dist, r16, x);
+                if (need11) {
+                    const float dist_b = reduce_rotations4(reinterpret_cast<const float (&)[4][4]>(PB[t0]), g);
+                    offer(std::false_type{}, x < m_new && x < y && y < m && mode_ok(y), dist_b, x, y);
+                }
+            }
+        } else {
         if (rotated) {
             float P[8][4], PB[NB > 1 ? 8 : 1][4];
 #pragma unroll
@@ -2633,30 +2763,14 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
         }
         __syncthreads();
         if (rotated) {
-            auto room = [&]() {      // a step adds at most two proposals per lane
-                if (q_fill + 2 * EF_WAVE > q_cap) {
-                    updates += drain_mid(queue, q_fill);
-                    q_fill = 0;
-                    __syncthreads();
-                }
-            };
+            offer_rotations(std::bool_constant<(NB > 1)>{});
+            if (NB > 1 && need11) {
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                const int rot = 2 * g + 1 + t, b = (r16 + dirn * rot) & 15;
-                // rotation 8 meets every pair from both ends: the lower row keeps it
-                const bool once = rot != 8 || r16 < b;
-                room();
-                q_fill = propose_pair(queue, q_fill,
-                                      once && r16 < m && b < m && min(r16, b) < m_new && mode_ok(max(r16, b)), two[t],
-                                      r16, b, thr, uid, mark);
-                __syncthreads();
-                if (NB > 1 && need11) {
-                    room();
-                    q_fill = propose_pair(queue, q_fill,
-                                          once && 16 + r16 < m && 16 + b < m && 16 + min(r16, b) < m_new &&
-                                              mode_ok(16 + max(r16, b)),
-                                          two_b[t], 16 + r16, 16 + b, thr, uid, mark);
-                    __syncthreads();
+                for (int t = 0; t < 2; ++t) {
+                    const int rot = 2 * g + 1 + t, b = (r16 + dirn * rot) & 15;
+                    offer(std::true_type{}, (rot != 8 || r16 < b) && 16 + r16 < m && 16 + b < m && 16 + min(r16, b) < m_new &&
+                              mode_ok(16 + max(r16, b)),
+                          two_b[t], 16 + r16, 16 + b);
                 }
             }
             if (NB > 1) {
@@ -2695,10 +2809,7 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
 #pragma unroll
                     for (int t = 0; t < 2; ++t) {
                         const int rot = 8 * h + 2 * g + t, b = 16 + ((r16 + dirn * rot) & 15);
-                        room();
-                        q_fill = propose_pair(queue, q_fill, b < m && r16 < m_new && mode_ok(b), cross[t], r16, b, thr,
-                                              uid, mark);
-                        __syncthreads();
+                        offer(std::true_type{}, b < m && r16 < m_new && mode_ok(b), cross[t], r16, b);
                     }
                 }
             }
@@ -2795,7 +2906,8 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
                 }
             }
         }
-        if (q_fill >= q_cap / 2) {
+        }      // few
+        if (q_fill >= (ONE ? q_cap / 2 : EF_WAVE)) {
             // whole passes of 64 only, from the end of the queue: what is left waits for the next
             // drain (a pass costs its two round trips however few lanes it fills)
             const int rest = q_fill & (EF_WAVE - 1);
@@ -3691,12 +3803,15 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
     if (!tiles && max_rows > rows1 && large_lds > kLdsLimit) return EFANNA_EUNSUPPORTED;
     if (!aligned && shape_for(max_rows).lds > kLdsLimit) return EFANNA_EUNSUPPORTED;      // (the documented limit of unaligned rows)
     // joins of at most 16 vectors from registers (d <= 128): room for a whole point's proposals
-    // (240) above the drain mark; the others drain between rounds as well (joins of 17..32
-    // vectors: 256 entries measured 3 % faster than 128, 512 no better)
-    auto reg_q_cap_for = [&](int R) { return R == 16 ? (d <= 128 ? 512 : 256) : (d <= 128 ? 256 : 384); };
+    // (240) above the drain mark; joins of 17..32 drain between rounds as well (256 entries measured 3 % faster
+    // than 128, 512 no better).  Long vectors: room on top of a pass for the 240 proposals of 16 vectors, and for
+    // the 552 of 24 vectors or the 440 of eight new members and 24 others; only the rest drains in between.
+    auto reg_q_cap_for = [&](int R) { return R == 16 ? (d <= 128 ? 512 : 320) : (d <= 128 ? 256 : 640); };
+    static_assert(EF_WAVE + (16 + kFewRest) * (15 + kFewRest) <= 640 && EF_WAVE + kFewNew * (kFewNew - 1 + 2 * (32 - kFewNew)) <= 640 &&
+                  EF_WAVE + 16 * 15 <= 320, "queue");
     auto reg_lds = [&](int R) {
         const int reg_q_cap = reg_q_cap_for(R);
-        return (size_t)(6 * R + align4(R * (R - 1) / 2 + 8)) * 4 +
+        return (size_t)(6 * R + (d <= 128 ? align4(R * (R - 1) / 2 + 8) : 0)) * 4 +
                (size_t)reg_q_cap * sizeof(Proposal);
     };
     // prepare: one thread per point with max_rows ids of LDS each

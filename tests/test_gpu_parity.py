@@ -508,6 +508,23 @@ def test_nndescent_tile_join_edges(ef, n, d, K, L):
         graph_equal(ef, graph, want)
 
 
+@pytest.mark.parametrize("d", [129, 132, 191, 256, 260])      # pieces of one coordinate, of four, ...; rows unaligned for odd d
+@pytest.mark.parametrize("K,L", [(10, 2), (10, 10), (16, 8), (7, 12)])      # few new members; second sets of up to 8 and of more rows
+def test_nndescent_long_vectors_few_and_many_new(ef, d, K, L):
+    """Joins of at most 32 long vectors: new members broadcast, rows of the second set broadcast, rotations; both markings."""
+    rng = np.random.default_rng(d + K)
+    X = rng.standard_normal((500, d)).astype(np.float32)
+    Xd = dev(X)
+    (perm, off, nl), (operm, ooff, onl) = trees_equal(ef, X, 2, 12, 11)
+    start = oracle.init_graph(X, operm, ooff, onl, K)
+    for cross in (False, True):
+        graph, want = ef.efanna_init_graph(Xd, perm, off, nl, 12, K), start
+        for it in range(4):
+            ef.efanna_nndescent(Xd, graph, 1, L, 11, first_iter=it, cross_old=cross)
+            want = oracle.nndescent(X, *want[:3], 1, L, 11, iter0=it, cross_old=cross)
+            graph_equal(ef, graph, want)
+
+
 @pytest.mark.parametrize("d,shift", [
     (4, 1), (5, 0), (7, 0), (17, 0), (50, 0), (61, 0), (126, 0), (127, 0),      # one stretch of 128 coordinates
     (129, 0), (131, 0), (255, 0), (300, 1),                                    # more than one
