@@ -34,18 +34,15 @@ __host__ __device__ inline int align4(int x) { return (x + 3) & ~3; }
 // number of overflow queues of the reverse lists, and ints between their counters
 constexpr int kOvfQueues = 256, kOvfCounterPitch = 16;
 
-// per-iteration reset: reverse-list fill counts and bounds, work-list sizes, insertion
-// counts of the join blocks.  The lists themselves need no reset: the first L arrivals
+// per-iteration reset of the counter scheme: reverse-list fill counts and bounds, work-list sizes.
+// The lists themselves need no reset: the first L arrivals
 // overwrite slots 0..L-1 in some order, readers stop at min(count, L), and the bounded
 // insertion only ever touches lists that are full.
-__global__ void fill_reverse_kernel(int *a_count, int *b_count, u64 *list_max, size_t n,
-                                    int *work_count, int *upd_block, int n_upd_block, int *ovf_count)
+__global__ void fill_reverse_kernel(int *a_count, int *b_count, u64 *list_max, size_t n, int *work_count, int *ovf_count)
 {
     size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < kMaxClasses) work_count[i] = 0;     // the work lists
     for (size_t j = i; j < (size_t)kOvfQueues * kOvfCounterPitch; j += (size_t)gridDim.x * blockDim.x) ovf_count[j] = 0;
-    // insertion counts of join blocks: kernels that are not launched leave theirs at zero
-    for (size_t j = i; j < (size_t)n_upd_block; j += (size_t)gridDim.x * blockDim.x) upd_block[j] = 0;
     if (i < n) {
         a_count[i] = 0;
         b_count[i] = 0;
@@ -1728,7 +1725,7 @@ template <int SHIFT, int LT, int RB>
 __global__ void __launch_bounds__(kBktThreads)
 bucket_lists_kernel(const u32 *__restrict__ offer_runs, const u32 *__restrict__ table, int n_blocks,
                     int run_cap, u64 stream_key, int n, int L_, int shift, u32 *__restrict__ lists,
-                    int *__restrict__ counts)
+                    int *__restrict__ counts, const int *__restrict__ nw_c, u32 *__restrict__ active, int *work_count)
 {
     const int L = LT ? LT : L_;
     extern __shared__ __align__(16) u64 list_sm[];
@@ -1791,11 +1788,18 @@ bucket_lists_kernel(const u32 *__restrict__ offer_runs, const u32 *__restrict__ 
     __syncthreads();
     // only the sources are wanted from here on (the keys decided who is in the list)
     for (int f = t; f < rows_here * L; f += n_thr) lists[(size_t)first * L + f] = (u32)ll[f];
+    int c = 0;
     if (t < rows_here) {
-        int c = 0;
         for (int a = 0; a < L; ++a) c += ll[t * L + a] != ~0ULL ? 1 : 0;
         counts[first + t] = c;
     }
+    if (!active) return;
+    // The reverse-new lists are complete: who joins anything in this iteration (see active_kernel; 32 points a
+    // word, so that the smallest ranges of targets own whole words), and the work lists are empty again.
+    const u64 mask = __ballot(t < rows_here && (c > 0 || nw_c[first + t] > 0));
+    const int t0 = t & ~(EF_WAVE - 1), half = ef_lane();
+    if (half < 2 && t0 + 32 * half < rows_here) active[(first + t0) / 32 + half] = (u32)(mask >> (32 * half));
+    if (blockIdx.x == 0 && t < kMaxClasses) work_count[t] = 0;
 }
 
 // Work lists by the number of vectors a join gathers: list c takes the joins of at most
@@ -2259,7 +2263,7 @@ __global__ void __launch_bounds__(512) join_kernel(const float *__restrict__ X, 
         if (tid == 0) block_updates += lds.meta[2];
         __syncthreads();
     }
-    if (tid == 0) upd_block[blockIdx.x] += block_updates;      // (zeroed once per iteration; passes add up)
+    if (tid == 0) upd_block[blockIdx.x] = block_updates + (mode == 2 ? upd_block[blockIdx.x] : 0);      // (mode 2 follows mode 1)
 }
 
 // ---------------------------------------------------------------------------------------
@@ -2919,7 +2923,7 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
     __syncthreads();
     updates += drain(queue, q_fill);
     updates = ef_wave_sum_i32(updates);
-    if (lane == 0) upd_block[blockIdx.x] += updates;      // (zeroed once per iteration; passes add up)
+    if (lane == 0) upd_block[blockIdx.x] = updates + (mode == 2 ? upd_block[blockIdx.x] : 0);      // (mode 2 follows mode 1)
 }
 
 // ---------------------------------------------------------------------------------------
@@ -3279,7 +3283,7 @@ join_tile_kernel(const float *__restrict__ X, int d, int K, u32 k_magic,
         __syncthreads();
     }
     updates = ef_wave_sum_i32(updates);
-    if (lane == 0) upd_block[blockIdx.x] += updates;      // (zeroed once per iteration; passes add up)
+    if (lane == 0) upd_block[blockIdx.x] = updates + (mode == 2 ? upd_block[blockIdx.x] : 0);      // (mode 2 follows mode 1)
 }
 
 // The ids of all graph entries (-1 for an empty slot), written once per iteration after the
@@ -3340,26 +3344,30 @@ xmax_kernel(const float *__restrict__ X, size_t total, u32 *xmax)
 // per-iteration counters from the per-block partial sums: part[b] = (pairs evaluated, vectors
 // gathered, vectors gathered by the smallest join class) of prepare block b; upd_block: insertions
 // per join block
-__global__ void stats_kernel(const long long *__restrict__ part, int n_part,
-                             const int *__restrict__ upd_block, int n_upd_block, u64 *stats)
+// (64 blocks of 1024 threads: with 16 of 256 a thread had thirty loads one after the other, 12 us for 10^6 points)
+constexpr int kStatsThreads = 1024;
+__global__ void __launch_bounds__(kStatsThreads)
+stats_kernel(const long long *__restrict__ part, int n_part, const int *__restrict__ upd_block, int n_upd_block, u64 *stats)
 {
-    long long ev = 0, up = 0, rw = 0, r0 = 0;
-    const int t = blockIdx.x * blockDim.x + threadIdx.x, nt = gridDim.x * blockDim.x;
+    long long sum[4] = {0, 0, 0, 0};      // pairs, insertions, vectors, vectors of the smallest class
+    const int t = blockIdx.x * kStatsThreads + threadIdx.x, nt = gridDim.x * kStatsThreads;
     for (int b = t; b < n_part; b += nt) {
-        ev += part[(size_t)b * 3];
-        rw += part[(size_t)b * 3 + 1];
-        r0 += part[(size_t)b * 3 + 2];
+        sum[0] += part[(size_t)b * 3];
+        sum[2] += part[(size_t)b * 3 + 1];
+        sum[3] += part[(size_t)b * 3 + 2];
     }
-    for (int b = t; b < n_upd_block; b += nt) up += upd_block[b];
-    ev = ef_wave_sum_i64(ev);
-    up = ef_wave_sum_i64(up);
-    rw = ef_wave_sum_i64(rw);
-    r0 = ef_wave_sum_i64(r0);
-    if (ef_lane() == 0) {
-        atomicAdd(stats, (u64)ev);
-        atomicAdd(stats + 1, (u64)up);
-        atomicAdd(stats + 2, (u64)rw);
-        atomicAdd(stats + 3, (u64)r0);
+    for (int b = t; b < n_upd_block; b += nt) sum[1] += upd_block[b];
+    __shared__ long long wave_sum[4][kStatsThreads / EF_WAVE];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        sum[q] = ef_wave_sum_i64(sum[q]);
+        if (ef_lane() == 0) wave_sum[q][threadIdx.x / EF_WAVE] = sum[q];
+    }
+    __syncthreads();
+    if (threadIdx.x < 4) {
+        long long all = 0;
+        for (int v = 0; v < kStatsThreads / EF_WAVE; ++v) all += wave_sum[threadIdx.x][v];
+        atomicAdd(stats + threadIdx.x, (u64)all);
     }
 }
 
@@ -3755,8 +3763,9 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
     const int rows1 = reg_ok ? 32 : 0;
     const JoinClasses jc = join_classes(max_rows, reg_ok);
     // (a work list has n entries at most: of few points more blocks would only start and end)
-    const int reg_grid = n < kRegGrid ? (int)n : kRegGrid;
-    const int n_upd_block = 2 * reg_grid + (jc.n - 2) * kMaxLargeGrid;
+    // (up to 2^17 points half the blocks: late iterations have little for them; 10^5 x 128, degree 20 4.93 -> 4.89 ms,
+    // but 10^6 x 960 63.7 -> 64.2)
+    const int reg_grid = n > (1 << 17) ? kRegGrid : (int)min(n, (int64_t)kRegGrid / 2);
     struct Shape {
         int cap_rows, threads, s_cap, q_cap, grid;
         size_t lds;
@@ -3862,7 +3871,7 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
     // (list lengths of 10 and 20 are compiled in: the scan of a list unrolls, 8 % off the kernel)
     typedef void (*SampleKernel)(u64 *, int, int, int, int *, int *, int *, int *, u32 *, int, int, u32 *, u32 *);
     typedef void (*ReverseOldKernel)(const int *, int, int, const u64 *, int, int, u32 *, u32 *);
-    typedef void (*ListsKernel)(const u32 *, const u32 *, int, int, u64, int, int, int, u32 *, int *);
+    typedef void (*ListsKernel)(const u32 *, const u32 *, int, int, u64, int, int, int, u32 *, int *, const int *, u32 *, int *);
     const SampleKernel bkt_sample = bkt_small ? (K <= 16 ? sample_bucket_kernel<2, 8> : sample_bucket_kernel<4, 8>)
                                               : (K <= 16 ? sample_bucket_kernel<2, 10> : sample_bucket_kernel<4, 10>);
     const ReverseOldKernel bkt_old = bkt_small ? reverse_old_bucket_kernel<8> : reverse_old_bucket_kernel<10>;
@@ -3909,10 +3918,10 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
     for (int it = 0; it < iters; ++it) {
         const int g = first_iter + it;
         if (ev) EF_HIP_CHECK(hipEventRecord(ev[5 * it], st));
-        // (the bucket scheme writes every list count itself: only the small arrays are reset)
-        fill_reverse_kernel<<<grid_for(bkt ? (size_t)n_upd_block : (size_t)n, kBlock), kBlock, 0, st>>>(
-            w.rnew_c, w.rold_c, w.list_max, bkt ? (size_t)0 : (size_t)n, w.work_count, w.upd_block,
-            n_upd_block, w.ovf_count);
+        // (the bucket scheme writes every list count itself and empties the work lists on the way)
+        if (!bkt)
+            fill_reverse_kernel<<<grid_for((size_t)n, kBlock), kBlock, 0, st>>>(w.rnew_c, w.rold_c, w.list_max, (size_t)n,
+                                                                                w.work_count, w.ovf_count);
         {
             const u64 kn = ef_stream_key(seed, 2 * g), ko = ef_stream_key(seed, 2 * g + 1);
             Overflow *ovf = (Overflow *)w.overflow;
@@ -3928,17 +3937,19 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
                 bkt_sample<<<bs.blocks, bkt_rows, bkt_lds(L), st>>>(graph, (int)n, K, L, w.nw, w.od, w.nw_c, w.od_c, w.worst,
                                                                    bs.buckets, bs.shift, w.offer_runs, w.run_table);
                 bkt_lists<<<bs.buckets, bs.threads, lists_lds, st>>>(w.offer_runs, w.run_table, bs.blocks, bkt_rows * L, kn,
-                                                                    (int)n, L, bs.shift, (u32 *)w.rnew, w.rnew_c);
+                                                                    (int)n, L, bs.shift, (u32 *)w.rnew, w.rnew_c, w.nw_c,
+                                                                    (u32 *)w.active, w.work_count);
             } else if (K <= 16) EF_SAMPLE(16, 1);
             else if (K <= 32) EF_SAMPLE(32, 1);
             else if (K <= 64) EF_SAMPLE(64, 1);
             else EF_SAMPLE(64, 2);
-            active_kernel<<<grid_for((size_t)n, kBlock), kBlock, 0, st>>>(w.nw_c, w.rnew_c, (int)n, w.active);
+            if (!bkt) active_kernel<<<grid_for((size_t)n, kBlock), kBlock, 0, st>>>(w.nw_c, w.rnew_c, (int)n, w.active);
             if (bkt) {
                 bkt_old<<<bs.blocks, bkt_rows, bkt_lds(K), st>>>(w.od, (int)n, K, w.active, bs.buckets, bs.shift, w.offer_runs,
                                                                 w.run_table);
                 bkt_lists<<<bs.buckets, bs.threads, lists_lds, st>>>(w.offer_runs, w.run_table, bs.blocks, bkt_rows * K, ko,
-                                                                    (int)n, L, bs.shift, (u32 *)w.rold, w.rold_c);
+                                                                    (int)n, L, bs.shift, (u32 *)w.rold, w.rold_c, nullptr,
+                                                                    nullptr, nullptr);
             } else if (K <= 16) EF_REVERSE_OLD(16);
             else if (K <= 32) EF_REVERSE_OLD(32);
             else EF_REVERSE_OLD(64);
@@ -3978,15 +3989,17 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
         // before any pair of a new and an old one (the phase events are recorded in the last pass:
         // the split by join size then says little).
         const int n_pass = cross_old ? 2 : 1;
+        int n_upd = 0;
         for (int pass = 0; pass < n_pass; ++pass) {
         const int mode = cross_old ? 1 + pass : 0;
+        n_upd = 0;      // (the joins' counts of insertions, one launch's blocks after the other's)
         const bool timed = ev && pass == n_pass - 1;
         if (reg_ok) {
 #define EF_JOIN_REG_K(NB, ONE, LIST, KT, ALIGNED)                                                  \
     join_reg_kernel<NB, ONE, KT, ALIGNED><<<reg_grid, EF_WAVE, reg_lds(16 * NB), st>>>(                     \
         X, d, K, w.work + (size_t)(LIST) * n, w.work_count + (LIST), reg_q_cap_for(16 * NB), \
         (ONE) ? margin_f16 : margin_rel, (ONE) ? thr_scale_f16 : thr_scale, u_f16, rho0_f16,       \
-        w.ulist, w.ucount, max_rows, graph, w.worst, w.upd_block + (LIST) * reg_grid, mode,        \
+        w.ulist, w.ucount, max_rows, graph, w.worst, w.upd_block + n_upd, mode,                    \
         kDenseSurvivors, w.xmax)
     // (a row length of 10 is compiled in: 3 % off the joins of 17..32 vectors)
 #define EF_JOIN_REG(NB, ONE, LIST)                                                                 \
@@ -3998,6 +4011,7 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
             if (K == 10) EF_JOIN_REG_K(NB, ONE, LIST, 10, false);                                  \
             else EF_JOIN_REG_K(NB, ONE, LIST, 0, false);                                           \
         }                                                                                          \
+        n_upd += reg_grid;                                                                         \
     } while (0)
             if (d <= 128) EF_JOIN_REG(1, true, 0);
             else EF_JOIN_REG(1, false, 0);
@@ -4017,7 +4031,7 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
         X, w.norms, d, dpad, stride, q4_magic_for(d), K, (u32)(((1ULL << 32) + K - 1) / K),       \
         w.work + (size_t)(C) * n, w.work_count + (C),                                              \
         large[C].cap_rows, large[C].s_cap, large[C].q_cap, margin_rel, thr_scale, w.ulist,         \
-        w.ucount, max_rows, graph, w.worst, w.upd_block + 2 * reg_grid + ((C) - 2) * kMaxLargeGrid, mode)
+        w.ucount, max_rows, graph, w.worst, w.upd_block + n_upd, mode)
         // the larger classes first: their blocks run longest
         for (int c = jc.n - 1; c >= 2 && max_rows > rows1; --c) {
             if (tiles) {      // vectors of at most 128 coordinates pass through registers
@@ -4025,7 +4039,8 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
                 long per_cu = (long)(kLdsLimit / tl);
                 per_cu = per_cu > 4 * kTileWaves ? 4 * kTileWaves : (per_cu < 1 ? 1 : per_cu);      // by registers
                 const int tgrid = (int)min((long)n, 256 * per_cu * 4);
-                int *upd = w.upd_block + 2 * reg_grid + (c - 2) * kMaxLargeGrid;
+                int *upd = w.upd_block + n_upd;
+                n_upd += tgrid;
                 const u32 km = (u32)(((1ULL << 32) + K - 1) / K);
                 const u32 kqm = (u32)(((1ULL << 32) + ((K + 3) >> 2) - 1) / ((K + 3) >> 2));
 #define EF_JOIN_TILE(LONG_ROWS, ALIGNED, QUADS)                                                            \
@@ -4047,15 +4062,18 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
                     else EF_JOIN_TILE(true, false, false);
                 }
 #undef EF_JOIN_TILE
-            } else if (K >= 2 * EF_WIDE_PIECES) EF_JOIN_LARGE(true, c);
-            else EF_JOIN_LARGE(false, c);
+            } else {
+                if (K >= 2 * EF_WIDE_PIECES) EF_JOIN_LARGE(true, c);
+                else EF_JOIN_LARGE(false, c);
+                n_upd += large[c].grid;
+            }
         }
 #undef EF_JOIN_LARGE
         }      // pass
         if (ev) EF_HIP_CHECK(hipEventRecord(ev[5 * it + 4], st));
         if (stats)
-            stats_kernel<<<16, kBlock, 0, st>>>(w.part, n_part, w.upd_block,
-                                                n_upd_block, stats + 4 * it);
+            stats_kernel<<<max(1, min(64, (n_part + n_upd) / (2 * kStatsThreads))), kStatsThreads, 0, st>>>(
+                w.part, n_part, w.upd_block, n_upd, stats + 4 * it);
         done = it + 1;
         if (delta > 0.0f) {      // early termination: the host looks at the count after every iteration
             u64 fresh = 0;
