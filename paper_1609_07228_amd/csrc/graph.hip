@@ -453,6 +453,62 @@ __device__ inline void broadcast_round(const float4 (&va)[N], const float4 (&vb)
     }
 }
 
+// x summed over lanes l and l + 32 in the lower half of the wave, y in the upper one; then the same with
+// neighbouring sixteens: x in the even ones, y in the odd ones.  One exchange of the vector ALU and an add
+// (the addends in either order: a float32 sum is the same), where a shuffle through the LDS took two selects, an
+// address and a wait besides.  All lanes of the wave must be active.  Builds: 10^6 x 128 16.53 -> 16.45 ms, 200 003 x 50
+// 5.31 -> 5.23, 10^5 x 128 4.89 -> 4.86, 10^6 x 96 at degree 100 328 -> 324; conquer three levels up 11.96 -> 11.84.
+__device__ inline float ef_add_halves(float x, float y)
+{
+    const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+}
+__device__ inline float ef_add_rows(float x, float y)
+{
+    const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+}
+
+// The fixed order's tree over the sixteen partial sums of a pair, which lie four in each of the lanes r, r + 16,
+// r + 32, r + 48; all four lanes get the distance.
+__device__ inline float ef_sum_partials(float p0, float p1, float p2, float p3)
+{
+    const float s = ef_add_rows(ef_add_halves(p0, p2), ef_add_halves(p1, p3));      // sum of p[g] in lane r + 16 g: 0 1 2 3 -> p0 p1 p2 p3
+    const float t = ef_add_halves(s, s);      // p0 + p2 in the even sixteens, p1 + p3 in the odd ones
+    return ef_add_rows(t, t);
+}
+
+// eight partial-sum sets (one per pair) -> lane g keeps the finished distances of pairs 2g
+// and 2g+1 of the eight; same adds, in the same tree, as the fixed order
+__device__ inline void reduce_rotations(const float (&P)[8][4], float (&out)[2])
+{
+    float Q[4][4], R[2][4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) Q[t][k] = ef_add_halves(P[t][k], P[t + 4][k]);
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) R[t][k] = ef_add_rows(Q[t][k], Q[t + 2][k]);
+#pragma unroll
+    for (int t = 0; t < 2; ++t) out[t] = (R[t][0] + R[t][2]) + (R[t][1] + R[t][3]);
+}
+
+// The same for four rotations (T0 + 1 .. T0 + 4 in P[0..3]): lane (r, g) ends up with the distance
+// from row r to the row T0 + 1 + g places on.
+__device__ inline float reduce_rotations4(const float (&P)[4][4])
+{
+    float Q[2][4], R[4];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) Q[t][k] = ef_add_halves(P[t][k], P[t + 2][k]);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) R[k] = ef_add_rows(Q[0][k], Q[1][k]);
+    return (R[0] + R[2]) + (R[1] + R[3]);
+}
+
 constexpr int kCandPitch = 17;      // u64 per row of the candidate table (odd: rows on different banks)
 
 template <bool ALIGNED>      // (see load_pieces)
@@ -509,29 +565,15 @@ init_reg_kernel(const float *__restrict__ X, int d, const int *__restrict__ perm
             init_round<8>(va, n_pieces, P[7]);
         }
         // partial sums l and l+8 live 2 lanes-of-g apart (xor 32), l and l+4 one apart (xor 16)
-        const bool hi = g & 2, odd = g & 1;
-        float Q[4][4], R[2][4];
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const float keep = hi ? P[t + 4][k] : P[t][k], send = hi ? P[t][k] : P[t + 4][k];
-                Q[t][k] = keep + __shfl_xor(send, 32, EF_WAVE);
-            }
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const float keep = odd ? Q[t + 2][k] : Q[t][k], send = odd ? Q[t][k] : Q[t + 2][k];
-                R[t][k] = keep + __shfl_xor(send, 16, EF_WAVE);
-            }
+        float two[2];
+        reduce_rotations(P, two);
         __syncthreads();                  // uid, pools visible
         // ---- candidates of row r16: rotations 2g+1, 2g+2, forwards and from the mirror lane ---
         u64 key[4];
         int lt[4];
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
-            const float dist = (R[t][0] + R[t][2]) + (R[t][1] + R[t][3]);
+            const float dist = two[t];
             const int rot = 2 * g + 1 + t;
             const int bf = (r16 + dirn * rot) & 15, br = (r16 - dirn * rot) & 15;
             const float dist_r = __shfl(dist, br + 16 * g, EF_WAVE);     // lane br met r16 at this rotation
@@ -674,51 +716,6 @@ __device__ inline void accumulate_pair(const float4 (&va)[8], const float4 (&vb)
     }
 }
 
-// eight partial-sum sets (one per pair) -> lane g keeps the finished distances of pairs 2g
-// and 2g+1 of the eight; same adds, in the same tree, as the fixed order
-__device__ inline void reduce_rotations(const float (&P)[8][4], int g, float (&out)[2])
-{
-    const bool hi = g & 2, odd = g & 1;
-    float Q[4][4], R[2][4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const float keep = hi ? P[t + 4][k] : P[t][k], send = hi ? P[t][k] : P[t + 4][k];
-            Q[t][k] = keep + __shfl_xor(send, 32, EF_WAVE);
-        }
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const float keep = odd ? Q[t + 2][k] : Q[t][k], send = odd ? Q[t][k] : Q[t + 2][k];
-            R[t][k] = keep + __shfl_xor(send, 16, EF_WAVE);
-        }
-#pragma unroll
-    for (int t = 0; t < 2; ++t) out[t] = (R[t][0] + R[t][2]) + (R[t][1] + R[t][3]);
-}
-
-// The same for four rotations (T0 + 1 .. T0 + 4 in P[0..3]): lane (r, g) ends up with the distance
-// from row r to the row T0 + 1 + g places on.
-__device__ inline float reduce_rotations4(const float (&P)[4][4], int g)
-{
-    const bool hi = g & 2, odd = g & 1;
-    float Q[2][4], R[4];
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const float keep = hi ? P[t + 2][k] : P[t][k], send = hi ? P[t][k] : P[t + 2][k];
-            Q[t][k] = keep + __shfl_xor(send, 32, EF_WAVE);
-        }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const float keep = odd ? Q[1][k] : Q[0][k], send = odd ? Q[0][k] : Q[1][k];
-        R[k] = keep + __shfl_xor(send, 16, EF_WAVE);
-    }
-    return (R[0] + R[2]) + (R[1] + R[3]);
-}
-
 // Which leaf of each sibling subtree every point reaches: etab[p * levels + k] for the point at
 // position p of the tree's id array and the k-th ancestor of its leaf (k = 0: the leaf's
 // parent), -1 where there is no such ancestor or its depth is below dep.  A wave takes one
@@ -839,7 +836,7 @@ conquer_kernel(const float *__restrict__ X, int d, const int *__restrict__ perm_
                         }
                     }
                     float two[2];
-                    reduce_rotations(P, g, two);
+                    reduce_rotations(P, two);
                     dist[2 * half] = two[0];
                     dist[2 * half + 1] = two[1];
                 }
@@ -1019,11 +1016,7 @@ conquer_tile_kernel(const float *__restrict__ X, int d, const int *__restrict__ 
                         p[2] = __builtin_fmaf(d2, d2, p[2]);
                         p[3] = __builtin_fmaf(d3, d3, p[3]);
                     }
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) p[q] += __shfl_xor(p[q], 32, EF_WAVE);
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) p[q] += __shfl_xor(p[q], 16, EF_WAVE);
-                    const float dist = (p[0] + p[2]) + (p[1] + p[3]);
+                    const float dist = ef_sum_partials(p[0], p[1], p[2], p[3]);
                     if (has && g == 0) cand[al * kCandPitch + atomicAdd(&ncand[al], 1)] = ef_pack(dist, uid_b[bl], 1);
                 }
                 __syncthreads();
@@ -2593,7 +2586,7 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
 #pragma unroll
                 for (int set = 0; set < NB; ++set) {
                     const float (&Q)[4][4] = reinterpret_cast<const float (&)[4][4]>(set == 0 ? P[a0] : PB[NB > 1 ? a0 : 0]);
-                    const float dist = reduce_rotations4(Q, g);      // row a0 + g to row 16 set + r16
+                    const float dist = reduce_rotations4(Q);      // row a0 + g to row 16 set + r16
                     const int a = a0 + g, b = 16 * set + r16;
                     offer(std::false_type{}, a < m_new && a < b && b < m && mode_ok(b), dist, a, b);
                 }
@@ -2627,7 +2620,7 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
                 EF_EACH_FEW(EF_BROADCAST)
 #undef EF_BROADCAST
             }
-            reduce_rotations(P, g, two);
+            reduce_rotations(P, two);
             __syncthreads();      // uid, thr visible
             t_pre = u_pre >= 0 ? worst[u_pre] : 0u;
             offer_rotations(std::false_type{});
@@ -2635,10 +2628,10 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
             for (int t0 = 0; t0 < kFewNew; t0 += 4) {
                 if (16 + t0 >= m) break;
                 const int x = 16 + t0 + g, y = 16 + r16;      // the broadcast row; the lane's row of the second set
-                const float dist = reduce_rotations4(reinterpret_cast<const float (&)[4][4]>(PX[t0]), g);
+                const float dist = reduce_rotations4(reinterpret_cast<const float (&)[4][4]>(PX[t0]));
                 offer(std::false_type{}, x < m && r16 < m_new && mode_ok(x), dist, r16, x);
                 if (need11) {
-                    const float dist_b = reduce_rotations4(reinterpret_cast<const float (&)[4][4]>(PB[t0]), g);
+                    const float dist_b = reduce_rotations4(reinterpret_cast<const float (&)[4][4]>(PB[t0]));
                     offer(std::false_type{}, x < m_new && x < y && y < m && mode_ok(y), dist_b, x, y);
                 }
             }
@@ -2675,8 +2668,8 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
                     init_round<8>(wb, n_pieces, PB[NB > 1 ? 7 : 0]);
                 }
             }
-            reduce_rotations(P, g, two);
-            if (NB > 1) reduce_rotations(reinterpret_cast<const float (&)[8][4]>(PB), g, two_b);
+            reduce_rotations(P, two);
+            if (NB > 1) reduce_rotations(reinterpret_cast<const float (&)[8][4]>(PB), two_b);
         }
         for (int c0 = 0; c0 < d && !rotated; c0 += 128) {
             if (c0 + 128 <= d) {     // a whole 128-coordinate piece: no per-load bounds test
@@ -2809,7 +2802,7 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     float cross[2];
-                    reduce_rotations(PX[h], g, cross);      // rotations 8h + 2g and 8h + 2g + 1
+                    reduce_rotations(PX[h], cross);      // rotations 8h + 2g and 8h + 2g + 1
 #pragma unroll
                     for (int t = 0; t < 2; ++t) {
                         const int rot = 8 * h + 2 * g + t, b = 16 + ((r16 + dirn * rot) & 15);
@@ -2851,7 +2844,7 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
                             init_round<7>(rows, n_pieces, P[2]);
                             init_round<8>(rows, n_pieces, P[3]);
                         }
-                        const float dist = reduce_rotations4(P, g);
+                        const float dist = reduce_rotations4(P);
                         const int rot = 4 * half + 1 + g, b = (r16 + dirn * rot) & 15;
                         const bool once = rot != 8 || r16 < b;      // rotation 8 meets every pair from both ends
                         if (NB > 1 && q_fill + 2 * EF_WAVE > q_cap) {
@@ -2887,17 +2880,8 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
                         p2s = __builtin_fmaf(d2, d2, p2s);
                         p3s = __builtin_fmaf(d3, d3, p3s);
                     }
-                    // partial sum l lives in lane g = l / 4, slot l % 4: l += l+8, l += l+4 across
-                    // lanes, l += l+2, l += l+1 inside lane g = 0
-                    p0s += __shfl_xor(p0s, 32, EF_WAVE);
-                    p1s += __shfl_xor(p1s, 32, EF_WAVE);
-                    p2s += __shfl_xor(p2s, 32, EF_WAVE);
-                    p3s += __shfl_xor(p3s, 32, EF_WAVE);
-                    p0s += __shfl_xor(p0s, 16, EF_WAVE);
-                    p1s += __shfl_xor(p1s, 16, EF_WAVE);
-                    p2s += __shfl_xor(p2s, 16, EF_WAVE);
-                    p3s += __shfl_xor(p3s, 16, EF_WAVE);
-                    const float dist = (p0s + p2s) + (p1s + p3s);
+                    // partial sum l lives in lane g = l / 4, slot l % 4
+                    const float dist = ef_sum_partials(p0s, p1s, p2s, p3s);
                     q_fill = propose_pair(queue, q_fill, has && g == 0, dist, 16 * bi + al, 16 * bj + bl, thr, uid, mark);
                     __syncthreads();
                     // NB = 1: the queue is sized so that a point's proposals always fit (at most 240
@@ -3237,11 +3221,7 @@ join_tile_kernel(const float *__restrict__ X, int d, int K, u32 k_magic,
             float p[4] = {0.f, 0.f, 0.f, 0.f};
             accumulate_pair(va, vb, (d + 15) >> 4, p);
             // partial sum l lives in lane g = l / 4, slot l % 4 (see join_reg_kernel)
-#pragma unroll
-            for (int k = 0; k < 4; ++k) p[k] += __shfl_xor(p[k], 32, EF_WAVE);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) p[k] += __shfl_xor(p[k], 16, EF_WAVE);
-            const float dist = (p[0] + p[2]) + (p[1] + p[3]);
+            const float dist = ef_sum_partials(p[0], p[1], p[2], p[3]);
             const bool take = mine && __float_as_uint(dist) <= lds.thr[a];
             const u64 mask = __ballot(take);
             if (take) {
