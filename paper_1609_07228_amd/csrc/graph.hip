@@ -217,7 +217,6 @@ __device__ inline void gather_rows(const float *__restrict__ X, int d, int strid
 
 // Drain the proposal queue: every thread applies whole proposals on its own, so all the
 // row reads of up to blockDim proposals are in flight together.
-template <bool REFINE = false>
 __device__ inline int drain_queue(const Proposal *queue, int count, u64 *graph, u32 *worst, int K,
                                   int tid, int nthr)
 {
@@ -225,8 +224,23 @@ __device__ inline int drain_queue(const Proposal *queue, int count, u64 *graph, 
     for (int e = tid; e < count; e += nthr) {
         const Proposal p = queue[e];
         u64 new_max;
-        if (ef_bounded_insert_t<false, REFINE>(graph + (size_t)p.target * K, K, p.key, 1, &new_max)) {
+        if (ef_bounded_insert(graph + (size_t)p.target * K, K, p.key, 1, &new_max)) {
             atomicMin(worst + p.target, ef_dist_bits(new_max));
+            ++updates;
+        }
+    }
+    return updates;
+}
+
+// The same for rows of 2 .. 16 entries (see ef_bounded_insert_row).
+__device__ inline int drain_queue_row(const Proposal *queue, int count, u64 *graph, u32 *worst, int K, int tid, int nthr)
+{
+    int updates = 0;
+    for (int e = tid; e < count; e += nthr) {
+        const Proposal p = queue[e];
+        u32 new_max_bits;
+        if (ef_bounded_insert_row(graph + (size_t)p.target * K, K, p.key, &new_max_bits)) {
+            atomicMin(worst + p.target, new_max_bits);
             ++updates;
         }
     }
@@ -2443,7 +2457,8 @@ __device__ inline int propose_pair(Proposal *queue, int fill, bool mine, float d
     return fill + __popcll(mask_b);
 }
 
-template <int NB, bool ONE, int KT, bool ALIGNED>      // KT: the row length if fixed at compile time (the row scans unroll), else 0
+// KT: the row length if fixed at compile time (the row scans unroll), else -16 (2 .. 16 entries) or 0
+template <int NB, bool ONE, int KT, bool ALIGNED>
 __global__ void __launch_bounds__(EF_WAVE) __attribute__((amdgpu_waves_per_eu(NB > 1 ? 3 : 4)))
 join_reg_kernel(const float *__restrict__ X, int d, int K_,
                 const int *__restrict__ work, const int *__restrict__ work_count, int q_cap,
@@ -2456,7 +2471,7 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
     // Alg. 4's second inner loop runs the joins twice, mode 1 before mode 2).  Rows 0 .. m_new - 1
     // of a list are its new members, so a pair (a, b), a < b, a new, is of two new members iff b is.
     const int mark = mode != 2;
-    const int K = KT ? KT : K_;
+    const int K = KT > 0 ? KT : K_;
     constexpr int R = 16 * NB;                    // rows
     constexpr int S_CAP = ONE ? R * (R - 1) / 2 + 8 : 0;    // every pair may survive
     extern __shared__ __align__(16) float smem[];
@@ -2491,7 +2506,11 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
     // registers, and a lane finds its slot from a ballot (no LDS counters, no round trips).
     int updates = 0, q_fill = 0;
     auto drain = [&](const Proposal *from, int cnt) {
-        return drain_queue<NB == 1>(from, cnt, graph, worst, K, lane, EF_WAVE);
+        const int lane = ef_opaque(threadIdx.x);
+        int len = K;
+        if constexpr (KT <= 0) asm volatile("" : "+s"(len));      // (see ef_opaque)
+        if constexpr (KT != 0) return drain_queue_row(from, cnt, graph, worst, len, lane, EF_WAVE);
+        else return drain_queue(from, cnt, graph, worst, len, lane, EF_WAVE);
     };
     auto drain_mid = drain;
     for (; i >= 0; w += gridDim.x) {
@@ -2824,8 +2843,8 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
                 // pass): all 120 pairs by row rotations, as for long vectors, cost what two rounds
                 // of sixteen survivors cost.  The filter never drops a pair that would pass a
                 // threshold, so which way a pair takes makes no difference to what is proposed.
-                // (only with the row length compiled in: the other variants would spill registers)
-                if (NB == 1 && KT != 0 && n_q > dense_min) {
+                if (NB == 1 && n_q > dense_min) {
+                    const int lane = ef_opaque(threadIdx.x), r16 = lane & 15, g = lane >> 4;
                     const float4 (&rows)[8] = reinterpret_cast<const float4 (&)[8]>(*(q == 0 ? va : vb));
                     const int n_pieces = (d + 15) >> 4, base = 16 * bi;
 #pragma unroll
@@ -3981,16 +4000,18 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
         (ONE) ? margin_f16 : margin_rel, (ONE) ? thr_scale_f16 : thr_scale, u_f16, rho0_f16,       \
         w.ulist, w.ucount, max_rows, graph, w.worst, w.upd_block + n_upd, mode,                    \
         kDenseSurvivors, w.xmax)
-    // (a row length of 10 is compiled in: 3 % off the joins of 17..32 vectors)
+    // (a row length of 10 is compiled in: 3 % off the joins of 17..32 vectors; rows of up to sixteen entries in general go
+    // in one piece, see ef_bounded_insert_row)
+#define EF_JOIN_REG_A(NB, ONE, LIST, ALIGNED)                                                       \
+    do {                                                                                           \
+        if (K == 10) EF_JOIN_REG_K(NB, ONE, LIST, 10, ALIGNED);                                    \
+        else if (K > 16 || K < 2) EF_JOIN_REG_K(NB, ONE, LIST, 0, ALIGNED);                        \
+        else EF_JOIN_REG_K(NB, ONE, LIST, -16, ALIGNED);                                           \
+    } while (0)
 #define EF_JOIN_REG(NB, ONE, LIST)                                                                 \
     do {                                                                                           \
-        if (aligned) {                                                                             \
-            if (K == 10) EF_JOIN_REG_K(NB, ONE, LIST, 10, true);                                   \
-            else EF_JOIN_REG_K(NB, ONE, LIST, 0, true);                                            \
-        } else {                                                                                   \
-            if (K == 10) EF_JOIN_REG_K(NB, ONE, LIST, 10, false);                                  \
-            else EF_JOIN_REG_K(NB, ONE, LIST, 0, false);                                           \
-        }                                                                                          \
+        if (aligned) EF_JOIN_REG_A(NB, ONE, LIST, true);                                           \
+        else EF_JOIN_REG_A(NB, ONE, LIST, false);                                                  \
         n_upd += reg_grid;                                                                         \
     } while (0)
             if (d <= 128) EF_JOIN_REG(1, true, 0);
@@ -4001,6 +4022,7 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
                 else EF_JOIN_REG(2, false, 1);
             }
 #undef EF_JOIN_REG
+#undef EF_JOIN_REG_A
 #undef EF_JOIN_REG_K
         } else if (timed) {
             EF_HIP_CHECK(hipEventRecord(ev[5 * it + 2], st));

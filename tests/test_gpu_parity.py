@@ -508,6 +508,21 @@ def test_nndescent_tile_join_edges(ef, n, d, K, L):
         graph_equal(ef, graph, want)
 
 
+@pytest.mark.parametrize("K,L", [(1, 7), (2, 7), (3, 8), (5, 6), (8, 4), (9, 11), (15, 8), (16, 8), (17, 7),      # rows of one to eight
+                                 (18, 7), (33, 2)])      # 16-byte pieces, odd and even, and longer ones
+def test_nndescent_row_lengths(ef, K, L):
+    """Insertions of the joins of at most 32 vectors, many of them to the same rows; ties of distance among them."""
+    rng = np.random.default_rng(K)
+    for X in (rng.standard_normal((500, 24)).astype(np.float32), rng.integers(0, 3, (500, 7)).astype(np.float32)):
+        Xd = dev(X)
+        (perm, off, nl), (operm, ooff, onl) = trees_equal(ef, X, 1, 8, 11)
+        graph, want = ef.efanna_init_graph(Xd, perm, off, nl, 8, K), oracle.init_graph(X, operm, ooff, onl, K)
+        for it in range(4):
+            ef.efanna_nndescent(Xd, graph, 1, L, 11, first_iter=it)
+            want = oracle.nndescent(X, *want[:3], 1, L, 11, iter0=it)
+            graph_equal(ef, graph, want)
+
+
 @pytest.mark.parametrize("d", [129, 132, 191, 256, 260])      # pieces of one coordinate, of four, ...; rows unaligned for odd d
 @pytest.mark.parametrize("K,L", [(10, 2), (10, 10), (16, 8), (7, 12)])      # few new members; second sets of up to 8 and of more rows
 def test_nndescent_long_vectors_few_and_many_new(ef, d, K, L):
