@@ -2932,7 +2932,7 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
 // ---------------------------------------------------------------------------------------
 // The local join for points whose join gathers more than 32 vectors of at most 128 coordinates
 // (d >= 4), without a row buffer: one wave per point.  Three passes over the join's list:
-//   1. Wants.  Up to four tiles of sixteen new rows (A) stand in registers as half-precision operands while
+//   1. Wants.  Up to kTileGroup tiles of sixteen new rows (A) stand in registers as half-precision operands while
 //      every tile of sixteen rows from the first of them onwards (B) passes by once: a Gram block per tile
 //      pair, join_reg_kernel's filter (the squared norms of the rounded rows are the diagonals of the tiles'
 //      blocks with themselves), and for either row of a pair one bit that says whether its own threshold lets
