@@ -69,7 +69,7 @@ typedef enum {
 
 /* A graph entry: bits 63..32 float32 bit pattern of the squared distance, bits 31..1
  * neighbour id, bit 0 the "new" mark of Alg. 4.  An empty slot has distance +inf.
- * Rows of `graph` are K such entries in no particular order. */
+ * Rows of `graph` are K such entries, no id twice, in no particular order. */
 typedef uint64_t efanna_entry;
 
 /* An internal tree node as the conquer step of Alg. 3 uses it.  A point x goes to the left
@@ -255,8 +255,9 @@ int efanna_get_graph(const efanna_entry *graph, int64_t n, int32_t k, int32_t *i
 
 /* Inverse of efanna_get_graph: packs (ids, dists, flags) rows into graph entries, so
  * that NN-descent can start from any initial graph (for example a random one).
- * Empty slots are given by id < 0 (ids >= n are treated the same way).  flags NULL marks
- * every entry new.  Asynchronous on `stream`. */
+ * Empty slots are given by id < 0 (ids >= n are treated the same way).  An id that a row names
+ * more than once is taken from the first slot that names it, the others stay empty.  flags
+ * NULL marks every entry new.  Asynchronous on `stream`. */
 int efanna_set_graph(efanna_entry *graph, int64_t n, int32_t k, const int32_t *ids,
                      const float *dists, const uint8_t *flags, void *stream);
 

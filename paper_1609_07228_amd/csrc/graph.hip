@@ -3452,15 +3452,25 @@ get_graph_group_kernel(const u64 *__restrict__ graph, int n, int K, int *__restr
     if (flags) flags[dst] = empty ? 0 : (unsigned char)(e & 1);
 }
 
-__global__ void set_graph_kernel(u64 *graph, size_t total, int n, int K, const int *__restrict__ ids,
-                                 const float *__restrict__ dists,
-                                 const unsigned char *__restrict__ flags)
+// Rows hold distinct entries: the ranks of sampling and of get_graph, and the insertions, rely on it (two entries
+// of one key have the same rank, and the place after it would keep what was there before).  A random start may
+// draw an id twice, so an id that an earlier slot of the row names leaves its slot empty.  A thread per slot of the
+// block's kBlock / K rows; the threads of a row walk its slots together, in LDS.
+__global__ void __launch_bounds__(kBlock)
+set_graph_kernel(u64 *graph, size_t n, int K, const int *__restrict__ ids, const float *__restrict__ dists,
+                 const unsigned char *__restrict__ flags)
 {
-    size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= total) return;
-    const int id = ids[i];
-    graph[i] = (id < 0 || id >= n) ? ef_empty_entry((int)(i % (size_t)K))
-                      : ef_pack(dists[i], id, flags ? flags[i] : 1);
+    __shared__ int id_sh[kBlock];
+    const int t = threadIdx.x, rows = kBlock / K, r = t / K, slot = t - r * K;
+    const size_t i = (size_t)blockIdx.x * rows + r;
+    const bool mine = r < rows && i < n;
+    const int id = mine ? ids[i * K + slot] : -1;
+    id_sh[t] = id;
+    __syncthreads();
+    if (!mine) return;
+    bool ok = id >= 0 && (size_t)id < n;
+    for (int s = 0; s < slot; ++s) ok &= id_sh[r * K + s] != id;
+    graph[i * K + slot] = ok ? ef_pack(dists[i * K + slot], id, flags ? flags[i * K + slot] : 1) : ef_empty_entry(slot);
 }
 
 __global__ void pair_distances_kernel(const float *__restrict__ X, int d,
@@ -4127,8 +4137,8 @@ extern "C" int efanna_set_graph(efanna_entry *graph_, int64_t n, int32_t k, cons
 {
     u64 *const graph = (u64 *)graph_;
     if (!graph || !ids || !dists || n < 1 || k < 1 || k > EFANNA_MAX_K) return EFANNA_EINVAL;
-    set_graph_kernel<<<grid_for((size_t)n * k, kBlock), kBlock, 0, (hipStream_t)stream>>>(
-        graph, (size_t)n * k, (int)n, k, ids, dists, flags);
+    set_graph_kernel<<<grid_for((size_t)n, kBlock / k), kBlock, 0, (hipStream_t)stream>>>(
+        graph, (size_t)n, k, ids, dists, flags);
     EF_HIP_CHECK(hipGetLastError());
     return EFANNA_OK;
 }

@@ -243,7 +243,7 @@ def efanna_get_graph(graph: torch.Tensor, with_flags: bool = False):
 
 
 def efanna_set_graph(ids: torch.Tensor, dists: torch.Tensor, flags: torch.Tensor | None = None):
-    """Pack rows into a graph tensor [n,k] int64."""
+    """Pack rows into a graph tensor [n,k] int64; of an id that a row names twice the first slot counts."""
     ids = _dev(ids, torch.int32)
     dists = _dev(dists, torch.float32)
     n, k = ids.shape

@@ -675,6 +675,36 @@ def test_nndescent_one_vector_far_out(ef, d, K, L):
         graph_equal(ef, graph, want)
 
 
+@pytest.mark.parametrize("K,L", [(1, 3), (7, 5), (10, 10), (20, 20), (33, 10), (64, 16), (100, 50), (128, 8)])
+@pytest.mark.parametrize("marks", ["new", "mixed"])
+def test_random_start_with_repeated_ids(ef, K, L, marks):
+    """Rows that name an id several times (a random start drawn with replacement): the first slot that names it
+    counts, the others are empty, and the refinement is the oracle's from those rows."""
+    rng = np.random.default_rng(K)
+    n, d = 301, 20
+    X = rng.standard_normal((n, d)).astype(np.float32)
+    ids = rng.integers(0, n, (n, K)).astype(np.int32)
+    ids[:, K // 2:] = ids[:, :K - K // 2]              # every row names half of its ids twice
+    ids[5], ids[6, 1:] = ids[5, 0], -1                 # one id only; nearly empty
+    ids[ids == np.arange(n)[:, None]] = -1
+    ids[9] = n                                         # outside the data: empty
+    dists = np.array([[oracle.dist(X[i], X[j]) if 0 <= j < n else np.inf for j in row] for i, row in enumerate(ids)], dtype=np.float32)
+    flags = rng.integers(0, 2, (n, K)).astype(np.uint8) if marks == "mixed" else None
+    graph = ef.efanna_set_graph(dev(ids), dev(dists), None if flags is None else dev(flags))
+    want = [np.full((n, K), -1, np.int32), np.full((n, K), np.inf, np.float32), np.zeros((n, K), np.uint8)]
+    for i in range(n):
+        first = {int(j): s for s, j in reversed(list(enumerate(ids[i]))) if 0 <= j < n}
+        row = sorted((dists[i, s], j, 1 if flags is None else flags[i, s]) for j, s in first.items())
+        for s, (dist, j, mark) in enumerate(row):
+            want[0][i, s], want[1][i, s], want[2][i, s] = j, dist, mark
+    graph_equal(ef, graph, want)
+    ws = torch.full((ef.lib().efanna_nndescent_workspace_bytes(n, K, L),), 255, dtype=torch.uint8, device="cuda:0")
+    for it in range(3):
+        ef.efanna_nndescent(dev(X), graph, 1, L, 5, first_iter=it, workspace=ws)
+        want = oracle.nndescent(X, *want[:3], 1, L, 5, iter0=it)
+        graph_equal(ef, graph, want)
+
+
 def test_nndescent_resume_and_recall(ef):
     name = "gmm10k_d32"
     p = synth.params(name)
