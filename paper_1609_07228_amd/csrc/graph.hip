@@ -2553,8 +2553,12 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
         // modifier on the subtract again) and meets all the others, 64 vector instructions per new member, row
         // set and 128 coordinates; all rows are read once.  17..32 rows with few in the second set: rotations for
         // the pairs of the first set, and the rows of the second are broadcast; again one pass.
+        // The latter up to degree 32 only: a broadcast queues sixteen proposals to one row side by side, they are
+        // applied together, and whoever finds its slot changed scans the row again.  (Joins of 17..32, 20 000 x 132,
+        // without and with: degree 64 3.17 and 3.53 ms, 48 1.87 and 2.00, 40 1.39 and 1.45, 32 1.03 both, 24 0.80 and 0.77;
+        // 200 000 x 132, degree 64 17.2 and 19.9.)
         constexpr bool rotated = !ONE;
-        const bool few = rotated && m_new <= kFewNew, few_rest = rotated && NB > 1 && m <= 16 + kFewRest;
+        const bool few = rotated && m_new <= kFewNew, few_rest = rotated && NB > 1 && (KT != 0 || K <= 32) && m <= 16 + kFewRest;
         float two[2] = {0.f, 0.f}, two_b[2] = {0.f, 0.f};
         // may_drain: only where a join can propose more than the queue holds (see reg_q_cap_for; every
         // place that drains is a copy of the insertion, in code and in registers)
@@ -2567,14 +2571,11 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
             q_fill = propose_pair(queue, q_fill, mine, dist, a, b, thr, uid, mark);
             __syncthreads();
         };
-        // the pairs inside rows 0..15 from rotations: lane (r, g) has the distances 2g+1 and 2g+2 places on
-        auto offer_rotations = [&](auto may_drain) {
-#pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                const int rot = 2 * g + 1 + t, b = (r16 + dirn * rot) & 15;
-                // rotation 8 meets every pair from both ends: the lower row keeps it
-                offer(may_drain, (rot != 8 || r16 < b) && r16 < m && b < m && min(r16, b) < m_new && mode_ok(max(r16, b)), two[t], r16, b);
-            }
+        // pairs inside rows 0..15 from rotations: lane (r, g) has the distances 2g+1 and 2g+2 places on (t = 0, 1)
+        auto offer_rotation = [&](auto may_drain, int t) {
+            const int rot = 2 * g + 1 + t, b = (r16 + dirn * rot) & 15;
+            // rotation 8 meets every pair from both ends: the lower row keeps it
+            offer(may_drain, (rot != 8 || r16 < b) && r16 < m && b < m && min(r16, b) < m_new && mode_ok(max(r16, b)), two[t], r16, b);
         };
 #define EF_EACH_FEW(X) X(0) X(1) X(2) X(3) X(4) X(5) X(6) X(7)
         if (few) {
@@ -2642,7 +2643,8 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
             reduce_rotations(P, two);
             __syncthreads();      // uid, thr visible
             t_pre = u_pre >= 0 ? worst[u_pre] : 0u;
-            offer_rotations(std::false_type{});
+            offer_rotation(std::false_type{}, 0);
+            offer_rotation(std::false_type{}, 1);
 #pragma unroll
             for (int t0 = 0; t0 < kFewNew; t0 += 4) {
                 if (16 + t0 >= m) break;
@@ -2779,10 +2781,12 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
         }
         __syncthreads();
         if (rotated) {
-            offer_rotations(std::bool_constant<(NB > 1)>{});
-            if (NB > 1 && need11) {
+            // (the two sets in turn: proposals to one row further apart in the queue; both rotations of the first
+            // set before those of the second: 200 000 x 132, degree 64 16.9 -> 17.2 ms)
 #pragma unroll
-                for (int t = 0; t < 2; ++t) {
+            for (int t = 0; t < 2; ++t) {
+                offer_rotation(std::bool_constant<(NB > 1)>{}, t);
+                if (NB > 1 && need11) {
                     const int rot = 2 * g + 1 + t, b = (r16 + dirn * rot) & 15;
                     offer(std::true_type{}, (rot != 8 || r16 < b) && 16 + r16 < m && 16 + b < m && 16 + min(r16, b) < m_new &&
                               mode_ok(16 + max(r16, b)),
