@@ -478,6 +478,115 @@ __device__ inline bool ef_bounded_insert_row(u64 *list, int cap, u64 key, u32 *n
     }
 }
 
+// ---- the same insertion by a group of sixteen lanes (long rows) ----------------------------
+// n (1..4) pieces from n addresses, in flight together
+__device__ inline void ef_load_pieces_at(const void *p0, const void *p1, const void *p2, const void *p3,
+                                         int n, ef_u32x4 (&q)[4])
+{
+    switch (n) {
+    case 1:
+        asm volatile(
+                     "global_load_dwordx4 %0, %1, off sc1\n\t"
+                     "s_waitcnt vmcnt(0)"
+                     : "=&v"(q[0])
+                     : "v"(p0)
+                     : "memory");
+        break;
+    case 2:
+        asm volatile(
+                     "global_load_dwordx4 %0, %2, off sc1\n\t"
+                     "global_load_dwordx4 %1, %3, off sc1\n\t"
+                     "s_waitcnt vmcnt(0)"
+                     : "=&v"(q[0]), "=&v"(q[1])
+                     : "v"(p0), "v"(p1)
+                     : "memory");
+        break;
+    case 3:
+        asm volatile(
+                     "global_load_dwordx4 %0, %3, off sc1\n\t"
+                     "global_load_dwordx4 %1, %4, off sc1\n\t"
+                     "global_load_dwordx4 %2, %5, off sc1\n\t"
+                     "s_waitcnt vmcnt(0)"
+                     : "=&v"(q[0]), "=&v"(q[1]), "=&v"(q[2])
+                     : "v"(p0), "v"(p1), "v"(p2)
+                     : "memory");
+        break;
+    default:
+        asm volatile(
+                     "global_load_dwordx4 %0, %4, off sc1\n\t"
+                     "global_load_dwordx4 %1, %5, off sc1\n\t"
+                     "global_load_dwordx4 %2, %6, off sc1\n\t"
+                     "global_load_dwordx4 %3, %7, off sc1\n\t"
+                     "s_waitcnt vmcnt(0)"
+                     : "=&v"(q[0]), "=&v"(q[1]), "=&v"(q[2]), "=&v"(q[3])
+                     : "v"(p0), "v"(p1), "v"(p2), "v"(p3)
+                     : "memory");
+    }
+}
+
+// The entry `key` is offered to a graph row of 2 .. 128 entries at any multiple of 8 bytes.  All sixteen lanes of a
+// group (lane gl = 0..15 of it) call this with the same arguments and get the same result; all of them must be active.
+// Lane gl reads the 16-byte pieces gl, gl + 16, ... of the row, so that the group fetches 256 contiguous bytes per
+// load (a 16-byte load asks for 4-byte alignment, and an 8-byte aligned entry never straddles a cache line); the last
+// piece of a row of odd length starts one entry earlier, at an entry that the piece before it delivers as well.
+// This is the form for the join with rows in LDS.  Eight lanes as in the tile join hold twice the pieces each: that
+// kernel took 142 registers instead of 102, and its larger joins 2 to 3 % more time (20 000 x 132, degree 64 3.33 -> 3.41 ms,
+// 100 000 x 200, degree 64 31.0 -> 32.3; with 141 registers and nothing kept across the joins 3.30, 31.5).
+__device__ inline bool ef_bounded_insert_g16(u64 *list, int cap, u64 key, u64 *new_max, int gl)
+{
+    const u64 kcmp = key >> 1;
+    const int np = (cap + 1) >> 1, n_ld = (np + 15) >> 4;
+    for (;;) {
+        u64 mx = 0, mx2 = 0;
+        int ms = 0;
+        bool dup = false;
+        ef_u32x4 q[4];
+        // pieces beyond the row read its last piece again and are not looked at
+        auto at = [&](int piece) { return (const void *)(list + min(2 * piece, cap - 2)); };
+        ef_load_pieces_at(at(gl), at(gl + 16), at(gl + 32), at(gl + 48), n_ld, q);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int piece = gl + 16 * k;
+            if (k >= n_ld || piece >= np) continue;
+            const u64 e2[2] = {((u64)q[k].y << 32) | q[k].x, ((u64)q[k].w << 32) | q[k].z};
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int s = min(2 * piece, cap - 2) + h;
+                if (s < 2 * piece) continue;      // (looked at already)
+                dup |= (e2[h] >> 1) == kcmp;
+                if (e2[h] > mx) {
+                    mx2 = mx;
+                    mx = e2[h];
+                    ms = s;
+                } else if (e2[h] > mx2) {
+                    mx2 = e2[h];
+                }
+            }
+        }
+        // the group's largest and second largest entry (entries of a row are distinct)
+        for (int m = 8; m >= 1; m >>= 1) {
+            const u64 omx = __shfl_xor(mx, m, 16), omx2 = __shfl_xor(mx2, m, 16);
+            const int oms = __shfl_xor(ms, m, 16);
+            dup |= (bool)__shfl_xor((int)dup, m, 16);
+            if (omx > mx) {
+                mx2 = mx > omx2 ? mx : omx2;
+                mx = omx;
+                ms = oms;
+            } else if (omx > mx2) {
+                mx2 = omx;
+            }
+        }
+        if (dup || kcmp >= (mx >> 1)) return false;
+        u64 seen = 0;
+        if (gl == 0) seen = atomicCAS(list + ms, mx, key);
+        seen = __shfl(seen, 0, 16);
+        if (seen == mx) {
+            *new_max = key > mx2 ? key : mx2;
+            return true;
+        }
+    }
+}
+
 // ---- the same insertion by a group of eight lanes (long rows) -------------------------------
 // n (1..8) pieces in flight together: n - 1 from p, p + 128, ..., the last one from `last`
 __device__ inline void ef_load_pieces_strided(const void *p, const void *last, int n, ef_u32x4 (&q)[8])

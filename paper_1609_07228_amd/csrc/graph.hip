@@ -247,12 +247,28 @@ __device__ inline int drain_queue_row(const Proposal *queue, int count, u64 *gra
     return updates;
 }
 
-// The same for long rows: a group of eight threads per
+// The same for long rows in the join with rows in LDS: a group of sixteen threads per
+// proposal (nthr a multiple of 16; all threads of the block call this together).
+__device__ inline int drain_queue_g16(const Proposal *queue, int count, u64 *graph, u32 *worst, int K, int tid, int nthr)
+{
+    int updates = 0;
+    for (int e = tid >> 4; e < count; e += nthr >> 4) {
+        const Proposal p = queue[e];
+        u64 new_max;
+        if (ef_bounded_insert_g16(graph + (size_t)p.target * K, K, p.key, &new_max, tid & 15) && (tid & 15) == 0) {
+            atomicMin(worst + p.target, ef_dist_bits(new_max));
+            ++updates;
+        }
+    }
+    return updates;
+}
+
+// The same for long rows in the tile join: a group of eight threads per
 // proposal (nthr a multiple of 8; all threads of the block call this together).
-// gid (or null): the mirror of the rows' ids (graph_ids_kernel), kept up to date with the insertions.
+// gid: the mirror of the rows' ids (graph_ids_kernel), kept up to date with the insertions.
 template <bool ODD>      // (see ef_bounded_insert_g8)
 __device__ inline int drain_queue_g8(const Proposal *queue, int count, u64 *graph, u32 *worst, int K,
-                                     int tid, int nthr, int *gid = nullptr)
+                                     int tid, int nthr, int *gid)
 {
     int updates = 0;
     for (int e = tid >> 3; e < count; e += nthr >> 3) {
@@ -262,7 +278,7 @@ __device__ inline int drain_queue_g8(const Proposal *queue, int count, u64 *grap
         if (ef_bounded_insert_g8<ODD>(graph + (size_t)p.target * K, K, p.key, &new_max_bits, tid & 7, &slot) && slot >= 0) {
             atomicMin(worst + p.target, new_max_bits);
             // (a plain store: whatever order stores to a slot land in, the slot names an id that was in the row)
-            if (gid) gid[(size_t)p.target * K + slot] = ef_id(p.key);
+            gid[(size_t)p.target * K + slot] = ef_id(p.key);
             ++updates;
         }
     }
@@ -2097,7 +2113,7 @@ __device__ inline JoinLds join_lds_carve(float *smem, int cap_rows, int stride, 
     return l;
 }
 
-template <bool WIDE>      // WIDE: graph rows of fifty entries or more are read fifty entries at a time
+template <bool WIDE>      // WIDE: graph rows of fifty entries or more, sixteen threads per proposal
 __global__ void __launch_bounds__(512) join_kernel(const float *__restrict__ X, const float *__restrict__ norms, int d,
                             int dpad, int stride, u32 q4_magic, int K, u32 k_magic,
                             const int *__restrict__ work, const int *__restrict__ work_count,
@@ -2255,7 +2271,7 @@ __global__ void __launch_bounds__(512) join_kernel(const float *__restrict__ X, 
                     // ---- 4. drain (one form for rows of any length: a second one for even, aligned rows makes
                     //      degree 64 0.7 % slower and degree 100 1 % faster, 30 000 x 256 and 20 000 x 160) ----
                     updates += WIDE
-                                   ? drain_queue_g8<true>(lds.queue, lds.meta[3], graph, worst, K, tid, nthr)
+                                   ? drain_queue_g16(lds.queue, lds.meta[3], graph, worst, K, tid, nthr)
                                    : drain_queue(lds.queue, lds.meta[3], graph, worst, K, tid, nthr);
                     __syncthreads();
                     if (tid == 0) lds.meta[3] = 0;

@@ -508,6 +508,24 @@ def test_nndescent_tile_join_edges(ef, n, d, K, L):
         graph_equal(ef, graph, want)
 
 
+@pytest.mark.parametrize("n,d,K,L", [
+    (200, 132, 50, 10), (200, 129, 51, 12),      # two 16-byte pieces per lane, even and odd rows; unaligned vectors
+    (190, 160, 64, 16), (190, 133, 65, 16), (180, 144, 96, 12), (180, 132, 97, 12), (190, 131, 127, 8), (200, 132, 128, 8),
+    (230, 3, 50, 20), (230, 2, 81, 30),          # fewer than four coordinates: joins of every size take this kernel
+])
+def test_nndescent_rows_in_lds(ef, n, d, K, L):
+    """The join with rows in LDS on long graph rows: sixteen threads per insertion, ties of distance in half of the cases."""
+    rng = np.random.default_rng(n + d + K)
+    for X in (rng.standard_normal((n, d)).astype(np.float32), rng.integers(0, 2, (n, d)).astype(np.float32)):
+        Xd = dev(X)
+        (perm, off, nl), (operm, ooff, onl) = trees_equal(ef, X, 2, 16, 11)
+        graph, want = ef.efanna_init_graph(Xd, perm, off, nl, 16, K), oracle.init_graph(X, operm, ooff, onl, K)
+        for it in range(3):
+            ef.efanna_nndescent(Xd, graph, 1, L, 11, first_iter=it)
+            want = oracle.nndescent(X, *want[:3], 1, L, 11, iter0=it)
+            graph_equal(ef, graph, want)
+
+
 @pytest.mark.parametrize("K,L", [(1, 7), (2, 7), (3, 8), (5, 6), (8, 4), (9, 11), (15, 8), (16, 8), (17, 7),      # rows of one to eight
                                  (18, 7), (33, 2)])      # 16-byte pieces, odd and even, and longer ones
 def test_nndescent_row_lengths(ef, K, L):
