@@ -3792,9 +3792,12 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
     const int rows1 = reg_ok ? 32 : 0;
     const JoinClasses jc = join_classes(max_rows, reg_ok);
     // (a work list has n entries at most: of few points more blocks would only start and end)
-    // (up to 2^17 points half the blocks: late iterations have little for them; 10^5 x 128, degree 20 4.93 -> 4.89 ms,
-    // but 10^6 x 960 63.7 -> 64.2)
-    const int reg_grid = n > (1 << 17) ? kRegGrid : (int)min(n, (int64_t)kRegGrid / 2);
+    // (Vectors of at most 160 coordinates, up to 2^17 points: half the blocks, where starting them is what late
+    // iterations take.  Joins of at most 32, all blocks and half: 50 000 x 32, degree 10 522 and 495 us, 131 072 x 32 982 and
+    // 948, 131 072 x 128 1255 and 1242, degree 20 2989 and 2980, 10^5 x 133, degree 7 966 and 938; beyond, 250 000 x 32 1605
+    // both, 250 000 x 128 2124 and 2135, degree 20 5314 and 5358.  Longer vectors: 10^5 x 200, degree 12 1601 and 1607,
+    // 50 000 x 960, degree 10 2140 and 2168, 10^5 x 960 4170 and 4220, degree 4 1651 and 1736.)
+    const int reg_grid = (int)min(n, (int64_t)(d <= 160 && n <= (1 << 17) ? kRegGrid / 2 : kRegGrid));
     struct Shape {
         int cap_rows, threads, s_cap, q_cap, grid;
         size_t lds;
