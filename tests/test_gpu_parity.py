@@ -493,6 +493,9 @@ def test_nndescent_more_shapes(ef, n, d, T, S, K, L, I):
     (230, 64, 100, 50),      # most pairs known beforehand: hits settled many times per join
     (400, 4, 4, 64),         # one load per row of ids, few of the many wants known
     (200, 96, 128, 64),      # places up to 199, the longest rows
+    # insertions by eight lanes: three to eight 16-byte pieces a lane, rows that end with a lane's piece and short of it
+    (180, 32, 34, 10), (180, 20, 48, 10), (180, 32, 49, 9), (180, 32, 65, 16), (190, 21, 72, 16), (190, 32, 79, 16), (190, 32, 80, 16),
+    (190, 32, 81, 16), (190, 24, 95, 16), (190, 32, 96, 16), (190, 32, 97, 16), (190, 32, 112, 16), (190, 23, 113, 16), (190, 32, 127, 16),
 ])
 def test_nndescent_tile_join_edges(ef, n, d, K, L):
     """Joins of more than 32 vectors with lists that cover most of the data (the oracle's graph, every iteration)."""
@@ -526,10 +529,12 @@ def test_nndescent_rows_in_lds(ef, n, d, K, L):
             graph_equal(ef, graph, want)
 
 
-@pytest.mark.parametrize("K,L", [(1, 7), (2, 7), (3, 8), (5, 6), (8, 4), (9, 11), (15, 8), (16, 8), (17, 7),      # rows of one to eight
-                                 (18, 7), (33, 2)])      # 16-byte pieces, odd and even, and longer ones
+@pytest.mark.parametrize("K,L", [(1, 7), (2, 7), (3, 8), (4, 8), (5, 6), (6, 8), (7, 8), (8, 4), (9, 11), (10, 7), (11, 8), (12, 8), (13, 8),
+                                 (14, 8), (15, 8), (16, 8),      # rows of one to eight 16-byte pieces, odd and even
+                                 (17, 7), (18, 7), (33, 2)])     # longer ones
 def test_nndescent_row_lengths(ef, K, L):
-    """Insertions of the joins of at most 32 vectors, many of them to the same rows; ties of distance among them."""
+    """Insertions of the joins of at most 32 vectors, many of them to the same rows; ties of distance among them, and
+    full rows of distance 0 (copies of a point) whose entries are replaced by smaller ids."""
     rng = np.random.default_rng(K)
     for X in (rng.standard_normal((500, 24)).astype(np.float32), rng.integers(0, 3, (500, 7)).astype(np.float32)):
         Xd = dev(X)
@@ -539,6 +544,17 @@ def test_nndescent_row_lengths(ef, K, L):
             ef.efanna_nndescent(Xd, graph, 1, L, 11, first_iter=it)
             want = oracle.nndescent(X, *want[:3], 1, L, 11, iter0=it)
             graph_equal(ef, graph, want)
+    c = 4 * K + 2                                              # copies of each point
+    X = rng.standard_normal((6, 9)).astype(np.float32)[rng.permutation(6 * c) % 6]
+    same = [np.flatnonzero((X == x).all(axis=1)) for x in X]
+    ids = np.stack([np.sort(rng.permutation(m[m != i])[:K]) for i, m in enumerate(same)]).astype(np.int32)
+    start = (ids, np.zeros(ids.shape, np.float32), np.ones(ids.shape, np.uint8))
+    graph, want = ef.efanna_set_graph(dev(ids), dev(start[1])), start
+    for it in range(4):
+        ef.efanna_nndescent(dev(X), graph, 1, L, 11, first_iter=it)
+        want = oracle.nndescent(X, *want[:3], 1, L, 11, iter0=it)
+        graph_equal(ef, graph, want)
+    assert (want[1] == 0).all() and (want[0].sum(axis=1) < ids.sum(axis=1)).mean() > 0.5
 
 
 @pytest.mark.parametrize("d", [129, 132, 191, 256, 260])      # pieces of one coordinate, of four, ...; rows unaligned for odd d
@@ -722,6 +738,36 @@ def test_random_start_with_repeated_ids(ef, K, L, marks):
         ef.efanna_nndescent(dev(X), graph, 1, L, 5, first_iter=it, workspace=ws)
         want = oracle.nndescent(X, *want[:3], 1, L, 5, iter0=it)
         graph_equal(ef, graph, want)
+
+
+@pytest.mark.parametrize("n,d,K,L", [
+    (500, 16, 10, 6), (500, 132, 10, 6),        # joins of at most 16 and at most 32 vectors in registers
+    (300, 32, 40, 20), (300, 32, 17, 20),       # ... and of more, tile by tile
+    (300, 132, 40, 20), (300, 132, 64, 20), (400, 3, 10, 10),      # rows in LDS
+])
+@pytest.mark.parametrize("cross", [False, True])
+def test_insertion_counts(ef, n, d, K, L, cross):
+    """stats column 1 in a workspace of junk and of a larger call: at least the entries that are new in the graph, at
+    most two per pair; none at all from the exact graph."""
+    rng = np.random.default_rng(n + d + K)
+    X = dev(rng.standard_normal((2 * n, d)).astype(np.float32))
+    ws = torch.full((ef.lib().efanna_nndescent_workspace_bytes(2 * n, K, L),), 255, dtype=torch.uint8, device="cuda:0")
+    for rows in (2 * n, n):      # the junk of the first call is what the second one finds
+        Xr = X[:rows]
+        graph = ef.efanna_init_graph(Xr, *ef.efanna_build_trees(Xr, 2, 12, 5), 12, K)
+        before = host(ef.efanna_get_graph(graph)[0])
+        stats = host(ef.efanna_nndescent(Xr, graph, 2, L, 5, workspace=ws, cross_old=cross))
+        after = host(ef.efanna_get_graph(graph)[0])
+        fresh = sum(len(set(a) - set(b) - {-1}) for a, b in zip(after.tolist(), before.tolist()))
+        assert fresh > 0 and fresh <= stats[:, 1].sum()
+        assert (stats[:, 1] <= 2 * stats[:, 0]).all()
+    a = torch.arange(n, dtype=torch.int32, device="cuda:0").repeat_interleave(n)
+    dist = ef.efanna_pair_distances(X[:n], a, torch.arange(n, dtype=torch.int32, device="cuda:0").repeat(n)).view(n, n)
+    dist.fill_diagonal_(float("inf"))
+    near, ids = dist.sort(dim=1, stable=True)      # (ties by id)
+    graph = ef.efanna_set_graph(ids[:, :K].int().contiguous(), near[:, :K].contiguous())
+    stats = host(ef.efanna_nndescent(X[:n], graph, 1, L, 5, workspace=ws, cross_old=cross))
+    assert stats[0, 0] > 0 and stats[0, 1] == 0
 
 
 def test_nndescent_resume_and_recall(ef):
