@@ -588,18 +588,10 @@ __device__ inline bool ef_bounded_insert_g16(u64 *list, int cap, u64 key, u64 *n
 }
 
 // ---- the same insertion by a group of eight lanes (long rows) -------------------------------
-// n (1..8) pieces in flight together: n - 1 from p, p + 128, ..., the last one from `last`
+// n (2..8: rows of 17 entries and more) pieces in flight together: n - 1 from p, p + 128, ..., the last one from `last`
 __device__ inline void ef_load_pieces_strided(const void *p, const void *last, int n, ef_u32x4 (&q)[8])
 {
     switch (n) {
-    case 1:
-        asm volatile(
-                     "global_load_dwordx4 %0, %1, off sc1\n\t"
-                     "s_waitcnt vmcnt(0)"
-                     : "=&v"(q[0])
-                     : "v"(last)
-                     : "memory");
-        break;
     case 2:
         asm volatile(
                      "global_load_dwordx4 %0, %2, off offset:0 sc1\n\t"
@@ -692,7 +684,7 @@ __device__ inline void ef_load_pieces_strided(const void *p, const void *last, i
 #define EF_DPP_XOR2 0x4E
 #define EF_DPP_HALF_MIRROR 0x141
 
-// The entry `key` is offered to a graph row of at most 128 entries (keys that agree but for the new mark are
+// The entry `key` is offered to a graph row of 17 .. 128 distinct entries (keys that agree but for the new mark are
 // the same entry).  All eight lanes of a group (lane gl = 0..7 of it) call this with the same arguments and get
 // the same result.  Lane gl reads the 16-byte pieces gl, gl + 8, ... of the row, so that the group fetches 128
 // contiguous bytes per load, all of a row in one round trip.

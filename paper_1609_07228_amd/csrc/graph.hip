@@ -2431,23 +2431,24 @@ prepare_wave_kernel(const int *__restrict__ nw, const int *__restrict__ od,
 // the vectors fit them in one piece (ONE: d <= 128): lane (a, g) fetches the matching
 // pieces of row b from lane (b, g) with cross-lane reads, accumulates the four partial
 // sums it owns (coordinates = 4g..4g+3 mod 16, ascending) and the 16 partial sums are
-// added in the fixed tree across the four lanes of row a.  Longer vectors are re-read
-// from memory (they are still in L2) by one 16-lane group per pair.
+// added in the fixed tree across the four lanes of row a.  Longer vectors take no filter:
+// every pair is evaluated from the registers as the coordinates pass (see below).
 // Requires d >= 4.
 
 // where the survivors of Gram blocks (0,0), (0,1), (1,1) start in the LDS survivor buffer
 __device__ constexpr int kSurvBase[3] = {0, 120, 376};
-// d > 128: up to this many surviving pairs of a Gram block (per 16 rows) are read pair by pair
-constexpr int kFewPairs = 4;
-// d <= 128: more survivors than this inside one set of sixteen rows and all its pairs are evaluated by row rotations
+// d <= 128, joins of at most 16: more survivors than this and all pairs are evaluated by row rotations
 constexpr int kDenseSurvivors = 24;
 // d > 128: up to this many new members, or rows of the second set of sixteen, are broadcast to the others; the
 // registers set the limits.  Rotations meet all pairs whatever the join asks for, 512 vector instructions per
 // 8 KB of rows, 2048 per 16 KB of 17..32 rows, which also had to be streamed twice: the vector ALU was busy for
 // 71 to 90 % of the joins' time.  10^6 x 960, iterations 1 to 6: 13.0 14.3 12.7 10.5 7.1 3.9 -> 11.0 12.6 10.3 7.6 4.7 2.6 ms,
-// from the fourth on 5.6 to 5.8 TB/s; build 78.0 -> 64.3.  (For d <= 128 the same next to the filter's code spilled
+// from the fourth on 5.6 to 5.8 TB/s; build 78.0 -> 64.3.  Unaligned rows, whose kernel for two sets keeps 48 registers
+// in scratch memory (26 before), gain as much: NN-descent of 10 000 x 957 1.22 -> 1.09 ms, of x 960 1.23 -> 1.08; 20 000 x 131
+// at degree 16 1.40 -> 1.16, x 132 1.29 -> 1.02.  (For d <= 128 the same next to the filter's code spilled
 // and cost a quarter.)
-constexpr int kFewNew = 8, kFewRest = 8;
+constexpr int kFewNew = 8, kFewRest = 8;      // (EF_EACH_FEW names eight of either)
+static_assert(kFewNew <= 8 && kFewRest <= 8 && kFewNew % 4 == 0 && kFewRest % 4 == 0, "EF_EACH_FEW");
 
 // One surviving pair (rows a, b of the point's list) per lane with `mine` set: its distance is
 // offered to row a and to row b where it passes their thresholds.  All lanes of the wave call
@@ -2480,7 +2481,7 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
                 const int *__restrict__ work, const int *__restrict__ work_count, int q_cap,
                 float margin_rel, float thr_scale, float u_rel, float rho0, const int *__restrict__ ulist,
                 const int2 *__restrict__ ucount, int ucap, u64 *graph, u32 *worst,
-                int *__restrict__ upd_block, int mode, int dense_min, const u32 *__restrict__ xmax)
+                int *__restrict__ upd_block, int mode, const u32 *__restrict__ xmax)
 {
     // mode 0: every pair of the join, fresh entries marked new.  1: only pairs of two new members.
     // 2: only pairs of a new and an old member, fresh entries marked old (the literal marking of
@@ -2499,7 +2500,7 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
     float *rr = sq + R;                           // [R] rounding radius      } the operands)
     u32 *surv = (u32 *)(rr + R);                  // [S_CAP] surviving pairs
     Proposal *queue = (Proposal *)(surv + align4(S_CAP));   // [q_cap]
-    const int lane = threadIdx.x, r16 = lane & 15, g = lane >> 4, gl = r16, grp = g;
+    const int lane = threadIdx.x, r16 = lane & 15, g = lane >> 4;
     const int dirn = (EF_ROW_ROR(r16, 1) - r16) & 15;      // a rotation by t brings row r + t * dirn to row r
     const int count = *work_count;
     // The filter works on the vectors times a power of two that suits half precision (see ef_f16_scale).
@@ -2528,7 +2529,6 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
         if constexpr (KT != 0) return drain_queue_row(from, cnt, graph, worst, len, lane, EF_WAVE);
         else return drain_queue(from, cnt, graph, worst, len, lane, EF_WAVE);
     };
-    auto drain_mid = drain;
     for (; i >= 0; w += gridDim.x) {
         // ---- 0. the point's U_new ++ U_old (the loop ends with a barrier: LDS is free) -------
         const int m_new = c_pre.x, m = c_pre.y;
@@ -2580,7 +2580,7 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
         // place that drains is a copy of the insertion, in code and in registers)
         auto offer = [&](auto may_drain, bool mine, float dist, int a, int b) {
             if (decltype(may_drain)::value && q_fill + 2 * EF_WAVE > q_cap) {      // a step adds at most two proposals per lane
-                updates += drain_mid(queue, q_fill);
+                updates += drain(queue, q_fill);
                 q_fill = 0;
                 __syncthreads();
             }
@@ -2628,10 +2628,11 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
                 }
             }
         } else if (few_rest) {
-            float P[8][4], PX[kFewNew][4], PB[kFewNew][4];
+            float P[8][4], PX[kFewRest][4], PB[kFewRest][4];
 #pragma unroll
-            for (int t = 0; t < kFewNew; ++t) {
-                P[t][0] = P[t][1] = P[t][2] = P[t][3] = 0.0f;
+            for (int t = 0; t < 8; ++t) P[t][0] = P[t][1] = P[t][2] = P[t][3] = 0.0f;
+#pragma unroll
+            for (int t = 0; t < kFewRest; ++t) {
                 PX[t][0] = PX[t][1] = PX[t][2] = PX[t][3] = 0.0f;
                 PB[t][0] = PB[t][1] = PB[t][2] = PB[t][3] = 0.0f;
             }
@@ -2662,7 +2663,7 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
             offer_rotation(std::false_type{}, 0);
             offer_rotation(std::false_type{}, 1);
 #pragma unroll
-            for (int t0 = 0; t0 < kFewNew; t0 += 4) {
+            for (int t0 = 0; t0 < kFewRest; t0 += 4) {
                 if (16 + t0 >= m) break;
                 const int x = 16 + t0 + g, y = 16 + r16;      // the broadcast row; the lane's row of the second set
                 const float dist = reduce_rotations4(reinterpret_cast<const float (&)[4][4]>(PX[t0]));
@@ -2859,42 +2860,34 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
             for (int q = 0; q < (NB > 1 ? 3 : 1); ++q) {
                 const int bi = q == 2 ? 1 : 0, bj = q == 0 ? 0 : 1;
                 const int n_q = n_surv[q];
-                // Many survivors inside one set of sixteen rows (early iterations: most pairs
+                // Joins of at most 16, many survivors (early iterations: most pairs
                 // pass): all 120 pairs by row rotations, as for long vectors, cost what two rounds
                 // of sixteen survivors cost.  The filter never drops a pair that would pass a
                 // threshold, so which way a pair takes makes no difference to what is proposed.
-                if (NB == 1 && n_q > dense_min) {
+                if (NB == 1 && n_q > kDenseSurvivors) {
                     const int lane = ef_opaque(threadIdx.x), r16 = lane & 15, g = lane >> 4;
-                    const float4 (&rows)[8] = reinterpret_cast<const float4 (&)[8]>(*(q == 0 ? va : vb));
-                    const int n_pieces = (d + 15) >> 4, base = 16 * bi;
+                    const int n_pieces = (d + 15) >> 4;
 #pragma unroll
                     for (int half = 0; half < 2; ++half) {      // rotations 1..4, then 5..8
                         float P[4][4];
 #pragma unroll
                         for (int t = 0; t < 4; ++t) P[t][0] = P[t][1] = P[t][2] = P[t][3] = 0.0f;
                         if (half == 0) {
-                            init_round<1>(rows, n_pieces, P[0]);
-                            init_round<2>(rows, n_pieces, P[1]);
-                            init_round<3>(rows, n_pieces, P[2]);
-                            init_round<4>(rows, n_pieces, P[3]);
+                            init_round<1>(va, n_pieces, P[0]);
+                            init_round<2>(va, n_pieces, P[1]);
+                            init_round<3>(va, n_pieces, P[2]);
+                            init_round<4>(va, n_pieces, P[3]);
                         } else {
-                            init_round<5>(rows, n_pieces, P[0]);
-                            init_round<6>(rows, n_pieces, P[1]);
-                            init_round<7>(rows, n_pieces, P[2]);
-                            init_round<8>(rows, n_pieces, P[3]);
+                            init_round<5>(va, n_pieces, P[0]);
+                            init_round<6>(va, n_pieces, P[1]);
+                            init_round<7>(va, n_pieces, P[2]);
+                            init_round<8>(va, n_pieces, P[3]);
                         }
                         const float dist = reduce_rotations4(P);
                         const int rot = 4 * half + 1 + g, b = (r16 + dirn * rot) & 15;
                         const bool once = rot != 8 || r16 < b;      // rotation 8 meets every pair from both ends
-                        if (NB > 1 && q_fill + 2 * EF_WAVE > q_cap) {
-                            updates += drain_mid(queue, q_fill);
-                            q_fill = 0;
-                            __syncthreads();
-                        }
-                        q_fill = propose_pair(queue, q_fill,
-                                              once && base + r16 < m && base + b < m && base + min(r16, b) < m_new &&
-                                                  mode_ok(base + max(r16, b)),
-                                              dist, base + r16, base + b, thr, uid, mark);
+                        q_fill = propose_pair(queue, q_fill, once && r16 < m && b < m && min(r16, b) < m_new && mode_ok(max(r16, b)),
+                                              dist, r16, b, thr, uid, mark);
                         __syncthreads();
                     }
                     continue;
@@ -2926,7 +2919,7 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
                     // NB = 1: the queue is sized so that a point's proposals always fit (at most 240
                     // on top of fewer than q_cap / 2): no drain while the operands are live
                     if (NB > 1 && q_fill + 32 > q_cap) {      // a round adds at most two proposals per pair
-                        updates += drain_mid(queue, q_fill);
+                        updates += drain(queue, q_fill);
                         q_fill = 0;
                         __syncthreads();
                     }
@@ -3363,7 +3356,8 @@ xmax_kernel(const float *__restrict__ X, size_t total, u32 *xmax)
 // per-iteration counters from the per-block partial sums: part[b] = (pairs evaluated, vectors
 // gathered, vectors gathered by the smallest join class) of prepare block b; upd_block: insertions
 // per join block
-// (64 blocks of 1024 threads: with 16 of 256 a thread had thirty loads one after the other, 12 us for 10^6 points)
+// (a block of 1024 threads per 2048 partial sums, 64 blocks at most - 33 for 10^6 points of degree 10: with 16 blocks of
+// 256 a thread had thirty loads one after the other, 12 us for 10^6 points)
 constexpr int kStatsThreads = 1024;
 __global__ void __launch_bounds__(kStatsThreads)
 stats_kernel(const long long *__restrict__ part, int n_part, const int *__restrict__ upd_block, int n_upd_block, u64 *stats)
@@ -4032,7 +4026,7 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
         X, d, K, w.work + (size_t)(LIST) * n, w.work_count + (LIST), reg_q_cap_for(16 * NB), \
         (ONE) ? margin_f16 : margin_rel, (ONE) ? thr_scale_f16 : thr_scale, u_f16, rho0_f16,       \
         w.ulist, w.ucount, max_rows, graph, w.worst, w.upd_block + n_upd, mode,                    \
-        kDenseSurvivors, w.xmax)
+        w.xmax)
     // (a row length of 10 is compiled in: 3 % off the joins of 17..32 vectors; rows of up to sixteen entries in general go
     // in one piece, see ef_bounded_insert_row)
 #define EF_JOIN_REG_A(NB, ONE, LIST, ALIGNED)                                                       \
