@@ -2569,12 +2569,15 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
         // modifier on the subtract again) and meets all the others, 64 vector instructions per new member, row
         // set and 128 coordinates; all rows are read once.  17..32 rows with few in the second set: rotations for
         // the pairs of the first set, and the rows of the second are broadcast; again one pass.
-        // The latter up to degree 32 only: a broadcast queues sixteen proposals to one row side by side, they are
-        // applied together, and whoever finds its slot changed scans the row again.  (Joins of 17..32, 20 000 x 132,
-        // without and with: degree 64 3.17 and 3.53 ms, 48 1.87 and 2.00, 40 1.39 and 1.45, 32 1.03 both, 24 0.80 and 0.77;
-        // 200 000 x 132, degree 64 17.2 and 19.9.)
+        // Both up to degree 32 only: a broadcast queues sixteen proposals to one row side by side, they are
+        // applied together, and whoever finds its slot changed scans the row again.  Rotations and broadcasts:
+        // rows of the second set, joins of 17..32 of 20 000 x 132, degree 64 3.17 and 3.53 ms, 48 1.87 and 2.00, 40 1.39 and 1.45,
+        // 32 1.03 both, 24 0.80 and 0.77; 200 000 x 132, degree 64 17.2 and 19.9.  New members, NN-descent of 30 000 x 200
+        // with samples of 3 and 4: degree 100 6.67 and 7.20 ms, 62 4.38 and 4.61, 44 2.99 and 3.04, 40 2.27 and 2.28, 33 2.66 and 2.64
+        // (samples of 8: degree 62 7.07 and 6.99, 40 4.40 and 4.37).
         constexpr bool rotated = !ONE;
-        const bool few = rotated && m_new <= kFewNew, few_rest = rotated && NB > 1 && (KT != 0 || K <= 32) && m <= 16 + kFewRest;
+        const bool broadcasts = rotated && (KT != 0 || K <= 32);
+        const bool few = broadcasts && m_new <= kFewNew, few_rest = broadcasts && NB > 1 && m <= 16 + kFewRest;
         float two[2] = {0.f, 0.f}, two_b[2] = {0.f, 0.f};
         // may_drain: only where a join can propose more than the queue holds (see reg_q_cap_for; every
         // place that drains is a copy of the insertion, in code and in registers)
