@@ -2474,7 +2474,8 @@ __device__ inline int propose_pair(Proposal *queue, int fill, bool mine, float d
     return fill + __popcll(mask_b);
 }
 
-// KT: the row length if fixed at compile time (the row scans unroll), else -16 (2 .. 16 entries) or 0
+// KT: the row length if fixed at compile time (the row scans unroll), else -16 (2 .. 16 entries), -24 (17 .. 24, long vectors
+// only) or 0
 template <int NB, bool ONE, int KT, bool ALIGNED>
 __global__ void __launch_bounds__(EF_WAVE) __attribute__((amdgpu_waves_per_eu(NB > 1 ? 3 : 4)))
 join_reg_kernel(const float *__restrict__ X, int d, int K_,
@@ -2526,7 +2527,7 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
         const int lane = ef_opaque(threadIdx.x);
         int len = K;
         if constexpr (KT <= 0) asm volatile("" : "+s"(len));      // (see ef_opaque)
-        if constexpr (KT != 0) return drain_queue_row(from, cnt, graph, worst, len, lane, EF_WAVE);
+        if constexpr (KT > 0 || KT == -16) return drain_queue_row(from, cnt, graph, worst, len, lane, EF_WAVE);
         else return drain_queue(from, cnt, graph, worst, len, lane, EF_WAVE);
     };
     for (; i >= 0; w += gridDim.x) {
@@ -2569,15 +2570,15 @@ join_reg_kernel(const float *__restrict__ X, int d, int K_,
         // modifier on the subtract again) and meets all the others, 64 vector instructions per new member, row
         // set and 128 coordinates; all rows are read once.  17..32 rows with few in the second set: rotations for
         // the pairs of the first set, and the rows of the second are broadcast; again one pass.
-        // Both up to degree 32 only: a broadcast queues sixteen proposals to one row side by side, they are
-        // applied together, and whoever finds its slot changed scans the row again.  Rotations and broadcasts:
-        // rows of the second set, joins of 17..32 of 20 000 x 132, degree 64 3.17 and 3.53 ms, 48 1.87 and 2.00, 40 1.39 and 1.45,
-        // 32 1.03 both, 24 0.80 and 0.77; 200 000 x 132, degree 64 17.2 and 19.9.  New members, NN-descent of 30 000 x 200
-        // with samples of 3 and 4: degree 100 6.67 and 7.20 ms, 62 4.38 and 4.61, 44 2.99 and 3.04, 40 2.27 and 2.28, 33 2.66 and 2.64
-        // (samples of 8: degree 62 7.07 and 6.99, 40 4.40 and 4.37).
+        // Not with long graph rows: a broadcast queues sixteen proposals to one row side by side, they are applied
+        // together, and whoever finds its slot changed scans the row again.  Rows of the second set are broadcast up to
+        // degree 24 (rotations and broadcasts: joins of 17..32 of 100 000 x 132, degree 17 3.35 and 2.88 ms, 20 3.54 and 3.12, 24
+        // 4.03 and 3.89, 28 4.33 and 4.36, 30 4.47 and 4.59; of 20 000 x 132, degree 40 1.39 and 1.45, 64 3.17 and 3.53), in a
+        // kernel of their own: next to them the rotations spill 47 registers instead of 34 where rows are unaligned.  New
+        // members up to degree 32 (NN-descent of 30 000 x 200, samples of 3 and 4, degree 100 6.67 and 7.20 ms, 62 4.38 and
+        // 4.61, 44 2.99 and 3.04, 40 2.27 and 2.28, 33 2.66 and 2.64; samples of 8, 62 7.07 and 6.99).
         constexpr bool rotated = !ONE;
-        const bool broadcasts = rotated && (KT != 0 || K <= 32);
-        const bool few = broadcasts && m_new <= kFewNew, few_rest = broadcasts && NB > 1 && m <= 16 + kFewRest;
+        const bool few = rotated && (KT != 0 || K <= 32) && m_new <= kFewNew, few_rest = rotated && NB > 1 && KT != 0 && m <= 16 + kFewRest;
         float two[2] = {0.f, 0.f}, two_b[2] = {0.f, 0.f};
         // may_drain: only where a join can propose more than the queue holds (see reg_q_cap_for; every
         // place that drains is a copy of the insertion, in code and in registers)
@@ -4031,10 +4032,11 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
         w.ulist, w.ucount, max_rows, graph, w.worst, w.upd_block + n_upd, mode,                    \
         w.xmax)
     // (a row length of 10 is compiled in: 3 % off the joins of 17..32 vectors; rows of up to sixteen entries in general go
-    // in one piece, see ef_bounded_insert_row)
+    // in one piece, see ef_bounded_insert_row; -24: see kFewRest's use)
 #define EF_JOIN_REG_A(NB, ONE, LIST, ALIGNED)                                                       \
     do {                                                                                           \
         if (K == 10) EF_JOIN_REG_K(NB, ONE, LIST, 10, ALIGNED);                                    \
+        else if (!(ONE) && (NB) > 1 && K > 16 && K <= 24) EF_JOIN_REG_K(NB, ONE, LIST, (ONE) || (NB) == 1 ? 0 : -24, ALIGNED); \
         else if (K > 16 || K < 2) EF_JOIN_REG_K(NB, ONE, LIST, 0, ALIGNED);                        \
         else EF_JOIN_REG_K(NB, ONE, LIST, -16, ALIGNED);                                           \
     } while (0)

@@ -559,7 +559,7 @@ def test_nndescent_row_lengths(ef, K, L):
 
 @pytest.mark.parametrize("d", [129, 132, 191, 256, 260])      # pieces of one coordinate, of four, ...; rows unaligned for odd d
 @pytest.mark.parametrize("K,L", [(10, 2), (10, 10), (16, 8), (7, 12),      # few new members; second sets of up to 8 and of more rows
-                                 (32, 6), (33, 6), (49, 4)])               # ... which are not broadcast from degree 33 on
+                                 (17, 7), (24, 4), (25, 3), (32, 6), (33, 6), (49, 4)])      # ... broadcast up to degrees 32 and 24
 def test_nndescent_long_vectors_few_and_many_new(ef, d, K, L):
     """Joins of at most 32 long vectors: new members broadcast, rows of the second set broadcast, rotations; both markings."""
     rng = np.random.default_rng(d + K)
