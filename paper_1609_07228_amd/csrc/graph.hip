@@ -3473,7 +3473,9 @@ get_graph_group_kernel(const u64 *__restrict__ graph, int n, int K, int *__restr
 // Rows hold distinct entries: the ranks of sampling and of get_graph, and the insertions, rely on it (two entries
 // of one key have the same rank, and the place after it would keep what was there before).  A random start may
 // draw an id twice, so an id that an earlier slot of the row names leaves its slot empty.  A thread per slot of the
-// block's kBlock / K rows; the threads of a row walk its slots together, in LDS.
+// block's kBlock / K rows; the threads of a row walk its slots together, in LDS.  (Without and with the walk: 10^6 rows
+// of 10 35 and 52 us, of 100 0.38 and 1.09 ms, vector instructions.  Four ids per LDS read, or eight reads in
+// flight: 1.4 ms and 1.3.)
 __global__ void __launch_bounds__(kBlock)
 set_graph_kernel(u64 *graph, size_t n, int K, const int *__restrict__ ids, const float *__restrict__ dists,
                  const unsigned char *__restrict__ flags)
