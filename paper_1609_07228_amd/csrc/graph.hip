@@ -1558,13 +1558,16 @@ reverse_overflow_kernel(const Overflow *__restrict__ overflow, size_t ovf_region
 //      bucket (a range of up to 1024 targets, of 512 if L > 16: the lists of a range have to fit the
 //      LDS), and writes them to its own part of the offer array, bucket after bucket;
 //      table[bucket][block] = start << 16 | count of that run;
-//   2. a list block (one per bucket) walks the runs of its bucket, one thread per offer, and
-//      enters every key into the target's list in LDS with the bounded insertion; lists and
-//      counts (filled slots) go out in one contiguous piece.
+//   2. a list block (one per bucket) walks the runs of its bucket, sorts the offers by target in LDS and
+//      writes every target's list (bucket_lists_kernel).
 // Whatever the order of the offers, a list ends up with the L smallest keys offered to it.
 
 constexpr int kBktRows = 1024;        // source rows per offer block, at most
 constexpr int kBktThreads = 1024;
+constexpr int kBktMany = 800;         // as many buckets are enough
+constexpr int kInsertTo = 6;          // lists up to this length take the bounded insertion (see bucket_insert_kernel)
+constexpr int kBktFew = 4;            // offers per thread up to which it looks for their runs
+constexpr int kBktWords = 16;         // offers a thread of a list block holds while they are sorted
 constexpr int kBktMaxRuns = 2 * kBktThreads;    // buckets and offer blocks a block-wide scan of two per thread takes
 
 // log2 of the targets per bucket where the buckets are as large as LDS lets them be
@@ -1586,28 +1589,41 @@ __host__ __device__ inline bool bucketed_lists(int64_t n, int K, int L)
 // ranges that make at most 512 buckets (from 32 targets up).  (The table of runs is then larger, up to
 // 8 bytes per point, and lies in the half of the reverse-old lists' room that 32-bit sources leave
 // free: L >= 4.)  Builds of 2500 x 24 / 10^4 x 32 / 6 10^4 x 100 with degree 10, and of the last with degree 20: 660 ->
-// 575 us, 890 -> 815, 2135 -> 2085, 3745 -> 3645; from 10^5 points on nothing is gained (the insertions of popular points decide), and at 2.6 10^5 2 % lost.
+// 575 us, 890 -> 815, 2135 -> 2085, 3745 -> 3645.
+// Beyond, ranges of 128 targets up, as large as make kBktMany of them (all list kernels of 10^5 points, degree 10, from a random
+// start: 390 -> 328 us; degree 20 235 -> 230), and no larger than lets 1024 threads hold ten offers each.  (More of them
+// for a million points, 1954 instead of 977: 998 -> 1039, and the offer kernels, which count and write runs per range, 1076 -> 1190.)
 struct BucketShape {
     int row_bits, blocks;           // log2 of the source rows of an offer block, number of blocks
     int shift, buckets, threads;    // log2 of the targets of a bucket, number of buckets, threads of a list block
+    bool table_behind;              // the table of runs lies behind the reverse-old lists' 32-bit sources
 };
-inline BucketShape bucket_shape(int64_t n, int L)
+inline BucketShape bucket_shape(int64_t n, int K, int L)
 {
+    const int per = K > L ? K : L;      // offers per target on average, if all rows are full
     BucketShape b;
+    auto cut = [&](int row_bits, int shift) {
+        b.row_bits = row_bits;
+        b.shift = shift;
+        b.blocks = (int)((n + (1 << row_bits) - 1) >> row_bits);
+        b.buckets = (int)((n - 1) >> shift) + 1;
+        b.threads = (per <= 10 || L <= kInsertTo ? 1 : per <= 20 ? 2 : 4) << shift;
+        b.threads = b.threads < 256 ? 256 : b.threads > kBktThreads ? kBktThreads : b.threads;
+        b.table_behind = (int64_t)b.blocks * b.buckets <= n * L;
+    };
     if (n <= (1 << 16) && L >= 4) {
-        b.row_bits = 8;
-        b.shift = 5;
-        while (((n - 1) >> b.shift) + 1 > 512) ++b.shift;
-        b.blocks = (int)((n + 255) >> 8);
-        b.buckets = (int)((n - 1) >> b.shift) + 1;
-        b.threads = b.shift <= 7 ? 256 : b.shift == 8 ? 512 : 1024;
-        if ((int64_t)b.blocks * b.buckets <= n * L) return b;
+        int shift = 5;
+        while (((n - 1) >> shift) + 1 > 512) ++shift;
+        cut(8, shift);
+        if (b.table_behind) return b;
     }
-    b.row_bits = 10;
-    b.shift = bucket_shift(L);
-    b.blocks = (int)((n + kBktRows - 1) / kBktRows);
-    b.buckets = (int)((n - 1) >> b.shift) + 1;
-    b.threads = kBktThreads;
+    const int top = per <= 10 ? 10 : per <= 20 ? 9 : 8;
+    for (int shift = 7; L > kInsertTo && (shift <= 9 || shift <= top); ++shift) {
+        cut(10, shift);
+        if (b.table_behind && b.buckets <= (shift < top ? kBktMany : kBktMaxRuns) && b.blocks <= 2 * b.threads) return b;
+    }
+    cut(10, bucket_shift(L));
+    b.table_behind = false;
     return b;
 }
 
@@ -1722,38 +1738,441 @@ reverse_old_bucket_kernel(const int *__restrict__ od, int n, int K, const u64 *_
 }
 
 // The lists of one bucket.  run_cap: offers per part of an offer block (its rows * L or * K).
-// Every key goes through the bounded insertion; all slots start as the largest key, so a list
-// fills from slot 0 up and then keeps its L smallest keys.
-// LDS: lists [bucket's targets * L] u64, scan [n_blocks + 1] and start [n_blocks] int;
+// Offers are sorted by target in LDS (histogram, prefix sum, scatter); a list that was offered no more than L
+// sources is written as it is, without a hash, and the others choose their L smallest keys: up to 32 offers
+// sixteen lanes rank them by row rotations of the hashes, up to 512 a wave finds a bound that L hashes lie below
+// bit by bit from ballots, and of more only those below a bound that some L + 6 sqrt(L) hashes lie below
+// are sorted at all (all threads of the block look at the popular points' offers).
+// Where the offers do not fit the threads' registers they are read twice, and where what is to be sorted does not
+// fit the LDS, keys enter lists there by the bounded insertion, as many targets at a time as there is room for.
+// What bounds it: instruction issue in the first iterations (10^6 points of degree 10: 3900 -> 3100 wave instructions per
+// wave of a launch, half of them choosing), a fixed 25 us of run descriptors and barriers in the last.  All
+// sixteen launches of that build 1338 -> 1010 us, with the bounded insertion for all (a list scanned in LDS per offer, again
+// whenever another thread was first) before; degree 20, 10^5 points 793 -> 231, where popular points' insertions waited for each other.
+// LDS: area words, run_at [n_blocks + 1] (later offs [targets]), hist [targets], order and bound [targets] of 16 bits;
 // n_blocks <= twice the threads, at least one thread per target.
-// What the time is made of (headline workload, 82 us per launch on average, 170 us for the
-// ten million offers of the first iteration): 18 us fixed, about 5 ns per thousand offers to
-// find and load them, the rest the insertions; by the counters the SIMDs issue an instruction
-// in 70 to 85 % of their clocks (500 to 600 instructions per 64 offers), the LDS is active a third
-// of the time.  Variants that were no faster or slower: a thread walking consecutive offers
-// instead of a search per offer; offers loaded eight ahead; list reads issued in groups; the
-// first L offers of a list placed by a counter and the others entered behind a per-list bound,
-// or smallest first in rounds between barriers; a per-list bound on the hash in front of the
-// scan; offers to popular points thinned out by a hash threshold first; the keys sorted by
-// target in LDS (count, prefix sum, scatter) and one thread per target selecting its L smallest
-// alone, without atomics (175 us: the popular points' threads run long, and the offers are
-// found twice).
+__host__ __device__ inline size_t bucket_lists_rest(int shift, int n_blocks)
+{
+    const size_t targets = (size_t)1 << shift, runs = (size_t)n_blocks + 1, most = runs > targets ? runs : targets;
+    return most * 4 + targets * 4 + targets * 2 * 2;
+}
+
+// Words of a list block for the offers of a bucket: what its threads can hold while they are sorted, 1.6 times what
+// there are on average if all rows are full, as far as the LDS goes.
+inline int bucket_lists_area(int K, int L, int shift, int n_blocks, int threads)
+{
+    const size_t most = (160 * 1024 - 512 - bucket_lists_rest(shift, n_blocks)) / 4, avg = (size_t)(K > L ? K : L) << shift;
+    size_t words = (size_t)kBktWords * threads;
+    if (words < avg * 8 / 5) words = avg * 8 / 5;
+    return (int)((words < most ? words : most) & ~(size_t)3);
+}
+
+// least LDS of a list block: the insertion's lists (what bucketed_lists asks for)
 __host__ __device__ inline size_t bucket_lists_lds(int L, int shift, int n_blocks)
 {
     return ((size_t)L << shift) * 8 + ((size_t)2 * n_blocks + 2) * 4;
 }
 
-// SHIFT: log2 of the bucket's targets, LT: the list length, if fixed at compile time (else 0); RB: row bits of an offer
-template <int SHIFT, int LT, int RB>
-__global__ void __launch_bounds__(kBktThreads)
+struct OfferRun {
+    int start, count;      // in its offer block's part of the array
+    int place;             // among the bucket's offers
+};
+
+// The offers of a bucket by their runs, lanes_bits: log2 of the lanes that walk a run together; run(r): an OfferRun.
+// found(run, place, offer word) for every offer.
+// U: runs in flight per group of lanes.
+template <int U, class Run, class Found>
+__device__ inline void walk_offers(const u32 *__restrict__ offer_runs, int n_blocks, int run_cap, int lanes_bits, int n_thr,
+                                   Run &&run, Found &&found)
+{
+    const int g = 1 << lanes_bits, gl = threadIdx.x & (g - 1), groups = n_thr >> lanes_bits;
+    for (int r0 = threadIdx.x >> lanes_bits; r0 < n_blocks; r0 += U * groups) {
+        u32 o[U];
+        OfferRun a[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int r = r0 + u * groups;
+            a[u] = run(min(r, n_blocks - 1));
+            if (r >= n_blocks) a[u].count = 0;
+            if (gl < a[u].count) o[u] = offer_runs[(size_t)r * run_cap + a[u].start + gl];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int r = r0 + u * groups;
+            if (gl < a[u].count) found(r, a[u].place + gl, o[u]);
+            for (int q = gl + g; q < a[u].count; q += g) found(r, a[u].place + q, offer_runs[(size_t)r * run_cap + a[u].start + q]);
+        }
+    }
+}
+
+// hash of a key (its high half; the low half is the source)
+__device__ inline u32 reverse_hash(u64 stream_key, int target, u32 source)
+{
+    return (u32)(reverse_key(stream_key, target, (int)source) >> 32);
+}
+
+// Row rotation T of the sixteen lanes of a group: how many of the rotated hashes are below the own ones.
+template <int T, int E>
+__device__ inline void rank_round(const u32 (&h)[E], int (&rank)[E])
+{
+#pragma unroll
+    for (int p = 0; p < E; ++p) {
+        const u32 o = T ? (u32)EF_ROW_ROR((int)h[p], T ? T : 1) : h[p];
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+            if (T || p != e) rank[e] += o < h[e] ? 1 : 0;
+    }
+}
+
+// Lists that were offered more than L, but at most 16 E sources: sixteen lanes to a list.
+template <int E>
+__device__ inline void select_by_group(const u32 *sorted, const int *end, const int *begin, const unsigned short *order,
+                                       int n_sel, int first, int L, u64 stream_key, int n_waves, u32 *__restrict__ lists)
+{
+    const int lane = ef_lane(), gl = lane & 15, shift = lane & 48, wave = threadIdx.x / EF_WAVE;
+    for (int q0 = 4 * wave; q0 < n_sel; q0 += 4 * n_waves) {
+        const int q = q0 + (lane >> 4);
+        const bool ok = q < n_sel;
+        const int row = order[ok ? q : n_sel - 1], s0 = begin[row], c = end[row] - s0;
+        u32 src[E], h[E];
+        int rank[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int j = gl + 16 * e;
+            src[e] = sorted[s0 + min(j, c - 1)];
+            h[e] = j < c ? reverse_hash(stream_key, first + row, src[e]) : ~0u;
+            rank[e] = 0;
+        }
+#define EF_RANK(T) rank_round<T>(h, rank);
+        EF_RANK(0) EF_RANK(1) EF_RANK(2) EF_RANK(3) EF_RANK(4) EF_RANK(5) EF_RANK(6) EF_RANK(7)
+        EF_RANK(8) EF_RANK(9) EF_RANK(10) EF_RANK(11) EF_RANK(12) EF_RANK(13) EF_RANK(14) EF_RANK(15)
+#undef EF_RANK
+        int place[E], taken = 0;
+        auto places = [&]() {
+            taken = 0;
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                const u32 mask = (u32)(__ballot(gl + 16 * e < c && rank[e] < L) >> shift) & 0xFFFFu;
+                place[e] = (mask >> gl) & 1 ? taken + __popc(mask & ((1u << gl) - 1)) : -1;
+                taken += __popc(mask);
+            }
+        };
+        places();
+        if (__ballot(taken > L)) {      // equal hashes around the L-th: the source decides
+#pragma unroll
+            for (int e = 0; e < E; ++e) rank[e] = 0;
+#pragma unroll
+            for (int p = 0; p < E; ++p)
+                for (int k = 0; k < 16; ++k) {
+                    const u32 oh = __shfl(h[p], k, 16), os = __shfl(src[p], k, 16);
+#pragma unroll
+                    for (int e = 0; e < E; ++e)
+                        rank[e] += 16 * p + k < c && (oh < h[e] || (oh == h[e] && os < src[e])) ? 1 : 0;
+                }
+            places();
+        }
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+            if (ok && place[e] >= 0) lists[(size_t)(first + row) * L + place[e]] = src[e];
+    }
+}
+
+constexpr int kSelect = 8 * EF_WAVE;      // offers to one target that a wave chooses among, at most
+constexpr int kRoom = 2 * EF_WAVE;        // room for the offers to a popular point that are left below its bound
+
+// Lists that were offered more than that many: a wave to a list, c offers to `target` in its registers.
+template <int N>
+__device__ inline void select_by_wave(const u32 *from, int c, int target, int L, u64 stream_key, u32 *__restrict__ out)
+{
+    const int lane = ef_lane();
+    u32 src[N], h[N];
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+        const int j = lane + EF_WAVE * e;
+        src[e] = from[min(j, c - 1)];
+        h[e] = reverse_hash(stream_key, target, src[e]);
+    }
+    auto count = [&](auto &&f) {
+        int n = 0;
+#pragma unroll
+        for (int e = 0; e < N; ++e) n += __popcll(__ballot(lane + EF_WAVE * e < c && f(h[e], src[e])));
+        return n;
+    };
+    // a bound that L hashes lie below: bit by bit, mostly found after some log2(c) + 3 of them
+    u32 t = 0, s_max = 0;
+    for (u32 bit = 1u << 31; bit; bit >>= 1) {
+        const int below = count([&](u32 hash, u32) { return hash < (t | bit); });
+        if (below > L) continue;
+        t |= bit;
+        if (below == L) break;
+    }
+    const int below = count([&](u32 hash, u32) { return hash < t; });
+    if (below < L)      // t is the L-th smallest hash and not the only one of its value: the smallest sources with it
+        for (u32 bit = 1u << 31; bit; bit >>= 1)
+            if (count([&](u32 hash, u32 s) { return hash == t && s < (s_max | bit); }) <= L - below) s_max |= bit;
+    int place = 0;
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+        const bool take = lane + EF_WAVE * e < c && (h[e] < t || (h[e] == t && src[e] < s_max));
+        const u64 mask = __ballot(take);
+        if (take) out[place + lanes_below(mask)] = src[e];
+        place += __popcll(mask);
+    }
+}
+
+// LT: the list length, if fixed at compile time (else 0); RB: row bits of an offer; shift: log2 of the bucket's targets
+template <int LT, int RB>
+__global__ void __launch_bounds__(kBktThreads) __attribute__((amdgpu_waves_per_eu(8)))
 bucket_lists_kernel(const u32 *__restrict__ offer_runs, const u32 *__restrict__ table, int n_blocks,
-                    int run_cap, u64 stream_key, int n, int L_, int shift, u32 *__restrict__ lists,
+                    int run_cap, u64 stream_key, int n, int L_, int shift, int area, int g_bits, u32 *__restrict__ lists,
                     int *__restrict__ counts, const int *__restrict__ nw_c, u32 *__restrict__ active, int *work_count)
 {
     const int L = LT ? LT : L_;
     extern __shared__ __align__(16) u64 list_sm[];
+    const int targets = 1 << shift, n_thr = (int)blockDim.x;
+    const int most = max(n_blocks + 1, targets);
+    u32 *words = (u32 *)list_sm;
+    u32 *run_at = words + area;      // start << 16 | place among the bucket's offers
+    int *offs = (int *)run_at, *hist = offs + most;
+    unsigned short *order = (unsigned short *)(hist + targets), *bound = order + targets;
+    __shared__ int total_sm, any_many, again;
+    __shared__ int wave_tot[kBktThreads / EF_WAVE];
+    __shared__ int n_class[3];
+    const int t = threadIdx.x, first = blockIdx.x * targets, rows_here = min(targets, n - first);
+    const int lane = ef_lane(), wave = t / EF_WAVE, n_waves = n_thr / EF_WAVE;
+    for (int f = t; f < targets; f += n_thr) hist[f] = 0;
+    if (t < 3) n_class[t] = 0;
+    if (t == 0) any_many = 0;
+    const u32 *runs = table + (size_t)blockIdx.x * n_blocks;
+    {
+        const int k0 = 2 * t;
+        const u32 r0 = k0 < n_blocks ? runs[k0] : 0u, r1 = k0 + 1 < n_blocks ? runs[k0 + 1] : 0u;
+        const int c0 = (int)(r0 & 0xffffu), c1 = (int)(r1 & 0xffffu);
+        const int incl = ef_wave_scan_i32(c0 + c1);
+        if (lane == EF_WAVE - 1) wave_tot[wave] = incl;
+        __syncthreads();
+        int off = incl - (c0 + c1);
+        for (int v = 0; v < wave; ++v) off += wave_tot[v];
+        // (places of 16 bits: only where the offers fit the LDS are they looked at)
+        if (k0 < n_blocks) run_at[k0] = (r0 & 0xFFFF0000u) | (u32)(off & 0xFFFF);
+        if (k0 + 1 < n_blocks) run_at[k0 + 1] = (r1 & 0xFFFF0000u) | (u32)((off + c0) & 0xFFFF);
+        if (t == n_thr - 1) {      // everything before it, and its own
+            total_sm = off + c0 + c1;
+            run_at[n_blocks] = (u32)(total_sm & 0xFFFF);
+        }
+    }
+    __syncthreads();
+    const int total = total_sm;
+    constexpr u32 kRowMask = (1u << RB) - 1;
+    int c = 0;      // filled slots of target t's list
+    const bool sorted_by_regs = total <= min(area, kBktWords * n_thr);
+    constexpr int SB = 21;      // source bits
+    constexpr u32 kNone = ~0u;
+    // (the places in run_at have 16 bits: where there are more offers, the runs' extents come from the table)
+    auto run_of = [&](int r) {
+        const u32 here = run_at[r];
+        const int place = (int)(here & 0xFFFFu);
+        return OfferRun{(int)(here >> 16), (int)(run_at[r + 1] & 0xFFFFu) - place, place};
+    };
+    auto table_run = [&](int r) { return OfferRun{(int)(runs[r] >> 16), (int)(runs[r] & 0xFFFFu), 0}; };
+    auto row_of = [&](u32 o) {      // (always inside: runs are filed by bucket)
+        const int row = (int)(o >> RB) - first;
+        return (unsigned)row < (unsigned)rows_here ? row : -1;
+    };
+    auto source_of = [&](int run, u32 o) { return ((u32)run << RB) + (o & kRowMask); };
+    // ---- the bucket's offers, in any order, as (target inside the bucket, source); offers per target --------------
+    if (sorted_by_regs) {
+        auto found = [&](int run, int at, u32 o) {
+            const int row = row_of(o);
+            words[at] = row >= 0 ? (u32)row << SB | source_of(run, o) : kNone;
+            if (row >= 0) atomicAdd(&hist[row], 1);
+        };
+        if (total <= kBktFew * n_thr) {      // few offers: a thread looks for the run of its offer
+            for (int j = t; j < total; j += n_thr) {
+                int lo = 0, hi = n_blocks;      // place of lo <= j < place of hi
+                while (hi - lo > 1) {
+                    const int mid = (lo + hi) >> 1;
+                    if ((int)(run_at[mid] & 0xFFFFu) <= j) lo = mid;
+                    else hi = mid;
+                }
+                const OfferRun r = run_of(lo);
+                found(lo, j, offer_runs[(size_t)lo * run_cap + r.start + (j - r.place)]);
+            }
+        } else
+            walk_offers<4>(offer_runs, n_blocks, run_cap, g_bits, n_thr, run_of, found);
+    } else
+        walk_offers<4>(offer_runs, n_blocks, run_cap, g_bits, n_thr, table_run, [&](int, int, u32 o) {
+            const int row = row_of(o);
+            if (row >= 0) atomicAdd(&hist[row], 1);
+        });
+    __syncthreads();      // (run_at is free from here on)
+    // ---- sorted by target, in place: every word is in a register before the first is written -----------------------
+    // (More offers than fit: the offers are walked again, and popular points get room for kRoom of them only.)
+    u32 w[kBktWords];
+    if (sorted_by_regs) {
+#pragma unroll
+        for (int u = 0; u < kBktWords; ++u)
+            if (u * n_thr < total) w[u] = u * n_thr + t < total ? words[u * n_thr + t] : kNone;
+    }
+    const int mine = t < rows_here ? hist[t] : 0, room = sorted_by_regs ? mine : min(mine, kRoom);
+    const bool many = mine > (sorted_by_regs ? kSelect : kRoom);
+    const int incl = ef_wave_scan_i32(room);
+    if (lane == EF_WAVE - 1) wave_tot[wave] = incl;
+    // lists with more than L offers, by what it takes to choose among them
+    const int cls = mine <= L ? -1 : mine <= 16 ? 0 : mine <= 32 ? 1 : 2;
+    const u64 in0 = __ballot(cls == 0), in1 = __ballot(cls == 1), in2 = __ballot(cls == 2);
+    int base = 0;
+    if (lane < 3 && (in0 | in1 | in2)) base = atomicAdd(&n_class[lane], __popcll(lane == 0 ? in0 : lane == 1 ? in1 : in2));
+    const int place = __shfl(base, max(cls, 0), EF_WAVE) + lanes_below(cls == 0 ? in0 : cls == 1 ? in1 : in2);
+    // Popular points (uniformly over the block: is there one?): only those offers with a hash below what some L + 6 sqrt(L) + 12 lie below.
+    float share = fminf((float)(L + 12) + 6.0f * __builtin_sqrtf((float)L), 0.875f * kRoom) / (float)max(mine, 1);
+    constexpr u32 kAll = 0xFFFFu;
+    if (many) any_many = 1;
+    if (t < targets) bound[t] = (unsigned short)(many ? (u32)(share * 65535.0f) : kAll);
+    __syncthreads();
+    int begin = incl - room, fits = 0;
+    for (int v = 0; v < n_waves; ++v) {
+        begin += v < wave ? wave_tot[v] : 0;
+        fits += wave_tot[v];
+    }
+    const int n0 = n_class[0], n1 = n_class[1], n2 = n_class[2];
+    const bool popular = any_many;
+    bool settled = sorted_by_regs || fits <= area;      // uniform over the block
+    if (settled) {
+        if (t < targets) offs[t] = hist[t] = begin;
+        if (cls >= 0) order[(cls == 0 ? 0 : cls == 1 ? n0 : n0 + n1) + place] = (unsigned short)t;
+        __syncthreads();
+        if (sorted_by_regs) {
+#pragma unroll
+            for (int u = 0; u < kBktWords; ++u) {
+                if (u * n_thr >= total) continue;
+                const int row = (int)(w[u] >> SB) & (targets - 1);
+                const u32 source = w[u] & ((1u << SB) - 1);
+                bool take = w[u] != kNone;
+                if (popular) {
+                    const u32 most = bound[row];
+                    if (__ballot(most != kAll)) take = take && (most == kAll || reverse_hash(stream_key, first + row, source) >> 16 <= most);
+                }
+                if (take) words[atomicAdd(&offs[row], 1)] = source;
+            }
+        }
+        // (once, but for a popular point that was left with fewer than L or more than kRoom: again with another bound)
+        for (int tries = 0;; ++tries) {
+            if (popular) {
+                if (t == 0) again = 0;
+                __syncthreads();
+            }
+            if (tries > 0 || !sorted_by_regs)
+                walk_offers<1>(offer_runs, n_blocks, run_cap, g_bits, n_thr, table_run, [&](int run, int, u32 o) {
+                    const int row = row_of(o);
+                    if (row < 0) return;
+                    const u32 source = source_of(run, o), most = bound[row];
+                    if (tries > 0 && most == kAll) return;
+                    if (most != kAll && reverse_hash(stream_key, first + row, source) >> 16 > most) return;
+                    const int p = atomicAdd(&offs[row], 1);
+                    if (most == kAll || p - hist[row] < kRoom) words[p] = source;
+                });
+            __syncthreads();      // (offs[r] is now the end of target r's sources)
+            if (!popular) break;      // (uniform over the block)
+            if (t < rows_here && bound[t] != kAll) {
+                const int kept = offs[t] - begin;
+                if (kept < L || kept > kRoom) {
+                    share *= kept < L ? 2.0f : 0.75f;
+                    bound[t] = (unsigned short)(fminf(share, 0.99f) * 65535.0f);
+                    offs[t] = begin;
+                    again = 1;
+                } else
+                    bound[t] = kAll;
+            }
+            __syncthreads();
+            if (!again) break;
+            if (tries == 15) {
+                settled = false;
+                break;
+            }
+            __syncthreads();
+        }
+    }
+    if (settled) {
+        // ---- the lists -----------------------------------------------------------------------------------------
+        for (int q = wave; q < n2; q += n_waves) {
+            const int row = __builtin_amdgcn_readfirstlane((int)order[n0 + n1 + q]);
+            const int from = __builtin_amdgcn_readfirstlane(hist[row]), cnt = __builtin_amdgcn_readfirstlane(offs[row]) - from;
+            u32 *out = lists + (size_t)(first + row) * L;
+            if (cnt <= EF_WAVE) select_by_wave<1>(words + from, cnt, first + row, L, stream_key, out);
+            else if (cnt <= 2 * EF_WAVE) select_by_wave<2>(words + from, cnt, first + row, L, stream_key, out);
+            else if (cnt <= 4 * EF_WAVE) select_by_wave<4>(words + from, cnt, first + row, L, stream_key, out);
+            else select_by_wave<8>(words + from, cnt, first + row, L, stream_key, out);
+        }
+        if (L < 32) select_by_group<2>(words, offs, hist, order + n0, n1, first, L, stream_key, n_waves, lists);
+        if (L < 16) select_by_group<1>(words, offs, hist, order, n0, first, L, stream_key, n_waves, lists);
+        // (places beyond a list's count are never read)
+        for (int f = t; f < rows_here * L; f += n_thr) {
+            const int row = LT ? f / LT : f / L, a = f - row * L, from = hist[row], cnt = offs[row] - from;
+            if (cnt <= L && a < cnt) lists[(size_t)first * L + f] = words[from + a];
+        }
+        c = min(mine, L);
+    }
+    if (!settled) {
+        // more offers than fit, or no bound found: bounded insertion, as many targets at a time as there is room for lists
+        __syncthreads();
+        u64 *ll = list_sm;
+        const int step = area / (2 * L);
+        for (int row0 = 0; row0 < rows_here; row0 += step) {
+            const int rows = min(step, rows_here - row0);
+            for (int f = t; f < rows * L; f += n_thr) ll[f] = ~0ULL;
+            __syncthreads();
+            walk_offers<1>(offer_runs, n_blocks, run_cap, g_bits, n_thr, table_run, [&](int run, int, u32 o) {
+                const int target = (int)(o >> RB), row = target - first - row0;
+                if ((unsigned)row >= (unsigned)rows) return;
+                const u64 key = reverse_key(stream_key, target, (int)source_of(run, o));
+                unsigned long long *list = (unsigned long long *)(ll + row * L);
+                for (;;) {
+                    u64 mx = 0;
+                    int ms = 0;
+                    for (int a = 0; a < L; ++a) {
+                        const u64 v = __hip_atomic_load(list + a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        if (v > mx) {      // the first of equal (empty) slots: lists fill from slot 0 up
+                            mx = v;
+                            ms = a;
+                        }
+                    }
+                    if (key >= mx) break;
+                    // slots only ever fall: if slot ms still holds mx, it still is the largest
+                    if (atomicCAS(list + ms, (unsigned long long)mx, (unsigned long long)key) == mx) break;
+                }
+            });
+            __syncthreads();
+            // only the sources are wanted from here on (the keys decided who is in the list)
+            for (int f = t; f < rows * L; f += n_thr) lists[(size_t)(first + row0) * L + f] = (u32)ll[f];
+            if (t >= row0 && t < row0 + rows)
+                for (int a = 0; a < L; ++a) c += ll[(t - row0) * L + a] != ~0ULL ? 1 : 0;
+            __syncthreads();
+        }
+    }
+    if (t < rows_here) counts[first + t] = c;
+    if (!active) return;
+    // The reverse-new lists are complete: who joins anything in this iteration (see active_kernel; 32 points a
+    // word, so that the smallest ranges of targets own whole words), and the work lists are empty again.
+    const u64 mask = __ballot(t < rows_here && (c > 0 || nw_c[first + t] > 0));
+    const int t0 = t & ~(EF_WAVE - 1), half = ef_lane();
+    if (half < 2 && t0 + 32 * half < rows_here) active[(first + t0) / 32 + half] = (u32)(mask >> (32 * half));
+    if (blockIdx.x == 0 && t < kMaxClasses) work_count[t] = 0;
+}
+
+// The same for lists of at most kInsertTo: every key goes through the bounded insertion; all slots start as the largest
+// key, so a list fills from slot 0 up and then keeps its L smallest keys.  Short scans and hardly a barrier: where
+// the sorting kernel takes longer (builds of 19 000 x 13, degree 7, lists of 5 / 3000 x 16, degree 3 / 300 000 x 32, degree 32, lists of 5:
+// 687 and 714 us, 454 and 473, 8.27 and 8.67 ms).  LDS: lists [bucket's targets * L] u64, scan [n_blocks + 1] and start [n_blocks] int.
+template <int RB>
+__global__ void __launch_bounds__(kBktThreads)
+bucket_insert_kernel(const u32 *__restrict__ offer_runs, const u32 *__restrict__ table, int n_blocks,
+                    int run_cap, u64 stream_key, int n, int L, int shift, int, int, u32 *__restrict__ lists,
+                    int *__restrict__ counts, const int *__restrict__ nw_c, u32 *__restrict__ active, int *work_count)
+{
+    extern __shared__ __align__(16) u64 list_sm[];
     u64 *ll = list_sm;
-    const int targets = 1 << (SHIFT ? SHIFT : shift), n_thr = SHIFT ? kBktThreads : (int)blockDim.x;
+    const int targets = 1 << shift, n_thr = (int)blockDim.x;
     int *scan = (int *)(ll + (size_t)targets * L), *start = scan + n_blocks + 1;
     __shared__ int wave_tot[kBktThreads / EF_WAVE];
     const int t = threadIdx.x, first = blockIdx.x * targets, rows_here = min(targets, n - first);
@@ -3558,7 +3977,7 @@ NndWs carve_nnd(void *ws, int64_t n, int K, int L)
     w.rnew = (u64 *)take((size_t)n * L * 8);
     w.rold = (u64 *)take((size_t)n * L * 8);
     // (32-bit sources fill the first half; the table of many small runs lies behind them)
-    if (bkt && bucket_shape(n, L).row_bits == 8) w.run_table = (u32 *)w.rold + (size_t)n * L;
+    if (bkt && bucket_shape(n, K, L).table_behind) w.run_table = (u32 *)w.rold + (size_t)n * L;
     w.list_max = (u64 *)take((size_t)n * 2 * 8);
     w.active = (u64 *)take((size_t)(n + 63) / 64 * 8);
     w.fresh = (u64 *)take(8);
@@ -3895,23 +4314,28 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
     // reverse lists by buckets (short rows and lists): LDS of an offer block (words) or a list
     // block (keys) with `per_row` of them per row, and one int per bucket or offer block twice over
     const bool bkt = bucketed_lists(n, K, L);
-    const BucketShape bs = bucket_shape(n, L);
+    const BucketShape bs = bucket_shape(n, K, L);
     const int bkt_rows = 1 << bs.row_bits;
     const bool bkt_small = bs.row_bits == 8;
     auto bkt_lds = [&](int per_row) { return (size_t)bkt_rows * per_row * 4 + ((size_t)2 * bs.buckets + 4) * 4; };
-    const size_t lists_lds = bkt ? bucket_lists_lds(L, bs.shift, bs.blocks) : 0;
-    // (list lengths of 10 and 20 are compiled in: the scan of a list unrolls, 8 % off the kernel)
+    const int lists_area = bkt ? bucket_lists_area(K, L, bs.shift, bs.blocks, bs.threads) : 0;
+    const size_t lists_lds = !bkt ? 0 : L <= kInsertTo ? bucket_lists_lds(L, bs.shift, bs.blocks)
+                                   : (size_t)lists_area * 4 + bucket_lists_rest(bs.shift, bs.blocks);
+    // lanes that walk a run of `per` offers per row together
+    auto run_lanes = [&](int per) {
+        const int64_t mean = n * per / ((int64_t)bs.blocks * bs.buckets);
+        return mean <= 6 ? 3 : mean <= 14 ? 4 : mean <= 40 ? 5 : 6;
+    };
     typedef void (*SampleKernel)(u64 *, int, int, int, int *, int *, int *, int *, u32 *, int, int, u32 *, u32 *);
     typedef void (*ReverseOldKernel)(const int *, int, int, const u64 *, int, int, u32 *, u32 *);
-    typedef void (*ListsKernel)(const u32 *, const u32 *, int, int, u64, int, int, int, u32 *, int *, const int *, u32 *, int *);
+    typedef void (*ListsKernel)(const u32 *, const u32 *, int, int, u64, int, int, int, int, int, u32 *, int *, const int *, u32 *, int *);
     const SampleKernel bkt_sample = bkt_small ? (K <= 16 ? sample_bucket_kernel<2, 8> : sample_bucket_kernel<4, 8>)
                                               : (K <= 16 ? sample_bucket_kernel<2, 10> : sample_bucket_kernel<4, 10>);
     const ReverseOldKernel bkt_old = bkt_small ? reverse_old_bucket_kernel<8> : reverse_old_bucket_kernel<10>;
     const ListsKernel bkt_lists =
-        bkt_small ? (L == 10 ? bucket_lists_kernel<0, 10, 8> : L == 20 ? bucket_lists_kernel<0, 20, 8> : bucket_lists_kernel<0, 0, 8>)
-        : L == 10 ? bucket_lists_kernel<10, 10, 10>
-        : L == 20 ? bucket_lists_kernel<9, 20, 10>
-        : bs.shift == 10 ? bucket_lists_kernel<10, 0, 10> : bucket_lists_kernel<9, 0, 10>;
+        L <= kInsertTo ? (bkt_small ? bucket_insert_kernel<8> : bucket_insert_kernel<10>)
+        : bkt_small ? (L == 10 ? bucket_lists_kernel<10, 8> : bucket_lists_kernel<0, 8>)
+                  : (L == 10 ? bucket_lists_kernel<10, 10> : bucket_lists_kernel<0, 10>);
     if (bkt) {
         EF_HIP_CHECK(hipFuncSetAttribute((const void *)bkt_sample, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bkt_lds(L)));
         EF_HIP_CHECK(hipFuncSetAttribute((const void *)bkt_old, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bkt_lds(K)));
@@ -3969,7 +4393,7 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
                 bkt_sample<<<bs.blocks, bkt_rows, bkt_lds(L), st>>>(graph, (int)n, K, L, w.nw, w.od, w.nw_c, w.od_c, w.worst,
                                                                    bs.buckets, bs.shift, w.offer_runs, w.run_table);
                 bkt_lists<<<bs.buckets, bs.threads, lists_lds, st>>>(w.offer_runs, w.run_table, bs.blocks, bkt_rows * L, kn,
-                                                                    (int)n, L, bs.shift, (u32 *)w.rnew, w.rnew_c, w.nw_c,
+                                                                    (int)n, L, bs.shift, lists_area, run_lanes(L), (u32 *)w.rnew, w.rnew_c, w.nw_c,
                                                                     (u32 *)w.active, w.work_count);
             } else if (K <= 16) EF_SAMPLE(16, 1);
             else if (K <= 32) EF_SAMPLE(32, 1);
@@ -3980,7 +4404,7 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
                 bkt_old<<<bs.blocks, bkt_rows, bkt_lds(K), st>>>(w.od, (int)n, K, w.active, bs.buckets, bs.shift, w.offer_runs,
                                                                 w.run_table);
                 bkt_lists<<<bs.buckets, bs.threads, lists_lds, st>>>(w.offer_runs, w.run_table, bs.blocks, bkt_rows * K, ko,
-                                                                    (int)n, L, bs.shift, (u32 *)w.rold, w.rold_c, nullptr,
+                                                                    (int)n, L, bs.shift, lists_area, run_lanes(K), (u32 *)w.rold, w.rold_c, nullptr,
                                                                     nullptr, nullptr);
             } else if (K <= 16) EF_REVERSE_OLD(16);
             else if (K <= 32) EF_REVERSE_OLD(32);

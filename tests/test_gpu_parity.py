@@ -663,6 +663,42 @@ def test_reverse_lists_of_popular_points(ef, hubs):
     oracle.check_graph_invariants(X, ids, dists)
 
 
+@pytest.mark.parametrize("stride", [37, 1])      # the popular points in ranges of their own, and side by side
+@pytest.mark.parametrize("K,L", [(10, 10), (10, 4), (20, 20), (24, 5), (32, 32), (33, 32), (64, 20), (100, 50), (128, 64), (128, 1)])
+def test_reverse_lists_of_given_lengths(ef, K, L, stride):
+    """Points that exactly c others name, around the sizes at which the choice among the offers changes hands (the
+    list's own length, 16, 32, 64, 128, more), two iterations of any graph against the oracle's."""
+    rng = np.random.default_rng(100 * K + L)
+    n, d = 2_100, 12
+    counts = [0, 1, L - 1, L, L + 1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 127, 128, 129, 130, 300, 1_500]
+    X = rng.standard_normal((n, d)).astype(np.float32)
+    special = 5 + stride * np.arange(len(counts))
+    ids = np.full((n, K), -1, dtype=np.int32)
+    used = np.zeros(n, dtype=int)
+    for v, c in sorted(zip(special, counts), key=lambda p: -p[1]):
+        free = np.flatnonzero((used < K) & (np.arange(n) != v))
+        for i in rng.permutation(free)[:c]:
+            ids[i, used[i]] = v
+            used[i] += 1
+    others = np.setdiff1d(np.arange(n), special)
+    for i in range(n):      # (the other places: anybody else, or nobody)
+        fill = rng.permutation(others[others != i])[:rng.integers(0, K - used[i] + 1)]
+        ids[i, used[i]:used[i] + len(fill)] = fill
+    for v, c in zip(special, counts):
+        assert (ids == v).sum() <= c
+    a, b = np.repeat(np.arange(n, dtype=np.int32), K), np.maximum(ids, 0).ravel()
+    dists = host(ef.efanna_pair_distances(dev(X), dev(a), dev(b))).reshape(n, K)
+    dists[ids < 0] = np.inf
+    order = np.lexsort((ids, dists), axis=1)
+    ids, dists = np.take_along_axis(ids, order, 1), np.take_along_axis(dists, order, 1)
+    want = (ids, dists, (ids >= 0).astype(np.uint8))
+    graph = ef.efanna_set_graph(dev(want[0]), dev(want[1]), dev(want[2]))
+    for it in range(2):
+        ef.efanna_nndescent(dev(X), graph, 1, L, 9, first_iter=it)
+        want = oracle.nndescent(X, *want[:3], 1, L, 9, iter0=it)
+        graph_equal(ef, graph, want)
+
+
 @pytest.mark.parametrize("K,L", [(33, 32), (64, 20), (100, 50), (128, 64), (128, 1)])
 def test_sampling_of_long_rows_with_ties(ef, K, L):
     """Rows of more than 32 entries on an integer grid (many equal distances): the L-th new entry is
