@@ -1550,7 +1550,7 @@ reverse_overflow_kernel(const Overflow *__restrict__ overflow, size_t ovf_region
 
 // ---------------------------------------------------------------------------------------
 // Reverse lists without device-wide atomics, for short rows and lists (K, L <= 32) of at most
-// 2^21 points (2^20 if L > 16).  A counter bump per offer is bound by the rate of atomics on random addresses;
+// 2^21 points (2^20 if L > 16; longer rows and lists: see wide_lists).  A counter bump per offer is bound by the rate of atomics on random addresses;
 // here the offers are sorted by target range instead, and the lists of a range are built in LDS:
 //   1. an offer block (one thread per row) handles 1024 consecutive source rows (256 of few points,
 //      see BucketShape), keeps their
@@ -1627,6 +1627,32 @@ inline BucketShape bucket_shape(int64_t n, int K, int L)
     return b;
 }
 
+// Longer rows or lists (K or L > 32) of at most 2^20 points: the same with a wave per row (sample_wide_kernel), 256 source
+// rows per offer block (their offers fill its LDS), 64 of up to 2^16 points, and ranges of 256 targets, of 128 for
+// more than a hundred offers each, smaller ones as long as there are fewer than 512.  Offers and table lie where the
+// counter scheme has its queues.  Beyond 2^20 points the runs would be of an offer or two each.
+// 10^6 x 96, degree 100, lists of 50, eight iterations: sampling, offers and lists 62.7 -> 19.9 ms (the queues' overflow, a
+// thread per parked key and a scan of fifty keys each, was 34 of them), build 327.6 -> 284.7; 65 536 x 64, degree 40 8.46 -> 7.05,
+// 10^4 x 64, degree 100 9.71 -> 8.17, 400 000 x 16, degree 128 and lists of 32 121.8 -> 115.6.
+inline size_t wide_offer_lds(int per_row, const BucketShape &b) { return ((size_t)per_row << b.row_bits) * 4 + ((size_t)2 * b.buckets + 4) * 4; }
+inline bool wide_lists(int64_t n, int K, int L, BucketShape *shape = nullptr)
+{
+    if (bucketed_lists(n, K, L) || K > 128 || n > (1 << 20)) return false;
+    const int per = K > L ? K : L;
+    BucketShape b;
+    b.row_bits = n <= (1 << 16) ? 6 : 8;
+    b.blocks = (int)((n + (1 << b.row_bits) - 1) >> b.row_bits);
+    b.shift = per <= 100 ? 8 : 7;
+    while (b.shift < 8 && (n - 1) >> b.shift >= 4 << 10) ++b.shift;
+    while (b.shift > 5 && (n - 1) >> (b.shift - 1) < 512) --b.shift;
+    b.buckets = (int)((n - 1) >> b.shift) + 1;
+    b.threads = b.shift == 8 ? 1024 : b.shift == 7 ? 512 : 256;
+    b.table_behind = false;
+    if (shape) *shape = b;
+    return b.buckets <= 16 << b.row_bits && b.blocks <= 4 * b.threads && wide_offer_lds(per, b) <= 160 * 1024 - 512 &&
+           (((size_t)per << b.row_bits) + b.buckets) * b.blocks * 4 <= ovf_region_for(n, K) * kOvfQueues * sizeof(Overflow);
+}
+
 // All lanes of the wave call this together; lanes with `take` set append `offer`.
 template <int RB>      // RB: row bits of an offer
 __device__ inline void offer_append(bool take, u32 offer, int shift, u32 *offers, int *hist, int *fill)
@@ -1644,30 +1670,34 @@ __device__ inline void offer_append(bool take, u32 offer, int shift, u32 *offers
 }
 
 // End of an offer block: runs per bucket in `out` (this block's part of the offer array) and
-// the block's column of the table.  hist, cursor: [n_buckets] in LDS; the block has 1 << RB threads and
-// n_buckets is at most twice that.
-template <int RB>
+// the block's column of the table.  hist, cursor: [n_buckets] in LDS; n_buckets is at most PER times the threads.
+template <int RB, int PER>
 __device__ inline void offers_flush(const u32 *offers, const int *hist, int *cursor, int n_buckets, int shift,
                                     int total, u32 *__restrict__ out, u32 *__restrict__ table)
 {
-    __shared__ int wave_tot[(1 << RB) / EF_WAVE];
-    const int t = threadIdx.x, b0 = 2 * t;
-    const int c0 = b0 < n_buckets ? hist[b0] : 0, c1 = b0 + 1 < n_buckets ? hist[b0 + 1] : 0;
-    const int incl = ef_wave_scan_i32(c0 + c1);
+    __shared__ int wave_tot[kBktThreads / EF_WAVE];
+    const int t = threadIdx.x, b0 = PER * t;
+    int c[PER], sum = 0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        c[k] = b0 + k < n_buckets ? hist[b0 + k] : 0;
+        sum += c[k];
+    }
+    const int incl = ef_wave_scan_i32(sum);
     if (ef_lane() == EF_WAVE - 1) wave_tot[t / EF_WAVE] = incl;
     __syncthreads();
-    int off = incl - (c0 + c1);
+    int off = incl - sum;
     for (int v = 0; v < t / EF_WAVE; ++v) off += wave_tot[v];
-    if (b0 < n_buckets) {
-        cursor[b0] = off;
-        table[(size_t)b0 * gridDim.x + blockIdx.x] = (u32)off << 16 | (u32)c0;
-    }
-    if (b0 + 1 < n_buckets) {
-        cursor[b0 + 1] = off + c0;
-        table[(size_t)(b0 + 1) * gridDim.x + blockIdx.x] = (u32)(off + c0) << 16 | (u32)c1;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        if (b0 + k < n_buckets) {
+            cursor[b0 + k] = off;
+            table[(size_t)(b0 + k) * gridDim.x + blockIdx.x] = (u32)off << 16 | (u32)c[k];
+        }
+        off += c[k];
     }
     __syncthreads();
-    for (int e = t; e < total; e += 1 << RB) {
+    for (int e = t; e < total; e += blockDim.x) {
         const u32 o = offers[e];
         out[atomicAdd(&cursor[o >> (RB + shift)], 1)] = o;
     }
@@ -1708,7 +1738,7 @@ sample_bucket_kernel(u64 *graph, int n, int K, int L, int *__restrict__ nw, int 
         });
     }
     __syncthreads();
-    offers_flush<RB>(offers, hist, cursor, n_buckets, shift, fill, offer_runs + (size_t)blockIdx.x * kRows * L, table);
+    offers_flush<RB, 2>(offers, hist, cursor, n_buckets, shift, fill, offer_runs + (size_t)blockIdx.x * kRows * L, table);
 }
 
 // Reverse-old offers of 1 << RB rows (to points that join something, as in reverse_old_kernel).
@@ -1734,7 +1764,75 @@ reverse_old_bucket_kernel(const int *__restrict__ od, int n, int K, const u64 *_
         offer_append<RB>(take, ((u32)id << RB) | (u32)(f / K), shift, offers, hist, &fill);
     }
     __syncthreads();
-    offers_flush<RB>(offers, hist, cursor, n_buckets, shift, fill, offer_runs + (size_t)blockIdx.x * kRows * K, table);
+    offers_flush<RB, 2>(offers, hist, cursor, n_buckets, shift, fill, offer_runs + (size_t)blockIdx.x * kRows * K, table);
+}
+
+// The two for long rows (see wide_lists): a wave per row, 4 << RB threads, E entries per lane.
+template <int E, int RB>
+__global__ void __launch_bounds__(4 << RB)
+sample_wide_kernel(u64 *graph, int n, int K, int L, int *__restrict__ nw, int *__restrict__ od,
+                   int *__restrict__ nw_c, int *__restrict__ od_c, u32 *worst, int n_buckets, int shift,
+                   u32 *__restrict__ offer_runs, u32 *__restrict__ table)
+{
+    extern __shared__ __align__(16) u32 offer_sm[];
+    u32 *offers = offer_sm;
+    constexpr int kRows = 1 << RB, kThreads = 4 << RB, kWaveRows = kRows / (kThreads / EF_WAVE);
+    int *hist = (int *)(offers + (size_t)kRows * L), *cursor = hist + n_buckets;
+    __shared__ int fill;
+    for (int b = threadIdx.x; b < n_buckets; b += kThreads) hist[b] = 0;
+    if (threadIdx.x == 0) fill = 0;
+    __syncthreads();
+    const int i0 = blockIdx.x * kRows + (int)(threadIdx.x / EF_WAVE) * kWaveRows;
+    u64 next[E];
+    sample_load<EF_WAVE, E>(graph, i0, i0 < n, K, next);
+    for (int p = 0; p < kWaveRows; ++p) {      // (the next row travels while this one is ranked)
+        const int i = i0 + p;
+        u64 e[E];
+#pragma unroll
+        for (int h = 0; h < E; ++h) e[h] = next[h];
+        if (p + 1 < kWaveRows) sample_load<EF_WAVE, E>(graph, i + 1, i + 1 < n, K, next);
+        sample_row<EF_WAVE, E>(graph, e, i, i < n, K, L, nw, od, nw_c, od_c, worst, [&](bool take, int id) {
+            offer_append<RB>(take && (unsigned)id < (unsigned)n, ((u32)id << RB) | (u32)(i & (kRows - 1)), shift, offers,
+                             hist, &fill);
+        });
+    }
+    __syncthreads();
+    offers_flush<RB, 4>(offers, hist, cursor, n_buckets, shift, fill, offer_runs + (size_t)blockIdx.x * kRows * L, table);
+}
+
+template <int RB>
+__global__ void __launch_bounds__(4 << RB)
+reverse_old_wide_kernel(const int *__restrict__ od, int n, int K, const u64 *__restrict__ active,
+                        int n_buckets, int shift, u32 *__restrict__ offer_runs, u32 *__restrict__ table)
+{
+    extern __shared__ __align__(16) u32 offer_sm[];
+    u32 *offers = offer_sm;
+    constexpr int kRows = 1 << RB, kThreads = 4 << RB, U = 4;      // U: ids in flight per thread
+    int *hist = (int *)(offers + (size_t)kRows * K), *cursor = hist + n_buckets;
+    __shared__ int fill;
+    for (int b = threadIdx.x; b < n_buckets; b += kThreads) hist[b] = 0;
+    if (threadIdx.x == 0) fill = 0;
+    __syncthreads();
+    const int first = blockIdx.x * kRows, ids_here = min(kRows, n - first) * K;
+    for (int f0 = 0; f0 < ids_here; f0 += U * kThreads) {      // all threads take every round
+        int id[U];
+        bool take[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int f = f0 + u * kThreads + (int)threadIdx.x;
+            id[u] = f < ids_here ? od[(size_t)first * K + f] : -1;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            take[u] = id[u] >= 0 && id[u] < n && ((active[id[u] / EF_WAVE] >> (id[u] % EF_WAVE)) & 1);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int f = f0 + u * kThreads + (int)threadIdx.x;
+            offer_append<RB>(take[u], ((u32)id[u] << RB) | (u32)(f / K), shift, offers, hist, &fill);
+        }
+    }
+    __syncthreads();
+    offers_flush<RB, 4>(offers, hist, cursor, n_buckets, shift, fill, offer_runs + (size_t)blockIdx.x * kRows * K, table);
 }
 
 // The lists of one bucket.  run_cap: offers per part of an offer block (its rows * L or * K).
@@ -1750,7 +1848,7 @@ reverse_old_bucket_kernel(const int *__restrict__ od, int n, int K, const u64 *_
 // sixteen launches of that build 1338 -> 1010 us, with the bounded insertion for all (a list scanned in LDS per offer, again
 // whenever another thread was first) before; degree 20, 10^5 points 793 -> 231, where popular points' insertions waited for each other.
 // LDS: area words, run_at [n_blocks + 1] (later offs [targets]), hist [targets], order and bound [targets] of 16 bits;
-// n_blocks <= twice the threads, at least one thread per target.
+// n_blocks <= twice the threads (four times if WIDE), at least one thread per target.
 __host__ __device__ inline size_t bucket_lists_rest(int shift, int n_blocks)
 {
     const size_t targets = (size_t)1 << shift, runs = (size_t)n_blocks + 1, most = runs > targets ? runs : targets;
@@ -1759,10 +1857,10 @@ __host__ __device__ inline size_t bucket_lists_rest(int shift, int n_blocks)
 
 // Words of a list block for the offers of a bucket: what its threads can hold while they are sorted, 1.6 times what
 // there are on average if all rows are full, as far as the LDS goes.
-inline int bucket_lists_area(int K, int L, int shift, int n_blocks, int threads)
+inline int bucket_lists_area(int K, int L, int shift, int n_blocks, int threads, int thread_words)
 {
     const size_t most = (160 * 1024 - 512 - bucket_lists_rest(shift, n_blocks)) / 4, avg = (size_t)(K > L ? K : L) << shift;
-    size_t words = (size_t)kBktWords * threads;
+    size_t words = (size_t)thread_words * threads;
     if (words < avg * 8 / 5) words = avg * 8 / 5;
     return (int)((words < most ? words : most) & ~(size_t)3);
 }
@@ -1920,14 +2018,16 @@ __device__ inline void select_by_wave(const u32 *from, int c, int target, int L,
     }
 }
 
-// LT: the list length, if fixed at compile time (else 0); RB: row bits of an offer; shift: log2 of the bucket's targets
-template <int LT, int RB>
-__global__ void __launch_bounds__(kBktThreads) __attribute__((amdgpu_waves_per_eu(8)))
+// LT: the list length, if fixed at compile time (else 0); RB: row bits of an offer; shift: log2 of the bucket's targets.
+// WIDE: for long rows and lists, one block per CU instead of two: twice the offers and offer blocks per thread.
+template <int LT, int RB, bool WIDE>
+__global__ void __launch_bounds__(kBktThreads) __attribute__((amdgpu_waves_per_eu(WIDE ? 4 : 8)))
 bucket_lists_kernel(const u32 *__restrict__ offer_runs, const u32 *__restrict__ table, int n_blocks,
                     int run_cap, u64 stream_key, int n, int L_, int shift, int area, int g_bits, u32 *__restrict__ lists,
                     int *__restrict__ counts, const int *__restrict__ nw_c, u32 *__restrict__ active, int *work_count)
 {
     const int L = LT ? LT : L_;
+    constexpr int kWords = WIDE ? 2 * kBktWords : kBktWords, PER = WIDE ? 4 : 2;
     extern __shared__ __align__(16) u64 list_sm[];
     const int targets = 1 << shift, n_thr = (int)blockDim.x;
     const int most = max(n_blocks + 1, targets);
@@ -1945,27 +2045,35 @@ bucket_lists_kernel(const u32 *__restrict__ offer_runs, const u32 *__restrict__ 
     if (t == 0) any_many = 0;
     const u32 *runs = table + (size_t)blockIdx.x * n_blocks;
     {
-        const int k0 = 2 * t;
-        const u32 r0 = k0 < n_blocks ? runs[k0] : 0u, r1 = k0 + 1 < n_blocks ? runs[k0 + 1] : 0u;
-        const int c0 = (int)(r0 & 0xffffu), c1 = (int)(r1 & 0xffffu);
-        const int incl = ef_wave_scan_i32(c0 + c1);
+        const int k0 = PER * t;
+        u32 r[PER];
+        int sum = 0;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            r[k] = k0 + k < n_blocks ? runs[k0 + k] : 0u;
+            sum += (int)(r[k] & 0xFFFFu);
+        }
+        const int incl = ef_wave_scan_i32(sum);
         if (lane == EF_WAVE - 1) wave_tot[wave] = incl;
         __syncthreads();
-        int off = incl - (c0 + c1);
+        int off = incl - sum;
         for (int v = 0; v < wave; ++v) off += wave_tot[v];
         // (places of 16 bits: only where the offers fit the LDS are they looked at)
-        if (k0 < n_blocks) run_at[k0] = (r0 & 0xFFFF0000u) | (u32)(off & 0xFFFF);
-        if (k0 + 1 < n_blocks) run_at[k0 + 1] = (r1 & 0xFFFF0000u) | (u32)((off + c0) & 0xFFFF);
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            if (k0 + k < n_blocks) run_at[k0 + k] = (r[k] & 0xFFFF0000u) | (u32)(off & 0xFFFF);
+            off += (int)(r[k] & 0xFFFFu);
+        }
         if (t == n_thr - 1) {      // everything before it, and its own
-            total_sm = off + c0 + c1;
-            run_at[n_blocks] = (u32)(total_sm & 0xFFFF);
+            total_sm = off;
+            run_at[n_blocks] = (u32)(off & 0xFFFF);
         }
     }
     __syncthreads();
     const int total = total_sm;
     constexpr u32 kRowMask = (1u << RB) - 1;
     int c = 0;      // filled slots of target t's list
-    const bool sorted_by_regs = total <= min(area, kBktWords * n_thr);
+    const bool sorted_by_regs = total <= min(area, kWords * n_thr);
     constexpr int SB = 21;      // source bits
     constexpr u32 kNone = ~0u;
     // (the places in run_at have 16 bits: where there are more offers, the runs' extents come from the table)
@@ -2008,10 +2116,10 @@ bucket_lists_kernel(const u32 *__restrict__ offer_runs, const u32 *__restrict__ 
     __syncthreads();      // (run_at is free from here on)
     // ---- sorted by target, in place: every word is in a register before the first is written -----------------------
     // (More offers than fit: the offers are walked again, and popular points get room for kRoom of them only.)
-    u32 w[kBktWords];
+    u32 w[kWords];
     if (sorted_by_regs) {
 #pragma unroll
-        for (int u = 0; u < kBktWords; ++u)
+        for (int u = 0; u < kWords; ++u)
             if (u * n_thr < total) w[u] = u * n_thr + t < total ? words[u * n_thr + t] : kNone;
     }
     const int mine = t < rows_here ? hist[t] : 0, room = sorted_by_regs ? mine : min(mine, kRoom);
@@ -2044,7 +2152,7 @@ bucket_lists_kernel(const u32 *__restrict__ offer_runs, const u32 *__restrict__ 
         __syncthreads();
         if (sorted_by_regs) {
 #pragma unroll
-            for (int u = 0; u < kBktWords; ++u) {
+            for (int u = 0; u < kWords; ++u) {
                 if (u * n_thr >= total) continue;
                 const int row = (int)(w[u] >> SB) & (targets - 1);
                 const u32 source = w[u] & ((1u << SB) - 1);
@@ -2321,9 +2429,10 @@ __device__ inline void append_points(int cls, int i, int n, int evals, int rows,
 // ids inside one sampled list are distinct, and so are the sources inside one reverse
 // list.  ulist: [n][cap] (written through LDS so that the stores coalesce), ucount: [n]
 // (m_new, m); work: [jc.n][n], work_count: [kMaxClasses].
+template <class Source>      // of a reverse list's entries: 32 bits, or the key's low half
 __global__ void prepare_kernel(const int *__restrict__ nw, const int *__restrict__ od,
                                const int *__restrict__ nw_c, const int *__restrict__ od_c,
-                               const u64 *__restrict__ rnew, const u64 *__restrict__ rold,
+                               const Source *__restrict__ rnew, const Source *__restrict__ rold,
                                const int *__restrict__ rnew_c, const int *__restrict__ rold_c,
                                int n, int K, int L, int cap, u32 cap_magic, JoinClasses jc,
                                int *__restrict__ ulist, int2 *__restrict__ ucount,
@@ -2717,10 +2826,11 @@ __global__ void __launch_bounds__(512) join_kernel(const float *__restrict__ X, 
 // points per round and appends them to the work lists together (one counter bump per list and
 // round).  Same lists as prepare_kernel up to the order of the ids inside U_new and U_old,
 // which nothing depends on.  part: one triple per block.
+template <class Source>      // (see prepare_kernel)
 __global__ void __launch_bounds__(kBlock)
 prepare_wave_kernel(const int *__restrict__ nw, const int *__restrict__ od,
                     const int *__restrict__ nw_c, const int *__restrict__ od_c,
-                    const u64 *__restrict__ rnew, const u64 *__restrict__ rold,
+                    const Source *__restrict__ rnew, const Source *__restrict__ rold,
                     const int *__restrict__ rnew_c, const int *__restrict__ rold_c,
                     int n, int K, int L, int cap, int hash_slots, JoinClasses jc,
                     int *__restrict__ ulist, int2 *__restrict__ ucount,
@@ -3978,6 +4088,11 @@ NndWs carve_nnd(void *ws, int64_t n, int K, int L)
     w.rold = (u64 *)take((size_t)n * L * 8);
     // (32-bit sources fill the first half; the table of many small runs lies behind them)
     if (bkt && bucket_shape(n, K, L).table_behind) w.run_table = (u32 *)w.rold + (size_t)n * L;
+    BucketShape wide;
+    if (wide_lists(n, K, L, &wide)) {
+        w.offer_runs = (u32 *)w.overflow;
+        w.run_table = w.offer_runs + (((size_t)(K > L ? K : L) << wide.row_bits) * wide.blocks);
+    }
     w.list_max = (u64 *)take((size_t)n * 2 * 8);
     w.active = (u64 *)take((size_t)(n + 63) / 64 * 8);
     w.fresh = (u64 *)take(8);
@@ -4313,13 +4428,14 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
     NndWs w = carve_nnd(ws, n, K, L);
     // reverse lists by buckets (short rows and lists): LDS of an offer block (words) or a list
     // block (keys) with `per_row` of them per row, and one int per bucket or offer block twice over
-    const bool bkt = bucketed_lists(n, K, L);
-    const BucketShape bs = bucket_shape(n, K, L);
+    BucketShape bs;
+    const bool wide = wide_lists(n, K, L, &bs), bkt = wide || bucketed_lists(n, K, L);
+    if (!wide) bs = bucket_shape(n, K, L);
     const int bkt_rows = 1 << bs.row_bits;
-    const bool bkt_small = bs.row_bits == 8;
+    const bool bkt_small = bs.row_bits != 10;
     auto bkt_lds = [&](int per_row) { return (size_t)bkt_rows * per_row * 4 + ((size_t)2 * bs.buckets + 4) * 4; };
-    const int lists_area = bkt ? bucket_lists_area(K, L, bs.shift, bs.blocks, bs.threads) : 0;
-    const size_t lists_lds = !bkt ? 0 : L <= kInsertTo ? bucket_lists_lds(L, bs.shift, bs.blocks)
+    const int lists_area = bkt ? bucket_lists_area(K, L, bs.shift, bs.blocks, bs.threads, wide ? 2 * kBktWords : kBktWords) : 0;
+    const size_t lists_lds = !bkt ? 0 : L <= kInsertTo && !wide ? bucket_lists_lds(L, bs.shift, bs.blocks)
                                    : (size_t)lists_area * 4 + bucket_lists_rest(bs.shift, bs.blocks);
     // lanes that walk a run of `per` offers per row together
     auto run_lanes = [&](int per) {
@@ -4329,13 +4445,19 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
     typedef void (*SampleKernel)(u64 *, int, int, int, int *, int *, int *, int *, u32 *, int, int, u32 *, u32 *);
     typedef void (*ReverseOldKernel)(const int *, int, int, const u64 *, int, int, u32 *, u32 *);
     typedef void (*ListsKernel)(const u32 *, const u32 *, int, int, u64, int, int, int, int, int, u32 *, int *, const int *, u32 *, int *);
-    const SampleKernel bkt_sample = bkt_small ? (K <= 16 ? sample_bucket_kernel<2, 8> : sample_bucket_kernel<4, 8>)
-                                              : (K <= 16 ? sample_bucket_kernel<2, 10> : sample_bucket_kernel<4, 10>);
-    const ReverseOldKernel bkt_old = bkt_small ? reverse_old_bucket_kernel<8> : reverse_old_bucket_kernel<10>;
+    const bool few_rows = bs.row_bits == 6;      // (of a wide offer block)
+    const SampleKernel bkt_sample = wide ? (K <= 64 ? (few_rows ? sample_wide_kernel<1, 6> : sample_wide_kernel<1, 8>)
+                                                    : (few_rows ? sample_wide_kernel<2, 6> : sample_wide_kernel<2, 8>))
+                                    : bkt_small ? (K <= 16 ? sample_bucket_kernel<2, 8> : sample_bucket_kernel<4, 8>)
+                                                : (K <= 16 ? sample_bucket_kernel<2, 10> : sample_bucket_kernel<4, 10>);
+    const ReverseOldKernel bkt_old = wide ? (few_rows ? reverse_old_wide_kernel<6> : reverse_old_wide_kernel<8>)
+                                          : bkt_small ? reverse_old_bucket_kernel<8> : reverse_old_bucket_kernel<10>;
     const ListsKernel bkt_lists =
-        L <= kInsertTo ? (bkt_small ? bucket_insert_kernel<8> : bucket_insert_kernel<10>)
-        : bkt_small ? (L == 10 ? bucket_lists_kernel<10, 8> : bucket_lists_kernel<0, 8>)
-                  : (L == 10 ? bucket_lists_kernel<10, 10> : bucket_lists_kernel<0, 10>);
+        wide ? (few_rows ? bucket_lists_kernel<0, 6, true> : bucket_lists_kernel<0, 8, true>)
+        : L <= kInsertTo ? (bkt_small ? bucket_insert_kernel<8> : bucket_insert_kernel<10>)
+        : bkt_small ? (L == 10 ? bucket_lists_kernel<10, 8, false> : bucket_lists_kernel<0, 8, false>)
+                    : (L == 10 ? bucket_lists_kernel<10, 10, false> : bucket_lists_kernel<0, 10, false>);
+    const int offer_threads = wide ? 4 * bkt_rows : bkt_rows;
     if (bkt) {
         EF_HIP_CHECK(hipFuncSetAttribute((const void *)bkt_sample, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bkt_lds(L)));
         EF_HIP_CHECK(hipFuncSetAttribute((const void *)bkt_old, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bkt_lds(K)));
@@ -4390,7 +4512,7 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
     reverse_old_kernel<G><<<grid_for((size_t)n * G, kBlock), kBlock, 0, st>>>(                   \
         w.od, (int)n, K, L, ko, w.active, w.rold, w.rold_c, ovf, ovf_region, w.ovf_count)
             if (bkt) {
-                bkt_sample<<<bs.blocks, bkt_rows, bkt_lds(L), st>>>(graph, (int)n, K, L, w.nw, w.od, w.nw_c, w.od_c, w.worst,
+                bkt_sample<<<bs.blocks, offer_threads, bkt_lds(L), st>>>(graph, (int)n, K, L, w.nw, w.od, w.nw_c, w.od_c, w.worst,
                                                                    bs.buckets, bs.shift, w.offer_runs, w.run_table);
                 bkt_lists<<<bs.buckets, bs.threads, lists_lds, st>>>(w.offer_runs, w.run_table, bs.blocks, bkt_rows * L, kn,
                                                                     (int)n, L, bs.shift, lists_area, run_lanes(L), (u32 *)w.rnew, w.rnew_c, w.nw_c,
@@ -4401,7 +4523,7 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
             else EF_SAMPLE(64, 2);
             if (!bkt) active_kernel<<<grid_for((size_t)n, kBlock), kBlock, 0, st>>>(w.nw_c, w.rnew_c, (int)n, w.active);
             if (bkt) {
-                bkt_old<<<bs.blocks, bkt_rows, bkt_lds(K), st>>>(w.od, (int)n, K, w.active, bs.buckets, bs.shift, w.offer_runs,
+                bkt_old<<<bs.blocks, offer_threads, bkt_lds(K), st>>>(w.od, (int)n, K, w.active, bs.buckets, bs.shift, w.offer_runs,
                                                                 w.run_table);
                 bkt_lists<<<bs.buckets, bs.threads, lists_lds, st>>>(w.offer_runs, w.run_table, bs.blocks, bkt_rows * K, ko,
                                                                     (int)n, L, bs.shift, lists_area, run_lanes(K), (u32 *)w.rold, w.rold_c, nullptr,
@@ -4429,13 +4551,21 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
             if (K <= 16 && L <= 16) EF_PREPARE_GROUP(2);
             else EF_PREPARE_GROUP(4);
         } else if (prep_wave) {
-            prepare_wave_kernel<<<prep_wave_grid, kBlock, prep_wave_lds, st>>>(
-                w.nw, w.od, w.nw_c, w.od_c, w.rnew, w.rold, w.rnew_c, w.rold_c, (int)n, K, L, max_rows, prep_hash, jc,
-                w.ulist, w.ucount, w.work, w.work_count, w.part);
+            auto go = [&](auto kernel, auto *rnew, auto *rold) {
+                kernel<<<prep_wave_grid, kBlock, prep_wave_lds, st>>>(
+                    w.nw, w.od, w.nw_c, w.od_c, rnew, rold, w.rnew_c, w.rold_c, (int)n, K, L, max_rows, prep_hash, jc,
+                    w.ulist, w.ucount, w.work, w.work_count, w.part);
+            };
+            if (wide) go(prepare_wave_kernel<u32>, (const u32 *)w.rnew, (const u32 *)w.rold);
+            else go(prepare_wave_kernel<u64>, (const u64 *)w.rnew, (const u64 *)w.rold);
         } else {
-            prepare_kernel<<<n_part, prep_threads, prep_lds, st>>>(
-                w.nw, w.od, w.nw_c, w.od_c, w.rnew, w.rold, w.rnew_c, w.rold_c, (int)n, K, L, max_rows, rows_magic, jc,
-                w.ulist, w.ucount, w.work, w.work_count, w.part);
+            auto go = [&](auto kernel, auto *rnew, auto *rold) {
+                kernel<<<n_part, prep_threads, prep_lds, st>>>(
+                    w.nw, w.od, w.nw_c, w.od_c, rnew, rold, w.rnew_c, w.rold_c, (int)n, K, L, max_rows, rows_magic, jc,
+                    w.ulist, w.ucount, w.work, w.work_count, w.part);
+            };
+            if (wide) go(prepare_kernel<u32>, (const u32 *)w.rnew, (const u32 *)w.rold);
+            else go(prepare_kernel<u64>, (const u64 *)w.rnew, (const u64 *)w.rold);
         }
 #undef EF_PREPARE_GROUP
         if (ev) EF_HIP_CHECK(hipEventRecord(ev[5 * it + 1], st));
