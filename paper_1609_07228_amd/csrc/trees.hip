@@ -39,6 +39,7 @@ struct Counters {
     int bad_input;
     int small_nodes;
     int max_depth;      // deepest internal node (only tracked with node export)
+    int wide_input;     // some |x| >= kNarrow
 };
 
 // A node small enough to be finished inside one workgroup (finish_kernel).
@@ -96,6 +97,7 @@ inline int finish_limit(int S)
 // spreads both ways through the tile over all banks.  (32 x 32 tiles with 4-byte accesses: 10^6 x 960
 // 2.06 -> 1.51 ms, 10^6 x 128 255 -> 192 us.)
 constexpr int kTrTile = 64;
+constexpr float kNarrow = 256.0f;      // below it eight quantised coordinates add up in 32 bits, a hundred squares in 64
 __global__ void __launch_bounds__(kBlock)
 transpose_check_kernel(const float *__restrict__ X, int n, int d, float *__restrict__ XT, Counters *c, double terms)
 {
@@ -147,6 +149,7 @@ transpose_check_kernel(const float *__restrict__ X, int n, int d, float *__restr
         }
     }
     if (__any(bad) && ef_lane() == 0) atomicOr(&c->bad_input, 1);
+    if (__any(!(largest < kNarrow)) && ef_lane() == 0) c->wide_input = 1;      // (whoever writes it writes a 1)
 }
 
 // ---------------------------------------------------------------------------------------
@@ -158,6 +161,20 @@ transpose_check_kernel(const float *__restrict__ X, int n, int d, float *__restr
 // rounds of a wave-wide maximum pop the overall order.  `ids` may point into LDS or global
 // memory; every lane of the wave must call with the same arguments.
 constexpr int kVarSample = 100, kVarDims = 5;
+
+// The largest of the wave's values, in every lane: exchanges inside the rows of sixteen lanes by lane permutations of the vector
+// ALU, then of rows and half waves.
+__device__ inline u32 ef_wave_max_u32(u32 v)
+{
+#define EF_MAX_DPP(CTRL) v = max(v, (u32)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false))
+    EF_MAX_DPP(0xB1);       // lanes 0 <-> 1, 2 <-> 3
+    EF_MAX_DPP(0x4E);       // lanes 0, 1 <-> 2, 3
+    EF_MAX_DPP(0x141);      // the halves of a row, mirrored
+    EF_MAX_DPP(0x140);      // the row mirrored
+#undef EF_MAX_DPP
+    const u32 a = max((u32)__builtin_amdgcn_readlane((int)v, 0), (u32)__builtin_amdgcn_readlane((int)v, 16));
+    return max(a, max((u32)__builtin_amdgcn_readlane((int)v, 32), (u32)__builtin_amdgcn_readlane((int)v, 48)));
+}
 constexpr int kDimPending = -2;      // Node::dim of a node whose dimension is still to be chosen
 
 struct VarKey {
@@ -175,38 +192,59 @@ __device__ inline bool var_before(const VarKey &a, const VarKey &b)
 // |hi|, |lo| <= 2^20: truncation, the fraction and its 2^20-fold are exact in float32, the steps round
 // as q does (hi 2^20 is even), the products and sums of a hundred of them fit 64 bits whatever the values,
 // and only the result is put together in 128.  10^6 x 128, eight trees of leaves of 16: the in-LDS finish
-// 14.9 -> 5.0 ms, the levels above 3.05 -> 0.32.  (Sums of q - q(first row) in 64 bits, with a second pass in 128
+// 14.9 -> 5.0 ms, the levels above 3.05 -> 0.32.  Where all |x| < 256 (the pass that checks the input says so) q fits 29 bits:
+// eight of them add up in 32, a hundred squares in 64, five instructions per value instead of eleven.  With that,
+// rows addressed from scalar registers (the compiler had masked the choice of the id per lane), a lane's own best two instead of five
+// up to 128 dimensions and the wave's maximum by lane permutations: 5.13 -> 3.61 and 0.32 -> 0.18 (wide values: the tree build of 10^6 x 128 7.75 -> 6.54 ms, others 7.85 -> 6.18).  (Sums of q - q(first row) in 64 bits, with a second pass in 128
 // where values lie 256.0 or more apart: 9.0 and 0.55; with that pass 10^4 x 32 took 1.20 ms in all, now 0.79.)
+template <bool NARROW, bool ONE>      // all |x| < kNarrow; d <= 128: one pass over the dimensions, two to a lane
 __device__ inline int variance_dim_wave(const float *__restrict__ X, int d, const int *ids, int cnt, u64 draw)
 {
     const int lane = ef_lane();
-    const int m = cnt < kVarSample ? cnt : kVarSample;
+    // (uniform, and said to be: the sample's rows are addressed from scalar registers)
+    const int m = __builtin_amdgcn_readfirstlane(cnt < kVarSample ? cnt : kVarSample);
     const int id_lo = ids[min(lane, m - 1)], id_hi = m > EF_WAVE ? ids[min(EF_WAVE + lane, m - 1)] : 0;
-    VarKey top[kVarDims];
+    constexpr int N = ONE ? 2 : kVarDims;      // (a lane's own best)
+    VarKey top[N];
 #pragma unroll
-    for (int r = 0; r < kVarDims; ++r) {
+    for (int r = 0; r < N; ++r) {
         top[r].v = -1;      // below every variance
         top[r].j = 0x7FFFFFFF;
     }
-    for (int j0 = 0; j0 < d; j0 += 2 * EF_WAVE) {
+    for (int j0 = 0; j0 < (ONE ? 1 : d); j0 += 2 * EF_WAVE) {
         const int j[2] = {j0 + lane, j0 + EF_WAVE + lane};
         const int jc[2] = {min(j[0], d - 1), min(j[1], d - 1)};      // (lanes beyond d read along)
         const bool second = j0 + EF_WAVE < d;
         int s_hi[2] = {0, 0}, s_lo[2] = {0, 0};                             // sums of hi and lo
         long long s_hh[2] = {0, 0}, s_hl[2] = {0, 0}, s_ll[2] = {0, 0};     // ... of hi^2, hi lo and lo^2
+        long long s_q[2] = {0, 0}, s_qq[2] = {0, 0};                        // narrow values: sums of q and q^2
         for (int p0 = 0; p0 < m; p0 += 8) {
             float x[2][8];
+            const float *row[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
-                const int p = min(p0 + u, m - 1);
-                const int id = p < EF_WAVE ? __builtin_amdgcn_readlane(id_lo, p) : __builtin_amdgcn_readlane(id_hi, p - EF_WAVE);
-                const float *row = X + (size_t)id * d;
-                x[0][u] = row[jc[0]];
-                x[1][u] = second ? row[jc[1]] : 0.f;
+                const int p = min(p0 + u, m - 1), lo = __builtin_amdgcn_readlane(id_lo, p & 63), hi = __builtin_amdgcn_readlane(id_hi, p & 63);
+                row[u] = X + (size_t)(p < EF_WAVE ? lo : hi) * d;
+                x[0][u] = row[u][jc[0]];
+            }
+            if (second) {
+#pragma unroll
+                for (int u = 0; u < 8; ++u) x[1][u] = row[u][jc[1]];
             }
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 if (h == 1 && !second) break;
+                if (NARROW) {
+                    int sum = 0;      // (eight values of less than 2^28)
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const int q = p0 + u < m ? (int)__builtin_rintf(x[h][u] * 1048576.0f) : 0;
+                        sum += q;
+                        s_qq[h] += (long long)q * q;
+                    }
+                    s_q[h] += sum;
+                    continue;
+                }
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
                     if (p0 + u >= m) break;
@@ -225,8 +263,8 @@ __device__ inline int variance_dim_wave(const float *__restrict__ X, int d, cons
             if (h == 1 && !second) break;
             VarKey c;
             c.j = j[h];
-            const long long s1 = (long long)s_hi[h] * 1048576 + s_lo[h];
-            const __int128 s2 = (__int128)s_hh[h] * ((__int128)1 << 40) + (__int128)s_hl[h] * ((__int128)1 << 21) + s_ll[h];
+            const long long s1 = NARROW ? s_q[h] : (long long)s_hi[h] * 1048576 + s_lo[h];
+            const __int128 s2 = NARROW ? (__int128)s_qq[h] : (__int128)s_hh[h] * ((__int128)1 << 40) + (__int128)s_hl[h] * ((__int128)1 << 21) + s_ll[h];
             c.v = s2 * m - (__int128)s1 * s1;
             if (j[h] >= d) continue;
             if (j0 == 0 && h == 0) {      // (up to 128 dimensions a lane has two: one comparison puts them in order)
@@ -239,7 +277,7 @@ __device__ inline int variance_dim_wave(const float *__restrict__ X, int d, cons
                 }
             } else {
 #pragma unroll
-                for (int r = 0; r < kVarDims; ++r)
+                for (int r = 0; r < N; ++r)
                     if (var_before(c, top[r])) {
                         const VarKey t = top[r];
                         top[r] = c;
@@ -254,11 +292,8 @@ __device__ inline int variance_dim_wave(const float *__restrict__ X, int d, cons
         // the largest of the lanes' best: by the leading 64 bits of variances below 2^71 (all bits of
         // them where one is larger), the rare ties among those exactly
         const u64 head = top[0].v < 0 ? 0 : (u64)(top[0].v >> 64) >= 128 ? ~0ULL : (u64)(top[0].v >> 7);
-        u64 best = head;
-        for (int o = EF_WAVE / 2; o >= 1; o >>= 1) {
-            const u64 other = __shfl_xor(best, o, EF_WAVE);
-            best = other > best ? other : best;
-        }
+        const u32 high = ef_wave_max_u32((u32)(head >> 32));
+        const u64 best = (u64)high << 32 | ef_wave_max_u32((u32)(head >> 32) == high ? (u32)head : 0u);
         u64 tied = __ballot(head == best && top[0].v >= 0);
         int winner = __ffsll((unsigned long long)tied) - 1;
         if (tied & (tied - 1)) {
@@ -280,9 +315,9 @@ __device__ inline int variance_dim_wave(const float *__restrict__ X, int d, cons
         chosen = __shfl(top[0].j, winner, EF_WAVE);
         if (lane == winner) {      // the winner's lane moves on to its next one
 #pragma unroll
-            for (int q = 0; q + 1 < kVarDims; ++q) top[q] = top[q + 1];
-            top[kVarDims - 1].v = -1;
-            top[kVarDims - 1].j = 0x7FFFFFFF;
+            for (int q = 0; q + 1 < N; ++q) top[q] = top[q + 1];
+            top[N - 1].v = -1;
+            top[N - 1].j = 0x7FFFFFFF;
         }
     }
     return chosen;
@@ -295,6 +330,7 @@ __device__ inline int node_dim(int rule, u64 draw, int d)
 }
 
 // One wave per live node of the level: fixes the dimension of the nodes that wait for one.
+template <bool NARROW, bool ONE>
 __global__ void __launch_bounds__(kBlock)
 choose_dims_kernel(const float *__restrict__ X, int d, int n, const int *__restrict__ perm, Node *nodes,
                    int *dims, const Counters *c, int level, u64 seed)
@@ -305,7 +341,7 @@ choose_dims_kernel(const float *__restrict__ X, int d, int n, const int *__restr
         const int b = nodes[s].b, e = nodes[s].e;
         if (nodes[s].dim != kDimPending) continue;      // (uniform)
         const u64 draw = ef_mix64(ef_stream_key(seed, b / n) + nodes[s].heap);
-        const int dim = variance_dim_wave(X, d, perm + b, e - b, draw);
+        const int dim = variance_dim_wave<NARROW, ONE>(X, d, perm + b, e - b, draw);
         if (ef_lane() == 0) {
             nodes[s].dim = dim;
             dims[s] = dim;
@@ -673,30 +709,40 @@ struct LNode {
     int parent, pad;           // parent: global position, as in Node
 };
 
-__global__ void __launch_bounds__(kFinThreads)
+// LDS of a block: ids, node indexes of 16 bits, the split tests as bits, two node tables of `nodes`.  A thread keeps the
+// ids, nodes and tested values of its positions (every kFinThreads-th) in registers: 26 KB for leaves of 16, four blocks per
+// CU (with all of it and prefix sums in LDS 78 KB, two blocks).  What bounds it, 10^6 x 128, eight trees: splits by one coordinate
+// the scattered 4-byte gathers (56 M of them, 128-byte lines at 6.8 TB/s; 1.08 -> 1.05 ms), splits by variance the rows of the
+// samples (14.5 GB, at 4.0 TB/s; 5.13 -> 3.61 ms, see variance_dim_wave; two blocks per CU 3.83).
+constexpr int kFinWords = kFinMax / EF_WAVE;
+// Random projections ask for one block per CU: the eight lines that a position reads of its row come the faster the fewer
+// waves ask for others in between (200 000 x 960: one block 1.65 ms, two 1.74, three 1.81, four 1.86).
+constexpr size_t kFinProjLds = 96 * 1024;
+inline size_t finish_lds(int nodes) { return (size_t)kFinMax * 6 + kFinWords * 12 + 64 + 2 * (size_t)nodes * sizeof(LNode); }
+
+template <int RULE, bool NARROW, bool ONE>      // the split rule; NARROW, ONE: see variance_dim_wave, which wants more registers
+__global__ void __launch_bounds__(kFinThreads) __attribute__((amdgpu_waves_per_eu(RULE == 1 ? 6 : RULE == 2 ? 4 : 8)))
 finish_kernel(const float *__restrict__ XT, int d, int *perm, const SmallNode *__restrict__ small,
               unsigned char *leaf_flag, int S, u64 seed, int n, NodeRec *rec, int *leaf_rec,
-              int *max_depth, const float *__restrict__ X, int rule)
+              int *max_depth, const float *__restrict__ X, int nodes)
 {
     // One 16-byte aligned LDS block carved by hand (no separate static LDS variables, whose
     // size would shift the 8-byte node records off their alignment).
     extern __shared__ __align__(16) int fsm[];
-    int *const ids_base = fsm, *const nidx_base = fsm + 2 * kFinMax;      // [2][kFinMax] each
-    float *val = (float *)(fsm + 4 * kFinMax);
-    int *lcnt = fsm + 5 * kFinMax;                                 // [kFinMax + 1]
-    int *wave_tot = fsm + 6 * kFinMax + 4;                         // [kFinThreads / EF_WAVE]
-    int &n_next_sh = fsm[6 * kFinMax + 2];
-    int &depth_sh = fsm[6 * kFinMax + 3];                          // deepest node of this subtree
-    LNode *const tabs_base = (LNode *)(fsm + 6 * kFinMax + 32);     // [2][kFinNodes], 8-byte aligned
-    long long *const pval = (long long *)(tabs_base + 2 * kFinNodes);      // [kFinMax] projections (only with that rule)
-    // the quantised value position p is tested on, in a node with the dimension code dim
-    auto tested = [&](int p, int dim) { return dim >= 0 ? ef_quantise(val[p]) : pval[p]; };
+    LNode *const tabs_base = (LNode *)fsm;                          // [2][nodes]
+    u64 *const bits = (u64 *)(tabs_base + 2 * nodes);               // [kFinWords] "goes left", one bit per position
+    int *const before = (int *)(bits + kFinWords);                  // [kFinWords + 1] set bits before each word
+    int *const n_next_sh = before + kFinWords + 1;                  // [2]
+    int &depth_sh = n_next_sh[2];                                   // deepest node of this subtree
+    int *const ids = before + kFinWords + 16;                       // [kFinMax]
+    unsigned short *const nidx = (unsigned short *)(ids + kFinMax); // [kFinMax], kDone: in a leaf
+    constexpr int kDone = 0xFFFF, PER = kFinMax / kFinThreads;
     const SmallNode seg = small[blockIdx.x];
-    const int cnt = seg.e - seg.b, tid = threadIdx.x;
+    const int cnt = seg.e - seg.b, tid = threadIdx.x, lane = ef_lane();
     const u64 key = ef_stream_key(seed, seg.b / n);
     for (int p = tid; p < cnt; p += kFinThreads) {
-        ids_base[p] = perm[seg.b + p];
-        nidx_base[p] = 0;
+        ids[p] = perm[seg.b + p];
+        nidx[p] = 0;
     }
     if (tid == 0) {
         LNode r;
@@ -707,75 +753,88 @@ finish_kernel(const float *__restrict__ XT, int d, int *perm, const SmallNode *_
         r.heap = seg.heap;
         r.sum = 0;
         r.depth = seg.depth;
-        r.dim = seg.depth < 60 ? node_dim(rule, ef_mix64(key + seg.heap), d) : -1;
+        r.dim = seg.depth < 60 ? node_dim(RULE, ef_mix64(key + seg.heap), d) : -1;
         r.child[0] = r.child[1] = -1;
         r.parent = seg.parent;
         r.pad = 0;
         tabs_base[0] = r;
-        n_next_sh = 0;
+        n_next_sh[0] = n_next_sh[1] = 0;
         depth_sh = seg.depth;
     }
     __syncthreads();
-    int cur = 0, n_cur = 1;
-    const int chunk = (cnt + kFinThreads - 1) / kFinThreads;      // consecutive positions per thread in the scan
-    while (n_cur > 0) {
-        int *idc = ids_base + cur * kFinMax, *idn = ids_base + (cur ^ 1) * kFinMax;
-        int *nc = nidx_base + cur * kFinMax, *nn = nidx_base + (cur ^ 1) * kFinMax;
-        LNode *tc = tabs_base + cur * kFinNodes, *tn = tabs_base + (cur ^ 1) * kFinNodes;
+    for (int cur = 0, n_cur = 1; n_cur > 0; cur ^= 1) {
+        LNode *tc = tabs_base + cur * nodes, *tn = tabs_base + (cur ^ 1) * nodes;
+        int id[PER], k[PER];
+        long long q[PER];
         // 0. split dimensions by variance, one wave per node
-        if (rule == 1) {
-            for (int k = tid / EF_WAVE; k < n_cur; k += kFinThreads / EF_WAVE) {
-                if (tc[k].dim != kDimPending) continue;      // (uniform)
-                const int dim = variance_dim_wave(X, d, idc + tc[k].b, tc[k].e - tc[k].b, ef_mix64(key + tc[k].heap));
-                if (ef_lane() == 0) tc[k].dim = dim;
+        if (RULE == 1) {
+            for (int s = tid / EF_WAVE; s < n_cur; s += kFinThreads / EF_WAVE) {
+                if (tc[s].dim != kDimPending) continue;      // (uniform)
+                const int dim = variance_dim_wave<NARROW, ONE>(X, d, ids + tc[s].b, tc[s].e - tc[s].b, ef_mix64(key + tc[s].heap));
+                if (lane == 0) tc[s].dim = dim;
             }
             __syncthreads();
         }
         // 1. sums
-        for (int p = tid; p < cnt; p += kFinThreads) {
-            const int k = nc[p];
-            if (k >= 0 && tc[k].dim >= 0) {
-                const float x = XT[(size_t)tc[k].dim * n + idc[p]];
-                val[p] = x;
-                atomicAdd((u64 *)&tc[k].sum, (u64)ef_quantise(x));
-            } else if (k >= 0 && tc[k].dim <= -3) {
-                const float *row = X + (size_t)idc[p] * d;
-                const long long v = ef_node_value([&](int j) { return row[j]; }, d, tc[k].dim);
-                pval[p] = v;
-                atomicAdd((u64 *)&tc[k].sum, (u64)v);
+        float x[PER];
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int p = tid + u * kFinThreads;
+            id[u] = p < cnt ? ids[p] : 0;
+            k[u] = p < cnt ? (int)nidx[p] : kDone;
+        }
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int dim = k[u] != kDone ? tc[k[u]].dim : -1;
+            x[u] = dim >= 0 ? XT[(size_t)dim * n + id[u]] : 0.0f;
+        }
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int dim = k[u] != kDone ? tc[k[u]].dim : -1;
+            q[u] = ef_quantise(x[u]);
+            if (RULE == 2 && dim <= -3) {
+                const float *row = X + (size_t)id[u] * d;
+                q[u] = ef_node_value([&](int j) { return row[j]; }, d, dim);
             }
+            // (positions of a node are neighbours: near the top a wave lies in one node and adds up among its lanes)
+            const int k0 = __builtin_amdgcn_readfirstlane(k[u]);
+            if (__all(k[u] == k0)) {
+                if (k0 == kDone) continue;
+                long long sum = q[u];
+                for (int o = EF_WAVE / 2; o >= 1; o >>= 1) sum += __shfl_xor(sum, o, EF_WAVE);
+                if (lane == 0) atomicAdd((u64 *)&tc[k0].sum, (u64)sum);
+            } else if (ef_has_test(dim))
+                atomicAdd((u64 *)&tc[k[u]].sum, (u64)q[u]);
+        }
+        if (tid == 0) n_next_sh[cur ^ 1] = 0;
+        __syncthreads();
+        // 2. the "goes left" predicate, and how often it holds before every word of positions
+        u32 left = 0;
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            bool f = false;
+            if (k[u] != kDone) {
+                const LNode &nd = tc[k[u]];
+                f = ef_has_test(nd.dim) && (long long)(nd.e - nd.b) * q[u] < nd.sum;
+            }
+            const u64 word = __ballot(f);
+            if (lane == 0) bits[(tid + u * kFinThreads) / EF_WAVE] = word;
+            left |= (f ? 1u : 0u) << u;
         }
         __syncthreads();
-        // 2. exclusive prefix sum of the "goes left" predicate over the segment
-        {
-            const int p0 = tid * chunk, p1 = min(cnt, p0 + chunk);
-            int mine = 0;
-            for (int p = p0; p < p1; ++p) {
-                const int k = nc[p];
-                int f = 0;
-                if (k >= 0 && ef_has_test(tc[k].dim))
-                    f = (long long)(tc[k].e - tc[k].b) * tested(p, tc[k].dim) < tc[k].sum ? 1 : 0;
-                lcnt[p] = f;
-                mine += f;
-            }
-            const int incl = ef_wave_scan_i32(mine);
-            if (ef_lane() == EF_WAVE - 1) wave_tot[tid / EF_WAVE] = incl;
-            __syncthreads();
-            int off = incl - mine;
-            for (int v = 0; v < tid / EF_WAVE; ++v) off += wave_tot[v];
-            for (int p = p0; p < p1; ++p) {
-                const int f = lcnt[p];
-                lcnt[p] = off;
-                off += f;
-            }
-            if (tid == kFinThreads - 1) lcnt[cnt] = off;      // the last thread's running sum is the total
+        if (tid < EF_WAVE) {
+            const int c = tid < kFinWords ? __popcll(bits[tid]) : 0, incl = ef_wave_scan_i32(c);
+            if (tid <= kFinWords) before[tid] = incl - c;
         }
         __syncthreads();
+        auto left_before = [&](int p) {      // p <= kFinMax
+            return before[p / EF_WAVE] + (p % EF_WAVE ? __popcll(bits[p / EF_WAVE] << (EF_WAVE - p % EF_WAVE)) : 0);
+        };
         // 3. children
-        for (int k = tid; k < n_cur; k += kFinThreads) {
-            LNode nd = tc[k];
+        for (int s = tid; s < n_cur; s += kFinThreads) {
+            LNode nd = tc[s];
             const int c = nd.e - nd.b;
-            const int nl = ef_has_test(nd.dim) ? lcnt[nd.e] - lcnt[nd.b] : 0;
+            const int nl = ef_has_test(nd.dim) ? left_before(nd.e) - left_before(nd.b) : 0;
             if (nl == 0 || nl == c) {
                 nd.moved = 0;
                 nd.mid = nd.b + c / 2;
@@ -785,7 +844,7 @@ finish_kernel(const float *__restrict__ XT, int d, int *perm, const SmallNode *_
             }
             if (rec) {
                 record_node(rec, leaf_rec, seg.b + nd.mid, nd.sum, nd.dim, c, nd.parent, nd.depth);
-                if (k == 0) depth_sh = nd.depth;      // levels are visited in order of depth
+                if (s == 0) depth_sh = nd.depth;      // levels are visited in order of depth
             }
             for (int side = 0; side < 2; ++side) {
                 const int cb = side ? nd.mid : nd.b, ce = side ? nd.e : nd.mid;
@@ -798,12 +857,12 @@ finish_kernel(const float *__restrict__ XT, int d, int *perm, const SmallNode *_
                     ch.moved = 0;
                     ch.depth = nd.depth + 1;
                     ch.heap = nd.depth < 60 ? 2 * nd.heap + side : nd.heap;
-                    ch.dim = ch.depth < 60 ? node_dim(rule, ef_mix64(key + ch.heap), d) : -1;
+                    ch.dim = ch.depth < 60 ? node_dim(RULE, ef_mix64(key + ch.heap), d) : -1;
                     ch.sum = 0;
                     ch.child[0] = ch.child[1] = -1;
                     ch.parent = seg.b + nd.mid;
                     ch.pad = 0;
-                    const int slot = atomicAdd(&n_next_sh, 1);
+                    const int slot = atomicAdd(&n_next_sh[cur], 1);
                     tn[slot] = ch;
                     nd.child[side] = slot;
                 } else {
@@ -811,36 +870,27 @@ finish_kernel(const float *__restrict__ XT, int d, int *perm, const SmallNode *_
                     if (rec) record_leaf(rec, leaf_rec, seg.b + cb, seg.b + nd.mid);
                 }
             }
-            tc[k] = nd;
+            tc[s] = nd;
         }
         __syncthreads();
-        // 4. stable scatter
-        for (int p = tid; p < cnt; p += kFinThreads) {
-            const int k = nc[p];
-            const int id = idc[p];
-            if (k < 0) {
-                idn[p] = id;
-                nn[p] = -1;
-                continue;
-            }
-            const LNode &nd = tc[k];
+        // 4. stable scatter (in place: everybody holds its ids)
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            if (k[u] == kDone) continue;      // (stays where it is)
+            const int p = tid + u * kFinThreads;
+            const LNode &nd = tc[k[u]];
             int dst = p;
             if (nd.moved) {
-                const bool left = (long long)(nd.e - nd.b) * tested(p, nd.dim) < nd.sum;
-                const int lc = lcnt[p] - lcnt[nd.b];
-                dst = left ? nd.b + lc : nd.mid + (p - nd.b - lc);
+                const int lc = left_before(p) - left_before(nd.b);
+                dst = (left >> u) & 1 ? nd.b + lc : nd.mid + (p - nd.b - lc);
             }
-            idn[dst] = id;
-            nn[dst] = nd.child[dst < nd.mid ? 0 : 1];
+            ids[dst] = id[u];
+            nidx[dst] = (unsigned short)nd.child[dst < nd.mid ? 0 : 1];      // (-1: kDone)
         }
-        __syncthreads();
-        n_cur = n_next_sh;
-        cur ^= 1;
-        __syncthreads();
-        if (tid == 0) n_next_sh = 0;
+        n_cur = n_next_sh[cur];
         __syncthreads();
     }
-    for (int p = tid; p < cnt; p += kFinThreads) perm[seg.b + p] = ids_base[cur * kFinMax + p];
+    for (int p = tid; p < cnt; p += kFinThreads) perm[seg.b + p] = ids[p];
     if (rec && tid == 0) atomicMax(max_depth, depth_sh);
 }
 
@@ -1038,9 +1088,11 @@ extern "C" int efanna_build_trees_rule(const float *X, int64_t n, int32_t d, int
     for (int level = 0; n_cur > 0; ++level) {
         // sixteen tiles per block while nodes are a million positions and more (levels 0..3 of the headline)
         const int tiles = (total >> level) / (size_t)T >= (size_t)kBlock * 256 ? 16 : 1;
+        auto choose = d <= 2 * EF_WAVE ? (host_c.wide_input ? choose_dims_kernel<false, true> : choose_dims_kernel<true, true>)
+                                       : (host_c.wide_input ? choose_dims_kernel<false, false> : choose_dims_kernel<true, false>);
         if (split_rule == EFANNA_SPLIT_VARIANCE)
             // (a wave per node: a quarter of the waves and the level waits four nodes long)
-            choose_dims_kernel<<<min((max_live + kBlock / EF_WAVE - 1) / (kBlock / EF_WAVE), 2048), kBlock, 0, st>>>(
+            choose<<<min((max_live + kBlock / EF_WAVE - 1) / (kBlock / EF_WAVE), 2048), kBlock, 0, st>>>(
                 X, d, (int)n, perm_cur, nodes_cur, dims_cur, w.counters, level, seed);
 #define EF_SUM_AND_SCAN(PROJECTION)      /* (node_nxt: free until the scatter) */                            \
     do {                                                                                                 \
@@ -1070,13 +1122,16 @@ extern "C" int efanna_build_trees_rule(const float *X, int64_t n, int32_t d, int
     }
     // host_c.small_nodes is current: it was read after the last level (or after the roots)
     if (host_c.small_nodes > 0) {
-        const size_t fin_lds = (size_t)(6 * kFinMax + 32) * 4 + 2 * (size_t)kFinNodes * sizeof(LNode) +
-                               (split_rule == EFANNA_SPLIT_PROJECTION ? (size_t)kFinMax * 8 : 0);
-        EF_HIP_CHECK(hipFuncSetAttribute((const void *)finish_kernel,
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)fin_lds));
-        finish_kernel<<<host_c.small_nodes, kFinThreads, fin_lds, st>>>(w.xt, d, perm_cur, w.small, w.leaf_flag,
-                                                                  S, seed, (int)n, w.rec, w.leaf_rec,
-                                                                  &w.counters->max_depth, X, split_rule);
+        const int fin_nodes = max(1, fin / (S + 1));      // live nodes have more than S positions
+        const size_t fin_lds = max(finish_lds(fin_nodes), (size_t)(split_rule == EFANNA_SPLIT_PROJECTION ? kFinProjLds : 0));
+        constexpr int V = EFANNA_SPLIT_VARIANCE;
+        auto finish = split_rule == EFANNA_SPLIT_PROJECTION ? finish_kernel<EFANNA_SPLIT_PROJECTION, false, false>
+                      : split_rule == EFANNA_SPLIT_UNIFORM  ? finish_kernel<EFANNA_SPLIT_UNIFORM, false, false>
+                      : d <= 2 * EF_WAVE ? (host_c.wide_input ? finish_kernel<V, false, true> : finish_kernel<V, true, true>)
+                                         : (host_c.wide_input ? finish_kernel<V, false, false> : finish_kernel<V, true, false>);
+        EF_HIP_CHECK(hipFuncSetAttribute((const void *)finish, hipFuncAttributeMaxDynamicSharedMemorySize, (int)fin_lds));
+        finish<<<host_c.small_nodes, kFinThreads, fin_lds, st>>>(w.xt, d, perm_cur, w.small, w.leaf_flag, S, seed, (int)n, w.rec,
+                                                                 w.leaf_rec, &w.counters->max_depth, X, fin_nodes);
     }
     if (perm_cur != perm)
         EF_HIP_CHECK(hipMemcpyAsync(perm, perm_cur, total * 4, hipMemcpyDeviceToDevice, st));

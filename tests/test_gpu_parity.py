@@ -699,6 +699,20 @@ def test_reverse_lists_of_given_lengths(ef, K, L, stride):
         graph_equal(ef, graph, want)
 
 
+@pytest.mark.parametrize("largest", [np.nextafter(np.float32(256), np.float32(0)), np.float32(256), np.float32(-300)])
+@pytest.mark.parametrize("n,d,S", [(2_048, 3, 16), (2_049, 64, 7), (513, 65, 1), (5_000, 128, 2), (4_097, 129, 64)])
+def test_tree_finish_all_rules(ef, n, d, S, largest):
+    """Every split rule at the sizes where the step inside a workgroup begins (a root of its own, one position more, the
+    most nodes of a level), one and several passes over the dimensions, and values on both sides of 256, where sums
+    by variance change from narrow to wide."""
+    rng = np.random.default_rng(n + d)
+    X = (60.0 * rng.standard_normal((n, d))).clip(-250, 250).astype(np.float32)
+    X[: n // 3] = np.round(X[: n // 3])
+    X[7 % n, d - 1] = largest
+    for rule in (ef.SPLIT_UNIFORM, ef.SPLIT_VARIANCE, ef.SPLIT_PROJECTION):
+        tree_nodes_equal(ef, X, 3, S, 11, rule)
+
+
 @pytest.mark.parametrize("K,L", [(33, 32), (64, 20), (100, 50), (128, 64), (128, 1)])
 def test_sampling_of_long_rows_with_ties(ef, K, L):
     """Rows of more than 32 entries on an integer grid (many equal distances): the L-th new entry is
