@@ -81,13 +81,17 @@ __device__ inline void record_leaf(NodeRec *rec, int *leaf_rec, int b, int paren
     if (parent >= 0) rec[parent].child[b >= parent ? 1 : 0] = ~b;
 }
 
-constexpr int kFinMax = 2048;      // largest segment finish_kernel takes
-constexpr int kFinNodes = 256;     // nodes of one level inside such a segment
-constexpr int kFinThreads = 512;    // threads of a finish_kernel block
-inline int finish_limit(int S)
+// What a finish_kernel block takes: segments of at most fin_max positions, kFinNodes of them per level at most, four
+// positions to a thread.  Splits by one coordinate take twice as much as the other rules: a level less of the device-wide
+// kernels, which cost six launches (builds of 10^4 x 32 778 -> 752 us, 200 003 x 50 4.77 -> 4.72 ms, 10^6 x 128 15.89 -> 15.77).  Splits by variance
+// have no registers for a thousand threads, projections are the faster the fewer rows they read at a time.
+constexpr int kFinNodes = 512;     // nodes of one level inside a segment, at most
+__host__ __device__ constexpr int fin_max(int rule) { return rule == EFANNA_SPLIT_UNIFORM ? 4096 : 2048; }
+__host__ __device__ constexpr int fin_threads(int rule) { return fin_max(rule) / 4; }
+inline int finish_limit(int S, int rule)
 {
-    long f = (long)kFinNodes * (S + 1);     // so that a level never has more than kFinNodes live nodes
-    return f < kFinMax ? (int)f : kFinMax;
+    const long f = (long)kFinNodes * (S + 1);     // so that a level never has more than kFinNodes live nodes
+    return f < fin_max(rule) ? (int)f : fin_max(rule);
 }
 
 
@@ -717,7 +721,7 @@ __global__ void scatter_kernel(const int *__restrict__ perm_in, int *__restrict_
     node_out[dst] = nd.child[dst < (size_t)nd.mid ? 0 : 1];
 }
 
-// Finishes the subtree of one small node (at most kFinMax positions) inside a workgroup:
+// Finishes the subtree of one small node (at most fin_max positions) inside a workgroup:
 // the same four steps per level as the device-wide kernels (integer sums, prefix sum of
 // the "goes left" predicate, children, stable scatter), but with the ids, the node table
 // and the prefix sums in LDS, so the lower half of a tree costs one launch instead of
@@ -732,18 +736,20 @@ struct LNode {
 };
 
 // LDS of a block: ids, node indexes of 16 bits, the split tests as bits, two node tables of `nodes`.  A thread keeps the
-// ids, nodes and tested values of its positions (every kFinThreads-th) in registers: 26 KB for leaves of 16, four blocks per
+// ids, nodes and tested values of its positions (every kFinThreads-th) in registers: 26 KB for leaves of 16 and 2048 positions, four blocks per
 // CU (with all of it and prefix sums in LDS 78 KB, two blocks).  What bounds it, 10^6 x 128, eight trees: splits by one coordinate
-// the scattered 4-byte gathers (56 M of them, 128-byte lines at 6.8 TB/s; 1.08 -> 1.05 ms), splits by variance the rows of the
+// the scattered 4-byte gathers (56 M of them in seven levels, 128-byte lines at 6.8 TB/s; 1.08 -> 1.05 ms), splits by variance the rows of the
 // samples (14.5 GB, at 4.0 TB/s; 5.13 -> 3.61 ms, see variance_dim_wave; two blocks per CU 3.83).
-constexpr int kFinWords = kFinMax / EF_WAVE;
 // Random projections ask for one block per CU: the eight lines that a position reads of its row come the faster the fewer
 // waves ask for others in between (200 000 x 960: one block 1.65 ms, two 1.74, three 1.81, four 1.86).
 constexpr size_t kFinProjLds = 96 * 1024;
-inline size_t finish_lds(int nodes) { return (size_t)kFinMax * 6 + kFinWords * 12 + 64 + 2 * (size_t)nodes * sizeof(LNode); }
+inline size_t finish_lds(int rule, int nodes)
+{
+    return (size_t)fin_max(rule) * 6 + fin_max(rule) / EF_WAVE * 12 + 64 + 2 * (size_t)nodes * sizeof(LNode);
+}
 
 template <int RULE, bool NARROW, bool ONE>      // the split rule; NARROW, ONE: see variance_dim_wave, which wants more registers
-__global__ void __launch_bounds__(kFinThreads) __attribute__((amdgpu_waves_per_eu(RULE == 1 ? 6 : RULE == 2 ? 4 : 8)))
+__global__ void __launch_bounds__(fin_threads(RULE)) __attribute__((amdgpu_waves_per_eu(RULE == 1 ? 6 : RULE == 2 ? 4 : 8)))
 finish_kernel(const float *__restrict__ XT, int d, int *perm, const SmallNode *__restrict__ small,
               unsigned char *leaf_flag, int S, u64 seed, int n, NodeRec *rec, int *leaf_rec,
               int *max_depth, const float *__restrict__ X, int nodes)
@@ -751,6 +757,8 @@ finish_kernel(const float *__restrict__ XT, int d, int *perm, const SmallNode *_
     // One 16-byte aligned LDS block carved by hand (no separate static LDS variables, whose
     // size would shift the 8-byte node records off their alignment).
     extern __shared__ __align__(16) int fsm[];
+    constexpr int kFinMax = fin_max(RULE), kFinThreads = fin_threads(RULE), kFinWords = kFinMax / EF_WAVE, kDone = 0xFFFF, PER = kFinMax / kFinThreads;
+    static_assert(kFinWords <= EF_WAVE, "a wave adds up the words");
     LNode *const tabs_base = (LNode *)fsm;                          // [2][nodes]
     u64 *const bits = (u64 *)(tabs_base + 2 * nodes);               // [kFinWords] "goes left", one bit per position
     int *const before = (int *)(bits + kFinWords);                  // [kFinWords + 1] set bits before each word
@@ -758,7 +766,6 @@ finish_kernel(const float *__restrict__ XT, int d, int *perm, const SmallNode *_
     int &depth_sh = n_next_sh[2];                                   // deepest node of this subtree
     int *const ids = before + kFinWords + 16;                       // [kFinMax]
     unsigned short *const nidx = (unsigned short *)(ids + kFinMax); // [kFinMax], kDone: in a leaf
-    constexpr int kDone = 0xFFFF, PER = kFinMax / kFinThreads;
     const SmallNode seg = small[blockIdx.x];
     const int cnt = seg.e - seg.b, tid = threadIdx.x, lane = ef_lane();
     const u64 key = ef_stream_key(seed, seg.b / n);
@@ -846,7 +853,8 @@ finish_kernel(const float *__restrict__ XT, int d, int *perm, const SmallNode *_
         __syncthreads();
         if (tid < EF_WAVE) {
             const int c = tid < kFinWords ? __popcll(bits[tid]) : 0, incl = ef_wave_scan_i32(c);
-            if (tid <= kFinWords) before[tid] = incl - c;
+            if (tid < kFinWords) before[tid] = incl - c;
+            if (tid == EF_WAVE - 1) before[kFinWords] = incl;
         }
         __syncthreads();
         auto left_before = [&](int p) {      // p <= kFinMax
@@ -1064,7 +1072,7 @@ extern "C" int efanna_build_trees_rule(const float *X, int64_t n, int32_t d, int
     transpose_check_kernel<<<dim3((unsigned)((n + kTrTile - 1) / kTrTile), (unsigned)((d + kTrTile - 1) / kTrTile)), kBlock, 0, st>>>(
         X, (int)n, d, w.xt, w.counters, split_rule == EFANNA_SPLIT_PROJECTION ? (double)kProjectionTerms : 1.0);
     iota_kernel<<<grid_pos, kBlock, 0, st>>>(perm, (int)n, total);
-    const int fin = finish_limit(S);
+    const int fin = finish_limit(S, split_rule);
     roots_kernel<<<grid_pos, kBlock, 0, st>>>(w.nodes_a, w.dims_a, w.node_a, w.leaf_flag, (int)n, T, S, fin,
                                               w.small, seed, d, w.counters, split_rule);
     // The level counters are read into pinned host memory (one small buffer per calling thread,
@@ -1134,14 +1142,14 @@ extern "C" int efanna_build_trees_rule(const float *X, int64_t n, int32_t d, int
     // host_c.small_nodes is current: it was read after the last level (or after the roots)
     if (host_c.small_nodes > 0) {
         const int fin_nodes = max(1, fin / (S + 1));      // live nodes have more than S positions
-        const size_t fin_lds = max(finish_lds(fin_nodes), (size_t)(split_rule == EFANNA_SPLIT_PROJECTION ? kFinProjLds : 0));
+        const size_t fin_lds = max(finish_lds(split_rule, fin_nodes), (size_t)(split_rule == EFANNA_SPLIT_PROJECTION ? kFinProjLds : 0));
         constexpr int V = EFANNA_SPLIT_VARIANCE;
         auto finish = split_rule == EFANNA_SPLIT_PROJECTION ? finish_kernel<EFANNA_SPLIT_PROJECTION, false, false>
                       : split_rule == EFANNA_SPLIT_UNIFORM  ? finish_kernel<EFANNA_SPLIT_UNIFORM, false, false>
                       : d <= 2 * EF_WAVE ? (host_c.wide_input ? finish_kernel<V, false, true> : finish_kernel<V, true, true>)
                                          : (host_c.wide_input ? finish_kernel<V, false, false> : finish_kernel<V, true, false>);
         EF_HIP_CHECK(hipFuncSetAttribute((const void *)finish, hipFuncAttributeMaxDynamicSharedMemorySize, (int)fin_lds));
-        finish<<<host_c.small_nodes, kFinThreads, fin_lds, st>>>(w.xt, d, perm_cur, w.small, w.leaf_flag, S, seed, (int)n, w.rec,
+        finish<<<host_c.small_nodes, fin_threads(split_rule), fin_lds, st>>>(w.xt, d, perm_cur, w.small, w.leaf_flag, S, seed, (int)n, w.rec,
                                                                  w.leaf_rec, &w.counters->max_depth, X, fin_nodes);
     }
     if (perm_cur != perm)
