@@ -1085,9 +1085,15 @@ extern "C" int efanna_build_trees_rule(const float *X, int64_t n, int32_t d, int
         (void)hipGetLastError();
     }
     Counters &host_c = host_pinned ? *host_pinned : host_local;
-    EF_HIP_CHECK(hipMemcpyAsync(&host_c, w.counters, sizeof(Counters), hipMemcpyDeviceToHost, st));
-    EF_HIP_CHECK(hipStreamSynchronize(st));
-    if (host_c.bad_input) return EFANNA_EINPUT;
+    // Splits by variance want to know the size of the values before the first level, and trees that are finished inside a
+    // workgroup have no other stop; otherwise the first look at the level counters says whether the input is good (until then
+    // a bad value only decides which side a position goes to).
+    if (n <= fin || split_rule == EFANNA_SPLIT_VARIANCE) {
+        EF_HIP_CHECK(hipMemcpyAsync(&host_c, w.counters, sizeof(Counters), hipMemcpyDeviceToHost, st));
+        EF_HIP_CHECK(hipStreamSynchronize(st));
+        if (host_c.bad_input) return EFANNA_EINPUT;
+    } else
+        host_c = Counters{};
 
     int *perm_cur = perm, *perm_nxt = w.perm_tmp;
     int *node_cur = w.node_a, *node_nxt = w.node_b;
@@ -1132,6 +1138,7 @@ extern "C" int efanna_build_trees_rule(const float *X, int64_t n, int32_t d, int
         if (level + 1 >= sure) {
             EF_HIP_CHECK(hipMemcpyAsync(&host_c, w.counters, sizeof(Counters), hipMemcpyDeviceToHost, st));
             EF_HIP_CHECK(hipStreamSynchronize(st));
+            if (host_c.bad_input) return EFANNA_EINPUT;
             n_cur = host_c.n_nodes[(level + 1) & 1];
         }
         int *tp = perm_cur; perm_cur = perm_nxt; perm_nxt = tp;
