@@ -1557,7 +1557,8 @@ reverse_overflow_kernel(const Overflow *__restrict__ overflow, size_t ovf_region
 //      offers (one word: target << row bits | source row inside the block) in LDS, counts them per
 //      bucket (a range of up to 1024 targets, of 512 if L > 16: the lists of a range have to fit the
 //      LDS), and writes them to its own part of the offer array, bucket after bucket;
-//      table[bucket][block] = start << 16 | count of that run;
+//      table[block][bucket] = start << 16 | count of that run (written in one piece; by bucket, a word into each
+//      of as many lines as there are buckets, it cost the offer kernels 8 us a launch at 10^6 points, reading it across 2);
 //   2. a list block (one per bucket) walks the runs of its bucket, sorts the offers by target in LDS and
 //      writes every target's list (bucket_lists_kernel).
 // Whatever the order of the offers, a list ends up with the L smallest keys offered to it.
@@ -1670,7 +1671,7 @@ __device__ inline void offer_append(bool take, u32 offer, int shift, u32 *offers
 }
 
 // End of an offer block: runs per bucket in `out` (this block's part of the offer array) and
-// the block's column of the table.  hist, cursor: [n_buckets] in LDS; n_buckets is at most PER times the threads.
+// the block's row of the table.  hist, cursor: [n_buckets] in LDS; n_buckets is at most PER times the threads.
 template <int RB, int PER>
 __device__ inline void offers_flush(const u32 *offers, const int *hist, int *cursor, int n_buckets, int shift,
                                     int total, u32 *__restrict__ out, u32 *__restrict__ table)
@@ -1692,7 +1693,7 @@ __device__ inline void offers_flush(const u32 *offers, const int *hist, int *cur
     for (int k = 0; k < PER; ++k) {
         if (b0 + k < n_buckets) {
             cursor[b0 + k] = off;
-            table[(size_t)(b0 + k) * gridDim.x + blockIdx.x] = (u32)off << 16 | (u32)c[k];
+            table[(size_t)blockIdx.x * n_buckets + b0 + k] = (u32)off << 16 | (u32)c[k];
         }
         off += c[k];
     }
@@ -1741,6 +1742,34 @@ sample_bucket_kernel(u64 *graph, int n, int K, int L, int *__restrict__ nw, int 
     offers_flush<RB, 2>(offers, hist, cursor, n_buckets, shift, fill, offer_runs + (size_t)blockIdx.x * kRows * L, table);
 }
 
+// The offers of a block's 1 << RB rows to the reverse-old lists of points that join something.  Four ids per thread travel at a
+// time, and then four words of the map: the two waits are what a block's time is made of.  (One id at a time:
+// six launches of 10^5 points, degree 20 125 -> 104 us, the wait of 10^6 points is for lines of the map, 444 -> 436.)
+template <int RB>
+__device__ inline void old_offers(const int *__restrict__ od, int n, int K, const u64 *__restrict__ active, int shift, u32 *offers,
+                                  int *hist, int *fill)
+{
+    constexpr int U = 4;
+    const int n_thr = (int)blockDim.x, first = blockIdx.x << RB, ids_here = min(1 << RB, n - first) * K;
+    for (int f0 = 0; f0 < ids_here; f0 += U * n_thr) {      // all threads take every round
+        int id[U];
+        bool take[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int f = f0 + u * n_thr + (int)threadIdx.x;
+            id[u] = f < ids_here ? od[(size_t)first * K + f] : -1;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            take[u] = id[u] >= 0 && id[u] < n && ((active[id[u] / EF_WAVE] >> (id[u] % EF_WAVE)) & 1);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int f = f0 + u * n_thr + (int)threadIdx.x;
+            offer_append<RB>(take[u], ((u32)id[u] << RB) | (u32)(f / K), shift, offers, hist, fill);
+        }
+    }
+}
+
 // Reverse-old offers of 1 << RB rows (to points that join something, as in reverse_old_kernel).
 // LDS: offers [K << RB] words, hist and cursor [n_buckets] int each.
 template <int RB>
@@ -1756,13 +1785,7 @@ reverse_old_bucket_kernel(const int *__restrict__ od, int n, int K, const u64 *_
     for (int b = threadIdx.x; b < n_buckets; b += kThreads) hist[b] = 0;
     if (threadIdx.x == 0) fill = 0;
     __syncthreads();
-    const int first = blockIdx.x * kRows, rows_here = min(kRows, n - first);
-    for (int f0 = 0; f0 < rows_here * K; f0 += kThreads) {      // all threads take every round
-        const int f = f0 + (int)threadIdx.x;
-        const int id = f < rows_here * K ? od[(size_t)first * K + f] : -1;
-        const bool take = id >= 0 && id < n && ((active[id / EF_WAVE] >> (id % EF_WAVE)) & 1);
-        offer_append<RB>(take, ((u32)id << RB) | (u32)(f / K), shift, offers, hist, &fill);
-    }
+    old_offers<RB>(od, n, K, active, shift, offers, hist, &fill);
     __syncthreads();
     offers_flush<RB, 2>(offers, hist, cursor, n_buckets, shift, fill, offer_runs + (size_t)blockIdx.x * kRows * K, table);
 }
@@ -1807,30 +1830,13 @@ reverse_old_wide_kernel(const int *__restrict__ od, int n, int K, const u64 *__r
 {
     extern __shared__ __align__(16) u32 offer_sm[];
     u32 *offers = offer_sm;
-    constexpr int kRows = 1 << RB, kThreads = 4 << RB, U = 4;      // U: ids in flight per thread
+    constexpr int kRows = 1 << RB, kThreads = 4 << RB;
     int *hist = (int *)(offers + (size_t)kRows * K), *cursor = hist + n_buckets;
     __shared__ int fill;
     for (int b = threadIdx.x; b < n_buckets; b += kThreads) hist[b] = 0;
     if (threadIdx.x == 0) fill = 0;
     __syncthreads();
-    const int first = blockIdx.x * kRows, ids_here = min(kRows, n - first) * K;
-    for (int f0 = 0; f0 < ids_here; f0 += U * kThreads) {      // all threads take every round
-        int id[U];
-        bool take[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int f = f0 + u * kThreads + (int)threadIdx.x;
-            id[u] = f < ids_here ? od[(size_t)first * K + f] : -1;
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            take[u] = id[u] >= 0 && id[u] < n && ((active[id[u] / EF_WAVE] >> (id[u] % EF_WAVE)) & 1);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int f = f0 + u * kThreads + (int)threadIdx.x;
-            offer_append<RB>(take[u], ((u32)id[u] << RB) | (u32)(f / K), shift, offers, hist, &fill);
-        }
-    }
+    old_offers<RB>(od, n, K, active, shift, offers, hist, &fill);
     __syncthreads();
     offers_flush<RB, 4>(offers, hist, cursor, n_buckets, shift, fill, offer_runs + (size_t)blockIdx.x * kRows * K, table);
 }
@@ -1869,6 +1875,14 @@ inline int bucket_lists_area(int K, int L, int shift, int n_blocks, int threads,
 __host__ __device__ inline size_t bucket_lists_lds(int L, int shift, int n_blocks)
 {
     return ((size_t)L << shift) * 8 + ((size_t)2 * n_blocks + 2) * 4;
+}
+
+// The bucket of a list block: workgroups go to the eight chiplets in turn, and neighbouring buckets, whose runs lie side by
+// side in every offer block's part of the array and share its lines, as the words of the table do, go to the same one's L2.
+__device__ inline int bucket_of_block()
+{
+    const int n = (int)gridDim.x, part = blockIdx.x % 8;
+    return part * (n / 8) + min(part, n % 8) + (int)(blockIdx.x / 8);
 }
 
 struct OfferRun {
@@ -2038,19 +2052,20 @@ bucket_lists_kernel(const u32 *__restrict__ offer_runs, const u32 *__restrict__ 
     __shared__ int total_sm, any_many, again;
     __shared__ int wave_tot[kBktThreads / EF_WAVE];
     __shared__ int n_class[3];
-    const int t = threadIdx.x, first = blockIdx.x * targets, rows_here = min(targets, n - first);
+    const int bucket = bucket_of_block(), t = threadIdx.x, first = bucket * targets, rows_here = min(targets, n - first);
     const int lane = ef_lane(), wave = t / EF_WAVE, n_waves = n_thr / EF_WAVE;
     for (int f = t; f < targets; f += n_thr) hist[f] = 0;
     if (t < 3) n_class[t] = 0;
     if (t == 0) any_many = 0;
-    const u32 *runs = table + (size_t)blockIdx.x * n_blocks;
+    const u32 *runs = table + bucket;      // (of block r: r * pitch words on)
+    const size_t pitch = gridDim.x;
     {
         const int k0 = PER * t;
         u32 r[PER];
         int sum = 0;
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
-            r[k] = k0 + k < n_blocks ? runs[k0 + k] : 0u;
+            r[k] = k0 + k < n_blocks ? runs[(k0 + k) * pitch] : 0u;
             sum += (int)(r[k] & 0xFFFFu);
         }
         const int incl = ef_wave_scan_i32(sum);
@@ -2082,7 +2097,7 @@ bucket_lists_kernel(const u32 *__restrict__ offer_runs, const u32 *__restrict__ 
         const int place = (int)(here & 0xFFFFu);
         return OfferRun{(int)(here >> 16), (int)(run_at[r + 1] & 0xFFFFu) - place, place};
     };
-    auto table_run = [&](int r) { return OfferRun{(int)(runs[r] >> 16), (int)(runs[r] & 0xFFFFu), 0}; };
+    auto table_run = [&](int r) { return OfferRun{(int)(runs[r * pitch] >> 16), (int)(runs[r * pitch] & 0xFFFFu), 0}; };
     auto row_of = [&](u32 o) {      // (always inside: runs are filed by bucket)
         const int row = (int)(o >> RB) - first;
         return (unsigned)row < (unsigned)rows_here ? row : -1;
@@ -2283,12 +2298,13 @@ bucket_insert_kernel(const u32 *__restrict__ offer_runs, const u32 *__restrict__
     const int targets = 1 << shift, n_thr = (int)blockDim.x;
     int *scan = (int *)(ll + (size_t)targets * L), *start = scan + n_blocks + 1;
     __shared__ int wave_tot[kBktThreads / EF_WAVE];
-    const int t = threadIdx.x, first = blockIdx.x * targets, rows_here = min(targets, n - first);
+    const int bucket = bucket_of_block(), t = threadIdx.x, first = bucket * targets, rows_here = min(targets, n - first);
     for (int f = t; f < targets * L; f += n_thr) ll[f] = ~0ULL;
-    const u32 *runs = table + (size_t)blockIdx.x * n_blocks;
+    const u32 *runs = table + bucket;      // (of block r: r * pitch words on)
+    const size_t pitch = gridDim.x;
     {
         const int k0 = 2 * t;
-        const u32 r0 = k0 < n_blocks ? runs[k0] : 0u, r1 = k0 + 1 < n_blocks ? runs[k0 + 1] : 0u;
+        const u32 r0 = k0 < n_blocks ? runs[k0 * pitch] : 0u, r1 = k0 + 1 < n_blocks ? runs[(k0 + 1) * pitch] : 0u;
         const int c0 = (int)(r0 & 0xffffu), c1 = (int)(r1 & 0xffffu);
         const int incl = ef_wave_scan_i32(c0 + c1);
         if (ef_lane() == EF_WAVE - 1) wave_tot[t / EF_WAVE] = incl;
