@@ -246,3 +246,30 @@ def test_two_million_short_vectors_bit_exact(n):
     assert np.array_equal(dists.view(np.uint32), want[1].view(np.uint32))
     assert np.array_equal(flags, want[2])
     assert np.array_equal(stats[:, 0].astype(np.int64), want[3][:, 0].astype(np.int64))
+
+
+@pytest.mark.timeout(600)
+@pytest.mark.parametrize("n", [1 << 20, (1 << 20) + 1])
+def test_a_million_long_rows_bit_exact(n):
+    """Degree 33: 2^20 points are the most whose reverse lists of long rows are built by target range (4096 ranges of 256,
+    4096 offer blocks of 256 rows), one more takes counters and queues."""
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU: there is no CPU fallback")
+    from paper_1609_07228_amd import efanna
+    rng = np.random.default_rng(21)
+    X = rng.standard_normal((n, 4)).astype(np.float32)
+    K, L, S = 33, 8, 40
+    Xd = torch.from_numpy(X).cuda()
+    perm, off, nl = efanna.efanna_build_trees(Xd, 1, S, 5)
+    graph = efanna.efanna_init_graph(Xd, perm, off, nl, S, K)
+    operm, ooff, onl = oracle.build_trees(X, 1, S, 5)
+    want = oracle.init_graph(X, operm, ooff, onl, K)
+    for it in range(2):
+        efanna.efanna_nndescent(Xd, graph, 1, L, 5, first_iter=it)
+        torch.cuda.synchronize()
+        _progress(f"n = {n}, iteration {it}: gpu done")
+        want = oracle.nndescent(X, *want[:3], 1, L, 5, iter0=it)
+    ids, dists, flags = efanna.efanna_get_graph(graph, with_flags=True)
+    assert np.array_equal(ids.cpu().numpy(), want[0])
+    assert dists.cpu().numpy().tobytes() == want[1].tobytes()
+    assert np.array_equal(flags.cpu().numpy(), want[2])
