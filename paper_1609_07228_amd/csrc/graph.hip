@@ -1594,6 +1594,9 @@ __host__ __device__ inline bool bucketed_lists(int64_t n, int K, int L)
 // Beyond, ranges of 128 targets up, as large as make kBktMany of them (all list kernels of 10^5 points, degree 10, from a random
 // start: 390 -> 328 us; degree 20 235 -> 230), and no larger than lets 1024 threads hold ten offers each.  (More of them
 // for a million points, 1954 instead of 977: 998 -> 1039, and the offer kernels, which count and write runs per range, 1076 -> 1190.)
+// At least 512 threads, for the ranges of popular points side by side, whose offers one block has to look at alone (200 000 x 8 from rows that
+// name low ids more often, degree 10: 4.67 ms with 256, 3.54 with 512; degree 20, 20 000 x 64 sorted by norm: 2.46 and 1.80); 256 where ranges
+// of at most 128 targets are offered ten each: there the waves cost more than they bring (100 000 x 8 1112 us, 1125 with 512).
 struct BucketShape {
     int row_bits, blocks;           // log2 of the source rows of an offer block, number of blocks
     int shift, buckets, threads;    // log2 of the targets of a bucket, number of buckets, threads of a list block
@@ -1609,7 +1612,8 @@ inline BucketShape bucket_shape(int64_t n, int K, int L)
         b.blocks = (int)((n + (1 << row_bits) - 1) >> row_bits);
         b.buckets = (int)((n - 1) >> shift) + 1;
         b.threads = (per <= 10 || L <= kInsertTo ? 1 : per <= 20 ? 2 : 4) << shift;
-        b.threads = b.threads < 256 ? 256 : b.threads > kBktThreads ? kBktThreads : b.threads;
+        const int least = L <= kInsertTo || (per <= 10 && shift <= 7) ? 256 : 512;
+        b.threads = b.threads < least ? least : b.threads > kBktThreads ? kBktThreads : b.threads;
         b.table_behind = (int64_t)b.blocks * b.buckets <= n * L;
     };
     if (n <= (1 << 16) && L >= 4) {
@@ -1847,8 +1851,12 @@ reverse_old_wide_kernel(const int *__restrict__ od, int n, int K, const u64 *__r
 // sixteen lanes rank them by row rotations of the hashes, up to 512 a wave finds a bound that L hashes lie below
 // bit by bit from ballots, and of more only those below a bound that some L + 6 sqrt(L) hashes lie below
 // are sorted at all (all threads of the block look at the popular points' offers).
-// Where the offers do not fit the threads' registers they are read twice, and where what is to be sorted does not
-// fit the LDS, keys enter lists there by the bounded insertion, as many targets at a time as there is room for.
+// Where the offers do not fit the threads' registers they are read twice, and where what is to be sorted cannot be sure to
+// fit the LDS, keys enter lists there by the bounded insertion, as many targets at a time as there is room for: ranges of
+// popular points side by side, data sorted by norm among them.  (Insertion alone with a scan per offer, before the offers were sorted /
+// offers counted first, walked by eight lanes a run, and every key's scan by its own lane / now: 100 000 x 64 sorted by norm, degree 20, four iterations
+// 6.33, 9.59 and 4.91 ms; 200 000 x 8, low ids named more often, degree 10, two 4.29, 6.00 and 3.54.  Not made up for: 500 000 x 16 sorted by
+// norm, degree 10, 3.91 and 4.24 ms, where two dozen ranges hold up to twice what fits and are walked twice.)
 // What bounds it: instruction issue in the first iterations (10^6 points of degree 10: 3900 -> 3100 wave instructions per
 // wave of a launch, half of them choosing), a fixed 25 us of run descriptors and barriers in the last.  All
 // sixteen launches of that build 1338 -> 1010 us, with the bounded insertion for all (a list scanned in LDS per offer, again
@@ -1892,8 +1900,8 @@ struct OfferRun {
 
 // The offers of a bucket by their runs, lanes_bits: log2 of the lanes that walk a run together; run(r): an OfferRun.
 // found(run, place, offer word) for every offer.
-// U: runs in flight per group of lanes.
-template <int U, class Run, class Found>
+// U: runs in flight per group of lanes, A: words of what is left of a run in flight per lane.
+template <int U, int A, class Run, class Found>
 __device__ inline void walk_offers(const u32 *__restrict__ offer_runs, int n_blocks, int run_cap, int lanes_bits, int n_thr,
                                    Run &&run, Found &&found)
 {
@@ -1912,7 +1920,15 @@ __device__ inline void walk_offers(const u32 *__restrict__ offer_runs, int n_blo
         for (int u = 0; u < U; ++u) {
             const int r = r0 + u * groups;
             if (gl < a[u].count) found(r, a[u].place + gl, o[u]);
-            for (int q = gl + g; q < a[u].count; q += g) found(r, a[u].place + q, offer_runs[(size_t)r * run_cap + a[u].start + q]);
+            for (int q0 = gl + g; q0 < a[u].count; q0 += A * g) {
+                u32 more[A];
+#pragma unroll
+                for (int k = 0; k < A; ++k)
+                    if (q0 + k * g < a[u].count) more[k] = offer_runs[(size_t)r * run_cap + a[u].start + q0 + k * g];
+#pragma unroll
+                for (int k = 0; k < A; ++k)
+                    if (q0 + k * g < a[u].count) found(r, a[u].place + q0 + k * g, more[k]);
+            }
         }
     }
 }
@@ -2089,13 +2105,15 @@ bucket_lists_kernel(const u32 *__restrict__ offer_runs, const u32 *__restrict__ 
     constexpr u32 kRowMask = (1u << RB) - 1;
     int c = 0;      // filled slots of target t's list
     const bool sorted_by_regs = total <= min(area, kWords * n_thr);
+    const bool insert = !sorted_by_regs && total > area && targets * kRoom > area;      // what is to be sorted might not fit
+    const int many_bits = total >= 40 * n_blocks ? 6 : g_bits;      // lanes to a run where there are more than usual
     constexpr int SB = 21;      // source bits
     constexpr u32 kNone = ~0u;
-    // (the places in run_at have 16 bits: where there are more offers, the runs' extents come from the table)
+    // (places have 16 bits: of more offers only the differences are good, which no run exceeds)
     auto run_of = [&](int r) {
         const u32 here = run_at[r];
         const int place = (int)(here & 0xFFFFu);
-        return OfferRun{(int)(here >> 16), (int)(run_at[r + 1] & 0xFFFFu) - place, place};
+        return OfferRun{(int)(here >> 16), (int)((run_at[r + 1] - here) & 0xFFFFu), place};
     };
     auto table_run = [&](int r) { return OfferRun{(int)(runs[r * pitch] >> 16), (int)(runs[r * pitch] & 0xFFFFu), 0}; };
     auto row_of = [&](u32 o) {      // (always inside: runs are filed by bucket)
@@ -2122,9 +2140,9 @@ bucket_lists_kernel(const u32 *__restrict__ offer_runs, const u32 *__restrict__ 
                 found(lo, j, offer_runs[(size_t)lo * run_cap + r.start + (j - r.place)]);
             }
         } else
-            walk_offers<4>(offer_runs, n_blocks, run_cap, g_bits, n_thr, run_of, found);
-    } else
-        walk_offers<4>(offer_runs, n_blocks, run_cap, g_bits, n_thr, table_run, [&](int, int, u32 o) {
+            walk_offers<4, 1>(offer_runs, n_blocks, run_cap, g_bits, n_thr, run_of, found);
+    } else if (!insert)
+        walk_offers<1, 4>(offer_runs, n_blocks, run_cap, many_bits, n_thr, run_of, [&](int, int, u32 o) {
             const int row = row_of(o);
             if (row >= 0) atomicAdd(&hist[row], 1);
         });
@@ -2153,14 +2171,11 @@ bucket_lists_kernel(const u32 *__restrict__ offer_runs, const u32 *__restrict__ 
     if (many) any_many = 1;
     if (t < targets) bound[t] = (unsigned short)(many ? (u32)(share * 65535.0f) : kAll);
     __syncthreads();
-    int begin = incl - room, fits = 0;
-    for (int v = 0; v < n_waves; ++v) {
-        begin += v < wave ? wave_tot[v] : 0;
-        fits += wave_tot[v];
-    }
+    int begin = incl - room;
+    for (int v = 0; v < wave; ++v) begin += wave_tot[v];
     const int n0 = n_class[0], n1 = n_class[1], n2 = n_class[2];
     const bool popular = any_many;
-    bool settled = sorted_by_regs || fits <= area;      // uniform over the block
+    bool settled = !insert;      // uniform over the block
     if (settled) {
         if (t < targets) offs[t] = hist[t] = begin;
         if (cls >= 0) order[(cls == 0 ? 0 : cls == 1 ? n0 : n0 + n1) + place] = (unsigned short)t;
@@ -2186,7 +2201,7 @@ bucket_lists_kernel(const u32 *__restrict__ offer_runs, const u32 *__restrict__ 
                 __syncthreads();
             }
             if (tries > 0 || !sorted_by_regs)
-                walk_offers<1>(offer_runs, n_blocks, run_cap, g_bits, n_thr, table_run, [&](int run, int, u32 o) {
+                walk_offers<1, 4>(offer_runs, n_blocks, run_cap, many_bits, n_thr, table_run, [&](int run, int, u32 o) {
                     const int row = row_of(o);
                     if (row < 0) return;
                     const u32 source = source_of(run, o), most = bound[row];
@@ -2237,34 +2252,86 @@ bucket_lists_kernel(const u32 *__restrict__ offer_runs, const u32 *__restrict__ 
         c = min(mine, L);
     }
     if (!settled) {
-        // more offers than fit, or no bound found: bounded insertion, as many targets at a time as there is room for lists
+        // more offers than are sure to fit, or no bound found: bounded insertion, as many targets at a time as there is room for.
+        // A wave walks a run, drops what is above the largest key that was seen in a full list (hist: its high half; keys
+        // only ever fall) and puts the others by until they fill its lanes: of the offers to popular points few are
+        // left, and a scan of the list costs a wave the same for one of them as for 64.
         __syncthreads();
         u64 *ll = list_sm;
-        const int step = area / (2 * L);
+        u32 *put_by = words + area - EF_WAVE * (wave + 1);
+        const int step = (area - n_thr) / (2 * L);
         for (int row0 = 0; row0 < rows_here; row0 += step) {
             const int rows = min(step, rows_here - row0);
             for (int f = t; f < rows * L; f += n_thr) ll[f] = ~0ULL;
+            if (t < rows) hist[t] = -1;
             __syncthreads();
-            walk_offers<1>(offer_runs, n_blocks, run_cap, g_bits, n_thr, table_run, [&](int run, int, u32 o) {
-                const int target = (int)(o >> RB), row = target - first - row0;
-                if ((unsigned)row >= (unsigned)rows) return;
-                const u64 key = reverse_key(stream_key, target, (int)source_of(run, o));
-                unsigned long long *list = (unsigned long long *)(ll + row * L);
-                for (;;) {
-                    u64 mx = 0;
-                    int ms = 0;
-                    for (int a = 0; a < L; ++a) {
-                        const u64 v = __hip_atomic_load(list + a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                        if (v > mx) {      // the first of equal (empty) slots: lists fill from slot 0 up
-                            mx = v;
-                            ms = a;
+            auto largest = [&](int row) { return __hip_atomic_load((u32 *)hist + row, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); };
+            int fill = 0;      // (the wave's)
+            auto wave_sync = [&]() {      // one wave: its LDS operations complete in program order
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+            };
+            auto drain = [&]() {
+                wave_sync();
+                if (lane < fill) {
+                    const u32 o = put_by[lane];
+                    const int row = (int)(o >> SB);
+                    const u64 key = reverse_key(stream_key, first + row0 + row, (int)(o & ((1u << SB) - 1)));
+                    unsigned long long *list = (unsigned long long *)(ll + row * L);
+                    while ((u32)(key >> 32) <= largest(row)) {
+                        u64 mx = 0;
+                        int ms = 0;
+#pragma unroll 4
+                        for (int a = 0; a < L; ++a) {
+                            const u64 v = __hip_atomic_load(list + a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                            if (v > mx) {      // the first of equal (empty) slots: lists fill from slot 0 up
+                                mx = v;
+                                ms = a;
+                            }
                         }
+                        atomicMin((u32 *)hist + row, (u32)(mx >> 32));
+                        if (key >= mx) break;
+                        // slots only ever fall: if slot ms still holds mx, it still is the largest
+                        if (atomicCAS(list + ms, (unsigned long long)mx, (unsigned long long)key) == mx) break;
                     }
-                    if (key >= mx) break;
-                    // slots only ever fall: if slot ms still holds mx, it still is the largest
-                    if (atomicCAS(list + ms, (unsigned long long)mx, (unsigned long long)key) == mx) break;
                 }
-            });
+                wave_sync();
+                fill = 0;
+            };
+            auto offer = [&](int run, u32 o) {      // all lanes of the wave together
+                const int row = (int)(o >> RB) - first - row0;
+                const bool take = (unsigned)row < (unsigned)rows &&
+                                  reverse_hash(stream_key, first + row0 + row, source_of(run, o)) <= largest(row);
+                const u64 mask = __ballot(take);
+                if (!mask) return;
+                if (fill + __popcll(mask) > EF_WAVE) drain();
+                if (take) put_by[fill + lanes_below(mask)] = (u32)row << SB | source_of(run, o);
+                fill += __popcll(mask);
+            };
+            constexpr int U = 8;      // runs in flight, a piece of 64 of each at a time
+            for (int r0 = wave; r0 < n_blocks; r0 += U * n_waves) {
+                const u32 *from[U];
+                int count[U], longest = 0;
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int r = min(r0 + u * n_waves, n_blocks - 1);
+                    const OfferRun run = insert ? run_of(r) : table_run(r);
+                    count[u] = r0 + u * n_waves < n_blocks ? __builtin_amdgcn_readfirstlane(run.count) : 0;
+                    from[u] = offer_runs + (size_t)r * run_cap + __builtin_amdgcn_readfirstlane(run.start);
+                    longest = max(longest, count[u]);
+                }
+                for (int q0 = 0; q0 < longest; q0 += EF_WAVE) {
+                    u32 o[U];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) o[u] = q0 + lane < count[u] ? from[u][q0 + lane] : ~0u;
+#pragma unroll 1
+                    for (int u = 0; u < U; ++u) {
+                        const u32 w = u == 0 ? o[0] : u == 1 ? o[1] : u == 2 ? o[2] : u == 3 ? o[3] : u == 4 ? o[4] : u == 5 ? o[5] : u == 6 ? o[6] : o[7];
+                        offer(r0 + u * n_waves, w);
+                    }
+                }
+            }
+            drain();
             __syncthreads();
             // only the sources are wanted from here on (the keys decided who is in the list)
             for (int f = t; f < rows * L; f += n_thr) lists[(size_t)(first + row0) * L + f] = (u32)ll[f];

@@ -699,6 +699,39 @@ def test_reverse_lists_of_given_lengths(ef, K, L, stride):
         graph_equal(ef, graph, want)
 
 
+@pytest.mark.parametrize("n,K,L,block,share,least", [
+    (70_000, 10, 10, 128, 0.05, 4_096),         # ranges of 128 targets: the lists fit the LDS in two goes
+    (100_000, 20, 20, 128, 0.05, 8_192),        # ... of 512 threads
+    (200_000, 10, 10, 256, 0.05, 8_192),        # ranges of 256
+    (150_000, 16, 16, 256, 0.05, 8_192),
+    (70_000, 32, 32, 256, 0.03, 16_384),        # lists that take all of the LDS
+    (500_000, 10, 10, 1_024, 0.02, 16_384),     # ranges of 1024
+    (500_000, 10, 10, 40, 0.02, 16_384),        # ... and a few popular points in the first of them
+    (65_536, 24, 9, 128, 0.05, 16_384),
+    (2_100, 128, 64, 32, 0.1, 8_192),           # long rows: offers walked twice, popular points have room for 128 each
+    (70_000, 100, 50, 256, 0.02, 32_768),
+])
+def test_reverse_lists_of_popular_neighbours(ef, n, K, L, block, share, least):
+    """Popular points side by side: one range of targets gets many times the offers of the others, more than its block can hold
+    at once.  The lists keep the L smallest keys all the same, two iterations of a random start against the oracle's."""
+    rng = np.random.default_rng(n + K)
+    X = rng.standard_normal((n, 4)).astype(np.float32)
+    ids = rng.integers(0, n, (n, K))
+    ids = np.where(rng.random((n, K)) < share, (ids * rng.random((n, K)) * block / n).astype(np.int64), ids).astype(np.int32)
+    ids[ids == np.arange(n)[:, None]] = -1
+    d = host(ef.efanna_pair_distances(dev(X), dev(np.repeat(np.arange(n, dtype=np.int32), K)), dev(np.maximum(ids, 0).ravel()))).reshape(n, K)
+    d[ids < 0] = np.inf
+    graph = ef.efanna_set_graph(dev(ids), dev(d))
+    want = [host(t) for t in ef.efanna_get_graph(graph, with_flags=True)]
+    named = np.bincount(want[0][want[0] >= 0], minlength=n)
+    assert named[:block].sum() > least      # the case is what it says
+    for it in range(2):
+        ef.efanna_nndescent(dev(X), graph, 1, L, 9, first_iter=it)
+        torch.cuda.synchronize()
+        want = oracle.nndescent(X, *want[:3], 1, L, 9, iter0=it)
+        graph_equal(ef, graph, want)
+
+
 @pytest.mark.parametrize("largest", [np.nextafter(np.float32(256), np.float32(0)), np.float32(256), np.float32(-300)])
 @pytest.mark.parametrize("n,d,S", [(2_048, 3, 16), (2_049, 64, 7), (513, 65, 1), (5_000, 128, 2), (4_097, 129, 64)])
 def test_tree_finish_all_rules(ef, n, d, S, largest):
