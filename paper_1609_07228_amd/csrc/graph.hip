@@ -1566,7 +1566,7 @@ reverse_overflow_kernel(const Overflow *__restrict__ overflow, size_t ovf_region
 constexpr int kBktRows = 1024;        // source rows per offer block, at most
 constexpr int kBktThreads = 1024;
 constexpr int kBktMany = 800;         // as many buckets are enough
-constexpr int kInsertTo = 6;          // lists up to this length take the bounded insertion (see bucket_insert_kernel)
+constexpr int kInsertTo = 7;          // lists up to this length take the bounded insertion (see bucket_insert_kernel)
 constexpr int kBktFew = 4;            // offers per thread up to which it looks for their runs
 constexpr int kBktWords = 16;         // offers a thread of a list block holds while they are sorted
 constexpr int kBktMaxRuns = 2 * kBktThreads;    // buckets and offer blocks a block-wide scan of two per thread takes
@@ -2353,7 +2353,8 @@ bucket_lists_kernel(const u32 *__restrict__ offer_runs, const u32 *__restrict__ 
 // The same for lists of at most kInsertTo: every key goes through the bounded insertion; all slots start as the largest
 // key, so a list fills from slot 0 up and then keeps its L smallest keys.  Short scans and hardly a barrier: where
 // the sorting kernel takes longer (builds of 19 000 x 13, degree 7, lists of 5 / 3000 x 16, degree 3 / 300 000 x 32, degree 32, lists of 5:
-// 687 and 714 us, 454 and 473, 8.27 and 8.67 ms).  LDS: lists [bucket's targets * L] u64, scan [n_blocks + 1] and start [n_blocks] int.
+// 687 and 714 us, 454 and 473, 8.27 and 8.67 ms; two iterations with lists of 7, 10^6 x 8, degree 7 / 16 000, degree 20: 2.53 and 2.59 ms, 592 and
+// 612 us; with lists of 8 the sorting kernel is level from degree 20 up and up to 2 % ahead below).  LDS: lists [bucket's targets * L] u64, scan [n_blocks + 1] and start [n_blocks] int.
 template <int RB>
 __global__ void __launch_bounds__(kBktThreads)
 bucket_insert_kernel(const u32 *__restrict__ offer_runs, const u32 *__restrict__ table, int n_blocks,

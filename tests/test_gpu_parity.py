@@ -708,6 +708,8 @@ def test_reverse_lists_of_given_lengths(ef, K, L, stride):
     (500_000, 10, 10, 1_024, 0.02, 16_384),     # ranges of 1024
     (500_000, 10, 10, 40, 0.02, 16_384),        # ... and a few popular points in the first of them
     (65_536, 24, 9, 128, 0.05, 16_384),
+    (70_000, 20, 7, 1_024, 0.05, 16_384), (70_000, 20, 8, 128, 0.05, 8_192),      # the longest lists of the kernel without a sort, one more
+    (20_000, 7, 7, 64, 0.1, 4_096), (20_000, 8, 8, 64, 0.1, 4_096),
     (2_100, 128, 64, 32, 0.1, 8_192),           # long rows: offers walked twice, popular points have room for 128 each
     (70_000, 100, 50, 256, 0.02, 32_768),
 ])
