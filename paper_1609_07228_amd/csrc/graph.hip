@@ -1635,14 +1635,26 @@ inline BucketShape bucket_shape(int64_t n, int K, int L)
 // Longer rows or lists (K or L > 32) of at most 2^20 points: the same with a wave per row (sample_wide_kernel), 256 source
 // rows per offer block (their offers fill its LDS), 64 of up to 2^16 points, and ranges of 256 targets, of 128 for
 // more than a hundred offers each, smaller ones as long as there are fewer than 512.  Offers and table lie where the
-// counter scheme has its queues.  Beyond 2^20 points the runs would be of an offer or two each.
+// counter scheme has its queues.  2^20 points are the most whose ranges an offer block and whose blocks a range can count
+// (4096 of each, four to a thread); what more of them would give has not been measured.
 // 10^6 x 96, degree 100, lists of 50, eight iterations: sampling, offers and lists 62.7 -> 19.9 ms (the queues' overflow, a
 // thread per parked key and a scan of fifty keys each, was 34 of them), build 327.6 -> 284.7; 65 536 x 64, degree 40 8.46 -> 7.05,
 // 10^4 x 64, degree 100 9.71 -> 8.17, 400 000 x 16, degree 128 and lists of 32 121.8 -> 115.6.
+// Short samples stay with counters and queues: where few entries are offered, a launch of offer and list blocks costs more than
+// the counters' bumps, and where rows are shorter than the lists hardly a list overflows.  Two iterations, counters / ranges:
+// degree 33, lists of 2, 1000 x 8 169 and 230 us, 200 000 930 and 1037; lists of 8, 1000 519 and 570, 65 537 2.51 and 2.57 ms, 10^6 27.1
+// and 27.1; of 10, 16 000 3 % for ranges, 65 537 1 % for counters (but with popular points side by side, degree 40, 70 000 11.4 and 9.8);
+// of 12, degree 128, 1000 3 % for counters; of 16, 1000 2 % for ranges; of 20, degree 48, 500 8 % for ranges; 200 points, degree 128, lists of 20 2 % for counters.
+// Degree 10, lists of 40, 1000 263 and 302, 10^5 and more the same; degree 20, lists of 33 10 % for ranges, of 64 4 % for counters up to 2^16.
+inline bool wide_pays(int64_t n, int K, int L)
+{
+    if (K <= 32) return K >= 20 && (2 * K >= L || n > (1 << 16));
+    return n >= 8000 ? L >= 10 : n >= 1000 ? L >= 16 : L >= 20 && 4 * L > K;
+}
 inline size_t wide_offer_lds(int per_row, const BucketShape &b) { return ((size_t)per_row << b.row_bits) * 4 + ((size_t)2 * b.buckets + 4) * 4; }
 inline bool wide_lists(int64_t n, int K, int L, BucketShape *shape = nullptr)
 {
-    if (bucketed_lists(n, K, L) || K > 128 || n > (1 << 20)) return false;
+    if (bucketed_lists(n, K, L) || K > 128 || n > (1 << 20) || !wide_pays(n, K, L)) return false;
     const int per = K > L ? K : L;
     BucketShape b;
     b.row_bits = n <= (1 << 16) ? 6 : 8;

@@ -450,7 +450,7 @@ def test_nndescent_filter_ranges_bit_exact(ef, kind, d, K, L):
     (5_000, 8, 2, 16, 16, 16, 2),        # the longest lists with ranges of 1024, a ragged last range
     (2_100, 8, 2, 16, 16, 17, 2),        # one more: ranges of 512 targets
     (3_000, 8, 2, 16, 32, 32, 2),        # the longest rows and lists that scheme takes
-    (2_000, 8, 2, 16, 33, 16, 1),        # one more: lists by counters
+    (2_000, 8, 2, 16, 33, 16, 1),        # one more: a wave per row
     (4_096, 12, 2, 16, 3, 1, 4),         # lists of a single key
     (2_000, 16, 2, 16, 64, 32, 2),       # join lists of 128 ids: a wave per point, hash table of 256 slots
     (1_500, 8, 2, 16, 128, 64, 1),       # the longest rows and samples the library takes (lists of 256 ids)
@@ -467,6 +467,10 @@ def test_nndescent_filter_ranges_bit_exact(ef, kind, d, K, L):
     (16_385, 4, 1, 16, 32, 32, 1),       # the longest lists, ranges of 64
     (70_000, 4, 1, 16, 3, 2, 2),         # two passes per block of the join lists, a ragged last block
     (140_000, 4, 1, 16, 3, 2, 1),        # four
+    (2_000, 8, 2, 16, 33, 15, 1),        # lists too short for that: by counters
+    (8_000, 8, 2, 16, 33, 10, 1), (8_000, 8, 2, 16, 33, 9, 1), (7_999, 8, 2, 16, 100, 15, 1),
+    (999, 8, 2, 16, 79, 20, 1), (999, 8, 2, 16, 80, 20, 1), (999, 8, 2, 16, 40, 19, 1),
+    (900, 8, 2, 16, 20, 40, 1), (900, 8, 2, 16, 20, 41, 1), (900, 8, 2, 16, 19, 33, 1), (65_537, 4, 1, 16, 20, 41, 1),
     (900, 8, 2, 16, 1, 20, 2),           # rows of one entry, joins of more than 32 vectors
     (900, 8, 2, 16, 3, 20, 2),
     (140_000, 4, 1, 16, 21, 21, 1),      # join lists of 63 ids, four passes: the most LDS of either kernel that
