@@ -173,9 +173,9 @@ def test_mixed4m_d96_full_size_properties():
 @pytest.mark.timeout(900)
 def test_mixed_d96_prefix_every_element_against_oracle():
     """The parameters of `mixed4m_d96` (K = 100, 16 trees, leaves of 64, L = 50) on its first
-    262 144 rows, three iterations: rows of a hundred entries take the per-list counters with their
-    overflow queues, the wide overflow kernel and the LDS-row join with its long-row list updates,
-    at a size where the queues fill and hubs are fought over.  Every element of the trees, of the
+    262 144 rows, three iterations: rows of a hundred entries take the reverse lists by target range
+    (counters and queues beyond 2^20 rows: test_a_million_long_rows_of_popular_points) and the tile join with
+    its long-row list updates, at a size where hubs are fought over.  Every element of the trees, of the
     initial and of the refined graph and the pairs evaluated per iteration against the oracle,
     and both accuracies against exact brute force (Alg. 3 at the leaves, Alg. 4)."""
     if not torch.cuda.is_available():
@@ -269,6 +269,37 @@ def test_a_million_long_rows_bit_exact(n):
         torch.cuda.synchronize()
         _progress(f"n = {n}, iteration {it}: gpu done")
         want = oracle.nndescent(X, *want[:3], 1, L, 5, iter0=it)
+    ids, dists, flags = efanna.efanna_get_graph(graph, with_flags=True)
+    assert np.array_equal(ids.cpu().numpy(), want[0])
+    assert dists.cpu().numpy().tobytes() == want[1].tobytes()
+    assert np.array_equal(flags.cpu().numpy(), want[2])
+
+
+@pytest.mark.timeout(600)
+@pytest.mark.parametrize("n", [1 << 20, (1 << 20) + 1])
+def test_a_million_long_rows_of_popular_points(n):
+    """Degree 65, lists of 50, on both sides of that line; every eighth entry names one of 256 neighbouring points, so that lists overflow
+    and ranges are uneven.  With counters: two entries per lane, the wide overflow kernel, join lists by a wave each, which is
+    what the 4 10^6 x 96 configuration of degree 100 runs."""
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU: there is no CPU fallback")
+    from paper_1609_07228_amd import efanna
+    rng = np.random.default_rng(22)
+    K, L = 65, 50
+    X = rng.standard_normal((n, 4)).astype(np.float32)
+    Xd = torch.from_numpy(X).cuda()
+    ids = rng.integers(0, n, (n, K), dtype=np.int32)
+    ids[:, ::8] %= 256
+    ids[ids == np.arange(n, dtype=np.int32)[:, None]] = -1
+    idd = torch.from_numpy(ids).cuda()
+    a = torch.arange(n, dtype=torch.int32, device="cuda").repeat_interleave(K)
+    d = efanna.efanna_pair_distances(Xd, a, idd.clamp(min=0).reshape(-1)).reshape(n, K)
+    graph = efanna.efanna_set_graph(idd, d.masked_fill(idd < 0, float("inf")))
+    want = [t.cpu().numpy() for t in efanna.efanna_get_graph(graph, with_flags=True)]
+    efanna.efanna_nndescent(Xd, graph, 1, L, 5)
+    torch.cuda.synchronize()
+    _progress(f"n = {n}: gpu done")
+    want = oracle.nndescent(X, *want[:3], 1, L, 5)
     ids, dists, flags = efanna.efanna_get_graph(graph, with_flags=True)
     assert np.array_equal(ids.cpu().numpy(), want[0])
     assert dists.cpu().numpy().tobytes() == want[1].tobytes()
