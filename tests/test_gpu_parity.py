@@ -739,7 +739,9 @@ def test_reverse_lists_of_popular_neighbours(ef, n, K, L, block, share, least):
 
 
 @pytest.mark.parametrize("largest", [np.nextafter(np.float32(256), np.float32(0)), np.float32(256), np.float32(-300)])
-@pytest.mark.parametrize("n,d,S", [(2_048, 3, 16), (2_049, 64, 7), (513, 65, 1), (5_000, 128, 2), (4_097, 129, 64)])
+@pytest.mark.parametrize("n,d,S", [(2_048, 3, 16), (2_049, 64, 7), (513, 65, 1), (5_000, 128, 2), (4_097, 129, 64),
+                                   (512, 4, 1), (511, 70, 3), (65, 2, 64), (64, 3, 1), (2, 5, 1),      # a position per thread
+                                   (4_096, 6, 7), (1_024, 3, 1), (1_025, 3, 1)])      # the most positions and nodes of one workgroup
 def test_tree_finish_all_rules(ef, n, d, S, largest):
     """Every split rule at the sizes where the step inside a workgroup begins (a root of its own, one position more, the
     most nodes of a level), one and several passes over the dimensions, and values on both sides of 256, where sums
