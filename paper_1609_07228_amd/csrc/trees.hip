@@ -737,9 +737,10 @@ struct LNode {
 };
 
 // LDS of a block: ids, node indexes of 16 bits, the split tests as bits, two node tables of `nodes`.  A thread keeps the
-// ids, nodes and tested values of its positions (every kFinThreads-th) in registers: 26 KB for leaves of 16 and 2048 positions, four blocks per
-// CU (with all of it and prefix sums in LDS 78 KB, two blocks).  What bounds it, 10^6 x 128, eight trees: splits by one coordinate
-// the scattered 4-byte gathers (56 M of them in seven levels, 128-byte lines at 6.8 TB/s; 1.08 -> 1.05 ms), splits by variance the rows of the
+// ids, nodes and tested values of its positions (every kFinThreads-th) in registers.  Leaves of 16: 52 KB for the 4096 positions of splits by one
+// coordinate, two blocks of 1024 threads per CU; 26 KB for 2048 positions and 512 threads, three blocks in the registers of splits by
+// variance (with all of it and prefix sums in LDS 78 KB, two blocks).  What bounds it, 10^6 x 128, eight trees: splits by one coordinate
+// the scattered 4-byte gathers (64 M of them in eight levels, 128-byte lines at 6.8 TB/s; 1.22 ms), splits by variance the rows of the
 // samples (14.5 GB, at 4.0 TB/s; 5.13 -> 3.61 ms, see variance_dim_wave; two blocks per CU 3.83).
 // Random projections ask for one block per CU: the eight lines that a position reads of its row come the faster the fewer
 // waves ask for others in between (200 000 x 960: one block 1.65 ms, two 1.74, three 1.81, four 1.86).
