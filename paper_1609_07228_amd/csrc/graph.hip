@@ -1594,9 +1594,10 @@ __host__ __device__ inline bool bucketed_lists(int64_t n, int K, int L)
 // Beyond, ranges of 128 targets up, as large as make kBktMany of them (all list kernels of 10^5 points, degree 10, from a random
 // start: 390 -> 328 us; degree 20 235 -> 230), and no larger than lets 1024 threads hold ten offers each.  (More of them
 // for a million points, 1954 instead of 977: 998 -> 1039, and the offer kernels, which count and write runs per range, 1076 -> 1190.)
-// At least 512 threads, for the ranges of popular points side by side, whose offers one block has to look at alone (200 000 x 8 from rows that
-// name low ids more often, degree 10: 4.67 ms with 256, 3.54 with 512; degree 20, 20 000 x 64 sorted by norm: 2.46 and 1.80); 256 where ranges
-// of at most 128 targets are offered ten each: there the waves cost more than they bring (100 000 x 8 1112 us, 1125 with 512).
+// There at least 512 threads, for the ranges of popular points side by side, whose offers one block has to look at alone (200 000 x 8 from rows
+// that name low ids more often, degree 10: 4.67 ms with 256, 3.54 with 512; 100 000 x 64 sorted by norm, degree 20: 6.31 and 4.94; 100 000 x 128, degree 20, with its offers spread evenly
+// 4.27 and 4.30); 256 where ranges
+// of at most 128 targets are offered ten each, and up to 2^16 points: the waves cost more than they bring (100 000 x 8 1112 us, 1125 with 512).
 struct BucketShape {
     int row_bits, blocks;           // log2 of the source rows of an offer block, number of blocks
     int shift, buckets, threads;    // log2 of the targets of a bucket, number of buckets, threads of a list block
@@ -1612,7 +1613,7 @@ inline BucketShape bucket_shape(int64_t n, int K, int L)
         b.blocks = (int)((n + (1 << row_bits) - 1) >> row_bits);
         b.buckets = (int)((n - 1) >> shift) + 1;
         b.threads = (per <= 10 || L <= kInsertTo ? 1 : per <= 20 ? 2 : 4) << shift;
-        const int least = L <= kInsertTo || (per <= 10 && shift <= 7) ? 256 : 512;
+        const int least = L <= kInsertTo || row_bits == 8 || (per <= 10 && shift <= 7) ? 256 : 512;
         b.threads = b.threads < least ? least : b.threads > kBktThreads ? kBktThreads : b.threads;
         b.table_behind = (int64_t)b.blocks * b.buckets <= n * L;
     };
@@ -2320,27 +2321,21 @@ bucket_lists_kernel(const u32 *__restrict__ offer_runs, const u32 *__restrict__ 
                 if (take) put_by[fill + lanes_below(mask)] = (u32)row << SB | source_of(run, o);
                 fill += __popcll(mask);
             };
-            constexpr int U = 8;      // runs in flight, a piece of 64 of each at a time
+            constexpr int U = 8;      // runs in flight, a piece of 64 of each at a time; lane u knows the u-th
             for (int r0 = wave; r0 < n_blocks; r0 += U * n_waves) {
-                const u32 *from[U];
-                int count[U], longest = 0;
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int r = min(r0 + u * n_waves, n_blocks - 1);
-                    const OfferRun run = insert ? run_of(r) : table_run(r);
-                    count[u] = r0 + u * n_waves < n_blocks ? __builtin_amdgcn_readfirstlane(run.count) : 0;
-                    from[u] = offer_runs + (size_t)r * run_cap + __builtin_amdgcn_readfirstlane(run.start);
-                    longest = max(longest, count[u]);
-                }
-                for (int q0 = 0; q0 < longest; q0 += EF_WAVE) {
+                const int r = r0 + (lane & (U - 1)) * n_waves, rr = min(r, n_blocks - 1);
+                const OfferRun run = insert ? run_of(rr) : table_run(rr);
+                const int count = r < n_blocks ? run.count : 0, from = rr * run_cap + run.start;
+                for (int q0 = 0; __ballot(q0 < count); q0 += EF_WAVE) {
                     u32 o[U];
 #pragma unroll
-                    for (int u = 0; u < U; ++u) o[u] = q0 + lane < count[u] ? from[u][q0 + lane] : ~0u;
-#pragma unroll 1
                     for (int u = 0; u < U; ++u) {
-                        const u32 w = u == 0 ? o[0] : u == 1 ? o[1] : u == 2 ? o[2] : u == 3 ? o[3] : u == 4 ? o[4] : u == 5 ? o[5] : u == 6 ? o[6] : o[7];
-                        offer(r0 + u * n_waves, w);
+                        const int c = __builtin_amdgcn_readlane(count, u), at = __builtin_amdgcn_readlane(from, u);
+                        o[u] = q0 + lane < c ? offer_runs[at + q0 + lane] : ~0u;
                     }
+#pragma unroll 1
+                    for (int u = 0; u < U; ++u)
+                        offer(r0 + u * n_waves, u == 0 ? o[0] : u == 1 ? o[1] : u == 2 ? o[2] : u == 3 ? o[3] : u == 4 ? o[4] : u == 5 ? o[5] : u == 6 ? o[6] : o[7]);
                 }
             }
             drain();
