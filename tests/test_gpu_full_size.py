@@ -304,3 +304,35 @@ def test_a_million_long_rows_of_popular_points(n):
     assert np.array_equal(ids.cpu().numpy(), want[0])
     assert dists.cpu().numpy().tobytes() == want[1].tobytes()
     assert np.array_equal(flags.cpu().numpy(), want[2])
+
+
+@pytest.mark.timeout(600)
+def test_reverse_lists_that_are_walked_twice():
+    """Degree 32, lists of 8, a million points: ranges of 1024 targets whose offers of old entries are more than a block's
+    registers hold and fit its LDS, and, for a few popular ranges, more than that."""
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU: there is no CPU fallback")
+    from paper_1609_07228_amd import efanna
+    rng = np.random.default_rng(23)
+    n, K, L = 1_050_000, 32, 8
+    X = rng.standard_normal((n, 4)).astype(np.float32)
+    Xd = torch.from_numpy(X).cuda()
+    ids = rng.integers(0, n, (n, K), dtype=np.int32)
+    ids[::16, 0] %= 3_000
+    ids[ids == np.arange(n, dtype=np.int32)[:, None]] = -1
+    idd = torch.from_numpy(ids).cuda()
+    marks = torch.from_numpy((rng.random((n, K)) < 0.2).astype(np.uint8)).cuda()
+    a = torch.arange(n, dtype=torch.int32, device="cuda").repeat_interleave(K)
+    d = efanna.efanna_pair_distances(Xd, a, idd.clamp(min=0).reshape(-1)).reshape(n, K)
+    graph = efanna.efanna_set_graph(idd, d.masked_fill(idd < 0, float("inf")), marks)
+    want = [t.cpu().numpy() for t in efanna.efanna_get_graph(graph, with_flags=True)]
+    old = np.bincount(want[0][(want[2] == 0) & (want[0] >= 0)] // 1024, minlength=(n + 1023) // 1024)
+    assert 16_384 < np.median(old) < 32_768 and old[0] > 40_000      # the case is what it says
+    efanna.efanna_nndescent(Xd, graph, 1, L, 5)
+    torch.cuda.synchronize()
+    _progress("gpu done")
+    want = oracle.nndescent(X, *want[:3], 1, L, 5)
+    ids, dists, flags = efanna.efanna_get_graph(graph, with_flags=True)
+    assert np.array_equal(ids.cpu().numpy(), want[0])
+    assert dists.cpu().numpy().tobytes() == want[1].tobytes()
+    assert np.array_equal(flags.cpu().numpy(), want[2])
