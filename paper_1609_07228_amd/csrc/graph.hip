@@ -1872,7 +1872,9 @@ reverse_old_wide_kernel(const int *__restrict__ od, int n, int K, const u64 *__r
 // popular points side by side, data sorted by norm among them.  (Insertion alone with a scan per offer, before the offers were sorted /
 // offers counted first, walked by eight lanes a run, and every key's scan by its own lane / now: 100 000 x 64 sorted by norm, degree 20, four iterations
 // 6.33, 9.59 and 4.91 ms; 200 000 x 8, low ids named more often, degree 10, two 4.29, 6.00 and 3.54.  Not made up for: 500 000 x 16 sorted by
-// norm, degree 10, 3.91 and 4.24 ms, where two dozen ranges hold up to twice what fits and are walked twice.)
+// norm, degree 10, 3.91 and 4.2 ms, where two dozen ranges of up to twice what fits make a launch 80 to 150 us instead of 50 to 75, ten of them
+// the descriptors and barriers of any launch; room for all lists at once, what is left for the second go moved to the front of its run,
+// a scan by every lane for its own offer, and ranges dealt to the chiplets in turn made no difference.)
 // What bounds it: instruction issue in the first iterations (10^6 points of degree 10: 3900 -> 3100 wave instructions per
 // wave of a launch, half of them choosing), a fixed 25 us of run descriptors and barriers in the last.  All
 // sixteen launches of that build 1338 -> 1035 us, with the bounded insertion for all (a list scanned in LDS per offer, again
