@@ -1566,7 +1566,8 @@ reverse_overflow_kernel(const Overflow *__restrict__ overflow, size_t ovf_region
 constexpr int kBktRows = 1024;        // source rows per offer block, at most
 constexpr int kBktThreads = 1024;
 constexpr int kBktMany = 800;         // as many buckets are enough
-constexpr int kInsertTo = 7;          // lists up to this length take the bounded insertion (see bucket_insert_kernel)
+// lists that take the bounded insertion (see bucket_insert_kernel)
+__host__ __device__ inline bool insert_lists(int64_t n, int L) { return L <= 6 || (L == 7 && n > (1 << 17)); }
 constexpr int kBktFew = 4;            // offers per thread up to which it looks for their runs
 constexpr int kBktWords = 16;         // offers a thread of a list block holds while they are sorted
                                       // (twice as many of long rows; two iterations with 12 and 24: the same where offers are spread evenly, 3 to 10 % longer
@@ -1615,8 +1616,8 @@ inline BucketShape bucket_shape(int64_t n, int K, int L)
         b.shift = shift;
         b.blocks = (int)((n + (1 << row_bits) - 1) >> row_bits);
         b.buckets = (int)((n - 1) >> shift) + 1;
-        b.threads = (per <= 10 || L <= kInsertTo ? 1 : per <= 20 ? 2 : 4) << shift;
-        const int least = L <= kInsertTo || row_bits == 8 || (per <= 10 && shift <= 7) ? 256 : 512;
+        b.threads = (per <= 10 || insert_lists(n, L) ? 1 : per <= 20 ? 2 : 4) << shift;
+        const int least = insert_lists(n, L) || row_bits == 8 || (per <= 10 && shift <= 7) ? 256 : 512;
         b.threads = b.threads < least ? least : b.threads > kBktThreads ? kBktThreads : b.threads;
         b.table_behind = (int64_t)b.blocks * b.buckets <= n * L;
     };
@@ -1627,7 +1628,7 @@ inline BucketShape bucket_shape(int64_t n, int K, int L)
         if (b.table_behind) return b;
     }
     const int top = per <= 10 ? 10 : per <= 20 ? 9 : 8;
-    for (int shift = 7; L > kInsertTo && (shift <= 9 || shift <= top); ++shift) {
+    for (int shift = 7; !insert_lists(n, L) && (shift <= 9 || shift <= top); ++shift) {
         cut(10, shift);
         if (b.table_behind && b.buckets <= (shift < top ? kBktMany : kBktMaxRuns) && b.blocks <= 2 * b.threads) return b;
     }
@@ -1644,16 +1645,16 @@ inline BucketShape bucket_shape(int64_t n, int K, int L)
 // 10^6 x 96, degree 100, lists of 50, eight iterations: sampling, offers and lists 62.7 -> 19.9 ms (the queues' overflow, a
 // thread per parked key and a scan of fifty keys each, was 34 of them), build 327.6 -> 284.7; 65 536 x 64, degree 40 8.46 -> 7.05,
 // 10^4 x 64, degree 100 9.71 -> 8.17, 400 000 x 16, degree 128 and lists of 32 121.8 -> 115.6.
-// Short samples stay with counters and queues: where few entries are offered, a launch of offer and list blocks costs more than
-// the counters' bumps, and where rows are shorter than the lists hardly a list overflows.  Two iterations, counters / ranges:
-// degree 33, lists of 2, 1000 x 8 169 and 230 us, 200 000 930 and 1037; lists of 8, 1000 519 and 570, 65 537 2.51 and 2.57 ms, 10^6 27.1
-// and 27.1; of 10, 16 000 3 % for ranges, 65 537 1 % for counters (but with popular points side by side, degree 40, 70 000 11.4 and 9.8);
-// of 12, degree 128, 1000 3 % for counters; of 16, 1000 2 % for ranges; of 20, degree 48, 500 8 % for ranges; 200 points, degree 128, lists of 20 2 % for counters.
-// Degree 10, lists of 40, 1000 263 and 302, 10^5 and more the same; degree 20, lists of 33 10 % for ranges, of 64 4 % for counters up to 2^16.
+// Short samples, and few points, stay with counters and queues: where few entries are offered, a launch of offer and list blocks costs
+// more than the counters' bumps.  Whole builds of clustered and even data, four iterations, time with counters over time with ranges:
+// degree 40, lists of 4 0.82 to 0.86 at 600 points, 0.95 to 0.99 from 3000 on; of 6 0.89 to 0.92 at 600, 1.01 to 1.04 at 3000 to 12 000, 0.98 to 1.02
+// beyond; of 8 0.94 to 0.97 at 600, 1.02 to 1.05 at 1500, up to 1.10 beyond; of 12 0.92 to 0.97 at 150, 1.04 at 600; of 20 1.0 to 1.12 at 150.  Degree 100,
+// lists of 6 0.97 to 1.0.  Rows of 20, lists of 33 0.91 to 1.23 at 250, 1.07 at 600, 1.3 to 2.3 from 1500 on; rows of 32, lists of 40 1.06 at 250; rows of 10,
+// lists of 64 0.91 to 1.39 at 1500, the same beyond; rows of 4, lists of 40 0.85 to 1.12, the same beyond.
 inline bool wide_pays(int64_t n, int K, int L)
 {
-    if (K <= 32) return K >= 20 && (2 * K >= L || n > (1 << 16));
-    return n >= 8000 ? L >= 10 : n >= 1000 ? L >= 16 : L >= 20 && 4 * L > K;
+    if (K <= 32) return n >= 1000 ? 8 * K >= L : 4 * K >= 3 * L;
+    return L >= 20 || (L >= 12 && n >= 500) || (L >= 8 && n >= 1000) || (L >= 6 && 10 * L >= K && n >= 3000);
 }
 inline size_t wide_offer_lds(int per_row, const BucketShape &b) { return ((size_t)per_row << b.row_bits) * 4 + ((size_t)2 * b.buckets + 4) * 4; }
 inline bool wide_lists(int64_t n, int K, int L, BucketShape *shape = nullptr)
@@ -2362,11 +2363,11 @@ bucket_lists_kernel(const u32 *__restrict__ offer_runs, const u32 *__restrict__ 
     if (blockIdx.x == 0 && t < kMaxClasses) work_count[t] = 0;
 }
 
-// The same for lists of at most kInsertTo: every key goes through the bounded insertion; all slots start as the largest
+// The same for the shortest lists (insert_lists): every key goes through the bounded insertion; all slots start as the largest
 // key, so a list fills from slot 0 up and then keeps its L smallest keys.  Short scans and hardly a barrier: where
 // the sorting kernel takes longer (builds of 19 000 x 13, degree 7, lists of 5 / 3000 x 16, degree 3 / 300 000 x 32, degree 32, lists of 5:
-// 687 and 714 us, 454 and 473, 8.27 and 8.67 ms; two iterations with lists of 7, 10^6 x 8, degree 7 / 16 000, degree 20: 2.53 and 2.59 ms, 592 and
-// 612 us; with lists of 8 the sorting kernel is level from degree 20 up and up to 2 % ahead below).  LDS: lists [bucket's targets * L] u64, scan [n_blocks + 1] and start [n_blocks] int.
+// 687 and 714 us, 454 and 473, 8.27 and 8.67 ms).  Lists of 7 take 1 to 3 % less with it from 2 10^5 points on (800 000 x 128, degree 7 8.33 and 8.55 ms) and
+// 1 to 6 % more below 10^5 (3000 x 128 655 and 615 us), lists of 8 up to 5 % more.  LDS: lists [bucket's targets * L] u64, scan [n_blocks + 1] and start [n_blocks] int.
 template <int RB>
 __global__ void __launch_bounds__(kBktThreads)
 bucket_insert_kernel(const u32 *__restrict__ offer_runs, const u32 *__restrict__ table, int n_blocks,
@@ -4531,7 +4532,7 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
     const bool bkt_small = bs.row_bits != 10;
     auto bkt_lds = [&](int per_row) { return (size_t)bkt_rows * per_row * 4 + ((size_t)2 * bs.buckets + 4) * 4; };
     const int lists_area = bkt ? bucket_lists_area(K, L, bs.shift, bs.blocks, bs.threads, wide ? 2 * kBktWords : kBktWords) : 0;
-    const size_t lists_lds = !bkt ? 0 : L <= kInsertTo && !wide ? bucket_lists_lds(L, bs.shift, bs.blocks)
+    const size_t lists_lds = !bkt ? 0 : insert_lists(n, L) && !wide ? bucket_lists_lds(L, bs.shift, bs.blocks)
                                    : (size_t)lists_area * 4 + bucket_lists_rest(bs.shift, bs.blocks);
     // lanes that walk a run of `per` offers per row together
     auto run_lanes = [&](int per) {
@@ -4550,7 +4551,7 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
                                           : bkt_small ? reverse_old_bucket_kernel<8> : reverse_old_bucket_kernel<10>;
     const ListsKernel bkt_lists =
         wide ? (few_rows ? bucket_lists_kernel<0, 6, true> : bucket_lists_kernel<0, 8, true>)
-        : L <= kInsertTo ? (bkt_small ? bucket_insert_kernel<8> : bucket_insert_kernel<10>)
+        : insert_lists(n, L) ? (bkt_small ? bucket_insert_kernel<8> : bucket_insert_kernel<10>)
         : bkt_small ? (L == 10 ? bucket_lists_kernel<10, 8, false> : bucket_lists_kernel<0, 8, false>)
                     : (L == 10 ? bucket_lists_kernel<10, 10, false> : bucket_lists_kernel<0, 10, false>);
     const int offer_threads = wide ? 4 * bkt_rows : bkt_rows;

@@ -251,14 +251,14 @@ def test_two_million_short_vectors_bit_exact(n):
 @pytest.mark.timeout(600)
 @pytest.mark.parametrize("n", [1 << 20, (1 << 20) + 1])
 def test_a_million_long_rows_bit_exact(n):
-    """Degree 33, lists of 10: 2^20 points are the most whose reverse lists of long rows are built by target range (4096 ranges
-    of 256, 4096 offer blocks of 256 rows), one more takes counters and queues."""
+    """Degree 33: 2^20 points are the most whose reverse lists of long rows are built by target range (4096 ranges of 256,
+    4096 offer blocks of 256 rows), one more takes counters and queues."""
     if not torch.cuda.is_available():
         pytest.fail("GPU tests need a GPU: there is no CPU fallback")
     from paper_1609_07228_amd import efanna
     rng = np.random.default_rng(21)
     X = rng.standard_normal((n, 4)).astype(np.float32)
-    K, L, S = 33, 10, 40
+    K, L, S = 33, 8, 40
     Xd = torch.from_numpy(X).cuda()
     perm, off, nl = efanna.efanna_build_trees(Xd, 1, S, 5)
     graph = efanna.efanna_init_graph(Xd, perm, off, nl, S, K)

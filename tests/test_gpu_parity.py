@@ -489,10 +489,10 @@ def test_nndescent_filter_ranges_bit_exact(ef, kind, d, K, L):
     (16_385, 4, 1, 16, 32, 32, 1),       # the longest lists, ranges of 64
     (70_000, 4, 1, 16, 3, 2, 2),         # two passes per block of the join lists, a ragged last block
     (140_000, 4, 1, 16, 3, 2, 1),        # four
-    (2_000, 8, 2, 16, 33, 15, 1),        # lists too short for that: by counters
-    (8_000, 8, 2, 16, 33, 10, 1), (8_000, 8, 2, 16, 33, 9, 1), (7_999, 8, 2, 16, 100, 15, 1),
-    (999, 8, 2, 16, 79, 20, 1), (999, 8, 2, 16, 80, 20, 1), (999, 8, 2, 16, 40, 19, 1),
-    (900, 8, 2, 16, 20, 40, 1), (900, 8, 2, 16, 20, 41, 1), (900, 8, 2, 16, 19, 33, 1), (65_537, 4, 1, 16, 20, 41, 1),
+    (3_000, 8, 2, 16, 33, 6, 1),         # the shortest lists that takes, at each number of points, and
+    (2_999, 8, 2, 16, 33, 7, 1), (3_000, 8, 2, 16, 61, 6, 1), (3_000, 8, 2, 16, 60, 6, 1), (3_000, 8, 2, 16, 33, 5, 1),      # shorter ones: by counters
+    (1_000, 8, 2, 16, 33, 8, 1), (999, 8, 2, 16, 33, 8, 1), (500, 8, 2, 16, 40, 12, 1), (499, 8, 2, 16, 40, 12, 1), (150, 8, 2, 16, 40, 20, 1),
+    (1_000, 8, 2, 16, 5, 40, 1), (1_000, 8, 2, 16, 4, 40, 1), (900, 8, 2, 16, 30, 40, 1), (900, 8, 2, 16, 29, 40, 1),
     (900, 8, 2, 16, 1, 20, 2),           # rows of one entry, joins of more than 32 vectors
     (900, 8, 2, 16, 3, 20, 2),
     (140_000, 4, 1, 16, 21, 21, 1),      # join lists of 63 ids, four passes: the most LDS of either kernel that
@@ -734,8 +734,8 @@ def test_reverse_lists_of_given_lengths(ef, K, L, stride):
     (500_000, 10, 10, 1_024, 0.02, 16_384),     # ranges of 1024
     (500_000, 10, 10, 40, 0.02, 16_384),        # ... and a few popular points in the first of them
     (65_536, 24, 9, 128, 0.05, 16_384),
-    (70_000, 20, 7, 1_024, 0.05, 16_384), (70_000, 20, 8, 128, 0.05, 8_192),      # the longest lists of the kernel without a sort, one more
-    (20_000, 7, 7, 64, 0.1, 4_096), (20_000, 8, 8, 64, 0.1, 4_096),
+    (140_000, 20, 7, 1_024, 0.05, 16_384), (131_072, 20, 7, 256, 0.05, 16_384),      # lists of 7, without and with a sort
+    (70_000, 20, 6, 1_024, 0.05, 16_384), (20_000, 7, 7, 64, 0.1, 4_096),
     (2_100, 128, 64, 32, 0.1, 8_192),           # long rows: offers walked twice, popular points have room for 128 each
     (70_000, 100, 50, 256, 0.02, 32_768),
 ])
