@@ -1598,10 +1598,10 @@ __host__ __device__ inline bool bucketed_lists(int64_t n, int K, int L)
 // Beyond, ranges of 128 targets up, as large as make kBktMany of them (all list kernels of 10^5 points, degree 10, from a random
 // start: 390 -> 328 us; degree 20 235 -> 230), and no larger than lets 1024 threads hold ten offers each.  (More of them
 // for a million points, 1954 instead of 977: 998 -> 1039, and the offer kernels, which count and write runs per range, 1076 -> 1190.)
-// There at least 512 threads, for the ranges of popular points side by side, whose offers one block has to look at alone (200 000 x 8 from rows
-// that name low ids more often, degree 10: 4.67 ms with 256, 3.54 with 512; 100 000 x 64 sorted by norm, degree 20: 6.31 and 4.94; 100 000 x 128, degree 20, with its offers spread evenly
-// 4.27 and 4.30); 256 where ranges
-// of at most 128 targets are offered ten each, and up to 2^16 points: the waves cost more than they bring (100 000 x 8 1112 us, 1125 with 512).
+// There at least 512 threads for ranges of 256 targets up, because of popular points side by side, whose offers one block has to look at alone
+// (200 000 x 8 from rows that name low ids more often, degree 10: 4.67 ms with 256, 3.54 with 512).  Ranges of 128 have 256: waves without
+// offers cost 2 us a launch (100 000 x 8, degree 10, 1112 us, 1125 with 512); where they are offered more than ten each they
+// have the LDS of 512 (see roomy).
 struct BucketShape {
     int row_bits, blocks;           // log2 of the source rows of an offer block, number of blocks
     int shift, buckets, threads;    // log2 of the targets of a bucket, number of buckets, threads of a list block
@@ -1617,7 +1617,7 @@ inline BucketShape bucket_shape(int64_t n, int K, int L)
         b.blocks = (int)((n + (1 << row_bits) - 1) >> row_bits);
         b.buckets = (int)((n - 1) >> shift) + 1;
         b.threads = (per <= 10 || insert_lists(n, L) ? 1 : per <= 20 ? 2 : 4) << shift;
-        const int least = insert_lists(n, L) || row_bits == 8 || (per <= 10 && shift <= 7) ? 256 : 512;
+        const int least = insert_lists(n, L) || row_bits == 8 || shift <= 7 ? 256 : 512;
         b.threads = b.threads < least ? least : b.threads > kBktThreads ? kBktThreads : b.threads;
         b.table_behind = (int64_t)b.blocks * b.buckets <= n * L;
     };
@@ -1872,7 +1872,7 @@ reverse_old_wide_kernel(const int *__restrict__ od, int n, int K, const u64 *__r
 // fit the LDS, keys enter lists there by the bounded insertion, as many targets at a time as there is room for: ranges of
 // popular points side by side, data sorted by norm among them.  (Insertion alone with a scan per offer, before the offers were sorted /
 // offers counted first, walked by eight lanes a run, and every key's scan by its own lane / now: 100 000 x 64 sorted by norm, degree 20, four iterations
-// 6.33, 9.59 and 4.91 ms; 200 000 x 8, low ids named more often, degree 10, two 4.29, 6.00 and 3.54.  Not made up for: 500 000 x 16 sorted by
+// 6.33, 9.59 and 5.34 ms; 200 000 x 8, low ids named more often, degree 10, two 4.29, 6.00 and 3.54.  Not made up for: 500 000 x 16 sorted by
 // norm, degree 10, 3.91 and 4.2 ms, where two dozen ranges of up to twice what fits make a launch 80 to 150 us instead of 50 to 75, ten of them
 // the descriptors and barriers of any launch; room for all lists at once, what is left for the second go moved to the front of its run,
 // a scan by every lane for its own offer, and ranges dealt to the chiplets in turn made no difference.)
@@ -4531,7 +4531,10 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
     const int bkt_rows = 1 << bs.row_bits;
     const bool bkt_small = bs.row_bits != 10;
     auto bkt_lds = [&](int per_row) { return (size_t)bkt_rows * per_row * 4 + ((size_t)2 * bs.buckets + 4) * 4; };
-    const int lists_area = bkt ? bucket_lists_area(K, L, bs.shift, bs.blocks, bs.threads, wide ? 2 * kBktWords : kBktWords) : 0;
+    // (degree 20, 100 000 x 64 sorted by norm, four iterations: 6.2 ms with 256 threads, 5.3 with the LDS of 512, 4.9 with 512; 100 000 x 128, not
+    // sorted: 4.27, 4.27 and 4.30)
+    const bool roomy = !wide && bs.row_bits == 10 && bs.shift == 7 && (K > 10 || L > 10);
+    const int lists_area = bkt ? bucket_lists_area(K, L, bs.shift, bs.blocks, bs.threads, wide || roomy ? 2 * kBktWords : kBktWords) : 0;
     const size_t lists_lds = !bkt ? 0 : insert_lists(n, L) && !wide ? bucket_lists_lds(L, bs.shift, bs.blocks)
                                    : (size_t)lists_area * 4 + bucket_lists_rest(bs.shift, bs.blocks);
     // lanes that walk a run of `per` offers per row together

@@ -727,8 +727,8 @@ def test_reverse_lists_of_given_lengths(ef, K, L, stride):
 
 @pytest.mark.parametrize("n,K,L,block,share,least", [
     (70_000, 10, 10, 128, 0.05, 4_096),         # ranges of 128 targets: the lists fit the LDS in two goes
-    (100_000, 20, 20, 128, 0.05, 8_192),        # ... of 512 threads
-    (200_000, 10, 10, 256, 0.05, 8_192),        # ranges of 256
+    (100_000, 20, 20, 128, 0.05, 8_192),        # ... with twice the room
+    (200_000, 10, 10, 256, 0.05, 8_192),        # ranges of 256, 512 threads
     (150_000, 16, 16, 256, 0.05, 8_192),
     (70_000, 32, 32, 256, 0.03, 16_384),        # lists that take all of the LDS
     (500_000, 10, 10, 1_024, 0.02, 16_384),     # ranges of 1024
