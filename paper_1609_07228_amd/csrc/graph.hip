@@ -1879,7 +1879,7 @@ reverse_old_wide_kernel(const int *__restrict__ od, int n, int K, const u64 *__r
 // What bounds it: instruction issue in the first iterations (10^6 points of degree 10: 3900 -> 3100 wave instructions per
 // wave of a launch, half of them choosing), a fixed 25 us of run descriptors and barriers in the last.  All
 // sixteen launches of that build 1338 -> 1035 us, with the bounded insertion for all (a list scanned in LDS per offer, again
-// whenever another thread was first) before; degree 20, 10^5 points 793 -> 257, where popular points' insertions waited for each other.
+// whenever another thread was first) before; degree 20, 10^5 points 793 -> 239, where popular points' insertions waited for each other.
 // LDS: area words, run_at [n_blocks + 1] (later offs [targets]), hist [targets], order and bound [targets] of 16 bits;
 // n_blocks <= twice the threads (four times if WIDE), at least one thread per target.
 __host__ __device__ inline size_t bucket_lists_rest(int shift, int n_blocks)
