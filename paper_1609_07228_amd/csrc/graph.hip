@@ -1567,7 +1567,10 @@ constexpr int kBktRows = 1024;        // source rows per offer block, at most
 constexpr int kBktThreads = 1024;
 constexpr int kBktMany = 800;         // as many buckets are enough
 // lists that take the bounded insertion (see bucket_insert_kernel)
-__host__ __device__ inline bool insert_lists(int64_t n, int L) { return L <= 6 || (L == 7 && n > (1 << 17)); }
+__host__ __device__ inline bool insert_lists(int64_t n, int K, int L)
+{
+    return L <= 6 || (L == 7 && n > (1 << 17)) || (K <= 10 && L <= 10 && n <= 256);
+}
 constexpr int kBktFew = 4;            // offers per thread up to which it looks for their runs
 constexpr int kBktWords = 16;         // offers a thread of a list block holds while they are sorted
                                       // (twice as many of long rows; two iterations with 12 and 24: the same where offers are spread evenly, 3 to 10 % longer
@@ -1616,8 +1619,8 @@ inline BucketShape bucket_shape(int64_t n, int K, int L)
         b.shift = shift;
         b.blocks = (int)((n + (1 << row_bits) - 1) >> row_bits);
         b.buckets = (int)((n - 1) >> shift) + 1;
-        b.threads = (per <= 10 || insert_lists(n, L) ? 1 : per <= 20 ? 2 : 4) << shift;
-        const int least = insert_lists(n, L) || row_bits == 8 || shift <= 7 ? 256 : 512;
+        b.threads = (per <= 10 || insert_lists(n, K, L) ? 1 : per <= 20 ? 2 : 4) << shift;
+        const int least = insert_lists(n, K, L) || row_bits == 8 || shift <= 7 ? 256 : 512;
         b.threads = b.threads < least ? least : b.threads > kBktThreads ? kBktThreads : b.threads;
         b.table_behind = (int64_t)b.blocks * b.buckets <= n * L;
     };
@@ -1628,7 +1631,7 @@ inline BucketShape bucket_shape(int64_t n, int K, int L)
         if (b.table_behind) return b;
     }
     const int top = per <= 10 ? 10 : per <= 20 ? 9 : 8;
-    for (int shift = 7; !insert_lists(n, L) && (shift <= 9 || shift <= top); ++shift) {
+    for (int shift = 7; !insert_lists(n, K, L) && (shift <= 9 || shift <= top); ++shift) {
         cut(10, shift);
         if (b.table_behind && b.buckets <= (shift < top ? kBktMany : kBktMaxRuns) && b.blocks <= 2 * b.threads) return b;
     }
@@ -2363,17 +2366,20 @@ bucket_lists_kernel(const u32 *__restrict__ offer_runs, const u32 *__restrict__ 
     if (blockIdx.x == 0 && t < kMaxClasses) work_count[t] = 0;
 }
 
-// The same for the shortest lists (insert_lists): every key goes through the bounded insertion; all slots start as the largest
+// The same for the shortest lists and the fewest points (insert_lists): every key goes through the bounded insertion; all slots start as the largest
 // key, so a list fills from slot 0 up and then keeps its L smallest keys.  Short scans and hardly a barrier: where
 // the sorting kernel takes longer (builds of 19 000 x 13, degree 7, lists of 5 / 3000 x 16, degree 3 / 300 000 x 32, degree 32, lists of 5:
 // 687 and 714 us, 454 and 473, 8.27 and 8.67 ms).  Lists of 7 take 1 to 3 % less with it from 2 10^5 points on (800 000 x 128, degree 7 8.33 and 8.55 ms) and
-// 1 to 6 % more below 10^5 (3000 x 128 655 and 615 us), lists of 8 up to 5 % more.  LDS: lists [bucket's targets * L] u64, scan [n_blocks + 1] and start [n_blocks] int.
-template <int RB>
+// 1 to 6 % more below 10^5 (3000 x 128 655 and 615 us), lists of 8 up to 5 % more.  Up to 256 points of degree 10 the sort's extra barriers are
+// 1.3 us of a launch of 4 to 6 (builds of 24, 100, 150 and 256 points 248 and 262 us, 310 and 319, 304 and 314, 329 and 332; of 350 points or of degree 12
+// level, 100 points of degree 20, lists of 10 637 and 625).  LDS: lists [bucket's targets * L] u64, scan [n_blocks + 1] and start [n_blocks] int.
+template <int LT, int RB>      // (see bucket_lists_kernel)
 __global__ void __launch_bounds__(kBktThreads)
 bucket_insert_kernel(const u32 *__restrict__ offer_runs, const u32 *__restrict__ table, int n_blocks,
-                    int run_cap, u64 stream_key, int n, int L, int shift, int, int, u32 *__restrict__ lists,
+                    int run_cap, u64 stream_key, int n, int L_, int shift, int, int, u32 *__restrict__ lists,
                     int *__restrict__ counts, const int *__restrict__ nw_c, u32 *__restrict__ active, int *work_count)
 {
+    const int L = LT ? LT : L_;
     extern __shared__ __align__(16) u64 list_sm[];
     u64 *ll = list_sm;
     const int targets = 1 << shift, n_thr = (int)blockDim.x;
@@ -4535,7 +4541,7 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
     // sorted: 4.27, 4.27 and 4.30)
     const bool roomy = !wide && bs.row_bits == 10 && bs.shift == 7 && (K > 10 || L > 10);
     const int lists_area = bkt ? bucket_lists_area(K, L, bs.shift, bs.blocks, bs.threads, wide || roomy ? 2 * kBktWords : kBktWords) : 0;
-    const size_t lists_lds = !bkt ? 0 : insert_lists(n, L) && !wide ? bucket_lists_lds(L, bs.shift, bs.blocks)
+    const size_t lists_lds = !bkt ? 0 : insert_lists(n, K, L) && !wide ? bucket_lists_lds(L, bs.shift, bs.blocks)
                                    : (size_t)lists_area * 4 + bucket_lists_rest(bs.shift, bs.blocks);
     // lanes that walk a run of `per` offers per row together
     auto run_lanes = [&](int per) {
@@ -4554,7 +4560,7 @@ int nndescent_run(const float *X, int64_t n, int32_t d, int32_t k, efanna_entry 
                                           : bkt_small ? reverse_old_bucket_kernel<8> : reverse_old_bucket_kernel<10>;
     const ListsKernel bkt_lists =
         wide ? (few_rows ? bucket_lists_kernel<0, 6, true> : bucket_lists_kernel<0, 8, true>)
-        : insert_lists(n, L) ? (bkt_small ? bucket_insert_kernel<8> : bucket_insert_kernel<10>)
+        : insert_lists(n, K, L) ? (!bkt_small ? bucket_insert_kernel<0, 10> : L == 10 ? bucket_insert_kernel<10, 8> : bucket_insert_kernel<0, 8>)
         : bkt_small ? (L == 10 ? bucket_lists_kernel<10, 8, false> : bucket_lists_kernel<0, 8, false>)
                     : (L == 10 ? bucket_lists_kernel<10, 10, false> : bucket_lists_kernel<0, 10, false>);
     const int offer_threads = wide ? 4 * bkt_rows : bkt_rows;

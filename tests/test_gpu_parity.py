@@ -493,6 +493,8 @@ def test_nndescent_filter_ranges_bit_exact(ef, kind, d, K, L):
     (2_999, 8, 2, 16, 33, 7, 1), (3_000, 8, 2, 16, 61, 6, 1), (3_000, 8, 2, 16, 60, 6, 1), (3_000, 8, 2, 16, 33, 5, 1),      # shorter ones: by counters
     (1_000, 8, 2, 16, 33, 8, 1), (999, 8, 2, 16, 33, 8, 1), (500, 8, 2, 16, 40, 12, 1), (499, 8, 2, 16, 40, 12, 1), (150, 8, 2, 16, 40, 20, 1),
     (1_000, 8, 2, 16, 5, 40, 1), (1_000, 8, 2, 16, 4, 40, 1), (900, 8, 2, 16, 30, 40, 1), (900, 8, 2, 16, 29, 40, 1),
+    (256, 8, 2, 16, 10, 10, 3), (257, 8, 2, 16, 10, 10, 3), (256, 8, 2, 16, 11, 10, 3),      # the most points of degree 10 whose lists
+    (24, 8, 1, 8, 10, 10, 2), (33, 8, 1, 8, 8, 9, 2), (32, 8, 1, 8, 7, 7, 2), (11, 8, 1, 4, 10, 8, 2),      # go without a sort, and fewer
     (900, 8, 2, 16, 1, 20, 2),           # rows of one entry, joins of more than 32 vectors
     (900, 8, 2, 16, 3, 20, 2),
     (140_000, 4, 1, 16, 21, 21, 1),      # join lists of 63 ids, four passes: the most LDS of either kernel that
@@ -736,6 +738,7 @@ def test_reverse_lists_of_given_lengths(ef, K, L, stride):
     (65_536, 24, 9, 128, 0.05, 16_384),
     (140_000, 20, 7, 1_024, 0.05, 16_384), (131_072, 20, 7, 256, 0.05, 16_384),      # lists of 7, without and with a sort
     (70_000, 20, 6, 1_024, 0.05, 16_384), (20_000, 7, 7, 64, 0.1, 4_096),
+    (256, 10, 10, 32, 0.3, 500), (250, 8, 7, 32, 0.3, 400), (257, 10, 10, 32, 0.3, 500),      # few points, without and with a sort
     (2_100, 128, 64, 32, 0.1, 8_192),           # long rows: offers walked twice, popular points have room for 128 each
     (70_000, 100, 50, 256, 0.02, 32_768),
 ])
